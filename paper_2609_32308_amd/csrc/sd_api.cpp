@@ -321,8 +321,7 @@ InstLayout layout_instance(const Lattice& L, char* A, char* B, Inst& I) {
         {I.ccap(), 4 * N, U}, {I.ccnt(), 4 * N, U}, {I.X(), 8 * N, U},
         {I.out_dst(), 16 * N, 2 * U}, {I.out_U(), 32 * N, 4 * U}, {I.alphaU(), 32 * N, 4 * U},
         {I.betaU(), 32 * N, 4 * U}, {I.fwd_off(), 4 * (int64_t)L.fwd_off.size(), 3 * U},
-        {I.bwd_off(), 4 * (int64_t)L.bwd_off.size(), 3 * U}, {I.hpB(), 8 * (int64_t)L.hpB.size(), 16 * U},
-        {I.OB(), 8 * (int64_t)L.OB.size(), 72 * U}, {I.OA(), 8 * (int64_t)L.OA.size(), 72 * U},
+        {I.bwd_off(), 4 * (int64_t)L.bwd_off.size(), 3 * U},
         {I.stats(), 96, U}, {I.visits(), 8 * (n + 1), U}, {I.feasible(), 8 * (n + 1), U},
         {I.inmask(), 4 * N, U}, {I.tr_seq(), 4 * n, U}, {I.tr_pair(), 4 * n, U},
         {I.tr_stack(), 16 * (n + 2), 2 * U}, {I.cstrict(), 4 * N, U},
@@ -330,8 +329,7 @@ InstLayout layout_instance(const Lattice& L, char* A, char* B, Inst& I) {
         {I.JDL(), 8 * (int64_t)kLMRing * N * 12, 12 * R}, {I.BI(), 8 * (int64_t)kLMRing * N, R},
         {I.BJ(), 8 * (int64_t)kLMRing * N, R}, {I.RS(), 8 * (int64_t)kLMRing * N * 16, 16 * R},
         {I.LS(), 8 * (int64_t)kLMRing * N * 16, 16 * R}, {I.MINI(), 8 * (int64_t)kLMRing * (n + 1) * 2, 2 * R}};
-    bool ok = L.fwd_crow.size() == L.fwd_meta.size() && (int64_t)L.inmask.size() == N && (int64_t)L.fwd_off.size() == 4 * N + 1 && (int64_t)L.bwd_off.size() == 4 * N + 1 &&
-              (int64_t)L.hpB.size() == 16 * N && (int64_t)L.OB.size() == 72 * N && (int64_t)L.OA.size() == 72 * N;
+    bool ok = L.fwd_crow.size() == L.fwd_meta.size() && (int64_t)L.inmask.size() == N && (int64_t)L.fwd_off.size() == 4 * N + 1 && (int64_t)L.bwd_off.size() == 4 * N + 1;
     for (const Ext& e : ea) ok = ok && e.bytes <= e.slot;
     // the span kernels locate the cells of edge neighbours from the layering: every edge must
     // join consecutive layers (the in-edges are the out-edges reversed)
@@ -382,9 +380,6 @@ void stage_inputs(const Lattice& L, const Inst& I, const char* devA, char* image
     put(I.bwd_off(), L.bwd_off.data(), L.bwd_off.size() * 4);
     put(I.bwd_meta(), L.bwd_meta.data(), L.bwd_meta.size() * 4);
     put(I.bwd_cost(), L.bwd_cost.data(), L.bwd_cost.size() * 8);
-    put(I.hpB(), L.hpB.data(), L.hpB.size() * 8);
-    put(I.OB(), L.OB.data(), L.OB.size() * 8);
-    put(I.OA(), L.OA.data(), L.OA.size() * 8);
     if (L.generic) {
         put(I.gjob_off(), L.gjob_off.data(), L.gjob_off.size() * 8);
         put(I.gjobs(), L.gjobs.data(), L.gjobs.size() * 4);
@@ -1147,9 +1142,6 @@ extern "C" sd_status sd_multiloop_abstract(sd_context* c, int N, const int32_t* 
         L.betaU.assign(4 * (size_t)N, kINF);
         L.fwd_off.assign(4 * (size_t)N + 1, 0);
         L.bwd_off.assign(4 * (size_t)N + 1, 0);
-        L.hpB.assign(16 * (size_t)N, kINF);
-        L.OB.assign(72 * (size_t)N, kINF);
-        L.OA.assign(72 * (size_t)N, kINF);
         // cells in row layout; worst-case candidate segments (a direct arc may have any span)
         L.rowoff.assign(N, 0);
         L.coff.assign(N, 0);

@@ -23,7 +23,9 @@ struct SmallE {
     alignas(16) int16_t int21[6][6][4][4][4];    // 1x2 loops (staged from the 16-bit copies)
     alignas(16) int16_t int22[6][6][4][4][4][4]; // 2x2 loops
     int32_t stack[6][6];
-    int32_t mmH[6][4][4], mmI[6][4][4], mm1n[6][4][4], mm23[6][4][4];
+    // boundary tables by class, addressed as one array [class][type][16]: hairpin, generic interior,
+    // 1xn, 2x3, and the terminal AU/GU penalty of the type (the same for all 16 label pairs)
+    int32_t mmH[6][4][4], mmI[6][4][4], mm1n[6][4][4], mm23[6][4][4], mmA[6][4][4];
     int32_t int11[6][6][4][4];
     int32_t hairpin[31], bulge[31], interior[31];
     int32_t ml_closing, ml_intern, ml_base, terminal_au, ninio, ninio_max;
@@ -45,6 +47,7 @@ __device__ inline void stage_tables(SmallE& S, const EnergyTables* __restrict__ 
         (&S.mmI[0][0][0])[i] = (&E->mmI[0][0][0])[i];
         (&S.mm1n[0][0][0])[i] = (&E->mm1n[0][0][0])[i];
         (&S.mm23[0][0][0])[i] = (&E->mm23[0][0][0])[i];
+        (&S.mmA[0][0][0])[i] = (i >> 4 == 1 || i >> 4 == 2) ? 0 : E->terminal_au;
     }
     for (int i = t; i < 576; i += nt) (&S.int11[0][0][0][0])[i] = (&E->int11[0][0][0][0])[i];
     for (int i = t; i < 31; i += nt) {
@@ -60,6 +63,21 @@ __device__ inline void stage_tables(SmallE& S, const EnergyTables* __restrict__ 
         S.ninio = E->ninio;
         S.ninio_max = E->ninio_max;
     }
+}
+
+// The region bases of an instance as global pointers the compiler knows nothing else about.  A
+// descriptor read from memory holds generic pointers, whose accesses would be flat instructions
+// (which also wait on the LDS counter); and array addresses derived from a laundered base are not
+// hoisted out of the loop that launders it, where they would crowd the scalar registers.
+__device__ __forceinline__ char* global_base(char* p) {
+    uint64_t x = (uint64_t)p;
+    asm volatile("" : "+s"(x));
+    return (char*)(__attribute__((address_space(1))) char*)x;
+}
+__device__ __forceinline__ Inst rebased(Inst I) {
+    I.ra = global_base(I.ra);
+    I.rb = global_base(I.rb);
+    return I;
 }
 
 __device__ __forceinline__ int ptype(int x, int y) { return kPairType[x * 4 + y]; }

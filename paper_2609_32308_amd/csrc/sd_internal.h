@@ -59,10 +59,10 @@ struct TFrame {
 //   0 layer[N]  1 off[n+2]  2 in_start[N+1]  3 tail[N]  4 pfx[N]  5 P[A+1]  6 hp_init[n+1]
 //   7 rowoff[N]  8 coff[N]  9 ccap[N]  10 ccnt[N]  11 X[N]  12-13 out_dst[4N]  14-17 out_U[4N]
 //   18-21 alphaU[4N]  22-25 betaU[4N]  26-28 fwd_off[4N+1]  29-31 bwd_off[4N+1]
-//   32-47 hpB[16N]  48-119 OB[72N]  120-191 OA[72N]  192 stats[4], trace results [8..11]
-//   193 visits[n+1]  194 feasible[n+1]  195 inmask[N]  196 tr_seq[n]  197 tr_pair[n]
-//   198-199 tr_stack[n+2] (16-byte frames)  200 cstrict[N]
-//   201.. in_src[nE], in_lab[nE], in_U[nE], fwd_meta[nF], fwd_cost[nF], bwd_meta[nB],
+//   32 stats[4], trace results [8..11]
+//   33 visits[n+1]  34 feasible[n+1]  35 inmask[N]  36 tr_seq[n]  37 tr_pair[n]
+//   38-39 tr_stack[n+2] (16-byte frames)  40 cstrict[N]
+//   41.. in_src[nE], in_lab[nE], in_U[nE], fwd_meta[nF], fwd_cost[nF], bwd_meta[nB],
 //         bwd_cost[nB], fwd_crow[nF] (each start 8-byte aligned)
 // Region B (DP tables) is cut into ring units of R = 512 * N bytes (N states x 64 spans x 8 B):
 //   0-1 LM  2-13 IDL  14-25 JDL  26 BI  27 BJ  28-43 RS  44-59 LS  60-61 MINI, then from 62 R:
@@ -73,7 +73,8 @@ struct TFrame {
 // Meaning of the arrays:
 //   layer/off: layer of a state, first state of a layer; out_dst/out_U: out-edge by label
 //   (-1 / cost); in_start/in_src/in_lab/in_U: in-edges (CSR, sorted by source and label);
-//   inmask: bit y set if the state has an in-edge labelled y; tail: cheapest completion of the
+//   inmask: bit y set if the state has an in-edge labelled y, bit 4 + x if it has an out-edge
+//   labelled x; tail: cheapest completion of the
 //   current codon from a state; pfx: 2-base prefix code of a
 //   phase-2 state (4x+y), base x of phase 1; P: prefix sums of per-codon minimum cost;
 //   hp_init: hairpin initiation per size (extrapolated above 30); rowoff: cell row offsets,
@@ -91,14 +92,12 @@ struct TFrame {
 //   MINI[layer p][span][class 2]: both-separable interior minimum of layer pair (p, p + span),
 //   prepared one step ahead.
 //   IDL/JDL[state][class 3][label 4][span]: inner minima per left / right inner state.
-//   fwd_*/bwd_*: label paths of 1..4 edges out of / into a state (CSR by state*4+l-1);
+//   fwd_*/bwd_*: label paths of 1..3 edges out of / into a state (CSR by state*4+l-1);
 //   meta = other_end << 4 | first_label << 2 | last_label, cost = sum of edge costs; fwd_crow =
 //   the cell-row base of the path's end state c (cell(c, d) = fwd_crow + d).
-//   hpB[b*16 + y*4 + z] = min over b2 -z-> b1 -y-> b of U(b2->b1) + U(b1->b).
-//   OB/OA[state][t][X][label]: outer minima of one-sided interior loops.
 //   BI[c][span] = min over d, t' of V_t'(c,d) + tail(d) + AU(t');  BJ[d][span] likewise without
 //   the tail.  RS[c][span][l-1][label], LS[d][span][l-1][label]: one-sided loops minimised over
-//   the separable side's length (explicit side of l <= 4 bases).
+//   the separable side's length (explicit side of l <= 3 bases).
 struct Inst {
     char *ra, *rb;         // region bases
     int64_t U;             // region-A unit in bytes
@@ -135,22 +134,19 @@ struct Inst {
     __host__ __device__ const int64_t* betaU() const { return (const int64_t*)ua(22); }
     __host__ __device__ const int* fwd_off() const { return (const int*)ua(26); }
     __host__ __device__ const int* bwd_off() const { return (const int*)ua(29); }
-    __host__ __device__ const int64_t* hpB() const { return (const int64_t*)ua(32); }
-    __host__ __device__ const int64_t* OB() const { return (const int64_t*)ua(48); }
-    __host__ __device__ const int64_t* OA() const { return (const int64_t*)ua(120); }
-    __host__ __device__ unsigned long long* stats() const { return (unsigned long long*)ua(192); }
-    __host__ __device__ unsigned long long* visits() const { return (unsigned long long*)ua(193); }
-    __host__ __device__ unsigned long long* feasible() const { return (unsigned long long*)ua(194); }
-    __host__ __device__ const int* inmask() const { return (const int*)ua(195); }
-    __host__ __device__ int* tr_seq() const { return (int*)ua(196); }
-    __host__ __device__ int* tr_pair() const { return (int*)ua(197); }
-    __host__ __device__ TFrame* tr_stack() const { return (TFrame*)ua(198); }
-    __host__ __device__ int* cstrict() const { return (int*)ua(200); }
-    __host__ __device__ long long* tr_res() const { return (long long*)ua(192) + 8; }
-    __host__ __device__ const int* in_src() const { return (const int*)ua(201); }
-    __host__ __device__ const int* in_lab() const { return (const int*)(ua(201) + al8(4 * nE)); }
-    __host__ __device__ const int64_t* in_U() const { return (const int64_t*)(ua(201) + 2 * al8(4 * nE)); }
-    __host__ __device__ char* paths() const { return ua(201) + 2 * al8(4 * nE) + 8 * nE; }
+    __host__ __device__ unsigned long long* stats() const { return (unsigned long long*)ua(32); }
+    __host__ __device__ unsigned long long* visits() const { return (unsigned long long*)ua(33); }
+    __host__ __device__ unsigned long long* feasible() const { return (unsigned long long*)ua(34); }
+    __host__ __device__ const int* inmask() const { return (const int*)ua(35); }
+    __host__ __device__ int* tr_seq() const { return (int*)ua(36); }
+    __host__ __device__ int* tr_pair() const { return (int*)ua(37); }
+    __host__ __device__ TFrame* tr_stack() const { return (TFrame*)ua(38); }
+    __host__ __device__ int* cstrict() const { return (int*)ua(40); }
+    __host__ __device__ long long* tr_res() const { return (long long*)ua(32) + 8; }
+    __host__ __device__ const int* in_src() const { return (const int*)ua(41); }
+    __host__ __device__ const int* in_lab() const { return (const int*)(ua(41) + al8(4 * nE)); }
+    __host__ __device__ const int64_t* in_U() const { return (const int64_t*)(ua(41) + 2 * al8(4 * nE)); }
+    __host__ __device__ char* paths() const { return ua(41) + 2 * al8(4 * nE) + 8 * nE; }
     __host__ __device__ const int* fwd_meta() const { return (const int*)paths(); }
     __host__ __device__ const int64_t* fwd_cost() const { return (const int64_t*)(paths() + al8(4 * nF)); }
     __host__ __device__ const int* bwd_meta() const { return (const int*)(paths() + al8(4 * nF) + 8 * nF); }

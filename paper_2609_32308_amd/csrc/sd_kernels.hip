@@ -34,23 +34,16 @@
 
 namespace sd {
 
-// (l1, l2) pairs in canonical order: l1 ascending, then l2 ascending, l1 + l2 <= 30
-__constant__ unsigned char kL1[kNumPairs];
-__constant__ unsigned char kL2[kNumPairs];
-// Two-loop (l1, l2) pairs by category for each phase (p mod 3, q mod 3), each list sorted by
-// l1 + l2 so that the pairs allowed at span g (l1 + l2 <= g - 7) form a prefix.  Entries:
-// l1 | l2 << 5 | side << 10 (side 1: left side separable).  Counts: kCnt[list][phase][cap].
-enum { kListBulge = 0, kListOne = 1, kListLab = 2, kListFast = 3, kListBulgeSep = 4 };
-__constant__ unsigned short kPairList[5][9][kNumPairs];
-__constant__ unsigned short kPairCnt[5][9][31];
+// (l1, l2) pairs whose two segments are both separable (see sep_left), for each phase
+// (p mod 3, q mod 3), sorted by l1 + l2 so that the pairs allowed at span g (l1 + l2 <= g - 7) form
+// a prefix.  Entries: l1 | l2 << 5.  Counts: kFastCnt[phase][cap].
+__constant__ unsigned short kFastList[9][kNumPairs];
+__constant__ unsigned short kFastCnt[9][31];
 
-// (l1, l2) handled by the separable layer-pair tables: both segments of length >= 2 crossing a
-// codon boundary, generic or 2x3 interior class.
-__device__ __forceinline__ bool fast_pair(int p, int q, int l1, int l2) {
-    if (l1 < 2 || l2 < 2 || (l1 == 2 && l2 == 2)) return false;
-    if ((q - 1 - l2) - (p + 1 + l1) < 5) return false;
-    return (p + 2) / 3 != (p + l1) / 3 && (q - l2) / 3 != (q - 2) / 3;
-}
+// Pair types as bit fields: 5' base, 3' base, and the type of the reversed pair.
+__device__ __forceinline__ constexpr int type_x(int t) { return (0xFA4 >> (2 * t)) & 3; }
+__device__ __forceinline__ constexpr int type_y(int t) { return (0x8DB >> (2 * t)) & 3; }
+__device__ __forceinline__ constexpr int type_rev(int t) { return t == 0 ? 4 : t == 1 ? 2 : t == 2 ? 1 : t == 3 ? 5 : t == 4 ? 0 : 3; }
 
 // ---- hairpin closure ------------------------------------------------------------------------
 template <class IT>
@@ -97,157 +90,19 @@ __device__ int64_t hairpin_lane(const IT& I, const SmallE& S, const int32_t* __r
         }
         return best;
     }
-    // generic size m >= 5: a -x-> a1 -x2-> a2 ~~> b2 -z-> b1 -y-> b.  a2 and b2 are >= 3 layers
-    // apart, so the gap is tail(a2) + whole codons and the minimum separates into
-    // alpha(a1, x2) + mmH[t][x2][z] + HB(b, y, z) plus layer constants.
-    if (lane < 16) {
-        const int x2 = lane >> 2, z = lane & 3;
-        const int64_t al = I.alphaU()[a1 * 4 + x2], hb = I.hpB()[b * 16 + y * 4 + z];
-        if (al < kINF && hb < kINF)
-            best = Ua + al + hb + I.P()[(la + g - 2) / 3] - I.P()[(la + 2) / 3 + 1] +
-                   fx(I.hp_init()[m] + S.mmH[t][x2][z], s);
-    }
     return best;
 }
 
-// ---- two-loop closure: bulges and stacks ----------------------------------------------------------
-// No boundary bases enter a bulge or stack energy, so each unpaired side costs its minimum
-// (the gap).  The explicit pairs (stack, bulges of 1 and 2) are flattened over the lanes as
-// (pair, inner left state, inner right state), counting only the states the inner layers hold;
-// each lane evaluates the six inner types.
-template <class IT>
-__device__ __forceinline__ int64_t gap_l(const IT& I, int a, int la, int b, int lb) {  // gap() with known layers
-    if (la == lb) return a == b ? 0 : kINF;
-    const int ka = la / 3, kb = lb / 3;
-    if (ka == kb) {
-        if (la % 3 == 0) return 0;
-        return (I.pfx()[b] >> 2) == I.pfx()[a] ? 0 : kINF;
-    }
-    return I.tail()[a] + I.P()[kb] - I.P()[ka + 1];
-}
-
-template <class IT>
-__device__ int64_t bulge_lanes(const IT& I, const SmallE& S, int t, int a1, int b1, int64_t Uab, int p,
-                               int q, int cap, int lane) {
-    const int s = I.shift;
-    // The explicit pairs (l1, l2) are (0,0), (0,1), (1,0), (0,2), (2,0), those with l1 + l2 <= cap.
-    // One side of a bulge is empty, so after the stack each pair's items are the states of its one
-    // inner layer: q-2, p+2, q-3, p+3.
-    const int r1 = cap >= 1 ? I.off()[q - 2] : 0, nr1 = cap >= 1 ? I.off()[q - 1] - r1 : 0;
-    const int l1s = cap >= 1 ? I.off()[p + 2] : 0, nl1 = cap >= 1 ? I.off()[p + 3] - l1s : 0;
-    const int r2 = cap >= 2 ? I.off()[q - 3] : 0, nr2 = cap >= 2 ? r1 - r2 : 0;
-    const int l2s = cap >= 2 ? I.off()[p + 3] : 0, nl2 = cap >= 2 ? I.off()[p + 4] - l2s : 0;
-    const int tot = 1 + nr1 + nl1 + nr2 + nl2;
-    int64_t best = kINF;
-    for (int idx = lane; idx < tot; idx += 64) {
-        int l1 = 0, l2 = 0, c = a1, d = b1, r = idx - 1;
-        if (idx == 0) {
-        } else if (r < nr1) {
-            l2 = 1;
-            d = r1 + r;
-        } else if ((r -= nr1) < nl1) {
-            l1 = 1;
-            c = l1s + r;
-        } else if ((r -= nl1) < nr2) {
-            l2 = 2;
-            d = r2 + r;
-        } else {
-            r -= nr2;
-            l1 = 2;
-            c = l2s + r;
-        }
-        const int cl = p + 1 + l1, dl = q - 1 - l2;
-        const int64_t gl = l1 == 0 ? 0 : gap_l(I, a1, p + 1, c, cl);
-        const int64_t gr = l2 == 0 ? 0 : gap_l(I, d, dl, b1, q - 1);
-        if (gl >= kINF || gr >= kINF) continue;
-        const int64_t* v = I.V() + (I.rowoff()[c] - I.off()[cl + 1] + d) * 6;
-        const int l = l1 + l2;
-#pragma unroll
-        for (int tp = 0; tp < 6; tp++) {
-            const int64_t vin = v[tp];
-            const int32_t e2 = l == 0 ? S.stack[t][kRev[tp]] : bulge_e(S, t, kRev[tp], l);
-            if (vin < kINF) best = mn(best, Uab + gl + vin + gr + fx(e2, s));
-        }
-    }
-    return best;
-}
-
-// ---- two-loop closure: both segments explicit (each has 1..4 bases inside one codon) -------------
-// Left segments are the label paths of l1 edges out of a1, right segments the paths of l2 edges
-// into b1.  The (pair, left path, right path) combinations of all such pairs are flattened over
-// the lanes: lane k < #pairs publishes its pair's combination count, a wave prefix sum gives
-// the offsets, and every lane decodes its own combinations.  When nh waves share the list, the
-// wave with index h takes the blocks of 64 combinations h, h + nh, ...
-struct LabPair {
-    int f0, nl, r0, nr, l1, l2, start;
-};
-
-template <class IT>
-__device__ int64_t labelled_pairs(const IT& I, const SmallE& S, const EnergyTables* __restrict__ E,
-                                  int t, int a1, int b1, int64_t Uab, int ph, int cap, int lane,
-                                  LabPair* lp, int h, int nh) {
-    const int s = I.shift;
-    const int npairs = kPairCnt[kListLab][ph][cap];  // <= 16
-    int cnt = 0;
-    if (lane < npairs) {
-        const int code = kPairList[kListLab][ph][lane], l1 = code & 31, l2 = (code >> 5) & 31;
-        LabPair x;
-        x.f0 = I.fwd_off()[a1 * 4 + l1 - 1];
-        x.nl = I.fwd_off()[a1 * 4 + l1] - x.f0;
-        x.r0 = I.bwd_off()[b1 * 4 + l2 - 1];
-        x.nr = I.bwd_off()[b1 * 4 + l2] - x.r0;
-        x.l1 = l1;
-        x.l2 = l2;
-        cnt = x.nl * x.nr;
-        lp[lane] = x;
-    }
-    // inclusive prefix over lanes 0..15 (the first row) by DPP row shifts; a shifted-in lane
-    // from outside the row reads 0
-    int incl = cnt;
-    incl += __builtin_amdgcn_update_dpp(0, incl, 0x111, 0xF, 0xF, false);  // row_shr:1
-    incl += __builtin_amdgcn_update_dpp(0, incl, 0x112, 0xF, 0xF, false);  // row_shr:2
-    incl += __builtin_amdgcn_update_dpp(0, incl, 0x114, 0xF, 0xF, false);  // row_shr:4
-    incl += __builtin_amdgcn_update_dpp(0, incl, 0x118, 0xF, 0xF, false);  // row_shr:8
-    if (lane < npairs) lp[lane].start = incl - cnt;
-    const int total = __builtin_amdgcn_readlane(incl, 15);
-    // pair starts on the scalar unit (a lane at or past npairs starts at total)
-    int pst[16];
-#pragma unroll
-    for (int j = 1; j < 16; j++) pst[j] = __builtin_amdgcn_readlane(incl - cnt, j);
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-    int64_t best = kINF;
-    for (int idx = lane + 64 * h; idx < total; idx += 64 * nh) {
-        int k = 0;  // the last pair whose start is <= idx
-#pragma unroll
-        for (int j = 1; j < 16; j++) k += pst[j] <= idx;
-        const LabPair x = lp[k];
-        const int r = idx - x.start, i = r / x.nr, j = r - i * x.nr;
-        const int fm = I.fwd_meta()[x.f0 + i], bm = I.bwd_meta()[x.r0 + j];
-        const int c = fm >> 4, xi = (fm >> 2) & 3, xk = fm & 3;
-        const int d = bm >> 4, xl = (bm >> 2) & 3, xj = bm & 3;
-        const int64_t base = Uab + I.fwd_cost()[x.f0 + i] + I.bwd_cost()[x.r0 + j];
-        const int64_t* v = I.V() + (I.fwd_crow()[x.f0 + i] + d) * 6;
-        for (int tp = 0; tp < 6; tp++) {
-            const int64_t vin = v[tp];
-            if (vin >= kINF) continue;
-            const int32_t e2 = interior_e(S, E, t, kRev[tp], x.l1, x.l2, xi, xk, xl, xj);
-            best = mn(best, base + vin + fx(e2, s));
-        }
-    }
-    __builtin_amdgcn_wave_barrier();
-    return best;
-}
-
-// ---- one-sided separable two-loops --------------------------------------------------------------
-// A side is separable when its segment has >= 2 bases and its two end edges lie in different
-// codons (then its minimum cost is first-edge part + last-edge part + whole codons).  With the
-// right side separable and the left side explicit (one edge, or both ends inside one codon):
-//   value = U_ab + base + PR + left cost + OB_X(b1, t, x_{i+1}) + IDL_X(c, span, x_{k-1})
-// and symmetrically with the left side separable:
-//   value = U_ab + base + PL + right cost + OA_X(a1, t, x_{j-1}) + JDL_X(d, span, x_{l+1}).
-__device__ __forceinline__ bool sep_left(int p, int l1) { return l1 >= 2 && (p + 2) / 3 != (p + l1) / 3; }
-__device__ __forceinline__ bool sep_right(int q, int l2) { return l2 >= 2 && (q - l2) / 3 != (q - 2) / 3; }
+// ---- separable loop segments ---------------------------------------------------------------------
+// An unpaired segment of l bases is separable when its first and last edges lie in different codons:
+// its cheapest path with given end labels then costs first edge + rest of the first edge's codon
+// + whole codons + last edge, with no coupling between the two labels.  The left segment of a loop
+// closed by (p, q) runs from layer p + 1 to p + 1 + l1, the right one from q - 1 - l2 to q - 1.
+// With alpha(d, x) = U(first edge) + tail and beta(c, x) = U(last edge) the whole codons are PLt / PRt;
+// a segment that starts with a third base takes all further bases from the next codon, whose
+// minimum is in alpha's tail and is taken off again by PLt / PRt (the weight cost sits on third edges).
+__host__ __device__ __forceinline__ bool sep_left(int p, int l1) { return (p + 1) / 3 != (p + l1) / 3; }
+__host__ __device__ __forceinline__ bool sep_right(int q, int l2) { return (q - 1 - l2) / 3 != (q - 2) / 3; }
 // per-state rings [state][class][label][span mod 64]: a consumer walks consecutive spans
 __device__ __forceinline__ int64_t ring_idx(int state, int span, int X, int lab) {
     return (((int64_t)state * 3 + X) * 4 + lab) * kLMRing + (span & (kLMRing - 1));
@@ -260,113 +115,270 @@ __device__ __forceinline__ int64_t lm_idx(int layer, int span, int X) {
 __device__ __forceinline__ int64_t mini_idx(int p, int span, int X) {
     return ((int64_t)p * kLMRing + (span & (kLMRing - 1))) * 2 + X;
 }
+// one-sided tables [state][span mod 64][explicit length - 1][label]
+__device__ __forceinline__ int64_t rs_idx(int state, int span, int l, int lab) {
+    return ((int64_t)state * kLMRing + (span & (kLMRing - 1))) * 16 + (l - 1) * 4 + lab;
+}
 template <class IT>
 __device__ __forceinline__ int64_t PLt(const IT& I, int p, int l1) { return I.P()[(p + l1) / 3] - I.P()[(p + 2) / 3 + 1]; }
 template <class IT>
 __device__ __forceinline__ int64_t PRt(const IT& I, int q, int l2) { return I.P()[(q - 2) / 3] - I.P()[(q - l2) / 3 + 1]; }
 
-// Outer minima of one-sided loops come from per-state tables built with the automaton:
-//   OB(b1, t)[X][x_{i+1}] = min_{x_{j-1}} beta(b1, x_{j-1}) + mm_X[t][x_{i+1}][x_{j-1}]
-//   OA(a1, t)[X][x_{j-1}] = min_{x_{i+1}} alpha(a1, x_{i+1}) + mm_X[t][x_{i+1}][x_{j-1}]
+// A value every lane of the wave holds, moved to a scalar register so that the addresses and loop
+// bounds derived from it stay scalar.
+__device__ __forceinline__ int uni(int x) { return __builtin_amdgcn_readfirstlane(x); }
+__device__ __forceinline__ int64_t uni(int64_t x) {
+    const int hi = __builtin_amdgcn_readfirstlane((int)(x >> 32)), lo = __builtin_amdgcn_readfirstlane((int)x);
+    return (int64_t)(((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo);
+}
+// Orders LDS accesses of the lanes of one wave (they execute in order; the compiler must not move them).
+__device__ __forceinline__ void wave_lds_order() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+__device__ __forceinline__ void lds_min(int64_t* p, int64_t v) {
+    __hip_atomic_fetch_min(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
 
-// left segment explicit (paths of l1 edges out of a1), right segment separable
+// Hairpins of 3, 4 or 6 unpaired bases (listed special loops) over the paths a1 ~> b1, closed by type t:
+// each lane walks the paths whose first three bases spell its lane id in base 4.
 template <class IT>
-__device__ int64_t rsep_pair(const IT& I, const SmallE& S, int a1, int64_t Uab, int l1, int l2,
-                             int cl, int dl, int q, const int64_t* __restrict__ ob, int first, int step) {
-    const int X = mm_class(l1, l2), g2 = dl - cl;
-    const int64_t base = Uab + fx(interior_base(S, l1, l2), I.shift) + PRt(I, q, l2);
-    const int f0 = I.fwd_off()[a1 * 4 + l1 - 1], f1 = I.fwd_off()[a1 * 4 + l1];
-    int64_t best = kINF;
-    for (int i = f0 + first; i < f1; i += step) {
-        const int fm = I.fwd_meta()[i], c = fm >> 4, xi = (fm >> 2) & 3, xk = fm & 3;
-        const int64_t o = ob[X * 4 + xi], idl = I.IDL()[ring_idx(c, g2, X, xk)];
-        if (o < kINF && idl < kINF) best = mn(best, base + I.fwd_cost()[i] + o + idl);
+__device__ __forceinline__ int64_t special_hairpin(const IT& I, const SmallE& S, const int32_t* __restrict__ spec, int a1,
+                                   int b1, int t, int g, int lane) {
+    const int m = g - 2, nfree = m - 3;  // 0, 1 or 3 bases after the first three
+    int st = a1, key = type_x(t);
+    int64_t cost = 0, best = kINF;
+    for (int i = 2; i >= 0; i--) {
+        const int lab = (lane >> (2 * i)) & 3, e = st * 4 + lab, d = I.out_dst()[e];
+        if (d < 0) return kINF;
+        cost += I.out_U()[e];
+        key = key * 4 + lab;
+        st = d;
+    }
+    for (int k = 0; k < 1 << (2 * nfree); k++) {
+        int st2 = st, key2 = key, last = lane & 3;
+        int64_t c2 = cost;
+        bool ok = true;
+        for (int i = nfree - 1; i >= 0 && ok; i--) {
+            const int lab = (k >> (2 * i)) & 3, e = st2 * 4 + lab, d = I.out_dst()[e];
+            ok = d >= 0;
+            if (!ok) break;
+            c2 += I.out_U()[e];
+            key2 = key2 * 4 + lab;
+            st2 = d;
+            last = lab;
+        }
+        if (!ok || st2 != b1) continue;
+        key2 = key2 * 4 + type_y(t);
+        int32_t en = spec[(m == 3 ? kSpecOff5 : m == 4 ? kSpecOff6 : kSpecOff8) + key2];
+        if (en == kNoSpecial) en = I.hp_init()[m] + (m == 3 ? au_pen(S, t) : S.mmH[t][(lane >> 4) & 3][last]);
+        best = mn(best, c2 + fx(en, I.shift));
     }
     return best;
 }
 
-// left segment separable, right segment explicit (paths of l2 edges into b1)
+// ---- closed values of one inner boundary pair -----------------------------------------------------
+// The loop closed by a pair (a -x-> a1 .. b1 -y-> b) of type t = (x, y) depends on a and b only through
+// the two edge costs, so its minimum W_t(a1, b1) over hairpins, two-loops and the multiloop is found
+// once per (a1, b1), for every type some edge pair can close, by one wave:
+//   T[K][xi][xj]  (64 lanes) everything whose type dependence is a boundary table of class K (hairpin,
+//                 generic interior, 1xn, 2x3) at the two bases next to the closing pair:
+//                 hairpins, interior loops with a separable segment (A / B: minima of the other,
+//                 explicit segment by its outer label; RS / LS hold them minimised over the separable
+//                 segment's length, MINI over both), and explicit generic loops (LDS minima);
+//   TA            everything whose type dependence is the AU/GU penalty: bulges of >= 2 bases and
+//                 the multiloop;
+//   special loops (stack, 1-base bulge, 1x1, 1x2, 2x1, 2x2), whose tables couple both pairs: per type.
+// The step is bound by chains of dependent loads, so what counts is how many chains there are: one
+// per (a1, b1) here, where one per (a, b, t) and per loop class walked the same inner cells again for
+// each type (a span's slowest pairs close six types), and few short paths, since a segment counts
+// as separable from its first codon boundary on.  300 aa fill 28.3 -> 19.5 ms, 1,976 aa 535 -> 391 ms, 64
+// proteins of 50-1,000 aa in one launch 1.29 -> 0.71 s.
+// The explicit loops are the combinations of the short label paths out of a1 and into b1 (the empty
+// path included), flattened over the lanes; each reads its inner cell's six typed values once.
+struct PairScratch {
+    int64_t T[64];    // [class][xi][xj] minima of explicit generic loops
+    int64_t AB[2][3][4];  // [left / right explicit][generic, 1xn, 2x3][outer label]
+};
+constexpr int64_t kBarred = ((int64_t)1 << 61) + ((int64_t)1 << 60) + ((int64_t)1 << 59);  // infeasible, and adding kINF stays in range
+
 template <class IT>
-__device__ int64_t lsep_pair(const IT& I, const SmallE& S, int b1, int64_t Uab, int l1, int l2,
-                             int cl, int dl, int p, const int64_t* __restrict__ oa, int first, int step) {
-    const int X = mm_class(l1, l2), g2 = dl - cl;
-    const int64_t base = Uab + fx(interior_base(S, l1, l2), I.shift) + PLt(I, p, l1);
-    const int r0 = I.bwd_off()[b1 * 4 + l2 - 1], r1 = I.bwd_off()[b1 * 4 + l2];
-    int64_t best = kINF;
-    for (int j = r0 + first; j < r1; j += step) {
-        const int bm = I.bwd_meta()[j], d = bm >> 4, xl = (bm >> 2) & 3, xj = bm & 3;
-        const int64_t o = oa[X * 4 + xj], jdl = I.JDL()[ring_idx(d, g2, X, xl)];
-        if (o < kINF && jdl < kINF) best = mn(best, base + I.bwd_cost()[j] + o + jdl);
-    }
-    return best;
-}
-
-// ---- one-sided pairs through the per-state tables RS / LS ---------------------------------------
-// The explicit side's short label paths are enumerated once; the separable side's length was
-// minimised by the producer.  The 2x3 and 3x2 pairs (whose mismatch class differs from the rest
-// of their row) are evaluated per pair.
-__device__ __forceinline__ int64_t rs_idx(int state, int span, int l, int lab) {
-    return ((int64_t)state * kLMRing + (span & (kLMRing - 1))) * 16 + (l - 1) * 4 + lab;
-}
-
-template <bool kSpread, class IT>
-__device__ int64_t one_sided(const IT& I, const SmallE& S, int a1, int b1, int64_t Uab, int p, int q,
-                             int cap, int lane, const int64_t* __restrict__ ob,
-                             const int64_t* __restrict__ oa) {
-    const int g = q - p;
-    int start[9];
-    int tot = 0;
-    for (int l = 1; l <= 4; l++) {  // left explicit (right separable) path lists
-        start[l - 1] = tot;
-        const bool ok = !sep_left(p, l) && g - 2 - l >= 8;
-        tot += ok ? I.fwd_off()[a1 * 4 + l] - I.fwd_off()[a1 * 4 + l - 1] : 0;
-    }
-    for (int l = 1; l <= 4; l++) {  // right explicit (left separable) path lists
-        start[3 + l] = tot;
-        const bool ok = !sep_right(q, l) && g - 2 - l >= 8;
-        tot += ok ? I.bwd_off()[b1 * 4 + l] - I.bwd_off()[b1 * 4 + l - 1] : 0;
-    }
-    start[8] = tot;
-    int64_t best = kINF;
-    for (int idx = lane; idx < tot; idx += 64) {
-        int k = 0;
-        while (k < 7 && start[k + 1] <= idx) k++;
-        const int i = idx - start[k];
-        if (k < 4) {
-            const int l1 = k + 1, X = l1 == 1 ? 2 : 0, e = I.fwd_off()[a1 * 4 + l1 - 1] + i;
-            const int fm = I.fwd_meta()[e], c = fm >> 4, xi = (fm >> 2) & 3, xk = fm & 3;
-            const int64_t rs = I.RS()[rs_idx(c, g - 2 - l1, l1, xk)], o = ob[X * 4 + xi];
-            if (rs < kINF && o < kINF) best = mn(best, Uab + I.fwd_cost()[e] + o + rs);
-        } else {
-            const int l2 = k - 3, X = l2 == 1 ? 2 : 0, e = I.bwd_off()[b1 * 4 + l2 - 1] + i;
-            const int bm = I.bwd_meta()[e], d = bm >> 4, xl = (bm >> 2) & 3, xj = bm & 3;
-            const int64_t ls = I.LS()[rs_idx(d, g - 2 - l2, l2, xl)], o = oa[X * 4 + xj];
-            if (ls < kINF && o < kINF) best = mn(best, Uab + I.bwd_cost()[e] + o + ls);
+__device__ __forceinline__ void closed_pair(const IT& I, const SmallE& S, const int32_t* __restrict__ spec, int p, int q,
+                            int a1, int b1, int tm, int lane, PairScratch& X, int64_t* wout) {
+    const int g = q - p, s = I.shift, m = g - 2;
+    const int cap = min(g - 7, kMaxLoop);
+    const int pl = p % 3, pr = (q - 2) % 3;
+    // listed path lengths: up to 3 bases inside one codon, and always 1 and 2 (the small-loop tables)
+    const int lmax = pl == 2 ? 3 : 2, rmax = pr == 2 ? 3 : 2;
+    const bool lsep2 = pl == 1, rsep2 = pr == 0;  // a 2-base segment is separable
+    // path list bounds: lanes 0-3 starts of the left lists of length 1..4, lanes 4-7 of the right ones
+    const int offv = lane < 4 ? I.fwd_off()[a1 * 4 + lane] : I.bwd_off()[b1 * 4 + (lane & 3)];
+    const int f0 = __builtin_amdgcn_readlane(offv, 0), f1 = __builtin_amdgcn_readlane(offv, 1),
+              f2 = __builtin_amdgcn_readlane(offv, 2), f3 = __builtin_amdgcn_readlane(offv, 3);
+    const int r0 = __builtin_amdgcn_readlane(offv, 4), r1 = __builtin_amdgcn_readlane(offv, 5),
+              r2 = __builtin_amdgcn_readlane(offv, 6), r3 = __builtin_amdgcn_readlane(offv, 7);
+    const int64_t a1row = uni(I.rowoff()[a1]) - I.off()[p + 2];
+    // hairpin and both-separable interior loops: lane = 16 K + 4 xi + xj
+    const int K = lane >> 4, xi4 = (lane >> 2) & 3, xj4 = lane & 3;
+    const int64_t al = I.alphaU()[a1 * 4 + xi4], be = I.betaU()[b1 * 4 + xj4];
+    const int64_t mini = (g >= 12 && (K & 1)) ? I.MINI()[mini_idx(p, g, K >> 1)] : kINF;
+    const int32_t hpi = I.hp_init()[m];
+    const int64_t hp = m >= 5 && m != 6 ? fx(hpi, s) + I.P()[(q - 2) / 3] - I.P()[(p + 2) / 3 + 1] : kINF;
+    // bulges of >= 3 bases (lanes 0-27 right side unpaired, 32-59 left side) and the multiloop (lane 63)
+    int64_t ta = kINF;
+    {
+        const int l = 3 + (lane & 31);
+        const bool right = lane < 32;
+        const int64_t* src = right ? I.BI() + (int64_t)a1 * kLMRing + ((m - l) & (kLMRing - 1))
+                                   : I.BJ() + (int64_t)b1 * kLMRing + ((m - l) & (kLMRing - 1));
+        const bool ok = l <= cap;
+        if (lane == 63) src = I.S2() + a1row + b1;
+        const int lc = ok ? l : 3;
+        const int hi = right ? (q - 1) / 3 : (p + 1 + lc) / 3, lo = right ? (q - 1 - lc) / 3 + 1 : (p + 1) / 3 + 1;
+        const int64_t v = *src, ph = I.P()[hi] - I.P()[lo];
+        const int64_t tl = I.tail()[a1];
+        if (lane == 63) {
+            ta = v + fx(S.ml_closing + S.ml_intern, s);
+        } else if (ok) {
+            ta = v + ph + (right ? 0 : tl) + fx(S.bulge[lc], s);
         }
     }
-    // 2x3 with the left side explicit, 3x2 with the right side explicit: with kSpread one label
-    // path of the explicit side per lane, else lane 0 (2x3) and lane 1 (3x2) walk them all (the
-    // spread costs the 8- and 16-wave span kernels registers they do not have under their caps)
-    if (kSpread) {
-        if (cap >= 5 && !sep_left(p, 2) && sep_right(q, 3))
-            best = mn(best, rsep_pair(I, S, a1, Uab, 2, 3, p + 3, q - 4, q, ob, lane, 64));
-        if (cap >= 5 && sep_left(p, 3) && !sep_right(q, 2))
-            best = mn(best, lsep_pair(I, S, b1, Uab, 3, 2, p + 4, q - 3, p, oa, lane, 64));
-    } else {
-        if (lane == 0 && cap >= 5 && !sep_left(p, 2) && sep_right(q, 3))
-            best = mn(best, rsep_pair(I, S, a1, Uab, 2, 3, p + 3, q - 4, q, ob, 0, 1));
-        if (lane == 1 && cap >= 5 && sep_left(p, 3) && !sep_right(q, 2))
-            best = mn(best, lsep_pair(I, S, b1, Uab, 3, 2, p + 4, q - 3, p, oa, 0, 1));
+    X.T[lane] = kINF;
+    if (lane < 24) (&X.AB[0][0][0])[lane] = kINF;
+    wave_lds_order();
+    // one-sided: explicit paths of length l (not separable) against RS / LS, and the 2x3 / 3x2 loops,
+    // whose mismatch class differs from the rest of their row, against IDL / JDL
+    {
+        const int ne = (lsep2 ? f1 : lmax == 3 ? f3 : f2) - f0, nr = (rsep2 ? r1 : rmax == 3 ? r3 : r2) - r0;
+        for (int idx = lane; idx < ne + nr; idx += 64) {
+            const bool left = idx < ne;
+            const int e = left ? f0 + idx : r0 + idx - ne;
+            const int l = left ? 1 + (e >= f1) + (e >= f2) : 1 + (e >= r1) + (e >= r2);
+            const int meta = left ? I.fwd_meta()[e] : I.bwd_meta()[e];
+            const int64_t cost = left ? I.fwd_cost()[e] : I.bwd_cost()[e];
+            const int st = meta >> 4;
+            // label next to the inner pair, label next to the closing pair
+            const int in = left ? meta & 3 : (meta >> 2) & 3, out = left ? (meta >> 2) & 3 : meta & 3;
+            const int64_t v = left ? I.RS()[rs_idx(st, m - l, l, in)] : I.LS()[rs_idx(st, m - l, l, in)];
+            const bool x23 = left ? (l == 2 && pr != 2) || (l == 3 && rsep2) : (l == 2 && pl != 2) || (l == 3 && lsep2);
+            int64_t w = kINF;
+            if (x23) {
+                w = left ? I.IDL()[ring_idx(st, m - 5, 1, in)] : I.JDL()[ring_idx(st, m - 5, 1, in)];
+                w += fx(interior_base(S, 2, 3), s) + (left ? PRt(I, q, 5 - l) : PLt(I, p, 5 - l));
+            }
+            int64_t* ab = &X.AB[left ? 0 : 1][0][0];
+            if (v < kHalfINF) lds_min(ab + (l == 1 ? 4 : 0) + out, cost + v);
+            if (w < kHalfINF) lds_min(ab + 8 + out, cost + w);
+        }
     }
-    return best;
+    if (lane < 6) wout[lane] = kINF;
+    // explicit loops, 64 path combinations a round (nearly always one round)
+    const int nl = 1 + (lmax == 3 ? f3 : f2) - f0, nr = 1 + (rmax == 3 ? r3 : r2) - r0;
+    const int tot = nl * nr, rcp = (65536 + nr - 1) / nr;
+    int64_t vin[6], bs;
+    int B0, St, Sr;
+    bool spl, half;
+    // this lane's special loop closed by type t: byte address B0 + t St + rev(t') Sr, entries of 4 or
+    // (1x2, 2x1, 2x2) 2 bytes
+    auto special = [&](int t) {
+        int64_t v = kINF;
+#pragma unroll
+        for (int tp = 0; tp < 6; tp++) {
+            const bool fin = spl && vin[tp] < kINF;
+            if (!__ballot(fin)) continue;
+            const int ad = B0 + type_rev(tp) * Sr + t * St;
+            const int w = *reinterpret_cast<const int*>(reinterpret_cast<const char*>(&S) + (ad & ~3));
+            const int e2 = half ? ((ad & 2) ? w >> 16 : (int)(int16_t)w) : w;
+            v = mn(v, (fin ? bs + vin[tp] : kINF) + fx(e2, s));
+        }
+        return v;
+    };
+    for (int idx = lane;; idx += 64) {
+        const bool in_list = idx < tot;
+        const int i = in_list ? (int)(((unsigned)idx * (unsigned)rcp) >> 16) : 0, j = in_list ? idx - i * nr : 0;
+        const int ef = f0 + i - 1, er = r0 + j - 1;
+        const int l1 = i == 0 ? 0 : 1 + (ef >= f1) + (ef >= f2), l2 = j == 0 ? 0 : 1 + (er >= r1) + (er >= r2);
+        const bool small = l1 <= 2 && l2 <= 2;
+        const bool ok = in_list && l1 + l2 <= max(cap, 0) &&
+                        (small || (l1 > 0 && l2 > 0 && !(l1 == 2 && lsep2) && !(l2 == 2 && rsep2)));
+        const int fm = i == 0 ? a1 << 4 : I.fwd_meta()[ef], bm = j == 0 ? b1 << 4 : I.bwd_meta()[er];
+        const int64_t fc = i == 0 ? 0 : I.fwd_cost()[ef], bc = j == 0 ? 0 : I.bwd_cost()[er];
+        const int64_t crow = i == 0 ? a1row : I.fwd_crow()[ef];
+        const int xi = (fm >> 2) & 3, xk = fm & 3, xl = (bm >> 2) & 3, xj = bm & 3;
+        const longlong2* vp = reinterpret_cast<const longlong2*>(I.V() + (ok ? crow + (bm >> 4) : a1row + b1) * 6);
+        const longlong2 v01 = vp[0], v23 = vp[1], v45 = vp[2];
+        vin[0] = v01.x, vin[1] = v01.y, vin[2] = v23.x, vin[3] = v23.y, vin[4] = v45.x, vin[5] = v45.y;
+        // type dependence of the loop: a special table (l1, l2 <= 2 except the 2-base bulge) or a
+        // boundary class (1 generic, 2 1xn, 3 2x3, 4 AU penalty only)
+        spl = small && (l1 + l2 != 2 || l1 == 1);
+        const int KK = small ? 4 : (l1 == 1 || l2 == 1) ? 2 : l1 + l2 == 5 ? 3 : 1;
+        const int32_t cst = !small ? interior_base(S, l1, l2) : l1 + l2 == 1 ? S.bulge[1] : spl ? 0 : S.bulge[2];
+        bs = (ok ? fc + bc : kBarred) + fx(cst, s);
+        // inner minimum over the inner pair's types for the boundary classes
+        {
+            const int32_t* tab = &S.mmH[0][0][0] + KK * 96 + xl * 4 + xk;
+            int64_t in = kINF;
+#pragma unroll
+            for (int tp = 0; tp < 6; tp++) in = mn(in, vin[tp] + fx(tab[type_rev(tp) * 16], s));
+            in += bs;
+            if (!spl) {
+                if (KK == 4) ta = mn(ta, in);
+                else if (in < kHalfINF) lds_min(&X.T[KK * 16 + xi * 4 + xj], in);
+            }
+        }
+        half = l1 + l2 > 2;
+        if (l1 + l2 <= 1) {
+            B0 = offsetof(SmallE, stack), St = 24, Sr = 4;
+        } else if (l1 + l2 == 2) {
+            B0 = (int)offsetof(SmallE, int11) + (xi * 4 + xj) * 4, St = 384, Sr = 64;
+        } else if (l1 + l2 == 4) {
+            B0 = (int)offsetof(SmallE, int22) + (xi * 64 + xk * 16 + xl * 4 + xj) * 2, St = 3072, Sr = 512;
+        } else if (l1 == 1) {
+            B0 = (int)offsetof(SmallE, int21) + (xi * 16 + xl * 4 + xj) * 2, St = 768, Sr = 128;
+        } else {
+            B0 = (int)offsetof(SmallE, int21) + (xl * 16 + xi * 4 + xk) * 2, St = 128, Sr = 768;
+        }
+        if (!spl) B0 = 0, St = 0, Sr = 0, half = true;  // any valid entry: added to an infinite value
+        if (idx - lane + 64 >= tot) break;
+#pragma unroll 1
+        for (int t = 0; t < 6; t++) {
+            if (!((tm >> t) & 1)) continue;
+            const int64_t v = wave_min(special(t));
+            if (lane == 0) wout[t] = mn(wout[t], v);
+        }
+    }
+    wave_lds_order();
+    // T: explicit generic minima, hairpin / both-separable, one-sided
+    int64_t T = X.T[lane];
+    {
+        const int64_t x = K == 0 ? hp : mini;
+        if (al < kINF && be < kINF && x < kINF) T = mn(T, al + be + x);
+        if (K > 0) {
+            const int64_t A = X.AB[0][K - 1][xi4], B = X.AB[1][K - 1][xj4];
+            if (A < kINF && be < kINF) T = mn(T, A + be);
+            if (al < kINF && B < kINF) T = mn(T, al + B);
+        }
+    }
+    ta = wave_min(ta);
+    const int32_t* tab = &S.mmH[0][0][0] + K * 96 + (lane & 15);
+#pragma unroll 1
+    for (int t = 0; t < 6; t++) {
+        if (!((tm >> t) & 1)) continue;
+        const int64_t v = mn(wave_min(mn(special(t), T + fx(tab[t * 16], s))), ta + fx(au_pen(S, t), s));
+        if (lane == 0) wout[t] = norm_inf(mn(wout[t], v));
+    }
+    if (m == 3 || m == 4 || m == 6) {
+#pragma unroll 1
+        for (int t = 0; t < 6; t++) {
+            if (!((tm >> t) & 1)) continue;
+            const int64_t v = wave_min(special_hairpin(I, S, spec, a1, b1, t, g, lane));
+            if (lane == 0) wout[t] = mn(wout[t], v);
+        }
+    }
 }
 
 // ---- the work of one layer pair (p, q) in span step g: one workgroup of several waves ----------
-struct GroupCounters {
-    unsigned long long visits, feasible;
-};
-
-
 // The threads that work on one layer pair: the whole workgroup (ordered by workgroup barriers),
 // or a single wavefront of a workgroup whose waves each work on their own pair (ordered within the
 // wave; a workgroup barrier there would pair up unrelated points of different waves).
@@ -394,225 +406,105 @@ struct WaveTeam {
     }
 };
 
-// A value every lane of the wave holds (read from one LDS address), moved to a scalar register so
-// that the addresses and loop bounds derived from it stay scalar.
-__device__ __forceinline__ int uni(int x) { return __builtin_amdgcn_readfirstlane(x); }
-__device__ __forceinline__ int64_t uni(int64_t x) {
-    const int hi = __builtin_amdgcn_readfirstlane((int)(x >> 32)), lo = __builtin_amdgcn_readfirstlane((int)x);
-    return (int64_t)(((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo);
-}
-
 template <int NW>  // waves per workgroup
 struct GroupShared {
-    int64_t vbuf[kMaxWidth * kMaxWidth][6];  // typed closed values of this layer pair's cells
-    int64_t cellB[kMaxWidth * kMaxWidth];
-    int keep[kMaxWidth * kMaxWidth];          // 0 none, 1 strict, 2 retained non-strict
-    uint8_t combo[kMaxWidth * kMaxWidth * 6]; // (cell, type) jobs with an out-edge of label x
-    int ncombo;
-    int64_t red[NW][2];
-    int64_t red2[NW][2];
-    LabPair lab[NW][16];
-    // the pair's automaton and segment metadata, read once per pair
-    int adst[kMaxWidth][4];      // out-edge targets of the left states by label (-1 none)
-    int64_t aU[kMaxWidth][4];    //   and their costs
-    int bin[kMaxWidth + 1];      // in-edge range starts of the right states (and the end)
-    int bcnt[kMaxWidth], bcap[kMaxWidth];
+    int64_t w[kMaxWidth * kMaxWidth][6];      // W_t(a1, b1) of the pair's inner boundary pairs
+    union {
+        PairScratch scratch[NW];                 // phase 1
+        int64_t vbuf[kMaxWidth * kMaxWidth][6];  // phase 2: typed closed values of the pair's cells
+    };
+    int64_t s2[kMaxWidth * kMaxWidth];        // S2 of the cells
+    int64_t ps[kMaxWidth * kMaxWidth];        // P_S of the cells; once they are completed, B
+    int64_t aU[kMaxWidth][4], bU[kMaxWidth][4];  // edge costs out of the left states and of layer q - 1
     int64_t boff[kMaxWidth];     // committed count, capacity and offset of each C_b
+    int bcnt[kMaxWidth], bcap[kMaxWidth];
+    // the edges' targets by label, counted from the first state of their layer (-1 none)
+    int8_t adst[kMaxWidth][4], bdst[kMaxWidth][4];
+    int8_t keep[kMaxWidth * kMaxWidth];       // 0 none, 1 strict, 2 retained non-strict
 };
 
-// Bulges of >= 3 bases through the in-edge b1 -> b: the unpaired side costs its gap (tail +
-// whole codons), read from the BI / BJ rings.
+// One-sided tables of state k of the pair for span g (left states c of layer p: RS, right states d of
+// layer q: LS), by one wave: the minimum over the separable side's length of IDL / JDL of spans
+// <= g - 3 + loop energy + whole codons, per explicit length 1..3 and inner label.  They read nothing
+// this span writes.
 template <class IT>
-__device__ int64_t long_bulges(const IT& I, const SmallE& S, int t, int a1, int b1, int64_t Uab, int p,
-                               int q, int cap, int lane) {
+__device__ __forceinline__ void produce_one_sided(const IT& I, const SmallE& S, int p, int g, bool left, int st, int lane) {
     const int s = I.shift;
-    int64_t v = kINF;
-    for (int k = lane; k < kPairCnt[kListBulgeSep][0][cap]; k += 64) {
-        const int code = kPairList[kListBulgeSep][0][k], l1 = code & 31, l2 = (code >> 5) & 31;
-        const int l = l1 + l2, cl = p + 1 + l1, dl = q - 1 - l2;
-        int64_t w;
-        if (l1 == 0) {
-            const int64_t bi = I.BI()[(int64_t)a1 * kLMRing + ((dl - cl) & (kLMRing - 1))];
-            w = bi >= kINF ? kINF : Uab + bi + I.P()[(q - 1) / 3] - I.P()[dl / 3 + 1];
-        } else {
-            const int64_t bj = I.BJ()[(int64_t)b1 * kLMRing + ((dl - cl) & (kLMRing - 1))];
-            w = bj >= kINF ? kINF : Uab + bj + I.tail()[a1] + I.P()[cl / 3] - I.P()[(p + 1) / 3 + 1];
-        }
-        if (w < kINF) v = mn(v, w + fx(S.bulge[l] + au_pen(S, t), s));
+    // lane = 4 * grp + lab covers separable lengths 3 + grp and 19 + grp
+    const int lab = lane & 3, grp = lane >> 2;
+    const int qc = p + g + 1, pc = p - 1;  // the consumer's closing layer of the separable side
+    int64_t o[3] = {kINF, kINF, kINF};
+    int64_t in0[2], in2[2], pt[2];
+#pragma unroll
+    for (int h = 0; h < 2; h++) {
+        const int ls = 3 + grp + 16 * h, g2 = g - ls;
+        const bool ok = ls <= 29 && g2 >= 5 && (left ? sep_right(qc, ls) : pc >= 0 && sep_left(pc, ls));
+        const int l = ok ? ls : 3, gr = ok ? g2 : 0;
+        const int64_t* T = left ? I.IDL() : I.JDL();
+        in0[h] = T[ring_idx(st, gr, 0, lab)];
+        in2[h] = T[ring_idx(st, gr, 2, lab)];
+        // P terms of the separable side, at clamped positions where it has none
+        const int hi = left ? (qc - 2) / 3 : (max(pc, 0) + l) / 3, lo = left ? (max(qc - l, 0)) / 3 + 1 : (max(pc, 0) + 2) / 3 + 1;
+        pt[h] = I.P()[min(hi, I.A)] - I.P()[min(lo, I.A)];
+        if (!ok) in0[h] = in2[h] = kINF;
     }
-    return v;
-}
-
-// One part of the typed closed value V_t(a, b), with the lanes of one wave:
-//   part 0: hairpin, stacks and bulges of 1-2 bases;
-//   part 1: interior loops with a separable side (one-sided, both separable);
-//   parts 2 .. nparts-1: interior loops with both sides explicit (labelled short paths), whose
-//   flattened items are dealt to these parts in blocks of 64;
-//   bulges of >= 3 bases and the multiloop closure: the last part when nparts >= 4, else part 0.
-// Returns this lane's minimum.  The parts of one (cell, type) run on different waves and meet in
-// an LDS minimum, or, in a one-wave group, run one after another into one wave reduction.
-template <bool kSpread, class IT>
-__device__ __forceinline__ int64_t closed_lanes(const IT& I, const SmallE& S, const EnergyTables* __restrict__ E,
-                               const int32_t* __restrict__ spec, int a, int b, int t, int p, int q,
-                               int part, int nparts, int64_t mini0, int64_t mini1, int lane, LabPair* lab,
-                               int a1, int64_t Ua, int ib0, int ib1) {
-    // a1 / Ua: the out-edge of a labelled x (type t's first base) and its cost; ib0 / ib1: b's
-    // in-edge range
-    const int g = q - p, s = I.shift;
-    const int y = kTY[t];
-    const int ph = (p % 3) * 3 + (q % 3), cap = min(g - 7, kMaxLoop);
-    int64_t v = kINF;
-    // bulges of >= 3 bases and the multiloop closure go with the last labelled part when the
-    // labelled list is split, else with part 0
-    const bool long_here = part == (nparts >= 4 ? nparts - 1 : 0);
-    // multiloop closure (ML_closing + ML_intern + AU + S2 of the interior (a1, b1)) over the same
-    // in-edges: b1 lies in layer q - 1 and a1 in layer p + 1, at least 10 layers apart from
-    // g = 12 on; its S2 value is read before the in-edge's other loops so that it overlaps them
-    const bool ml_here = long_here && g >= 12;
-    const int64_t a1row = ml_here ? I.rowoff()[a1] - I.off()[p + 2] : 0;
-    const int64_t mlc = fx(S.ml_closing + S.ml_intern + au_pen(S, t), s);
-    if (part == 0) {
-        v = hairpin_lane(I, S, spec, a, b, t, a1, Ua, p, g, lane);
-        if (g >= 7) {
-            for (int eb = ib0; eb < ib1; eb++) {
-                if (I.in_lab()[eb] != y) continue;
-                const int b1 = I.in_src()[eb];
-                const int64_t Uab = Ua + I.in_U()[eb];
-                const int64_t s2 = ml_here ? I.S2()[a1row + b1] : kINF;
-                v = mn(v, bulge_lanes(I, S, t, a1, b1, Uab, p, q, cap, lane));
-                if (long_here) v = mn(v, long_bulges(I, S, t, a1, b1, Uab, p, q, cap, lane));
-                if (s2 < kINF) v = mn(v, s2 + Uab + mlc);
-            }
-        }
-    } else if (part >= 2) {
-        if (g >= 7) {
-            for (int eb = ib0; eb < ib1; eb++) {
-                if (I.in_lab()[eb] != y) continue;
-                const int b1 = I.in_src()[eb];
-                const int64_t Uab = Ua + I.in_U()[eb];
-                const int64_t s2 = ml_here ? I.S2()[a1row + b1] : kINF;
-                v = mn(v, labelled_pairs(I, S, E, t, a1, b1, Uab, ph, cap, lane, lab, part - 2, nparts - 2));
-                if (long_here) v = mn(v, long_bulges(I, S, t, a1, b1, Uab, p, q, cap, lane));
-                if (s2 < kINF) v = mn(v, s2 + Uab + mlc);
-            }
-        }
-    } else {
-        if (g >= 7) {
-            const int64_t* oa = I.OA() + (int64_t)(a1 * 6 + t) * 12;
-            for (int eb = ib0; eb < ib1; eb++) {
-                if (I.in_lab()[eb] != y) continue;
-                const int b1 = I.in_src()[eb];
-                const int64_t Uab = Ua + I.in_U()[eb];
-                v = mn(v, one_sided<kSpread>(I, S, a1, b1, Uab, p, q, cap, lane, I.OB() + (int64_t)(b1 * 6 + t) * 12, oa));
-            }
-        }
-        if (g >= 12) {
-            // both segments separable: OUT(a1, b1, t) + layer-pair minimum
-            const int nbx = (ib1 - ib0) * 32;
-            for (int k = lane; k < nbx; k += 64) {
-                const int eb = ib0 + (k >> 5), X = (k >> 4) & 1, xi = (k >> 2) & 3, xj = k & 3;
-                if (I.in_lab()[eb] != y) continue;
-                const int64_t mini = X ? mini1 : mini0;
-                const int64_t al = I.alphaU()[a1 * 4 + xi], be = I.betaU()[I.in_src()[eb] * 4 + xj];
-                if (mini >= kINF || al >= kINF || be >= kINF) continue;
-                v = mn(v, Ua + I.in_U()[eb] + al + be + fx(mmx(S, X, t, xi, xj), s) + mini);
-            }
+#pragma unroll
+    for (int h = 0; h < 2; h++) {
+        const int ls = 3 + grp + 16 * h;
+#pragma unroll
+        for (int le = 1; le <= 3; le++) {
+            if (le + ls > kMaxLoop || (le == 2 && ls == 3)) continue;
+            // the energy depends on |l1 - l2| and l1 + l2 only
+            o[le - 1] = mn(o[le - 1], (le == 1 ? in2[h] : in0[h]) + pt[h] + fx(interior_base(S, le, ls), s));
         }
     }
-    return v;  // this lane's minimum
+#pragma unroll
+    for (int j = 0; j < 3; j++) {
+        // over the lanes that share lane & 3: rotations by 4 and 8 within each row, then rows
+        o[j] = mn(o[j], dpp64<kDppRor4>(o[j]));
+        o[j] = mn(o[j], dpp64<kDppRor8>(o[j]));
+        o[j] = mn(o[j], shfl_xor64(o[j], 16));
+        o[j] = mn(o[j], shfl_xor64(o[j], 32));
+    }
+    if (grp < 3) {
+        int64_t* T = left ? I.RS() : I.LS();
+        T[rs_idx(st, g, grp + 1, lab)] = norm_inf(grp == 0 ? o[0] : grp == 1 ? o[1] : o[2]);
+    }
 }
 
-template <bool kSpread, class IT>
-__device__ int64_t closed_part(const IT& I, const SmallE& S, const EnergyTables* __restrict__ E,
-                               const int32_t* __restrict__ spec, int a, int b, int t, int p, int q,
-                               int part, int nparts, int64_t mini0, int64_t mini1, int lane, LabPair* lab,
-                               int a1, int64_t Ua, int ib0, int ib1) {
-    return norm_inf(wave_min(closed_lanes<kSpread>(I, S, E, spec, a, b, t, p, q, part, nparts, mini0, mini1, lane,
-                                                   lab, a1, Ua, ib0, ib1)));
-}
-
-// Per-state tables of span g for later two-loops, one state per wave (lanes as noted):
-//   left state c (layer p):  RS(c, g), IDL(c, g), BI(c, g) and its LM contribution;
-//   right state d (layer q): LS(d, g), JDL(d, g), BJ(d, g).
-// RS / LS read IDL / JDL of spans <= g - 3 only; the rest reads this group's typed values.
+// Inner minima of state k of the pair for span g from its typed values, by one wave: IDL (left
+// states, with their LM contribution) or JDL (right states), and the bulge rings BI / BJ.
 template <int NW, class IT>
-__device__ void produce_state(const IT& I, const SmallE& S, const GroupShared<NW>& G, int p, int g,
-                              int k, int a_lo, int b_lo, int wa, int wb, int lane,
-                              int64_t& lm0, int64_t& lm1) {
-    const int s = I.shift;
-    const bool left = k < wa;
-    const int i = left ? k : k - wa, st = left ? a_lo + i : b_lo + i;
-    // one-sided tables: lane = 4 * grp + lab covers separable lengths 3 + grp and 19 + grp;
-    // outputs per explicit length 1..4, minimised over the 16 lane groups
-    {
-        const int lab = lane & 3, grp = lane >> 2;
-        const int qc = p + g + 1, pc = p - 1;  // consumer closing layers (left / right state)
-        int64_t o[4] = {kINF, kINF, kINF, kINF};
-        // one separable length at a time in workgroup teams: unrolling keeps both lengths' ring
-        // values and tails live at once, which made the 80-VGPR instantiation spill here; a
-        // one-wave team (128 VGPRs) issues both lengths' loads together
-#pragma unroll (NW == 1 ? 2 : 1)
-        for (int h = 0; h < 2; h++) {
-            const int ls = 3 + grp + 16 * h, g2 = g - ls;
-            if (ls > 29 || g2 < 5) continue;
-            if (left ? !sep_right(qc, ls) : (pc < 0 || !sep_left(pc, ls))) continue;
-            const int64_t ptail = left ? PRt(I, qc, ls) : PLt(I, pc, ls);
-            const int64_t in0 = left ? I.IDL()[ring_idx(st, g2, 0, lab)] : I.JDL()[ring_idx(st, g2, 0, lab)];
-            const int64_t in2 = left ? I.IDL()[ring_idx(st, g2, 2, lab)] : I.JDL()[ring_idx(st, g2, 2, lab)];
-#pragma unroll
-            for (int le = 1; le <= 4; le++) {
-                if (le + ls > kMaxLoop || (le == 2 && ls == 3)) continue;
-                const int64_t in = le == 1 ? in2 : in0;
-                if (in >= kINF) continue;
-                const int32_t eb = left ? interior_base(S, le, ls) : interior_base(S, ls, le);
-                o[le - 1] = mn(o[le - 1], in + fx(eb, s) + ptail);
-            }
-        }
-#pragma unroll
-        for (int j = 0; j < 4; j++) {
-            // over the lanes that share lane & 3: rotations by 4 and 8 within each row, then rows
-            o[j] = mn(o[j], dpp64<kDppRor4>(o[j]));
-            o[j] = mn(o[j], dpp64<kDppRor8>(o[j]));
-            o[j] = mn(o[j], shfl_xor64(o[j], 16));
-            o[j] = mn(o[j], shfl_xor64(o[j], 32));
-        }
-        if (grp == 0) {
-            int64_t* T = left ? I.RS() : I.LS();
-#pragma unroll
-            for (int j = 0; j < 4; j++) T[rs_idx(st, g, j + 1, lab)] = norm_inf(o[j]);
-        }
-    }
+__device__ __forceinline__ void produce_inner(const IT& I, const SmallE& S, const GroupShared<NW>& G, int p, int g,
+                              bool left, int i, int a_lo, int b_lo, int wa, int wb, int lane, int64_t& lm0, int64_t& lm1) {
+    const int s = I.shift, st = left ? a_lo + i : b_lo + i, nother = left ? wb : wa;
     // inner minima: lane = 16 * X + 4 * xx + z (48 lanes), minimised over z
     {
         const int X = lane >> 4, xx = (lane >> 2) & 3, z = lane & 3;
+        const int cls = X == 0 ? 1 : X == 1 ? 3 : 2;  // boundary class of X (row 3 repeats 1xn and is not stored)
+        const int32_t* tab = &S.mmH[0][0][0] + cls * 96 + (left ? z * 4 + xx : xx * 4 + z);
+        const int64_t be = I.betaU()[st * 4 + xx];
         int64_t acc = kINF;
-        if (X < 3) {
-            const int nother = left ? wb : wa;
-            for (int o = 0; o < nother; o++) {
-                const int ci = left ? i * wb + o : o * wb + i;
-                // left: vary x_{l+1} = z with alpha(d); right: vary x_{k-1} = z with beta(c)
-                const int64_t w = left ? I.alphaU()[(b_lo + o) * 4 + z] : I.betaU()[(a_lo + o) * 4 + z];
-                if (w >= kINF) continue;
-                for (int tp = 0; tp < 6; tp++) {
-                    const int64_t vin = G.vbuf[ci][tp];
-                    if (vin < kINF)
-                        acc = mn(acc, vin + w + fx(left ? mmx(S, X, kRev[tp], z, xx) : mmx(S, X, kRev[tp], xx, z), s));
-                }
+        for (int o = 0; o < nother; o++) {
+            const int ci = left ? i * wb + o : o * wb + i;
+            // left: vary x_{l+1} = z with alpha(d); right: vary x_{k-1} = z with beta(c)
+            const int64_t w = left ? I.alphaU()[(b_lo + o) * 4 + z] : I.betaU()[(a_lo + o) * 4 + z];
+#pragma unroll
+            for (int tp = 0; tp < 6; tp++) {
+                const int64_t vin = uni(G.vbuf[ci][tp]);
+                if (vin >= kINF) continue;
+                const int64_t v = vin + w + fx(tab[type_rev(tp) * 16], s);
+                if (w < kINF) acc = mn(acc, v);
             }
         }
         acc = mn(acc, dpp64<kDppXor1>(acc));
         acc = mn(acc, dpp64<kDppXor2>(acc));
         acc = norm_inf(acc);
         if (X < 3 && z == 0) {
-            if (left) {
-                I.IDL()[ring_idx(st, g, X, xx)] = acc;
-                const int64_t be = I.betaU()[st * 4 + xx];
-                if (acc < kINF && be < kINF) {
-                    if (X == 0) lm0 = mn(lm0, acc + be);
-                    if (X == 1) lm1 = mn(lm1, acc + be);
-                }
-            } else {
-                I.JDL()[ring_idx(st, g, X, xx)] = acc;
+            (left ? I.IDL() : I.JDL())[ring_idx(st, g, X, xx)] = acc;
+            if (left && acc < kINF && be < kINF) {
+                if (X == 0) lm0 = mn(lm0, acc + be);
+                if (X == 1) lm1 = mn(lm1, acc + be);
             }
         }
     }
@@ -620,40 +512,71 @@ __device__ void produce_state(const IT& I, const SmallE& S, const GroupShared<NW
     {
         const int o = lane / 6, tp = lane - 6 * o;
         int64_t acc = kINF;
-        if (lane < 24 && o < (left ? wb : wa)) {
+        if (lane < 24 && o < nother) {
             const int64_t vin = G.vbuf[left ? i * wb + o : o * wb + i][tp];
             if (vin < kINF) acc = vin + (left ? I.tail()[b_lo + o] : 0) + fx(au_pen(S, tp), s);
         }
         acc = norm_inf(wave_min(acc));
-        if (lane == 0) {
-            if (left) I.BI()[(int64_t)st * kLMRing + (g & (kLMRing - 1))] = acc;
-            else I.BJ()[(int64_t)st * kLMRing + (g & (kLMRing - 1))] = acc;
-        }
+        if (lane == 0) (left ? I.BI() : I.BJ())[(int64_t)st * kLMRing + (g & (kLMRing - 1))] = acc;
     }
 }
 
-// The multiloop part of one cell (a, b) of layer pair (p, q) given its direct branch cost Bv
-// (eq. 2), by one wave: S2 (eq. 7: in-edge extensions, then the committed prefix of C_b with
-// the gathered S1(a, c)), P_S, S1 = min(B, P_S) and the retention test B < P_S (eq. 6).  Every
-// scan reads only entries committed by earlier spans (their start states lie in layers after
-// p, so the guard of eq. 7 holds for each).  Lane 0 writes B, S2 and S1 and returns the keep
-// flag: 0 none, 1 strict, 2 retained non-strict (retain-all control).
+// Both-separable interior minima of layer pair (p, q), q - p >= 12, into the ring MINI, by one wave:
+// LM of the inner layer pairs (spans <= q - p - 8) + loop energy + whole codons.
 template <class IT>
-__device__ int multiloop_cell(const IT& I, int a, int b, int p, int q, int64_t cell, int64_t Bv, int lane,
-                              GroupCounters& ctr, int committed, int64_t cbase, int ib0, int ib1,
-                              const int* adst, const int64_t* aU) {
-    // Every edge joins consecutive layers, so the in-edge sources of b lie in layer q - 1 and the
-    // out-edge targets of a in layer p + 1: both are inner states of the pair exactly when g >= 2,
-    // and their cells are found without reading their layers.  committed / cbase: C_b's count and
-    // offset; ib0 / ib1: b's in-edge range; adst / aU: a's out-edge targets by label (-1 none)
-    // and their costs.
+__device__ __forceinline__ void prepare_mini(const IT& I, const SmallE& S, int p, int q, int lane) {
+    const int s = I.shift, g = q - p, ph = (p % 3) * 3 + (q % 3), cap = min(g - 7, kMaxLoop);
+    const int cnt = kFastCnt[ph][cap];
+    int64_t m0 = kINF, m1 = kINF;
+#pragma unroll 2
+    for (int k = lane; k < cnt; k += 64) {
+        const int code = kFastList[ph][k], l1 = code & 31, l2 = code >> 5;
+        const int X = pair_class(l1, l2);
+        const int64_t lm = I.LM()[lm_idx(p + 1 + l1, g - 2 - l1 - l2, X)];
+        const int64_t v = lm + fx(interior_base(S, l1, l2), s) + PLt(I, p, l1) + PRt(I, q, l2);
+        if (X) m1 = mn(m1, v);
+        else m0 = mn(m0, v);
+    }
+    m0 = wave_min(m0);
+    m1 = wave_min(m1);
+    if (lane < 2) I.MINI()[mini_idx(p, g, lane)] = norm_inf(lane ? m1 : m0);
+}
+
+struct GroupCounters {
+    unsigned long long visits, feasible;
+};
+
+// The split part of one cell (a, b) of layer pair (p, q), by one wave: S2 (eq. 7: in-edge
+// extensions, then the committed prefix of C_b with the gathered S1(a, c)) and P_S.  Every scan
+// reads only entries committed by earlier spans (their start states lie in layers after p, so the
+// guard of eq. 7 holds for each); neither value depends on the cell's direct cost.
+template <class IT>
+__device__ __forceinline__ void multiloop_scan(const IT& I, int a, int b, int p, int q, int64_t cell, int lane, int committed,
+                               int64_t cbase, int64_t* s2_out, int64_t* ps_out) {
+    // Every edge joins consecutive layers, so the in-edge sources of b are the states of layer q - 1
+    // with an edge to b and the out-edge targets of a lie in layer p + 1: both are inner states of
+    // the pair exactly when g >= 2, and their cells are found without reading their layers.
     const int g = q - p;
     const int64_t arow = cell - b;  // cell(a, c) = arow + c for every c
     const int64_t* __restrict__ S1r = I.S1() + arow;
     const int64_t* __restrict__ S2r = I.S2() + arow;
-    int64_t s2 = kINF;
-    if (g >= 2)
-        for (int eb = ib0 + lane; eb < ib1; eb += 64) s2 = mn(s2, S2r[I.in_src()[eb]] + I.in_U()[eb] + I.mlbase_fx);
+    int64_t s2 = kINF, ps = kINF;
+    if (g >= 2) {
+        const int blo = I.off()[q - 1], n4 = 4 * (I.off()[q] - blo);
+        for (int k = lane; k < n4; k += 64) {
+            const int c = blo + (k >> 2);
+            const int64_t x2 = S2r[c], x1 = S1r[c];
+            if (I.out_dst()[blo * 4 + k] == b) {
+                const int64_t u = I.out_U()[blo * 4 + k] + I.mlbase_fx;
+                s2 = mn(s2, x2 + u);
+                ps = mn(ps, x1 + u);
+            }
+        }
+        if (lane < 4) {
+            const int ap = I.out_dst()[a * 4 + lane];
+            if (ap >= 0) ps = mn(ps, I.S1()[I.rowoff()[ap] + (b - I.off()[p + 2])] + I.out_U()[a * 4 + lane] + I.mlbase_fx);
+        }
+    }
     const int* __restrict__ cc = I.cc() + cbase;
     const int64_t* __restrict__ cB = I.cB() + cbase;
     // four entries per lane and round, their loads issued together: the gathers of S1(a, c)
@@ -669,15 +592,19 @@ __device__ int multiloop_cell(const IT& I, int a, int b, int p, int q, int64_t c
     }
     for (; k < committed; k += 64) s2 = mn(s2, S1r[cc[k] & 0x7fffffff] + cB[k]);
     s2 = norm_inf(wave_min(s2));
-    int64_t ps = s2;
-    if (g >= 2) {
-        if (lane < 4) {
-            const int ap = adst[lane];
-            if (ap >= 0) ps = mn(ps, I.S1()[I.rowoff()[ap] + (b - I.off()[p + 2])] + aU[lane] + I.mlbase_fx);
-        }
-        for (int eb = ib0 + lane; eb < ib1; eb += 64) ps = mn(ps, S1r[I.in_src()[eb]] + I.in_U()[eb] + I.mlbase_fx);
-    }
-    ps = norm_inf(wave_min(ps));
+    *s2_out = s2;
+    *ps_out = norm_inf(mn(s2, wave_min(ps)));
+}
+
+// The multiloop part of one cell given its direct branch cost Bv (eq. 2), by one wave: the split
+// part, S1 = min(B, P_S) and the retention test B < P_S (eq. 6).  Lane 0 writes B, S2 and S1 and
+// returns the keep flag: 0 none, 1 strict, 2 retained non-strict (retain-all control).
+template <class IT>
+__device__ int multiloop_cell(const IT& I, int a, int b, int p, int q, int64_t cell, int64_t Bv, int lane,
+                              GroupCounters& ctr) {
+    const int committed = I.ccnt()[b];
+    int64_t s2, ps;
+    multiloop_scan(I, a, b, p, q, cell, lane, committed, I.coff()[b], &s2, &ps);
     int keep = 0;
     if (lane == 0) {
         I.Bt()[cell] = Bv;
@@ -691,20 +618,12 @@ __device__ int multiloop_cell(const IT& I, int a, int b, int p, int q, int64_t c
     return keep;
 }
 
-// The same with the per-pair metadata read from the instance.
-template <class IT>
-__device__ int multiloop_cell(const IT& I, int a, int b, int p, int q, int64_t cell, int64_t Bv, int lane,
-                              GroupCounters& ctr) {
-    return multiloop_cell(I, a, b, p, q, cell, Bv, lane, ctr, I.ccnt()[b], I.coff()[b], I.in_start()[b],
-                          I.in_start()[b + 1], I.out_dst() + a * 4, I.out_U() + a * 4);
-}
-
 // Appends the retained entries (a, B(a, b)) of layer pair (p, q) to the segments C_b in
 // start-state order, one lane per right endpoint: the caller's workgroup owns these segments in
 // step g (endpoint ownership), so no atomics are needed and the layout is deterministic.  An
 // append beyond a segment's capacity records the earliest overflowing span instead.
 template <class IT>
-__device__ void append_candidates(const IT& I, int a_lo, int wa, int b_lo, int wb, const int* keep,
+__device__ void append_candidates(const IT& I, int a_lo, int wa, int b_lo, int wb, const int8_t* keep,
                                   const int64_t* cellB, int g, int lane, int committed, int cap,
                                   int64_t base) {
     // committed / cap / base: lane < wb's segment C_(b_lo + lane), count, capacity and offset
@@ -728,175 +647,138 @@ __device__ void append_candidates(const IT& I, int a_lo, int wa, int b_lo, int w
 
 // The same with the segments' counts, capacities and offsets read from the instance.
 template <class IT>
-__device__ void append_candidates(const IT& I, int a_lo, int wa, int b_lo, int wb, const int* keep,
+__device__ void append_candidates(const IT& I, int a_lo, int wa, int b_lo, int wb, const int8_t* keep,
                                   const int64_t* cellB, int g, int lane) {
     const bool mine = lane < wb;
     append_candidates(I, a_lo, wa, b_lo, wb, keep, cellB, g, lane, mine ? I.ccnt()[b_lo + lane] : 0,
                       mine ? I.ccap()[b_lo + lane] : 0, mine ? I.coff()[b_lo + lane] : 0);
 }
 
+// One layer pair of span step g.  Phase 1 is a list of tasks that read only earlier spans and are
+// dealt to the team's waves: the closed values W(a1, b1) of each inner boundary pair, the split
+// part of each cell, the one-sided tables of each state, and the next span's both-separable
+// minima.  After one barrier, the cells are completed (typed values, branch value, S1, retention,
+// appends) by one wave while others derive the inner minima for later two-loops.
 template <int NW, class IT, class Team = BlockTeam>
-__device__ GroupCounters span_group(const IT& I, const SmallE& S, const EnergyTables* __restrict__ E,
-                                    const int32_t* __restrict__ spec, int p, int q, GroupShared<NW>& G,
-                                    Team T = Team()) {
+__device__ __forceinline__ GroupCounters span_group(const IT& I, const SmallE& S, const int32_t* __restrict__ spec, int p, int q,
+                                    GroupShared<NW>& G, Team T = Team()) {
     const int g = q - p, s = I.shift;
-    const int tid = T.tid(), wave = tid >> 6, lane = T.lane(), nw = T.size() >> 6;
+    const int wave = T.tid() >> 6, lane = T.lane(), nw = T.size() >> 6;
     GroupCounters ctr{0, 0};
-    const int a_lo = I.off()[p], a_hi = I.off()[p + 1], b_lo = I.off()[q], b_hi = I.off()[q + 1];
-    const int wa = a_hi - a_lo, wb = b_hi - b_lo, ncell = wa * wb;
-    // both-separable interior minima of this layer pair, per class (prepared one step ahead)
-    int64_t mini0 = kINF, mini1 = kINF;
-    if (g >= 12) {
-        mini0 = I.MINI()[mini_idx(p, g, 0)];
-        mini1 = I.MINI()[mini_idx(p, g, 1)];
-    }
-    // (cell, type) jobs: the type's first label leaves a and its last label enters b (any other
-    // type is infeasible for the cell); typed values cleared.  Alongside, the pair's metadata is
-    // read once: lanes 0-15 the out-edges of the left states, 16-20 the in-edge range starts of
-    // the right states (and the end of the last), 32-35 their candidate segments.
-    if (wave == 0) {
+    const int a_lo = I.off()[p], a1_lo = I.off()[p + 1], b_lo = I.off()[q], b_hi = I.off()[q + 1], b1_lo = I.off()[q - 1];
+    const int wa = a1_lo - a_lo, wb = b_hi - b_lo, ncell = wa * wb;
+    const int wa1 = I.off()[p + 2] - a1_lo, wb1 = b_lo - b1_lo;
+    // the pair's metadata: lanes 0-15 the out-edges of the left states, 16-31 those of layer q - 1,
+    // 32-35 the right states' candidate segments
+    if (wave == nw - 1) {
         if (lane < 4 * wa) {
-            const int e = a_lo * 4 + lane;
-            G.adst[lane >> 2][lane & 3] = I.out_dst()[e];
-            G.aU[lane >> 2][lane & 3] = I.out_U()[e];
-        } else if (lane >= 16 && lane <= 16 + wb) {
-            G.bin[lane - 16] = I.in_start()[b_lo + lane - 16];
+            const int d = I.out_dst()[a_lo * 4 + lane];
+            (&G.adst[0][0])[lane] = d < 0 ? -1 : d - a1_lo;
+            (&G.aU[0][0])[lane] = I.out_U()[a_lo * 4 + lane];
+        } else if (lane >= 16 && lane < 16 + 4 * wb1) {
+            const int d = I.out_dst()[b1_lo * 4 + lane - 16];
+            (&G.bdst[0][0])[lane - 16] = d < 0 ? -1 : d - b_lo;
+            (&G.bU[0][0])[lane - 16] = I.out_U()[b1_lo * 4 + lane - 16];
         } else if (lane >= 32 && lane < 32 + wb) {
             const int b = b_lo + lane - 32;
             G.bcnt[lane - 32] = I.ccnt()[b];
             G.bcap[lane - 32] = I.ccap()[b];
             G.boff[lane - 32] = I.coff()[b];
         }
-        int base = 0;
-        for (int k0 = 0; k0 < ncell * 6; k0 += 64) {
-            const int k = k0 + lane;
-            bool job = false;
-            if (k < ncell * 6) {
-                const int ci = k / 6, t = k - 6 * ci;
-                G.vbuf[ci][t] = kINF;
-                job = g >= 5 && I.out_dst()[(a_lo + ci / wb) * 4 + kTX[t]] >= 0 &&
-                      ((I.inmask()[b_lo + ci % wb] >> kTY[t]) & 1);
-            }
-            const unsigned long long m = __ballot(job);
-            if (job) G.combo[base + __popcll(m & ((1ull << lane) - 1ull))] = (uint8_t)k;
-            base += __popcll(m);
-        }
-        if (lane == 0) G.ncombo = base;
     }
-    T.sync();
-    // phase 1: typed closed values; the parts of every (cell, type) job on separate waves
-    // labelled pairs over 1, 2 or 4 waves: wide workgroups run spans with few layer pairs
-    constexpr int nparts = NW >= 16 ? 6 : NW >= 8 ? 4 : 3;
-    if constexpr (NW == 1) {
-        // one wave runs every part of a job: one reduction per job, and the value is stored
-        // directly (each (cell, type) is one job)
-        for (int j = 0; j < G.ncombo; j++) {
-            const int cmb = G.combo[j], ci = cmb / 6, t = cmb - 6 * ci;
-            const int ia = ci / wb, ib = ci - wb * ia, a = a_lo + ia, b = b_lo + ib;
-            const int a1 = uni(G.adst[ia][kTX[t]]), i0 = uni(G.bin[ib]), i1 = uni(G.bin[ib + 1]);
-            const int64_t Ua = uni(G.aU[ia][kTX[t]]);
-            int64_t v = kINF;
+    const int nclosed = g >= 5 ? wa1 * wb1 : 0, nstate = g >= 5 ? wa + wb : 0;
+    const int ntask = nclosed + ncell + nstate + (g + 1 >= 12 && q + 1 <= I.n ? 1 : 0);
+    for (int k0 = wave; k0 < ntask; k0 += nw) {
+        int k = k0;
+        if (k < nclosed) {
+            const int ia1 = k / wb1, ib1 = k - wb1 * ia1, a1 = a1_lo + ia1, b1 = b1_lo + ib1;
+            // types some edge pair around (a1, b1) has: first base entering a1, last base leaving b1
+            const IT J = rebased(I);
+            const int im = uni(J.inmask()[a1]), om = uni(J.inmask()[b1]) >> 4;
+            int tm = 0;
 #pragma unroll
-            for (int part = 0; part < nparts; part++)
-                v = mn(v, closed_lanes<true>(I, S, E, spec, a, b, t, p, q, part, nparts, mini0, mini1, lane,
-                                             G.lab[wave], a1, Ua, i0, i1));
-            v = norm_inf(wave_min(v));
-            if (lane == 0) G.vbuf[ci][t] = v;
+            for (int t = 0; t < 6; t++) tm |= ((im >> type_x(t)) & (om >> type_y(t)) & 1) << t;
+            if (tm) closed_pair(J, S, spec, p, q, a1, b1, tm, lane, G.scratch[wave], G.w[ia1 * kMaxWidth + ib1]);
+            continue;
         }
-    }
-    const int njobs = NW == 1 ? 0 : nparts * G.ncombo;
-    for (int k = wave; k < njobs; k += nw) {
-        const int cmb = G.combo[k / nparts], ci = cmb / 6, t = cmb - 6 * ci;
-        const int ia = ci / wb, ib = ci - wb * ia, a = a_lo + ia, b = b_lo + ib;
-        const int64_t v = closed_part<(NW <= 4)>(I, S, E, spec, a, b, t, p, q, k % nparts, nparts, mini0, mini1, lane,
-                                                  G.lab[wave], uni(G.adst[ia][kTX[t]]), uni(G.aU[ia][kTX[t]]),
-                                                  uni(G.bin[ib]), uni(G.bin[ib + 1]));
-        if (lane == 0 && v < kINF)
-            __hip_atomic_fetch_min(&G.vbuf[ci][t], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    }
-    T.sync();
-    // phase 2: branch value (eq. 2), S2 (eq. 7), P_S, S1 and the retention test (eq. 6); one
-    // cell per wave from the first wave on.  Every scan reads only entries committed by earlier
-    // spans.
-    for (int ci = wave; ci < ncell; ci += nw) {
-        const int ia = ci / wb, ib = ci - wb * ia, a = a_lo + ia, b = b_lo + ib;
-        const int64_t cell = I.rowoff()[a] + (b - I.off()[p + 1]);
-        int64_t Bv = kINF;
-        for (int t = 0; t < 6; t++) {
-            const int64_t v = G.vbuf[ci][t];
-            if (lane == t) I.V()[cell * 6 + t] = v;
-            if (v < kINF) Bv = mn(Bv, v + fx(S.ml_intern + au_pen(S, t), s));
-        }
-        const int keep = multiloop_cell(I, a, b, p, q, cell, Bv, lane, ctr, uni(G.bcnt[ib]), uni(G.boff[ib]),
-                                        uni(G.bin[ib]), uni(G.bin[ib + 1]), G.adst[ia], G.aU[ia]);
-        if (lane == 0) {
-            G.keep[ci] = keep;
-            G.cellB[ci] = Bv;
-        }
-    }
-    // producers for later two-loops, one state per wave from the last wave down, so that they
-    // overlap phase 2 (they read typed values and earlier spans only)
-    int64_t lm0 = kINF, lm1 = kINF;
-    if (g >= 5)
-        for (int k = nw - 1 - wave; k < wa + wb; k += nw)
-            produce_state(I, S, G, p, g, k, a_lo, b_lo, wa, wb, lane, lm0, lm1);
-    lm0 = wave_min(lm0);
-    lm1 = wave_min(lm1);
-    if (lane == 0) {
-        G.red[wave][0] = lm0;
-        G.red[wave][1] = lm1;
-    }
-    T.sync();
-    if (wave == 0) {
-        // LM: layer-pair minimum of the both-separable form
-        if (lane == 0 && g >= 5) {
-            int64_t r0 = kINF, r1 = kINF;
-            for (int w = 0; w < nw; w++) {
-                r0 = mn(r0, G.red[w][0]);
-                r1 = mn(r1, G.red[w][1]);
+        k -= nclosed;
+        if (k < ncell) {
+            const int ia = k / wb, ib = k - wb * ia, a = a_lo + ia, b = b_lo + ib;
+            int64_t s2, ps;
+            const IT J = rebased(I);
+            multiloop_scan(J, a, b, p, q, uni(J.rowoff()[a]) + (b - a1_lo), lane, uni(J.ccnt()[b]), uni(J.coff()[b]), &s2, &ps);
+            if (lane == 0) {
+                G.s2[k] = s2;
+                G.ps[k] = ps;
             }
-            I.LM()[lm_idx(p, g, 0)] = norm_inf(r0);
-            I.LM()[lm_idx(p, g, 1)] = norm_inf(r1);
+            continue;
         }
-        // appends in start-state order, one lane per right endpoint (this group owns C_b in
-        // this step)
+        k -= ncell;
+        if (k < nstate) {
+            produce_one_sided(rebased(I), S, p, g, k < wa, k < wa ? a_lo + k : b_lo + k - wa, lane);
+            continue;
+        }
+        prepare_mini(rebased(I), S, p, q + 1, lane);
+    }
+    T.sync();
+    // typed values of the cells: every wave that needs them completes all of them (each writes the
+    // same values)
+    const bool left_role = g >= 5 && (1 % nw) == wave, right_role = g >= 5 && (2 % nw) == wave;
+    if (wave != 0 && !left_role && !right_role) return ctr;
+    for (int k = lane; k < ncell * 6; k += 64) {
+        const int ci = k / 6, t = k - 6 * ci, ia = ci / wb, ib = ci - wb * ia;
+        int64_t v = kINF;
+        if (g >= 5) {
+            const int a1 = G.adst[ia][type_x(t)];
+            if (a1 >= 0)
+                for (int j = 0; j < wb1; j++)
+                    if (G.bdst[j][type_y(t)] == ib)
+                        v = mn(v, G.aU[ia][type_x(t)] + G.bU[j][type_y(t)] + G.w[a1 * kMaxWidth + j][t]);
+        }
+        v = norm_inf(v);
+        G.vbuf[ci][t] = v;
+        if (wave == 0) I.V()[(I.rowoff()[a_lo + ia] + (b_lo + ib - a1_lo)) * 6 + t] = v;
+    }
+    wave_lds_order();
+    if (wave == 0) {
+        // branch value (eq. 2), S1 and the retention test (eq. 6), one lane per cell
+        bool feasible = false;
+        if (lane < ncell) {
+            const int ia = lane / wb, ib = lane - wb * ia;
+            int64_t Bv = kINF;
+#pragma unroll
+            for (int t = 0; t < 6; t++) Bv = mn(Bv, G.vbuf[lane][t] + fx(S.ml_intern + au_pen(S, t), s));
+            Bv = norm_inf(Bv);
+            const int64_t cell = I.rowoff()[a_lo + ia] + (b_lo + ib - a1_lo), ps = G.ps[lane];
+            I.Bt()[cell] = Bv;
+            I.S2()[cell] = G.s2[lane];
+            I.S1()[cell] = mn(Bv, ps);
+            const bool strict = Bv < ps;
+            G.keep[lane] = I.retain_all ? (Bv < kINF ? (strict ? 1 : 2) : 0) : (strict ? 1 : 0);
+            G.ps[lane] = Bv;
+            feasible = Bv < kINF;
+        }
+        ctr.feasible = __popcll(__ballot(feasible));
+        int vis = 0;
+        for (int j = 0; j < wb; j++) vis += G.bcnt[j];
+        ctr.visits = (unsigned long long)vis * wa;
+        wave_lds_order();
+        // appends in start-state order, one lane per right endpoint (this team owns C_b in this step)
         const bool mine = lane < wb;
-        append_candidates(I, a_lo, wa, b_lo, wb, G.keep, G.cellB, g, lane, mine ? G.bcnt[lane] : 0,
+        append_candidates(I, a_lo, wa, b_lo, wb, G.keep, G.ps, g, lane, mine ? G.bcnt[lane] : 0,
                           mine ? G.bcap[lane] : 0, mine ? G.boff[lane] : (int64_t)0);
     }
-    // both-separable minima of the next span's pair (p, q + 1), by the waves other than wave 0
-    // (busy with the appends): they read LM of spans <= g - 7, complete before this step
-    if (g + 1 >= 12 && q + 1 <= I.n) {
-        const int w0 = nw > 1 ? 1 : 0;
-        if (wave >= w0) {
-            int64_t m0 = kINF, m1 = kINF;
-            const int qn = q + 1, ph = (p % 3) * 3 + (qn % 3), cap = min(g + 1 - 7, kMaxLoop);
-            for (int k = tid - 64 * w0; k < kPairCnt[kListFast][ph][cap]; k += T.size() - 64 * w0) {
-                const int code = kPairList[kListFast][ph][k], l1 = code & 31, l2 = (code >> 5) & 31;
-                const int cl = p + 1 + l1, dl = qn - 1 - l2, X = pair_class(l1, l2);
-                const int64_t lm = I.LM()[lm_idx(cl, dl - cl, X)];
-                if (lm >= kINF) continue;
-                const int64_t v = lm + fx(interior_base(S, l1, l2), s) + PLt(I, p, l1) + PRt(I, qn, l2);
-                if (X) m1 = mn(m1, v);
-                else m0 = mn(m0, v);
-            }
-            m0 = wave_min(m0);
-            m1 = wave_min(m1);
-            if (lane == 0) {
-                G.red2[wave][0] = m0;
-                G.red2[wave][1] = m1;
-            }
-        }
-        T.sync();
-        if (tid == 64 * w0) {
-            int64_t r0 = kINF, r1 = kINF;
-            for (int w = w0; w < nw; w++) {
-                r0 = mn(r0, G.red2[w][0]);
-                r1 = mn(r1, G.red2[w][1]);
-            }
-            I.MINI()[mini_idx(p, g + 1, 0)] = norm_inf(r0);
-            I.MINI()[mini_idx(p, g + 1, 1)] = norm_inf(r1);
-        }
+    if (left_role) {
+        int64_t lm0 = kINF, lm1 = kINF;
+        for (int i = 0; i < wa; i++) produce_inner(I, S, G, p, g, true, i, a_lo, b_lo, wa, wb, lane, lm0, lm1);
+        // LM: layer-pair minimum of the both-separable form
+        lm0 = wave_min(lm0);
+        lm1 = wave_min(lm1);
+        if (lane < 2) I.LM()[lm_idx(p, g, lane)] = norm_inf(lane ? lm1 : lm0);
+    }
+    if (right_role) {
+        int64_t u0 = kINF, u1 = kINF;
+        for (int i = 0; i < wb; i++) produce_inner(I, S, G, p, g, false, i, a_lo, b_lo, wa, wb, lane, u0, u1);
     }
     return ctr;
 }
@@ -974,7 +856,7 @@ void k_span(Inst I, const EnergyTables* __restrict__ E, const int32_t* __restric
         return;
     }
     const int p = xcd_band(blockIdx.x, nblk_cells), q = p + g;
-    GroupCounters c = span_group(I, S, E, spec, p, q, G);
+    GroupCounters c = span_group(I, S, spec, p, q, G);
     // each wave counted its own cells
     const int lane = threadIdx.x & 63;
     flush_counters(I, c, p, lane);
@@ -999,7 +881,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
     const int item = xcd_band(blockIdx.x, nblk) * NWV + wave;
     const WaveTeam T;
     if (item < npairs) {
-        GroupCounters c = span_group(I, S, E, spec, item, item + g, G[wave], T);
+        GroupCounters c = span_group(I, S, spec, item, item + g, G[wave], T);
         flush_counters(I, c, item, lane);
     } else if (item == npairs && ext_layer >= 0) {
         ext_column(I, S, ext_layer, nullptr, T);
@@ -1050,7 +932,7 @@ __global__ void k_init(Inst I) {
 // One wave per layer pair of span g runs the span step's own multiloop_cell and
 // append_candidates: the exact-integer abstract test of Sec. 7.1 on the GPU code path.
 __global__ __launch_bounds__(64) void k_ml_abstract(Inst I, int g) {
-    __shared__ int keep[kMaxWidth * kMaxWidth];
+    __shared__ int8_t keep[kMaxWidth * kMaxWidth];
     __shared__ int64_t cellB[kMaxWidth * kMaxWidth];
     const int p = blockIdx.x, q = p + g, lane = threadIdx.x;
     const int a_lo = I.off()[p], wa = I.off()[p + 1] - a_lo, b_lo = I.off()[q], wb = I.off()[q + 1] - b_lo;
@@ -1163,7 +1045,7 @@ __device__ __forceinline__ const int64_t* gen_lg(const IT& I, int u, int lu, int
 
 struct GenShared {
     int64_t cellB[kGenMaxWidth * kGenMaxWidth];
-    int keep[kGenMaxWidth * kGenMaxWidth];
+    int8_t keep[kGenMaxWidth * kGenMaxWidth];
 };
 
 // interior loop (l1, l2 >= 1) closed by type t around inner cell values vin[6], with the left
@@ -1232,6 +1114,11 @@ __device__ __forceinline__ int64_t gen_interior_fast(const SmallE& S, int X, con
     int64_t R[16];
 #pragma unroll
     for (int k = 0; k < 16; k++) R[k] = Rp[k];
+    // the class's table through an offset the compiler cannot hoist: keeping the 96 scaled entries in
+    // registers across the inner states' loop spills them (1.6 KB of scratch per lane)
+    int off = (X == 0 ? 1 : X == 2 ? 2 : 3) * 96;
+    asm volatile("" : "+v"(off));
+    const int32_t* tab = &S.mmH[0][0][0] + off;
     int64_t best = kINF;
 #pragma unroll
     for (int xk = 0; xk < 4; xk++)
@@ -1247,7 +1134,7 @@ __device__ __forceinline__ int64_t gen_interior_fast(const SmallE& S, int X, con
             int64_t in = kINF;
 #pragma unroll
             for (int tp = 0; tp < 6; tp++)
-                if (vin[tp] < kINF) in = mn(in, vin[tp] + fx(mmx(S, X, kRev[tp], xl, xk), s));
+                if (vin[tp] < kINF) in = mn(in, vin[tp] + fx(tab[type_rev(tp) * 16 + xl * 4 + xk], s));
             if (in < kINF) best = mn(best, out + in);
         }
     return best >= kINF ? kINF : best + fx(interior_base(S, l1, l2), s);
@@ -1647,11 +1534,11 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
             const int item = (int)(lo_item + (ticket - base));
             // the instance index is block-uniform
             const int inst = __builtin_amdgcn_readfirstlane(item_instance(pref, ninst, item));
-            const Inst I = insts[inst];  // a few scalar registers: bases and sizes
+            const Inst I = rebased(insts[inst]);  // a few scalar registers: bases and sizes
             const int local = item - pref[inst], g = I.g0 + step;
             const int n = I.n, ncell_items = g <= n ? n - g + 1 : 0;
             if (local < ncell_items) {
-                GroupCounters c = span_group(I, S, E, spec, local, local + g, G);
+                GroupCounters c = span_group(I, S, spec, local, local + g, G);
                 flush_counters(I, c, local, threadIdx.x & 63);
             } else {
                 ext_column(I, S, n - g + 1, red);
@@ -1697,11 +1584,11 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
             if (lane == 0) nxt = atomicAdd(&ctl->next[grp].v, 1u);  // drawn now, used after the item
             const int item = (int)(lo_item + (ticket - base));
             const int inst = __builtin_amdgcn_readfirstlane(item_instance(pref, ninst, item));
-            const Inst I = insts[inst];
+            const Inst I = rebased(insts[inst]);
             const int local = item - pref[inst], g = I.g0 + step;
             const int n = I.n, ncell_items = g <= n ? n - g + 1 : 0;
             if (local < ncell_items) {
-                GroupCounters c = span_group(I, S, E, spec, local, local + g, G[wave], T);
+                GroupCounters c = span_group(I, S, spec, local, local + g, G[wave], T);
                 flush_counters(I, c, local, lane);
             } else {
                 ext_column(I, S, n - g + 1, nullptr, T);
@@ -1716,7 +1603,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
 
 // Resets the barrier state and initialises every instance whose g0 is 1 (new instances).
 __global__ void k_batch_init(const Inst* __restrict__ insts, int ninst, BatchCtl* ctl) {
-    const Inst& I = insts[blockIdx.x];
+    const Inst I = rebased(insts[blockIdx.x]);
     const int tid = threadIdx.x, nt = blockDim.x;
     if (blockIdx.x == 0 && tid < 8) {
         ctl->arrive[tid].v = 0;
@@ -1759,50 +1646,26 @@ __global__ void k_batch_init(const Inst* __restrict__ insts, int ninst, BatchCtl
 namespace sd {
 
 hipError_t upload_pair_order() {
-    unsigned char l1[kNumPairs], l2[kNumPairs];
-    int k = 0;
-    for (int a = 0; a <= kMaxLoop; a++)
-        for (int b = 0; a + b <= kMaxLoop; b++) {
-            l1[k] = (unsigned char)a;
-            l2[k] = (unsigned char)b;
-            k++;
-        }
-    hipError_t e = hipMemcpyToSymbol(HIP_SYMBOL(kL1), l1, sizeof(l1));
-    if (e != hipSuccess) return e;
-    e = hipMemcpyToSymbol(HIP_SYMBOL(kL2), l2, sizeof(l2));
-    if (e != hipSuccess) return e;
-    // categorised pair lists per phase (p mod 3, q mod 3)
-    static unsigned short list[5][9][kNumPairs];
-    static unsigned short cnt[5][9][31];
+    static unsigned short list[9][kNumPairs];
+    static unsigned short cnt[9][31];
     memset(list, 0, sizeof(list));
     memset(cnt, 0, sizeof(cnt));
     for (int pm = 0; pm < 3; pm++)
         for (int qm = 0; qm < 3; qm++) {
             const int ph = pm * 3 + qm, p = 3 + pm, q = 300 + qm;  // representatives of the phases
-            int len[5] = {0, 0, 0, 0, 0};
+            int len = 0;
             for (int sum = 0; sum <= kMaxLoop; sum++) {
-                for (int a = 0; a <= sum; a++) {
+                for (int a = 2; a + 2 <= sum; a++) {
                     const int b = sum - a;
-                    const bool sl = a >= 2 && (p + 2) / 3 != (p + a) / 3;
-                    const bool sr = b >= 2 && (q - b) / 3 != (q - 2) / 3;
-                    int lst;
-                    unsigned short code = (unsigned short)(a | b << 5);
-                    if ((a == 0 || b == 0) && a + b >= 3) lst = kListBulgeSep;
-                    else if (a == 0 || b == 0) lst = kListBulge;  // (0,0) (0,1) (1,0) (0,2) (2,0), enumerated directly by bulge_lanes
-                    else if (sl && sr) lst = kListFast;
-                    else if (!sl && !sr) lst = kListLab;
-                    else {
-                        lst = kListOne;
-                        if (sl) code |= 1 << 10;
-                    }
-                    list[lst][ph][len[lst]++] = code;
+                    // 2x2 loops read their full table and are always enumerated
+                    if (sum > 4 && sep_left(p, a) && sep_right(q, b)) list[ph][len++] = (unsigned short)(a | b << 5);
                 }
-                for (int l = 0; l < 5; l++) cnt[l][ph][sum] = (unsigned short)len[l];
+                cnt[ph][sum] = (unsigned short)len;
             }
         }
-    e = hipMemcpyToSymbol(HIP_SYMBOL(kPairList), list, sizeof(list));
+    hipError_t e = hipMemcpyToSymbol(HIP_SYMBOL(kFastList), list, sizeof(list));
     if (e != hipSuccess) return e;
-    return hipMemcpyToSymbol(HIP_SYMBOL(kPairCnt), cnt, sizeof(cnt));
+    return hipMemcpyToSymbol(HIP_SYMBOL(kFastCnt), cnt, sizeof(cnt));
 }
 
 hipError_t launch_init(const Inst& I, hipStream_t st) {

@@ -277,6 +277,9 @@ void index_in_edges(Lattice& L) {
     L.inmask.assign(N, 0);
     for (int v = 0; v < N; v++)
         for (int j = L.in_start[v]; j < L.in_start[v + 1]; j++) L.inmask[v] |= 1 << L.in_lab[j];
+    for (int v = 0; v < N; v++)
+        for (int x = 0; x < 4; x++)
+            if (L.out_dst[4 * v + x] >= 0) L.inmask[v] |= 16 << x;
 }
 
 // hairpin initiation per size, extrapolated above 30 (rounded half away from zero)
@@ -511,47 +514,15 @@ int build_lattice(const char* protein, const CodonTable& T, const Params& P, dou
     for (int v = 0; v < N; v++)
         for (int j = L.in_start[v]; j < L.in_start[v + 1]; j++)
             L.betaU[4 * v + L.in_lab[j]] = std::min(L.betaU[4 * v + L.in_lab[j]], L.in_U[j]);
-    // hairpin closing side: min over b2 -z-> b1 -y-> b of the two edge costs
-    L.hpB.assign((size_t)16 * N, kINF);
-    for (int v = 0; v < N; v++)
-        for (int j = L.in_start[v]; j < L.in_start[v + 1]; j++) {
-            const int b1 = L.in_src[j], y = L.in_lab[j];
-            for (int j2 = L.in_start[b1]; j2 < L.in_start[b1 + 1]; j2++) {
-                const int z = L.in_lab[j2];
-                int64_t& h = L.hpB[16 * v + 4 * y + z];
-                h = std::min(h, L.in_U[j] + L.in_U[j2]);
-            }
-        }
-    // outer minima of one-sided interior loops, per state, closing type t, mismatch class X
-    // (0 generic, 1 2x3, 2 1xn) and boundary label x:
-    //   OB(b1, t, X, x) = min_o beta(b1, o) + mm_X[t][x][o]    (x = x_{i+1}, o = x_{j-1})
-    //   OA(a1, t, X, x) = min_o alpha(a1, o) + mm_X[t][o][x]   (o = x_{i+1}, x = x_{j-1})
-    L.OB.assign((size_t)72 * N, kINF);
-    L.OA.assign((size_t)72 * N, kINF);
-    {
-        const int32_t(*mm[3])[4][4] = {P.E.mmI, P.E.mm23, P.E.mm1n};
-        const int64_t unit = (int64_t)1 << shift;
-        for (int v = 0; v < N; v++)
-            for (int t = 0; t < 6; t++)
-                for (int X = 0; X < 3; X++)
-                    for (int x = 0; x < 4; x++) {
-                        int64_t rb = kINF, ra = kINF;
-                        for (int o = 0; o < 4; o++) {
-                            const int64_t be = L.betaU[4 * v + o], al = L.alphaU[4 * v + o];
-                            if (be < kINF) rb = std::min(rb, be + (int64_t)mm[X][t][x][o] * unit);
-                            if (al < kINF) ra = std::min(ra, al + (int64_t)mm[X][t][o][x] * unit);
-                        }
-                        L.OB[(size_t)72 * v + (t * 3 + X) * 4 + x] = rb;
-                        L.OA[(size_t)72 * v + (t * 3 + X) * 4 + x] = ra;
-                    }
-    }
-    // label paths of 1..4 edges out of / into every state (explicit short loop segments)
+    // label paths of 1..3 edges out of / into every state (explicit short loop segments); the fourth
+    // offset of a state ends its list
     L.fwd_off.assign((size_t)4 * N + 1, 0);
     L.bwd_off.assign((size_t)4 * N + 1, 0);
     L.fwd_meta.clear(); L.fwd_cost.clear(); L.bwd_meta.clear(); L.bwd_cost.clear();
     for (int u = 0; u < N; u++)
         for (int len = 1; len <= 4; len++) {
             L.fwd_off[4 * u + len - 1] = (int)L.fwd_meta.size();
+            if (len == 4) break;
             struct Fr { int state, first_lab, last_lab; int64_t cost; int depth; };
             std::vector<Fr> stack{{u, -1, -1, 0, 0}};
             while (!stack.empty()) {
@@ -573,6 +544,7 @@ int build_lattice(const char* protein, const CodonTable& T, const Params& P, dou
     for (int v = 0; v < N; v++)
         for (int len = 1; len <= 4; len++) {
             L.bwd_off[4 * v + len - 1] = (int)L.bwd_meta.size();
+            if (len == 4) break;
             // backward walk over in-edge sequences; record (start, first label, last label)
             struct Fr { int state, first_lab, last_lab; int64_t cost; int depth; };
             std::vector<Fr> stack{{v, -1, -1, 0, 0}};
@@ -740,9 +712,6 @@ int build_motif_lattice(const char* protein, const CodonTable& T, const Params& 
     L.P.assign(L.A + 1, 0);
     L.alphaU.assign((size_t)4 * N, kINF);
     L.betaU.assign((size_t)4 * N, kINF);
-    L.hpB.assign((size_t)16 * N, kINF);
-    L.OB.assign((size_t)72 * N, kINF);
-    L.OA.assign((size_t)72 * N, kINF);
     L.fwd_off.assign((size_t)4 * N + 1, 0);
     L.bwd_off.assign((size_t)4 * N + 1, 0);
     L.generic = true;
