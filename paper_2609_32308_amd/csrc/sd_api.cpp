@@ -1284,7 +1284,7 @@ sd_status run_batch(sd_context* c, std::vector<Lattice>& Ls, std::vector<Inst>& 
         hipError_t e1 = launch_batch_init(insts_dev, n, ctl, c->stream);
         hipError_t e2 = e1 == hipSuccess ? launch_persistent(insts_dev, n, maxn + 1, (const EnergyTables*)c->E_dev,
                                                              (const int32_t*)c->spec_dev, ctl, sc.grid, sc.threads, sc.item_waves,
-                                                             spin_cap, c->stream)
+                                                             c->num_cu, spin_cap, c->stream)
                                          : e1;
         hipError_t e3 = hipStreamEndCapture(c->stream, &graph);
         if (e2 == hipSuccess && e3 == hipSuccess && graph &&
@@ -1299,7 +1299,7 @@ sd_status run_batch(sd_context* c, std::vector<Lattice>& Ls, std::vector<Inst>& 
         if (e == hipSuccess) e = launch_batch_init(insts_dev, n, ctl, c->stream);
         if (e == hipSuccess)
             e = launch_persistent(insts_dev, n, maxn + 1, (const EnergyTables*)c->E_dev, (const int32_t*)c->spec_dev,
-                                  ctl, sc.grid, sc.threads, sc.item_waves, spin_cap, c->stream);
+                                  ctl, sc.grid, sc.threads, sc.item_waves, c->num_cu, spin_cap, c->stream);
     }
     if (e == hipSuccess) e = hipEventRecord(c->ev1, c->stream);
     BatchCtl hctl;

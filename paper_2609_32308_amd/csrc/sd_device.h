@@ -112,7 +112,7 @@ hipError_t launch_batch_init(const Inst* insts_dev, int ninst, BatchCtl* ctl, hi
 bool persistent_schedule_valid(int threads, int item_waves);
 hipError_t persistent_occupancy(int threads, int item_waves, int* blocks_per_cu);
 hipError_t launch_persistent(const Inst* insts_dev, int ninst, int nsteps, const EnergyTables* E,
-                             const int32_t* spec, BatchCtl* ctl, int grid, int threads, int item_waves,
+                             const int32_t* spec, BatchCtl* ctl, int grid, int threads, int item_waves, int num_cu,
                              unsigned spin_cap, hipStream_t st);
 }  // namespace sd
 

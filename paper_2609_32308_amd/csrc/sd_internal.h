@@ -196,17 +196,21 @@ constexpr int kGenLoopWin = 30;   // layer distances covered by the labelled gap
 constexpr int kMaxWaves = 16;  // waves per workgroup of the span-step kernels (1024 threads)
 static_assert(sizeof(Inst) % 8 == 0, "instance descriptors are copied as 8-byte words");
 
-// Batched persistent launch: barrier and work-ticket state shared by all workgroups.  Workgroup
-// i belongs to group i mod 8 (the XCD it is dispatched to); every contended word sits on its own
-// 128-byte line.
+// Batched persistent launch: barrier and work-ticket state shared by all workgroups.  Every contended
+// word sits on its own 128-byte line.  Barrier words are per XCD (the one a workgroup runs on); the
+// work bands and their tickets are per group, block index mod 8.
 struct alignas(128) CtlWord {
     unsigned int v;
     unsigned int pad[31];
 };
+constexpr int kMaxXcd = 16;
 struct BatchCtl {
-    CtlWord arrive[8];  // arrivals of each group at the current barrier
-    CtlWord top;        // groups complete at the current barrier
-    CtlWord gen;        // barrier generation
+    CtlWord count[kMaxXcd];    // workgroups of each XCD
+    CtlWord joined;            // workgroups counted
+    CtlWord arrive[kMaxXcd];   // arrivals of each XCD at the current barrier
+    CtlWord top;               // XCDs complete at the current barrier
+    CtlWord gen;               // barrier generation
+    CtlWord release[kMaxXcd];  // generation each XCD's workgroups are released to
     CtlWord next[8];    // work tickets handed out per group (its band of every step, in order)
     CtlWord err;        // set when a barrier wait exceeds its spin limit (every group then exits)
     CtlWord steps_done; // spans completed (diagnostics)

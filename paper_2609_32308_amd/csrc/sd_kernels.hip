@@ -383,14 +383,19 @@ __device__ __forceinline__ void closed_pair(const IT& I, const SmallE& S, const 
 // or a single wavefront of a workgroup whose waves each work on their own pair (ordered within the
 // wave; a workgroup barrier there would pair up unrelated points of different waves).
 struct BlockTeam {
-    __device__ int tid() const { return threadIdx.x; }
+    __device__ int wave() const { return threadIdx.x >> 6; }
     __device__ int lane() const { return threadIdx.x & 63; }
-    __device__ int size() const { return blockDim.x; }
-    __device__ void sync() const { __syncthreads(); }
+    __device__ int waves() const { return blockDim.x >> 6; }
+    __device__ void sync() { __syncthreads(); }
 };
+// `n` consecutive waves of a workgroup, ordered by an LDS arrival counter (zero when the team is
+// formed; every wave of the workgroup is resident, so the wait ends).  One wave needs no counter.
 struct WaveTeam {
-    __device__ int tid() const { return threadIdx.x & 63; }
-    // The lane index produced per call: a one-wave team runs inside the persistent loop, and lane
+    unsigned* ctr = nullptr;
+    int w = 0, n = 1;
+    unsigned epoch = 0;
+    __device__ int wave() const { return w; }
+    // The lane index produced per call: a wave team runs inside the persistent loop, and lane
     // predicates derived from threadIdx would be hoisted to the kernel entry and held for the
     // whole launch, where they crowd the scalar registers and are spilled to vector lanes.
     __device__ int lane() const {
@@ -398,19 +403,26 @@ struct WaveTeam {
         asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
         return l;
     }
-    __device__ int size() const { return 64; }
-    __device__ void sync() const {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    __device__ int waves() const { return n; }
+    __device__ void sync() {
+        if (n == 1) {
+            wave_lds_order();
+            return;
+        }
+        epoch += n;
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        if (lane() == 0) __hip_atomic_fetch_add(ctr, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        while (__hip_atomic_load(ctr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) < epoch) __builtin_amdgcn_s_sleep(1);
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
     }
 };
 
-template <int NW>  // waves per workgroup
+// LDS of one team; a wave's own scratch lies in the element of its own index, so that an array of
+// as many elements as waves serves teams of any size.
 struct GroupShared {
     int64_t w[kMaxWidth * kMaxWidth][6];      // W_t(a1, b1) of the pair's inner boundary pairs
     union {
-        PairScratch scratch[NW];                 // phase 1
+        PairScratch scratch;                     // phase 1
         int64_t vbuf[kMaxWidth * kMaxWidth][6];  // phase 2: typed closed values of the pair's cells
     };
     int64_t s2[kMaxWidth * kMaxWidth];        // S2 of the cells
@@ -474,8 +486,8 @@ __device__ __forceinline__ void produce_one_sided(const IT& I, const SmallE& S, 
 
 // Inner minima of state k of the pair for span g from its typed values, by one wave: IDL (left
 // states, with their LM contribution) or JDL (right states), and the bulge rings BI / BJ.
-template <int NW, class IT>
-__device__ __forceinline__ void produce_inner(const IT& I, const SmallE& S, const GroupShared<NW>& G, int p, int g,
+template <class IT>
+__device__ __forceinline__ void produce_inner(const IT& I, const SmallE& S, const GroupShared& G, int p, int g,
                               bool left, int i, int a_lo, int b_lo, int wa, int wb, int lane, int64_t& lm0, int64_t& lm1) {
     const int s = I.shift, st = left ? a_lo + i : b_lo + i, nother = left ? wb : wa;
     // inner minima: lane = 16 * X + 4 * xx + z (48 lanes), minimised over z
@@ -659,11 +671,13 @@ __device__ void append_candidates(const IT& I, int a_lo, int wa, int b_lo, int w
 // part of each cell, the one-sided tables of each state, and the next span's both-separable
 // minima.  After one barrier, the cells are completed (typed values, branch value, S1, retention,
 // appends) by one wave while others derive the inner minima for later two-loops.
-template <int NW, class IT, class Team = BlockTeam>
+template <class IT, class Team>
 __device__ __forceinline__ GroupCounters span_group(const IT& I, const SmallE& S, const int32_t* __restrict__ spec, int p, int q,
-                                    GroupShared<NW>& G, Team T = Team()) {
+                                    GroupShared* Gs, Team& T) {
+    // Gs: the team's elements, one per wave; the first holds the pair's shared state
     const int g = q - p, s = I.shift;
-    const int wave = T.tid() >> 6, lane = T.lane(), nw = T.size() >> 6;
+    const int wave = T.wave(), lane = T.lane(), nw = T.waves();
+    GroupShared& G = Gs[0];
     GroupCounters ctr{0, 0};
     const int a_lo = I.off()[p], a1_lo = I.off()[p + 1], b_lo = I.off()[q], b_hi = I.off()[q + 1], b1_lo = I.off()[q - 1];
     const int wa = a1_lo - a_lo, wb = b_hi - b_lo, ncell = wa * wb;
@@ -698,7 +712,7 @@ __device__ __forceinline__ GroupCounters span_group(const IT& I, const SmallE& S
             int tm = 0;
 #pragma unroll
             for (int t = 0; t < 6; t++) tm |= ((im >> type_x(t)) & (om >> type_y(t)) & 1) << t;
-            if (tm) closed_pair(J, S, spec, p, q, a1, b1, tm, lane, G.scratch[wave], G.w[ia1 * kMaxWidth + ib1]);
+            if (tm) closed_pair(J, S, spec, p, q, a1, b1, tm, lane, Gs[wave].scratch, G.w[ia1 * kMaxWidth + ib1]);
             continue;
         }
         k -= nclosed;
@@ -783,10 +797,14 @@ __device__ __forceinline__ GroupCounters span_group(const IT& I, const SmallE& S
     return ctr;
 }
 
-// ---- external column: X(a) for every a of layer L (one workgroup) ------------------------------
-template <class IT, class Team = BlockTeam>
-__device__ void ext_column(const IT& I, const SmallE& S, int L, int64_t* red, Team T = Team()) {
-    const int tid = T.tid(), nt = T.size();
+// ---- external column: X(a) for every a of layer L (one team) ------------------------------------
+// X(a) = min(U + X of the out-edges, AU + V_t(a, b) + X(b) over closing pairs).  The branch value holds
+// min over t of V_t + ML_intern + AU, so the scan reads it (8 contiguous bytes per b) and takes
+// ML_intern off.
+template <class IT, class Team>
+__device__ __forceinline__ void ext_column(const IT& I, const SmallE& S, int L, GroupShared* Gs, Team& T) {
+    const int tid = T.wave() * 64 + T.lane(), nt = T.waves() * 64;
+    const int64_t mi = fx(S.ml_intern, I.shift);
     for (int a = I.off()[L]; a < I.off()[L + 1]; a++) {
         int64_t v = kINF;
         if (tid < 4) {
@@ -794,28 +812,15 @@ __device__ void ext_column(const IT& I, const SmallE& S, int L, int64_t* red, Te
             if (d >= 0) v = I.out_U()[a * 4 + tid] + I.X()[d];
         }
         if (L + 5 <= I.n) {
-            const int bstart = I.off()[L + 5];
-            const int64_t base = I.rowoff()[a] - I.off()[L + 1];
-            for (int bb = bstart + tid; bb < I.N; bb += nt) {
-                const int64_t* vr = I.V() + (base + bb) * 6;
-                const int64_t xb = I.X()[bb];
-#pragma unroll
-                for (int t = 0; t < 6; t++) {
-                    const int64_t vt = vr[t];
-                    if (vt < kINF) v = mn(v, vt + fx(au_pen(S, t), I.shift) + xb);
-                }
-            }
+            const int64_t* Br = I.Bt() + I.rowoff()[a] - I.off()[L + 1];
+#pragma unroll 4
+            for (int bb = I.off()[L + 5] + tid; bb < I.N; bb += nt) v = mn(v, Br[bb] + (I.X()[bb] - mi));
         }
-        if constexpr (std::is_same<Team, WaveTeam>::value) {
-            v = wave_min(v);
-        } else {  // tree over the workgroup (the wave reduction costs the 512-thread span kernel a spill)
-            red[tid] = v;
+        v = wave_min(v);
+        if (T.waves() > 1) {
+            if (T.lane() == 0) Gs[T.wave()].s2[0] = v;
             T.sync();
-            for (int w = nt / 2; w > 0; w >>= 1) {
-                if (tid < w) red[tid] = mn(red[tid], red[tid + w]);
-                T.sync();
-            }
-            v = red[0];
+            for (int w = 0; w < T.waves(); w++) v = mn(v, Gs[w].s2[0]);
         }
         if (tid == 0) I.X()[a] = norm_inf(v);
         T.sync();
@@ -847,19 +852,16 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT == 512 ? 
 void k_span(Inst I, const EnergyTables* __restrict__ E, const int32_t* __restrict__ spec, int g,
             int ext_layer, int nblk_cells) {
     __shared__ SmallE S;
-    __shared__ int64_t red[NT];
-    __shared__ GroupShared<NT / 64> G;
+    __shared__ GroupShared G[NT / 64];
     stage_tables(S, E);
     __syncthreads();
+    BlockTeam T;
     if ((int)blockIdx.x >= nblk_cells) {
-        if (ext_layer >= 0) ext_column(I, S, ext_layer, red);
+        if (ext_layer >= 0) ext_column(I, S, ext_layer, G, T);
         return;
     }
     const int p = xcd_band(blockIdx.x, nblk_cells), q = p + g;
-    GroupCounters c = span_group(I, S, spec, p, q, G);
-    // each wave counted its own cells
-    const int lane = threadIdx.x & 63;
-    flush_counters(I, c, p, lane);
+    flush_counters(I, span_group(I, S, spec, p, q, G, T), p, threadIdx.x & 63);
 }
 
 // The span step with every wave on its own layer pair: four pairs per workgroup and one staging of
@@ -872,28 +874,28 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
     Inst I, const EnergyTables* __restrict__ E, const int32_t* __restrict__ spec, int g, int ext_layer, int npairs) {
     constexpr int NWV = NT / 64;
     __shared__ SmallE S;
-    __shared__ GroupShared<1> G[NWV];
+    __shared__ GroupShared G[NWV];
     stage_tables(S, E);
     __syncthreads();
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int wave = threadIdx.x >> 6;
     const int items = npairs + (ext_layer >= 0 ? 1 : 0);
     const int nblk = (items + NWV - 1) / NWV;
     const int item = xcd_band(blockIdx.x, nblk) * NWV + wave;
-    const WaveTeam T;
+    WaveTeam T;
     if (item < npairs) {
-        GroupCounters c = span_group(I, S, spec, item, item + g, G[wave], T);
-        flush_counters(I, c, item, lane);
+        flush_counters(I, span_group(I, S, spec, item, item + g, &G[wave], T), item, T.lane());
     } else if (item == npairs && ext_layer >= 0) {
-        ext_column(I, S, ext_layer, nullptr, T);
+        ext_column(I, S, ext_layer, &G[wave], T);
     }
 }
 
 __global__ __launch_bounds__(256) void k_ext(Inst I, const EnergyTables* __restrict__ E, int L) {
     __shared__ SmallE S;
-    __shared__ int64_t red[256];
+    __shared__ GroupShared G[4];
     stage_tables(S, E);
     __syncthreads();
-    ext_column(I, S, L, red);
+    BlockTeam T;
+    ext_column(I, S, L, G, T);
 }
 
 __global__ void k_init(Inst I) {
@@ -1373,12 +1375,13 @@ __global__ __launch_bounds__(256) void k_span_gen(Inst I, const EnergyTables* __
                                                   const int32_t* __restrict__ spec, int g,
                                                   int ext_layer, int nblk_cells) {
     __shared__ SmallE S;
-    __shared__ int64_t red[256];
+    __shared__ GroupShared X[4];
     __shared__ GenShared G;
     stage_tables(S, E);
     __syncthreads();
     if ((int)blockIdx.x >= nblk_cells) {
-        if (ext_layer >= 0) ext_column(I, S, ext_layer, red);
+        BlockTeam T;
+        if (ext_layer >= 0) ext_column(I, S, ext_layer, X, T);
         return;
     }
     const int p = xcd_band(blockIdx.x, nblk_cells), q = p + g;
@@ -1390,63 +1393,100 @@ __global__ __launch_bounds__(256) void k_span_gen(Inst I, const EnergyTables* __
 // All instances advance one global span per grid barrier.  At step g the work items are the layer
 // pairs of span g of every instance with n >= g, followed (per instance) by the external column
 // of layer n - g + 1 (one layer behind).  The items of a step are cut into 8 contiguous bands, one
-// per workgroup group (XCD); a group's workgroups draw its band's items from the group's ticket
-// counter.  The barrier is two-level: the last arrival of a group counts the group at the top
-// word, the last group bumps the generation (agent-scope release / acquire).
+// per workgroup group (XCD).
 //
-// Release: the cell values (S1, S2, B, V) and the candidate appends are stored by many waves,
-// and a workgroup barrier alone does not wait for their stores (no vmcnt wait before
-// s_barrier), while thread 0's agent-scope fence (L2 write-back, then its own vmcnt wait) only
-// covers the stores that have reached this XCD's L2.  So every wave first waits until its own
-// stores are acknowledged by L2 (vmcnt 0); after the workgroup barrier, thread 0's write-back
-// then carries every wave's stores to memory before the arrival.  Without the per-wave wait a
-// workgroup on another XCD could read a value of the previous span from memory before it was
-// written back (a stale S1 makes P_S too large and the retention test then keeps extra
-// non-strict candidates).  A full agent-scope fence in every wave is also correct but repeats
-// the L2 write-back once per wave (8 s instead of 5 s for the 256-design batch).
+// Grid barrier.  The cell values and candidate appends are stored by many waves, and a workgroup
+// barrier alone does not wait for their stores (no vmcnt wait before s_barrier).  So every wave
+// first waits until its own stores are acknowledged by its XCD's L2 (vmcnt 0); after the workgroup
+// barrier the workgroup arrives at the counter of its XCD (read from the hardware register, not
+// assumed from the block index).  The last arrival of an XCD writes that L2 back once for all of
+// them, waits for the other XCDs, and invalidates; only then are the XCD's workgroups released,
+// each invalidating its own CU's cache.  A write-back and an invalidation per workgroup, on both
+// sides of the barrier, queue up at the L2: with 1,024 workgroups of 256 threads a bare barrier
+// took 31.2 us that way, 11.5 us with one write-back per XCD, and 4.8 us with one workgroup of
+// 1,024 threads per CU; early arrivals also invalidated the caches of workgroups still working.
+// Waits are polled with relaxed loads (an acquire per poll would invalidate likewise).
 __device__ __forceinline__ void wait_own_stores() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");  // keeps the compiler from sinking stores
     __builtin_amdgcn_s_waitcnt(0x0F70);                      // vmcnt(0), expcnt and lgkmcnt untouched
 }
+__device__ __forceinline__ unsigned ctl_load(const CtlWord& w) {
+    return __hip_atomic_load(&w.v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void ctl_store(CtlWord& w, unsigned v) {
+    __hip_atomic_store(&w.v, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ unsigned ctl_add(CtlWord& w) {
+    return __hip_atomic_fetch_add(&w.v, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u;
+}
+// The XCD this workgroup runs on (hardware register XCC_ID, 4 bits).
+__device__ __forceinline__ unsigned xcd_id() { return __builtin_amdgcn_s_getreg(20 | (3 << 11)) & (kMaxXcd - 1); }
 
-__device__ bool grid_barrier(BatchCtl* ctl, unsigned spin_cap, int* s_flag) {
+// Thread 0's share of the barrier state.
+struct BarrierTeam {
+    unsigned xcd = 0, members = 0, xcds = 0, gen = 0;
+};
+
+// Waits until `w` no longer holds `old`; false when the wait exceeds its cap or another workgroup has
+// given up.  The pause between polls grows to about 0.4 us.
+__device__ __forceinline__ bool ctl_wait(BatchCtl* ctl, const CtlWord& w, unsigned old, unsigned spin_cap) {
+    int pause = 1;
+    for (unsigned spins = 0; ctl_load(w) == old; spins++) {
+        if (spins > spin_cap || ctl_load(ctl->err)) {
+            ctl_store(ctl->err, 1u);
+            return false;
+        }
+        for (int k = 0; k < pause; k++) __builtin_amdgcn_s_sleep(2);
+        if (pause < 8) pause <<= 1;
+    }
+    return true;
+}
+
+// Counts this workgroup at its XCD (thread 0, once, at kernel start).
+__device__ __forceinline__ void barrier_join(BatchCtl* ctl, BarrierTeam& B) {
+    B.xcd = xcd_id();
+    ctl_add(ctl->count[B.xcd]);
+    __builtin_amdgcn_s_waitcnt(0x0F70);
+    ctl_add(ctl->joined);
+}
+
+__device__ bool grid_barrier(BatchCtl* ctl, BarrierTeam& B, unsigned spin_cap, int* s_flag) {
     wait_own_stores();
     __syncthreads();
     if (threadIdx.x == 0) {
-        __threadfence();
-        const unsigned grp = blockIdx.x & 7, ngrp = gridDim.x < 8 ? gridDim.x : 8;
-        const unsigned members = (gridDim.x - grp + 7) >> 3;
-        const unsigned g0 = __hip_atomic_load(&ctl->gen.v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        int err = 0;
-        bool last = false;
-        const unsigned a = __hip_atomic_fetch_add(&ctl->arrive[grp].v, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) + 1u;
-        if (a == members) {
-            __hip_atomic_store(&ctl->arrive[grp].v, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            const unsigned t = __hip_atomic_fetch_add(&ctl->top.v, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) + 1u;
-            if (t == ngrp) {
-                __hip_atomic_store(&ctl->top.v, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                __hip_atomic_fetch_add(&ctl->gen.v, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-                last = true;
-            }
-        }
-        if (!last) {
-            // poll with relaxed loads: an acquire per poll would invalidate this XCD's caches
-            // over and over under the feet of the workgroups still working; one acquire fence
-            // follows the wait.  The pause between polls grows to about 1.7 us.
-            unsigned spins = 0;
+        bool ok = true;
+        if (!B.members) {  // the first barrier: every workgroup has to be counted first
             int pause = 1;
-            while (__hip_atomic_load(&ctl->gen.v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == g0) {
-                if (__hip_atomic_load(&ctl->err.v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) || ++spins > spin_cap) {
-                    __hip_atomic_store(&ctl->err.v, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    err = 1;
-                    break;
+            for (unsigned spins = 0; ok && ctl_load(ctl->joined) < gridDim.x; spins++) {
+                if (spins > spin_cap || ctl_load(ctl->err)) {
+                    ctl_store(ctl->err, 1u);
+                    ok = false;
                 }
-                for (int k = 0; k < pause; k++) __builtin_amdgcn_s_sleep(4);
-                if (pause < 16) pause <<= 1;
+                for (int k = 0; k < pause; k++) __builtin_amdgcn_s_sleep(2);
+                if (pause < 8) pause <<= 1;
             }
+            B.members = ctl_load(ctl->count[B.xcd]);
+            for (int x = 0; x < kMaxXcd; x++) B.xcds += ctl_load(ctl->count[x]) != 0;
         }
-        __threadfence();
-        *s_flag = err;
+        if (ok && ctl_add(ctl->arrive[B.xcd]) == B.members) {
+            ctl_store(ctl->arrive[B.xcd], 0u);  // before any of its workgroups is released
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");  // writes this XCD's L2 back
+            if (ctl_add(ctl->top) == B.xcds) {
+                ctl_store(ctl->top, 0u);
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+                ctl_store(ctl->gen, B.gen + 1u);
+            } else {
+                ok = ctl_wait(ctl, ctl->gen, B.gen, spin_cap);
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+            ctl_store(ctl->release[B.xcd], B.gen + 1u);
+        } else if (ok) {
+            ok = ctl_wait(ctl, ctl->release[B.xcd], B.gen, spin_cap);
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        }
+        B.gen++;
+        *s_flag = !ok;
     }
     __syncthreads();
     return *s_flag == 0;
@@ -1500,103 +1540,78 @@ __device__ __forceinline__ int item_instance(const int* pref, int ninst, int ite
     return lo;
 }
 
-// Persistent batched launch, the workgroup's waves sharing each work item (NT = 64: one wave).
+// Persistent launch.  The workgroup's waves share the staged energy tables and the step's prefix and
+// work in teams of consecutive waves, one work item per team at a time.  A step with more items than
+// the launch has waves gives every wave items of its own, drawn from the band's ticket counter (the
+// items' costs differ); with fewer items the teams grow (to the whole workgroup when there is at
+// most one item per workgroup), since a step then takes its longest item's time, and each team's
+// items follow from its index.  min_team is the schedule's waves per item (1, or all of a 256- or
+// 512-thread workgroup's).  With the barrier above: 7 proteins of 50-150 aa 21.0 -> 12.6 ms, 64 of
+// 50-1,000 aa 0.71 -> 0.55 s per launch.
 template <int NT>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_persistent(
     const Inst* __restrict__ insts, int ninst, int nsteps, const EnergyTables* __restrict__ E,
-    const int32_t* __restrict__ spec, BatchCtl* ctl, unsigned spin_cap) {
+    const int32_t* __restrict__ spec, BatchCtl* ctl, int min_team, unsigned spin_cap) {
+    constexpr int NWV = NT / 64;
     __shared__ SmallE S;
-    __shared__ int64_t red[NT];
-    __shared__ GroupShared<NT / 64> G;
+    __shared__ GroupShared G[NWV];
     __shared__ int pref[kMaxBatch + 1];
-    __shared__ int wsum[NT / 64];
+    __shared__ int wsum[NWV];
+    __shared__ unsigned team_ctr[NWV];
     __shared__ int s_flag;
-    __shared__ unsigned s_ticket;
+    BarrierTeam B;
+    if (threadIdx.x == 0) barrier_join(ctl, B);
     stage_tables(S, E);
-    // Work tickets of group grp number the items of its band of step 0, then of step 1, ...  A
-    // workgroup that draws a ticket beyond the current step keeps it for the step it belongs to.
     const unsigned grp = blockIdx.x & 7, ngrp = gridDim.x < 8 ? gridDim.x : 8;
-    if (threadIdx.x == 0) s_ticket = atomicAdd(&ctl->next[grp].v, 1u);
-    __syncthreads();
-    unsigned ticket = s_ticket, base = 0;
+    const unsigned grp_blocks = (gridDim.x - grp + 7) >> 3;  // workgroups of this group
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    unsigned ticket = 0, base = 0;
+    bool have_ticket = false;
     for (int step = 0; step < nsteps; step++) {
+        if (threadIdx.x < NWV) team_ctr[threadIdx.x] = 0;
         step_prefix<NT>(insts, ninst, step, pref, wsum);
-        const unsigned total = (unsigned)pref[ninst];
+        const unsigned total = (unsigned)__builtin_amdgcn_readfirstlane(pref[ninst]);
         const unsigned lo_item = (unsigned)((uint64_t)total * grp / ngrp);
         const unsigned band = (unsigned)((uint64_t)total * (grp + 1) / ngrp) - lo_item;
-        while (ticket < base + band) {
-            // the next ticket is drawn by the last wave when the item starts (in four-wave
-            // workgroups that wave rarely has a typed-value part) and published when it ends,
-            // so the atomic's latency overlaps the item instead of following it
-            const bool drawer = threadIdx.x == NT - 64;
-            unsigned nxt = 0;
-            if (drawer) nxt = atomicAdd(&ctl->next[grp].v, 1u);
-            const int item = (int)(lo_item + (ticket - base));
-            // the instance index is block-uniform
+        // the largest team that still gives every item a team at once, at least the schedule's
+        int tw = min_team;
+        while (tw < NWV && (uint64_t)total * (2 * tw) <= (uint64_t)gridDim.x * NWV) tw *= 2;
+        WaveTeam T;
+        T.n = tw;
+        T.w = wave & (tw - 1);
+        T.ctr = &team_ctr[wave - T.w];
+        GroupShared* Gs = &G[wave - T.w];
+        // team 1: tickets; larger teams: every grp_blocks * NWV / tw -th item
+        const unsigned stride = grp_blocks * (unsigned)(NWV / tw);
+        unsigned next = (blockIdx.x >> 3) * (unsigned)(NWV / tw) + (unsigned)(wave / tw);
+        if (tw == 1 && !have_ticket) {
+            unsigned t0 = 0;
+            if (T.lane() == 0) t0 = atomicAdd(&ctl->next[grp].v, 1u);
+            ticket = __builtin_amdgcn_readfirstlane(t0);
+            have_ticket = true;
+        }
+        for (;;) {
+            unsigned k = next, nxt = 0;
+            if (tw == 1) {
+                // tickets number the items of the band over the steps that draw them; one drawn beyond
+                // this step is kept for the step it belongs to
+                k = ticket - base;
+                if (k < band && T.lane() == 0) nxt = atomicAdd(&ctl->next[grp].v, 1u);  // used after the item
+            }
+            if (k >= band) break;
+            const int item = (int)(lo_item + k);
             const int inst = __builtin_amdgcn_readfirstlane(item_instance(pref, ninst, item));
             const Inst I = rebased(insts[inst]);  // a few scalar registers: bases and sizes
-            const int local = item - pref[inst], g = I.g0 + step;
+            const int local = __builtin_amdgcn_readfirstlane(item - pref[inst]), g = I.g0 + step;
             const int n = I.n, ncell_items = g <= n ? n - g + 1 : 0;
-            if (local < ncell_items) {
-                GroupCounters c = span_group(I, S, spec, local, local + g, G);
-                flush_counters(I, c, local, threadIdx.x & 63);
-            } else {
-                ext_column(I, S, n - g + 1, red);
-            }
-            if (drawer) s_ticket = nxt;
-            __syncthreads();  // the item is done and the next ticket is published
-            ticket = s_ticket;
-            __syncthreads();  // every thread has read it before the next item's drawer writes
+            if (local < ncell_items) flush_counters(I, span_group(I, S, spec, local, local + g, Gs, T), local, T.lane());
+            else ext_column(I, S, n - g + 1, Gs, T);
+            if (tw == 1) ticket = __builtin_amdgcn_readfirstlane(nxt);
+            else T.sync();  // the team's shared state is free for its next item
+            next += stride;
         }
-        base += band;
-        if (!grid_barrier(ctl, spin_cap, &s_flag)) return;
-        if (blockIdx.x == 0 && threadIdx.x == 0) ctl->steps_done.v = step + 1;
-    }
-}
-
-// Persistent batched launch, every wave of the workgroup on its own work items: the waves share
-// the staged energy tables and the step's prefix, and each draws its own tickets and works on its
-// own layer pair with wave-level ordering only.  Between a step's prefix and the grid barrier no
-// workgroup barrier is executed, since the waves run different numbers of items.
-template <int NT>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_persistent_waves(
-    const Inst* __restrict__ insts, int ninst, int nsteps, const EnergyTables* __restrict__ E,
-    const int32_t* __restrict__ spec, BatchCtl* ctl, unsigned spin_cap) {
-    __shared__ SmallE S;
-    __shared__ GroupShared<1> G[NT / 64];
-    __shared__ int pref[kMaxBatch + 1];
-    __shared__ int wsum[NT / 64];
-    __shared__ int s_flag;
-    stage_tables(S, E);
-    const unsigned grp = blockIdx.x & 7, ngrp = gridDim.x < 8 ? gridDim.x : 8;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const WaveTeam T;
-    unsigned ticket = 0, base = 0;
-    if (lane == 0) ticket = atomicAdd(&ctl->next[grp].v, 1u);
-    ticket = __builtin_amdgcn_readfirstlane(ticket);
-    for (int step = 0; step < nsteps; step++) {
-        step_prefix<NT>(insts, ninst, step, pref, wsum);
-        const unsigned total = (unsigned)pref[ninst];
-        const unsigned lo_item = (unsigned)((uint64_t)total * grp / ngrp);
-        const unsigned band = (unsigned)((uint64_t)total * (grp + 1) / ngrp) - lo_item;
-        while (ticket < base + band) {
-            unsigned nxt = 0;
-            if (lane == 0) nxt = atomicAdd(&ctl->next[grp].v, 1u);  // drawn now, used after the item
-            const int item = (int)(lo_item + (ticket - base));
-            const int inst = __builtin_amdgcn_readfirstlane(item_instance(pref, ninst, item));
-            const Inst I = rebased(insts[inst]);
-            const int local = item - pref[inst], g = I.g0 + step;
-            const int n = I.n, ncell_items = g <= n ? n - g + 1 : 0;
-            if (local < ncell_items) {
-                GroupCounters c = span_group(I, S, spec, local, local + g, G[wave], T);
-                flush_counters(I, c, local, lane);
-            } else {
-                ext_column(I, S, n - g + 1, nullptr, T);
-            }
-            ticket = __builtin_amdgcn_readfirstlane(nxt);
-        }
-        base += band;
-        if (!grid_barrier(ctl, spin_cap, &s_flag)) return;
+        if (tw == 1) base += band;
+        if (!grid_barrier(ctl, B, spin_cap, &s_flag)) return;
         if (blockIdx.x == 0 && threadIdx.x == 0) ctl->steps_done.v = step + 1;
     }
 }
@@ -1605,10 +1620,13 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
 __global__ void k_batch_init(const Inst* __restrict__ insts, int ninst, BatchCtl* ctl) {
     const Inst I = rebased(insts[blockIdx.x]);
     const int tid = threadIdx.x, nt = blockDim.x;
-    if (blockIdx.x == 0 && tid < 8) {
+    if (blockIdx.x == 0 && tid < kMaxXcd) {
         ctl->arrive[tid].v = 0;
-        ctl->next[tid].v = 0;
+        ctl->release[tid].v = 0;
+        ctl->count[tid].v = 0;
+        if (tid < 8) ctl->next[tid].v = 0;
         if (tid == 0) {
+            ctl->joined.v = 0;
             ctl->top.v = 0;
             ctl->gen.v = 0;
             ctl->err.v = 0;
@@ -1729,24 +1747,27 @@ hipError_t persistent_occupancy(int threads, int item_waves, int* blocks_per_cu)
     if (!persistent_schedule_valid(threads, item_waves)) return hipErrorInvalidValue;
     if (threads == 64) return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, k_persistent<64>, 64, 0);
     if (threads == 512) return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, k_persistent<512>, 512, 0);
-    if (item_waves == 1)
-        return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, k_persistent_waves<256>, 256, 0);
     return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, k_persistent<256>, 256, 0);
 }
 
+// A schedule of 2 or 4 workgroups of 256 threads on every CU runs as one workgroup of 512 or 1,024
+// threads per CU: the same waves, one staging of the energy tables and one barrier arrival per CU.
 hipError_t launch_persistent(const Inst* insts_dev, int ninst, int nsteps, const EnergyTables* E,
-                             const int32_t* spec, BatchCtl* ctl, int grid, int threads, int item_waves,
+                             const int32_t* spec, BatchCtl* ctl, int grid, int threads, int item_waves, int num_cu,
                              unsigned spin_cap, hipStream_t st) {
     if (!persistent_schedule_valid(threads, item_waves)) return hipErrorInvalidValue;
-    if (threads == 64)
-        hipLaunchKernelGGL(k_persistent<64>, dim3(grid), dim3(64), 0, st, insts_dev, ninst, nsteps, E, spec, ctl, spin_cap);
-    else if (threads == 512)
-        hipLaunchKernelGGL(k_persistent<512>, dim3(grid), dim3(512), 0, st, insts_dev, ninst, nsteps, E, spec, ctl, spin_cap);
-    else if (item_waves == 1)
-        hipLaunchKernelGGL(k_persistent_waves<256>, dim3(grid), dim3(256), 0, st, insts_dev, ninst, nsteps, E, spec,
-                           ctl, spin_cap);
-    else
-        hipLaunchKernelGGL(k_persistent<256>, dim3(grid), dim3(256), 0, st, insts_dev, ninst, nsteps, E, spec, ctl, spin_cap);
+    if (threads == 256 && (grid == 2 * num_cu || grid == 4 * num_cu)) {
+        threads *= grid / num_cu;
+        grid = num_cu;
+    }
+#define SD_LAUNCH(NT)                                                                                              \
+    hipLaunchKernelGGL(k_persistent<NT>, dim3(grid), dim3(NT), 0, st, insts_dev, ninst, nsteps, E, spec, ctl, item_waves, \
+                       spin_cap)
+    if (threads == 64) SD_LAUNCH(64);
+    else if (threads == 256) SD_LAUNCH(256);
+    else if (threads == 512) SD_LAUNCH(512);
+    else SD_LAUNCH(1024);
+#undef SD_LAUNCH
     return hipGetLastError();
 }
 

@@ -267,7 +267,8 @@ sd_status round_once(sd_server* S) {
     if (e == hipSuccess) e = launch_batch_init(insts, n, ctl, st);
     if (e == hipSuccess)
         e = launch_persistent(insts, n, S->cfg.steps_per_round, (const EnergyTables*)S->ctx->E_dev,
-                              (const int32_t*)S->ctx->spec_dev, ctl, S->grid, S->threads, S->item_waves, 1u << 22,
+                              (const int32_t*)S->ctx->spec_dev, ctl, S->grid, S->threads, S->item_waves,
+                              S->ctx->num_cu, 1u << 22,
                               st);
     BatchCtl h;
     if (e == hipSuccess) e = hipMemcpyAsync(&h, ctl, sizeof(h), hipMemcpyDeviceToHost, st);
