@@ -195,7 +195,6 @@ sd_status context_create(int device, const sd_options* opt, bool ext, void* ext_
     } else if (e == hipSuccess) {
         e = hipStreamCreateWithFlags(&c->stream, hipStreamNonBlocking);
     }
-    if (e == hipSuccess) e = upload_pair_order();
     // this device's address of the static scratch array of sd_design_noalloc (its own error
     // is reported by that entry point; the other entry points do not use the array)
     if (e == hipSuccess && scratch_setup(device) != SD_OK) g_err.clear();
@@ -297,8 +296,7 @@ InstLayout layout_instance(const Lattice& L, char* A, char* B, Inst& I) {
     I.ra = A;
     I.rb = B;
     I.nE = (int64_t)L.in_src.size();
-    I.nF = (int64_t)L.fwd_meta.size();
-    I.nB = (int64_t)L.bwd_meta.size();
+    I.nrec = (int64_t)L.recs.size();
     I.cells = L.cells;
     I.slots = L.cand_slots;
     I.n = L.n;
@@ -319,9 +317,7 @@ InstLayout layout_instance(const Lattice& L, char* A, char* B, Inst& I) {
         {I.tail(), 8 * N, U}, {I.pfx(), 4 * N, U}, {I.P(), 8 * ((int64_t)L.A + 1), U},
         {I.hp_init(), 4 * (n + 1), U}, {I.rowoff(), 8 * N, U}, {I.coff(), 8 * N, U},
         {I.ccap(), 4 * N, U}, {I.ccnt(), 4 * N, U}, {I.X(), 8 * N, U},
-        {I.out_dst(), 16 * N, 2 * U}, {I.out_U(), 32 * N, 4 * U}, {I.alphaU(), 32 * N, 4 * U},
-        {I.betaU(), 32 * N, 4 * U}, {I.fwd_off(), 4 * (int64_t)L.fwd_off.size(), 3 * U},
-        {I.bwd_off(), 4 * (int64_t)L.bwd_off.size(), 3 * U},
+        {I.out_dst(), 16 * N, 2 * U}, {I.out_U(), 32 * N, 4 * U},
         {I.stats(), 96, U}, {I.visits(), 8 * (n + 1), U}, {I.feasible(), 8 * (n + 1), U},
         {I.inmask(), 4 * N, U}, {I.tr_seq(), 4 * n, U}, {I.tr_pair(), 4 * n, U},
         {I.tr_stack(), 16 * (n + 2), 2 * U}, {I.cstrict(), 4 * N, U},
@@ -329,7 +325,7 @@ InstLayout layout_instance(const Lattice& L, char* A, char* B, Inst& I) {
         {I.JDL(), 8 * (int64_t)kLMRing * N * 12, 12 * R}, {I.BI(), 8 * (int64_t)kLMRing * N, R},
         {I.BJ(), 8 * (int64_t)kLMRing * N, R}, {I.RS(), 8 * (int64_t)kLMRing * N * 16, 16 * R},
         {I.LS(), 8 * (int64_t)kLMRing * N * 16, 16 * R}, {I.MINI(), 8 * (int64_t)kLMRing * (n + 1) * 2, 2 * R}};
-    bool ok = L.fwd_crow.size() == L.fwd_meta.size() && (int64_t)L.inmask.size() == N && (int64_t)L.fwd_off.size() == 4 * N + 1 && (int64_t)L.bwd_off.size() == 4 * N + 1;
+    bool ok = (int64_t)L.inmask.size() == N && (L.recs.empty() || (int64_t)L.recs.size() == 2 * (n + 1));
     for (const Ext& e : ea) ok = ok && e.bytes <= e.slot;
     // the span kernels locate the cells of edge neighbours from the layering: every edge must
     // join consecutive layers (the in-edges are the out-edges reversed)
@@ -371,15 +367,7 @@ void stage_inputs(const Lattice& L, const Inst& I, const char* devA, char* image
     put(I.rowoff(), L.rowoff.data(), L.rowoff.size() * 8);
     put(I.coff(), L.coff.data(), L.coff.size() * 8);
     put(I.ccap(), L.ccap.data(), L.ccap.size() * 4);
-    put(I.alphaU(), L.alphaU.data(), L.alphaU.size() * 8);
-    put(I.betaU(), L.betaU.data(), L.betaU.size() * 8);
-    put(I.fwd_off(), L.fwd_off.data(), L.fwd_off.size() * 4);
-    put(I.fwd_meta(), L.fwd_meta.data(), L.fwd_meta.size() * 4);
-    put(I.fwd_cost(), L.fwd_cost.data(), L.fwd_cost.size() * 8);
-    put(I.fwd_crow(), L.fwd_crow.data(), L.fwd_crow.size() * 8);
-    put(I.bwd_off(), L.bwd_off.data(), L.bwd_off.size() * 4);
-    put(I.bwd_meta(), L.bwd_meta.data(), L.bwd_meta.size() * 4);
-    put(I.bwd_cost(), L.bwd_cost.data(), L.bwd_cost.size() * 8);
+    put(I.recs(), L.recs.data(), L.recs.size() * sizeof(SlotRec));
     if (L.generic) {
         put(I.gjob_off(), L.gjob_off.data(), L.gjob_off.size() * 8);
         put(I.gjobs(), L.gjobs.data(), L.gjobs.size() * 4);
@@ -436,18 +424,12 @@ hipError_t read_stats(const Inst& I, hipStream_t st, unsigned long long out[4]) 
     return hipSuccess;
 }
 
-// Tile of the span step for a span with `pairs` layer pairs when no tuning data decide it.  Eight
-// or sixteen waves per pair shorten each pair's critical path (more of its typed-value job parts
-// run at once) but leave fewer workgroups resident per CU (three of eight waves, against four of
-// four), so eight pay only up to about SPAN_WIDE_PER_CU pairs per CU (of 2, 3, 4, 6, 12 and 64,
-// 12 was fastest on a 1,976-aa design and 4 to 64 tied on a 300-aa one), and sixteen while there
-// is at most one pair per CU.
-#ifndef SPAN_WIDE_PER_CU
-#define SPAN_WIDE_PER_CU 12
-#endif
-#ifndef SPAN_XWIDE_PER_CU
-#define SPAN_XWIDE_PER_CU 1
-#endif
+// Tile of the span step for a span with `pairs` layer pairs when no tuning data decide it: the widest
+// workgroup of which the chip holds one per pair (one of 16 waves per CU, two of 8, four of 4), since
+// a span then takes its slowest pair's time and more waves shorten it; four waves beyond.  Fill times
+// with one tile for every span, 16 / 8 / 4 waves: 50 aa (150 pairs at most) 2.10 / 2.19 / 2.49 ms, 120 aa
+// (360) 5.74 / 5.47 / 6.12 ms, 300 aa (900) 20.5 / 17.1 / 16.7 ms, 925 aa (2,775) 134 / 93 / 79 ms.
+constexpr int kSpanXwidePerCu = 1, kSpanWidePerCu = 2;
 sd_status run_plain_on(sd_context* c, const Lattice& L, Inst& I, const EnergyTables* Et, const int32_t* spec,
                        int kernel_timing, int64_t* overflow_span);
 
@@ -459,7 +441,7 @@ constexpr int kSpanCandWaves[sd_context::kSpanCands] = {16, 8, 4, 1};
 
 SpanTile span_tile_default(const sd_context* c, int pairs) {
     SpanTile t;
-    t.threads = pairs <= SPAN_XWIDE_PER_CU * c->num_cu ? 1024 : pairs <= SPAN_WIDE_PER_CU * c->num_cu ? 512 : 256;
+    t.threads = pairs <= kSpanXwidePerCu * c->num_cu ? 1024 : pairs <= kSpanWidePerCu * c->num_cu ? 512 : 256;
     t.item_waves = t.threads / 64;
     return t;
 }
@@ -565,7 +547,7 @@ sd_status run_plain_on(sd_context* c, const Lattice& L, Inst& I, const EnergyTab
         if (e == hipSuccess && L.generic)
             e = launch_span_gen(I, Et, spec, g, ext, c->num_cu, st);
         else if (e == hipSuccess)
-            e = launch_span(I, Et, spec, g, ext, tile.threads, tile.item_waves, st);
+            e = launch_span(I, Et, spec, g, ext, tile.threads, tile.item_waves, c->num_cu, st);
         if (timed && e == hipSuccess) e = hipEventRecord(c->tev[2 * (g - 1) + 1], st);
         if (check && e == hipSuccess) {
             // the same step again with another workgroup size from the same inputs
@@ -578,7 +560,7 @@ sd_status run_plain_on(sd_context* c, const Lattice& L, Inst& I, const EnergyTab
             SpanTile other;
             other.threads = tile.threads == 1024 ? 256 : 1024;
             other.item_waves = tile.threads == 1024 ? 1 : 16;
-            if (e == hipSuccess) e = launch_span(I, Et, spec, g, ext, other.threads, other.item_waves, st);
+            if (e == hipSuccess) e = launch_span(I, Et, spec, g, ext, other.threads, other.item_waves, c->num_cu, st);
             if (e == hipSuccess) e = launch_checksum(I, g, dsum + 1, st);
             unsigned long long h[2] = {0, 0};
             if (e == hipSuccess) e = hipMemcpyAsync(h, dsum, sizeof(h), hipMemcpyDeviceToHost, st);
@@ -1138,10 +1120,6 @@ extern "C" sd_status sd_multiloop_abstract(sd_context* c, int N, const int32_t* 
         L.pfx.assign(N, 0);
         L.P.assign(2, 0);
         L.hp_init.assign(L.n + 1, 0);
-        L.alphaU.assign(4 * (size_t)N, kINF);
-        L.betaU.assign(4 * (size_t)N, kINF);
-        L.fwd_off.assign(4 * (size_t)N + 1, 0);
-        L.bwd_off.assign(4 * (size_t)N + 1, 0);
         // cells in row layout; worst-case candidate segments (a direct arc may have any span)
         L.rowoff.assign(N, 0);
         L.coff.assign(N, 0);

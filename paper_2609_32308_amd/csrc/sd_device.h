@@ -87,12 +87,11 @@ struct Params;
 InstLayout layout_instance(const Lattice& L, char* A, char* B, Inst& I);
 hipError_t read_stats(const Inst& I, hipStream_t st, unsigned long long out[4]);
 void stage_inputs(const Lattice& L, const Inst& I, const char* devA, char* image);
-hipError_t upload_pair_order();
 hipError_t launch_init(const Inst& I, hipStream_t st);
 // one span step: threads per workgroup with item_waves = threads / 64 (the waves share each layer
 // pair), or 256 threads with item_waves = 1 (every wave on its own pair)
 hipError_t launch_span(const Inst& I, const EnergyTables* E, const int32_t* spec, int g,
-                       int ext_layer, int threads, int item_waves, hipStream_t st);
+                       int ext_layer, int threads, int item_waves, int num_cu, hipStream_t st);
 hipError_t launch_ext(const Inst& I, const EnergyTables* E, int L, hipStream_t st);
 // canonical traceback of one design (one workgroup of eight wavefronts) / of every design of a
 // device Inst array (one such workgroup each)

@@ -17,52 +17,24 @@ static __constant__ int kTY[6] = {3, 2, 1, 3, 0, 2};  // 3' base
 static __constant__ int kRev[6] = {4, 2, 1, 5, 0, 3}; // type of the reversed pair
 static __constant__ int kPairType[16] = {-1, -1, -1, 0, -1, -1, 1, -1, -1, 2, -1, 3, 4, -1, 5, -1};
 
-// Loop tables staged in LDS per workgroup (~27 KB; the 1x2 and 2x2 full-loop tables as 16-bit
-// copies).
-struct SmallE {
-    alignas(16) int16_t int21[6][6][4][4][4];    // 1x2 loops (staged from the 16-bit copies)
-    alignas(16) int16_t int22[6][6][4][4][4][4]; // 2x2 loops
-    int32_t stack[6][6];
-    // boundary tables by class, addressed as one array [class][type][16]: hairpin, generic interior,
-    // 1xn, 2x3, and the terminal AU/GU penalty of the type (the same for all 16 label pairs)
-    int32_t mmH[6][4][4], mmI[6][4][4], mm1n[6][4][4], mm23[6][4][4], mmA[6][4][4];
-    int32_t int11[6][6][4][4];
-    int32_t hairpin[31], bulge[31], interior[31];
-    int32_t ml_closing, ml_intern, ml_base, terminal_au, ninio, ninio_max;
-};
-
-__device__ inline void stage_tables(SmallE& S, const EnergyTables* __restrict__ E) {
-    const int t = threadIdx.x, nt = blockDim.x;
-    {
-        static_assert(sizeof(S.int21) + sizeof(S.int22) == 23040, "int21 + int22 copies");
-        static_assert(offsetof(EnergyTables, int22h) == offsetof(EnergyTables, int21h) + sizeof(S.int21),
-                      "adjacent 16-bit tables");
-        const uint4* src = reinterpret_cast<const uint4*>(&E->int21h[0][0][0][0][0]);
-        uint4* dst = reinterpret_cast<uint4*>(&S.int21[0][0][0][0][0]);
-        for (int i = t; i < 23040 / 16; i += nt) dst[i] = src[i];
-    }
-    for (int i = t; i < 36; i += nt) (&S.stack[0][0])[i] = (&E->stack[0][0])[i];
-    for (int i = t; i < 96; i += nt) {
-        (&S.mmH[0][0][0])[i] = (&E->mmH[0][0][0])[i];
-        (&S.mmI[0][0][0])[i] = (&E->mmI[0][0][0])[i];
-        (&S.mm1n[0][0][0])[i] = (&E->mm1n[0][0][0])[i];
-        (&S.mm23[0][0][0])[i] = (&E->mm23[0][0][0])[i];
-        (&S.mmA[0][0][0])[i] = (i >> 4 == 1 || i >> 4 == 2) ? 0 : E->terminal_au;
-    }
-    for (int i = t; i < 576; i += nt) (&S.int11[0][0][0][0])[i] = (&E->int11[0][0][0][0])[i];
-    for (int i = t; i < 31; i += nt) {
-        S.hairpin[i] = E->hairpin[i];
-        S.bulge[i] = E->bulge[i];
-        S.interior[i] = E->interior[i];
-    }
-    if (t == 0) {
-        S.ml_closing = E->ml_closing;
-        S.ml_intern = E->ml_intern;
-        S.ml_base = E->ml_base;
-        S.terminal_au = E->terminal_au;
-        S.ninio = E->ninio;
-        S.ninio_max = E->ninio_max;
-    }
+// Copies the loop tables to LDS, straight from memory (no registers in between): one KiB per wave and
+// instruction.  stage_wait ends the copy for the whole workgroup; loads that do not need the tables
+// can be issued in between.
+__device__ __forceinline__ void stage_begin(SmallE& S, const EnergyTables* __restrict__ E) {
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, nw = blockDim.x >> 6;
+    const char* src = reinterpret_cast<const char*>(&E->small);
+    char* dst = reinterpret_cast<char*>(&S);
+    for (int c = wave; c < (int)(sizeof(SmallE) / 1024); c += nw)
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src + c * 1024 + lane * 16),
+                                         (__attribute__((address_space(3))) void*)(dst + c * 1024), 16, 0, 0);
+}
+__device__ __forceinline__ void stage_wait() {
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this wave's share has landed
+    __syncthreads();
+}
+__device__ __forceinline__ void stage_tables(SmallE& S, const EnergyTables* __restrict__ E) {
+    stage_begin(S, E);
+    stage_wait();
 }
 
 // The region bases of an instance as global pointers the compiler knows nothing else about.  A
@@ -78,6 +50,16 @@ __device__ __forceinline__ Inst rebased(Inst I) {
     I.ra = global_base(I.ra);
     I.rb = global_base(I.rb);
     return I;
+}
+
+// A descriptor from memory that no kernel writes: scalar loads.
+__device__ __forceinline__ Inst load_inst(const Inst* p) {
+    const __attribute__((address_space(4))) uint64_t* w = (const __attribute__((address_space(4))) uint64_t*)(uintptr_t)p;
+    Inst I;
+    uint64_t* d = reinterpret_cast<uint64_t*>(&I);
+#pragma unroll
+    for (int k = 0; k < (int)(sizeof(Inst) / 8); k++) d[k] = w[k];
+    return rebased(I);
 }
 
 __device__ __forceinline__ int ptype(int x, int y) { return kPairType[x * 4 + y]; }

@@ -22,6 +22,22 @@ constexpr int64_t kHalfINF = int64_t(1) << 61;  // anything above is infeasible
 constexpr int kMaxLoop = 30;                    // bulge / interior unpaired cap (Sec. 3)
 constexpr int kNumPairs = 496;                  // (l1,l2) with l1 + l2 <= 30
 
+// Loop tables as the kernels stage them in LDS, a multiple of 1 KiB (the 1x2 and 2x2 full-loop tables as
+// 16-bit copies; the parser requires entries in [-32768, 32767]).
+struct SmallE {
+    alignas(16) int16_t int21[6][6][4][4][4];    // 1x2 loops
+    alignas(16) int16_t int22[6][6][4][4][4][4]; // 2x2 loops
+    int32_t stack[6][6];
+    // boundary tables by class, addressed as one array [class][type][16]: hairpin, generic interior,
+    // 1xn, 2x3, and the terminal AU/GU penalty of the type (the same for all 16 label pairs)
+    int32_t mmH[6][4][4], mmI[6][4][4], mm1n[6][4][4], mm23[6][4][4], mmA[6][4][4];
+    int32_t int11[6][6][4][4];
+    int32_t hairpin[31], bulge[31], interior[31];
+    int32_t ml_closing, ml_intern, ml_base, terminal_au, ninio, ninio_max;
+    int32_t pad[217];
+};
+static_assert(sizeof(SmallE) % 1024 == 0, "staged in pieces of 1 KiB");
+
 // Energy tables in 0.01 kcal/mol; two-loop tables index the inner pair from inside the loop.
 struct EnergyTables {
     int32_t stack[6][6];
@@ -32,10 +48,7 @@ struct EnergyTables {
     int32_t hairpin[31], bulge[31], interior[31];
     int32_t ml_closing, ml_intern, ml_base, terminal_au, ninio, ninio_max;
     int32_t pad[2];
-    // 16-bit copies of int21 / int22 (the parser requires entries in [-32768, 32767]) that the
-    // kernels stage into LDS with 16-byte copies
-    alignas(16) int16_t int21h[6][6][4][4][4];
-    alignas(16) int16_t int22h[6][6][4][4][4][4];
+    alignas(16) SmallE small;  // what the kernels stage
 };
 
 // Special hairpin lookup: key = base-4 number of the loop sequence (closing pair included),
@@ -58,12 +71,11 @@ struct TFrame {
 // >= 8 * (n + 2) and >= 8 * (A + 1), a multiple of 256; unit k starts at ra + k * U:
 //   0 layer[N]  1 off[n+2]  2 in_start[N+1]  3 tail[N]  4 pfx[N]  5 P[A+1]  6 hp_init[n+1]
 //   7 rowoff[N]  8 coff[N]  9 ccap[N]  10 ccnt[N]  11 X[N]  12-13 out_dst[4N]  14-17 out_U[4N]
-//   18-21 alphaU[4N]  22-25 betaU[4N]  26-28 fwd_off[4N+1]  29-31 bwd_off[4N+1]
-//   32 stats[4], trace results [8..11]
-//   33 visits[n+1]  34 feasible[n+1]  35 inmask[N]  36 tr_seq[n]  37 tr_pair[n]
-//   38-39 tr_stack[n+2] (16-byte frames)  40 cstrict[N]
-//   41.. in_src[nE], in_lab[nE], in_U[nE], fwd_meta[nF], fwd_cost[nF], bwd_meta[nB],
-//         bwd_cost[nB], fwd_crow[nF] (each start 8-byte aligned)
+//   18 stats[4], trace results [8..11]
+//   19 visits[n+1]  20 feasible[n+1]  21 inmask[N]  22 tr_seq[n]  23 tr_pair[n]
+//   24-25 tr_stack[n+2] (16-byte frames)  26 cstrict[N]
+//   27.. in_src[nE], in_lab[nE], in_U[nE] (each start 8-byte aligned), then for the codon trie
+//        recs[nrec] (64-byte aligned, SlotRec)
 // Region B (DP tables) is cut into ring units of R = 512 * N bytes (N states x 64 spans x 8 B):
 //   0-1 LM  2-13 IDL  14-25 JDL  26 BI  27 BJ  28-43 RS  44-59 LS  60-61 MINI, then from 62 R:
 //   V[cells][6], Bt[cells], S1[cells], S2[cells], cc[slots], cB[slots], and for generic lattices
@@ -87,21 +99,44 @@ struct TFrame {
 //   strict candidates per right endpoint (retain-all control only); visits / feasible:
 //   candidate visits and cells with finite B, summed per left layer (one adder per layer pair
 //   and step, so the counters see no contention).
-//   alphaU[d*4+x] = U(d -x-> d2) + tail(d2); betaU[c*4+x] = min U over in-edges of c labelled x.
-//   LM[layer][class 2][span]: layer-pair minima of the both-separable interior form.
+//   LM[layer][class 2][span]: layer-pair minima of the both-separable interior form.  The rings of a
+//   separable side (LM, IDL, JDL, BI, BJ) already hold the whole-codon prefix term of their own
+//   layers; a consumer adds the one of its closing pair.
 //   MINI[layer p][span][class 2]: both-separable interior minimum of layer pair (p, p + span),
 //   prepared one step ahead.
 //   IDL/JDL[state][class 3][label 4][span]: inner minima per left / right inner state.
-//   fwd_*/bwd_*: label paths of 1..3 edges out of / into a state (CSR by state*4+l-1);
-//   meta = other_end << 4 | first_label << 2 | last_label, cost = sum of edge costs; fwd_crow =
-//   the cell-row base of the path's end state c (cell(c, d) = fwd_crow + d).
 //   BI[c][span] = min over d, t' of V_t'(c,d) + tail(d) + AU(t');  BJ[d][span] likewise without
 //   the tail.  RS[c][span][l-1][label], LS[d][span][l-1][label]: one-sided loops minimised over
 //   the separable side's length (explicit side of l <= 3 bases).
+// Everything the span step needs of one state of the codon trie in one record, two records per layer
+// (a layer of the trie holds one or two states), so that it is found from the layer alone with one
+// level of loads.
+constexpr int kTrieWidth = 2, kFwdPaths = 12, kBwdPaths = 18;
+struct alignas(64) SlotRec {
+    int32_t state;            // state index (-1: the layer has no second state)
+    uint8_t inmask, outmask;  // labels of the in- and out-edges
+    uint8_t nf[3], nb[3];     // forward / backward paths of 1, up to 2, up to 3 edges
+    int8_t dst[4];            // out-edge by label: slot in the next layer (-1: none)
+    int64_t rowbase;          // cell(state, b) = rowbase + b
+    int64_t tail, coff;       // cheapest completion of the codon; candidate segment
+    int32_t ccap, pad;
+    // whole-codon prefix terms of the layer l as the closing layer of a pair (P at (l + 1) / 3 + 1,
+    // (l + 2) / 3 + 1, (l - 1) / 3, (l - 2) / 3) and as an inner layer (P at l / 3 + 1 and
+    // (l + 1) / 3 + 1 to take off, l / 3 and (l - 1) / 3 to add)
+    int64_t pa1, pa2, pb1, pb2, in1, in2, ip0, ip1;
+    int64_t outU[4];          // out-edge costs by label
+    int64_t alpha[4];         // U of the out-edge labelled x + tail of its target
+    int64_t beta[4];          // min U over the in-edges labelled x
+    // label paths of 1..3 edges out of / into the state, by length (3 from / into codon boundaries
+    // only): meta = other end << 4 | first label << 2 | last label, cost, row base of the end state
+    int64_t fcost[kFwdPaths], fcrow[kFwdPaths], bcost[kBwdPaths];
+    int32_t fmeta[kFwdPaths], bmeta[kBwdPaths];
+};
+
 struct Inst {
     char *ra, *rb;         // region bases
     int64_t U;             // region-A unit in bytes
-    int64_t nE, nF, nB;    // in-edges, forward and backward path entries
+    int64_t nE, nrec;      // in-edges, slot records (0 for generic lattices)
     int64_t cells, slots;  // DP cells, candidate slots
     int64_t mlbase_fx;     // ML_base * 2^s
     int64_t njobs;         // generic lattices: typed-value jobs over all spans
@@ -130,37 +165,24 @@ struct Inst {
     __host__ __device__ int64_t* X() const { return (int64_t*)ua(11); }
     __host__ __device__ const int* out_dst() const { return (const int*)ua(12); }
     __host__ __device__ const int64_t* out_U() const { return (const int64_t*)ua(14); }
-    __host__ __device__ const int64_t* alphaU() const { return (const int64_t*)ua(18); }
-    __host__ __device__ const int64_t* betaU() const { return (const int64_t*)ua(22); }
-    __host__ __device__ const int* fwd_off() const { return (const int*)ua(26); }
-    __host__ __device__ const int* bwd_off() const { return (const int*)ua(29); }
-    __host__ __device__ unsigned long long* stats() const { return (unsigned long long*)ua(32); }
-    __host__ __device__ unsigned long long* visits() const { return (unsigned long long*)ua(33); }
-    __host__ __device__ unsigned long long* feasible() const { return (unsigned long long*)ua(34); }
-    __host__ __device__ const int* inmask() const { return (const int*)ua(35); }
-    __host__ __device__ int* tr_seq() const { return (int*)ua(36); }
-    __host__ __device__ int* tr_pair() const { return (int*)ua(37); }
-    __host__ __device__ TFrame* tr_stack() const { return (TFrame*)ua(38); }
-    __host__ __device__ int* cstrict() const { return (int*)ua(40); }
-    __host__ __device__ long long* tr_res() const { return (long long*)ua(32) + 8; }
-    __host__ __device__ const int* in_src() const { return (const int*)ua(41); }
-    __host__ __device__ const int* in_lab() const { return (const int*)(ua(41) + al8(4 * nE)); }
-    __host__ __device__ const int64_t* in_U() const { return (const int64_t*)(ua(41) + 2 * al8(4 * nE)); }
-    __host__ __device__ char* paths() const { return ua(41) + 2 * al8(4 * nE) + 8 * nE; }
-    __host__ __device__ const int* fwd_meta() const { return (const int*)paths(); }
-    __host__ __device__ const int64_t* fwd_cost() const { return (const int64_t*)(paths() + al8(4 * nF)); }
-    __host__ __device__ const int* bwd_meta() const { return (const int*)(paths() + al8(4 * nF) + 8 * nF); }
-    __host__ __device__ const int64_t* bwd_cost() const {
-        return (const int64_t*)(paths() + al8(4 * nF) + 8 * nF + al8(4 * nB));
-    }
-    __host__ __device__ const int64_t* fwd_crow() const {
-        return (const int64_t*)(paths() + al8(4 * nF) + 8 * nF + al8(4 * nB) + 8 * nB);
+    __host__ __device__ unsigned long long* stats() const { return (unsigned long long*)ua(18); }
+    __host__ __device__ unsigned long long* visits() const { return (unsigned long long*)ua(19); }
+    __host__ __device__ unsigned long long* feasible() const { return (unsigned long long*)ua(20); }
+    __host__ __device__ const int* inmask() const { return (const int*)ua(21); }
+    __host__ __device__ int* tr_seq() const { return (int*)ua(22); }
+    __host__ __device__ int* tr_pair() const { return (int*)ua(23); }
+    __host__ __device__ TFrame* tr_stack() const { return (TFrame*)ua(24); }
+    __host__ __device__ int* cstrict() const { return (int*)ua(26); }
+    __host__ __device__ long long* tr_res() const { return (long long*)ua(18) + 8; }
+    __host__ __device__ const int* in_src() const { return (const int*)ua(27); }
+    __host__ __device__ const int* in_lab() const { return (const int*)(ua(27) + al8(4 * nE)); }
+    __host__ __device__ const int64_t* in_U() const { return (const int64_t*)(ua(27) + 2 * al8(4 * nE)); }
+    __host__ __device__ const SlotRec* recs() const {
+        return (const SlotRec*)(ra + ((ua(27) + 2 * al8(4 * nE) + 8 * nE - ra + 63) & ~(int64_t)63));
     }
     // generic lattices: per span g the typed-value jobs [gjob_off[g], gjob_off[g+1]) of gjobs
     // (pairs a, b * 8 + type), and one work-ticket counter per span
-    __host__ __device__ int64_t* gjob_off() const {
-        return (int64_t*)(paths() + al8(4 * nF) + 8 * nF + al8(4 * nB) + 8 * nB + 8 * nF);
-    }
+    __host__ __device__ int64_t* gjob_off() const { return (int64_t*)(recs() + nrec); }
     __host__ __device__ int* gjobs() const { return (int*)(gjob_off() + (gwin ? n + 2 : 0)); }
     __host__ __device__ unsigned* gtickets() const { return (unsigned*)(gjobs() + 2 * njobs); }
     __host__ __device__ int64_t a_bytes() const {
@@ -190,7 +212,7 @@ struct Inst {
 };
 
 constexpr int kLMRing = 64;
-constexpr int kMaxWidth = 4;  // states per layer (the lattice build rejects wider layers)
+constexpr int kMaxWidth = 4;  // states per layer of an abstract DAG (the multiloop test hook)
 constexpr int kGenMaxWidth = 16;  // states per layer of a generic (motif-constrained) lattice
 constexpr int kGenLoopWin = 30;   // layer distances covered by the labelled gap table
 constexpr int kMaxWaves = 16;  // waves per workgroup of the span-step kernels (1024 threads)

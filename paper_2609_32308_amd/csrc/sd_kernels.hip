@@ -27,18 +27,12 @@
 #include <stddef.h>
 #include <string.h>
 
-#include <type_traits>
+#include <algorithm>
 
 #include "sd_devutil.h"
 #include "sd_internal.h"
 
 namespace sd {
-
-// (l1, l2) pairs whose two segments are both separable (see sep_left), for each phase
-// (p mod 3, q mod 3), sorted by l1 + l2 so that the pairs allowed at span g (l1 + l2 <= g - 7) form
-// a prefix.  Entries: l1 | l2 << 5.  Counts: kFastCnt[phase][cap].
-__constant__ unsigned short kFastList[9][kNumPairs];
-__constant__ unsigned short kFastCnt[9][31];
 
 // Pair types as bit fields: 5' base, 3' base, and the type of the reversed pair.
 __device__ __forceinline__ constexpr int type_x(int t) { return (0xFA4 >> (2 * t)) & 3; }
@@ -98,11 +92,12 @@ __device__ int64_t hairpin_lane(const IT& I, const SmallE& S, const int32_t* __r
 // its cheapest path with given end labels then costs first edge + rest of the first edge's codon
 // + whole codons + last edge, with no coupling between the two labels.  The left segment of a loop
 // closed by (p, q) runs from layer p + 1 to p + 1 + l1, the right one from q - 1 - l2 to q - 1.
-// With alpha(d, x) = U(first edge) + tail and beta(c, x) = U(last edge) the whole codons are PLt / PRt;
+// With alpha(d, x) = U(first edge) + tail and beta(c, x) = U(last edge) the whole codons are
+// P[(p + l1) / 3] - P[(p + 2) / 3 + 1] on the left and P[(q - 2) / 3] - P[(q - l2) / 3 + 1] on the right;
 // a segment that starts with a third base takes all further bases from the next codon, whose
-// minimum is in alpha's tail and is taken off again by PLt / PRt (the weight cost sits on third edges).
-__host__ __device__ __forceinline__ bool sep_left(int p, int l1) { return (p + 1) / 3 != (p + l1) / 3; }
-__host__ __device__ __forceinline__ bool sep_right(int q, int l2) { return (q - 1 - l2) / 3 != (q - 2) / 3; }
+// minimum is in alpha's tail and is taken off again by the prefix difference (the weight cost sits on
+// third edges).  Shortest separable lengths: left 3, 2, 4 for p mod 3 = 0, 1, 2; right 2, 3, 4 for
+// (q - 2) mod 3 = 0, 1, 2; every longer one is separable too.
 // per-state rings [state][class][label][span mod 64]: a consumer walks consecutive spans
 __device__ __forceinline__ int64_t ring_idx(int state, int span, int X, int lab) {
     return (((int64_t)state * 3 + X) * 4 + lab) * kLMRing + (span & (kLMRing - 1));
@@ -119,10 +114,10 @@ __device__ __forceinline__ int64_t mini_idx(int p, int span, int X) {
 __device__ __forceinline__ int64_t rs_idx(int state, int span, int l, int lab) {
     return ((int64_t)state * kLMRing + (span & (kLMRing - 1))) * 16 + (l - 1) * 4 + lab;
 }
-template <class IT>
-__device__ __forceinline__ int64_t PLt(const IT& I, int p, int l1) { return I.P()[(p + l1) / 3] - I.P()[(p + 2) / 3 + 1]; }
-template <class IT>
-__device__ __forceinline__ int64_t PRt(const IT& I, int q, int l2) { return I.P()[(q - 2) / 3] - I.P()[(q - l2) / 3 + 1]; }
+// The slot records, read-only while a kernel runs: through the constant address space, so that
+// uniform reads go to scalar registers.
+typedef const __attribute__((address_space(4))) SlotRec* SlotPtr;
+__device__ __forceinline__ SlotPtr slot_ptr(const Inst& I) { return (SlotPtr)(uintptr_t)I.recs(); }
 
 // A value every lane of the wave holds, moved to a scalar register so that the addresses and loop
 // bounds derived from it stay scalar.
@@ -198,85 +193,104 @@ __device__ __forceinline__ int64_t special_hairpin(const IT& I, const SmallE& S,
 // The explicit loops are the combinations of the short label paths out of a1 and into b1 (the empty
 // path included), flattened over the lanes; each reads its inner cell's six typed values once.
 struct PairScratch {
-    int64_t T[64];    // [class][xi][xj] minima of explicit generic loops
+    int64_t T[64];        // [class][xi][xj] minima of explicit generic loops
     int64_t AB[2][3][4];  // [left / right explicit][generic, 1xn, 2x3][outer label]
+    // the pair's label paths: the empty one, then the states' lists
+    int64_t fcost[kFwdPaths + 1], fcrow[kFwdPaths + 1], bcost[kBwdPaths + 1];
+    int fmeta[kFwdPaths + 1], bmeta[kBwdPaths + 1];
 };
 constexpr int64_t kBarred = ((int64_t)1 << 61) + ((int64_t)1 << 60) + ((int64_t)1 << 59);  // infeasible, and adding kINF stays in range
 
-template <class IT>
-__device__ __forceinline__ void closed_pair(const IT& I, const SmallE& S, const int32_t* __restrict__ spec, int p, int q,
-                            int a1, int b1, int tm, int lane, PairScratch& X, int64_t* wout) {
+__device__ __forceinline__ void closed_pair(const Inst& I, const SmallE& S, const int32_t* __restrict__ spec, int p, int q,
+                            SlotPtr ra, SlotPtr rb, int tm, int parts, int lane, PairScratch& X, int64_t* wout) {
+    // ra / rb: the records of a1 and b1.  parts: 1 the loops read through rings (hairpins, separable
+    // segments, long bulges, multiloop), 2 the explicit loops, 3 both; two waves of a team share them
+    const bool rings = parts & 1, paths = parts & 2;
     const int g = q - p, s = I.shift, m = g - 2;
     const int cap = min(g - 7, kMaxLoop);
     const int pl = p % 3, pr = (q - 2) % 3;
-    // listed path lengths: up to 3 bases inside one codon, and always 1 and 2 (the small-loop tables)
-    const int lmax = pl == 2 ? 3 : 2, rmax = pr == 2 ? 3 : 2;
     const bool lsep2 = pl == 1, rsep2 = pr == 0;  // a 2-base segment is separable
-    // path list bounds: lanes 0-3 starts of the left lists of length 1..4, lanes 4-7 of the right ones
-    const int offv = lane < 4 ? I.fwd_off()[a1 * 4 + lane] : I.bwd_off()[b1 * 4 + (lane & 3)];
-    const int f0 = __builtin_amdgcn_readlane(offv, 0), f1 = __builtin_amdgcn_readlane(offv, 1),
-              f2 = __builtin_amdgcn_readlane(offv, 2), f3 = __builtin_amdgcn_readlane(offv, 3);
-    const int r0 = __builtin_amdgcn_readlane(offv, 4), r1 = __builtin_amdgcn_readlane(offv, 5),
-              r2 = __builtin_amdgcn_readlane(offv, 6), r3 = __builtin_amdgcn_readlane(offv, 7);
-    const int64_t a1row = uni(I.rowoff()[a1]) - I.off()[p + 2];
+    const SlotPtr rp = slot_ptr(I) + 2 * p, rq = slot_ptr(I) + 2 * q;
+    const int a1 = ra->state, b1 = rb->state;
+    const int f1 = ra->nf[0], f2 = ra->nf[1], r1 = rb->nb[0], r2 = rb->nb[1];  // list ends by length
+    const int nf = ra->nf[2], nb = rb->nb[2];
+    // path lists: lanes 0-11 left, 16-33 right
+    const bool lleft = lane < kFwdPaths;
+    const int le = lleft ? lane : min(max(lane - 16, 0), kBwdPaths - 1);
+    const int64_t lcost = *(lleft ? &ra->fcost[le] : &rb->bcost[le]);
+    const int lmeta = *(lleft ? &ra->fmeta[le] : &rb->bmeta[le]);
+    const int64_t lcrow = ra->fcrow[min(lane, kFwdPaths - 1)];
     // hairpin and both-separable interior loops: lane = 16 K + 4 xi + xj
     const int K = lane >> 4, xi4 = (lane >> 2) & 3, xj4 = lane & 3;
-    const int64_t al = I.alphaU()[a1 * 4 + xi4], be = I.betaU()[b1 * 4 + xj4];
-    const int64_t mini = (g >= 12 && (K & 1)) ? I.MINI()[mini_idx(p, g, K >> 1)] : kINF;
-    const int32_t hpi = I.hp_init()[m];
-    const int64_t hp = m >= 5 && m != 6 ? fx(hpi, s) + I.P()[(q - 2) / 3] - I.P()[(p + 2) / 3 + 1] : kINF;
+    const int64_t al = ra->alpha[xi4], be = rb->beta[xj4];
+    int64_t mini = I.MINI()[mini_idx(p, g, K >> 1)];  // (written from span 12 on)
     // bulges of >= 3 bases (lanes 0-27 right side unpaired, 32-59 left side) and the multiloop (lane 63)
-    int64_t ta = kINF;
-    {
-        const int l = 3 + (lane & 31);
-        const bool right = lane < 32;
-        const int64_t* src = right ? I.BI() + (int64_t)a1 * kLMRing + ((m - l) & (kLMRing - 1))
-                                   : I.BJ() + (int64_t)b1 * kLMRing + ((m - l) & (kLMRing - 1));
-        const bool ok = l <= cap;
-        if (lane == 63) src = I.S2() + a1row + b1;
-        const int lc = ok ? l : 3;
-        const int hi = right ? (q - 1) / 3 : (p + 1 + lc) / 3, lo = right ? (q - 1 - lc) / 3 + 1 : (p + 1) / 3 + 1;
-        const int64_t v = *src, ph = I.P()[hi] - I.P()[lo];
-        const int64_t tl = I.tail()[a1];
-        if (lane == 63) {
-            ta = v + fx(S.ml_closing + S.ml_intern, s);
-        } else if (ok) {
-            ta = v + ph + (right ? 0 : tl) + fx(S.bulge[lc], s);
-        }
-    }
+    const bool bright = lane < 32;
+    const int bl = 3 + (lane & 31);
+    const int64_t* bsrc = (bright ? I.BI() + (int64_t)a1 * kLMRing : I.BJ() + (int64_t)b1 * kLMRing) + ((m - bl) & (kLMRing - 1));
+    const int64_t bring = *(lane == 63 ? I.S2() + ra->rowbase + b1 : bsrc);
     X.T[lane] = kINF;
     if (lane < 24) (&X.AB[0][0][0])[lane] = kINF;
-    wave_lds_order();
-    // one-sided: explicit paths of length l (not separable) against RS / LS, and the 2x3 / 3x2 loops,
-    // whose mismatch class differs from the rest of their row, against IDL / JDL
-    {
-        const int ne = (lsep2 ? f1 : lmax == 3 ? f3 : f2) - f0, nr = (rsep2 ? r1 : rmax == 3 ? r3 : r2) - r0;
-        for (int idx = lane; idx < ne + nr; idx += 64) {
-            const bool left = idx < ne;
-            const int e = left ? f0 + idx : r0 + idx - ne;
-            const int l = left ? 1 + (e >= f1) + (e >= f2) : 1 + (e >= r1) + (e >= r2);
-            const int meta = left ? I.fwd_meta()[e] : I.bwd_meta()[e];
-            const int64_t cost = left ? I.fwd_cost()[e] : I.bwd_cost()[e];
-            const int st = meta >> 4;
-            // label next to the inner pair, label next to the closing pair
-            const int in = left ? meta & 3 : (meta >> 2) & 3, out = left ? (meta >> 2) & 3 : meta & 3;
-            const int64_t v = left ? I.RS()[rs_idx(st, m - l, l, in)] : I.LS()[rs_idx(st, m - l, l, in)];
-            const bool x23 = left ? (l == 2 && pr != 2) || (l == 3 && rsep2) : (l == 2 && pl != 2) || (l == 3 && lsep2);
-            int64_t w = kINF;
-            if (x23) {
-                w = left ? I.IDL()[ring_idx(st, m - 5, 1, in)] : I.JDL()[ring_idx(st, m - 5, 1, in)];
-                w += fx(interior_base(S, 2, 3), s) + (left ? PRt(I, q, 5 - l) : PLt(I, p, 5 - l));
-            }
-            int64_t* ab = &X.AB[left ? 0 : 1][0][0];
-            if (v < kHalfINF) lds_min(ab + (l == 1 ? 4 : 0) + out, cost + v);
-            if (w < kHalfINF) lds_min(ab + 8 + out, cost + w);
-        }
-    }
     if (lane < 6) wout[lane] = kINF;
-    // explicit loops, 64 path combinations a round (nearly always one round)
-    const int nl = 1 + (lmax == 3 ? f3 : f2) - f0, nr = 1 + (rmax == 3 ? r3 : r2) - r0;
-    const int tot = nl * nr, rcp = (65536 + nr - 1) / nr;
+    if (lleft) {
+        X.fcost[lane + 1] = lcost;
+        X.fmeta[lane + 1] = lmeta;
+        X.fcrow[lane + 1] = lcrow;
+    } else if (lane >= 16 && lane < 16 + kBwdPaths) {
+        X.bcost[lane - 15] = lcost;
+        X.bmeta[lane - 15] = lmeta;
+    } else if (lane == 63) {
+        X.fcost[0] = X.bcost[0] = 0;
+        X.fcrow[0] = ra->rowbase;
+        X.fmeta[0] = a1 << 4;
+        X.bmeta[0] = b1 << 4;
+    }
+    wave_lds_order();
+    // explicit loops, 64 path combinations a round (nearly always one round); the inner cells of a
+    // round are read before the one-sided tables are waited for
+    const int nl = 1 + nf, nr = 1 + nb;
+    const int tot = paths ? nl * nr : 0, rcp = (65536 + nr - 1) / nr;
+    int l1, l2, xi, xk, xl, xj;
     int64_t vin[6], bs;
+    auto read_cells = [&](int idx) {
+        const bool in_list = idx < tot;
+        const int i = in_list ? (int)(((unsigned)idx * (unsigned)rcp) >> 16) : 0, j = in_list ? idx - i * nr : 0;
+        l1 = (i > 0) + (i > f1) + (i > f2);
+        l2 = (j > 0) + (j > r1) + (j > r2);
+        const bool ok = in_list && l1 + l2 <= max(cap, 0) &&
+                        ((l1 <= 2 && l2 <= 2) || (l1 > 0 && l2 > 0 && !(l1 == 2 && lsep2) && !(l2 == 2 && rsep2)));
+        const int fm = X.fmeta[i], bm = X.bmeta[j];
+        bs = ok ? X.fcost[i] + X.bcost[j] : kBarred;
+        xi = (fm >> 2) & 3, xk = fm & 3, xl = (bm >> 2) & 3, xj = bm & 3;
+        const longlong2* vp = reinterpret_cast<const longlong2*>(I.V() + (ok ? X.fcrow[i] + (bm >> 4) : ra->rowbase + b1) * 6);
+        const longlong2 v01 = vp[0], v23 = vp[1], v45 = vp[2];
+        vin[0] = v01.x, vin[1] = v01.y, vin[2] = v23.x, vin[3] = v23.y, vin[4] = v45.x, vin[5] = v45.y;
+    };
+    if (paths) read_cells(lane);
+    int64_t ta = kINF;
+    if (rings) {
+        // one-sided: explicit paths of length l (not separable; at most 30 of them) against RS / LS, and
+        // the 2x3 / 3x2 loops, whose mismatch class differs from the rest of their row, against IDL / JDL
+        const int ne = lsep2 ? f1 : nf, nt = ne + (rsep2 ? r1 : nb);
+        const bool left = lane < ne;
+        const int e = lane < nt ? (left ? lane : lane - ne) : 0;
+        const int l = left ? 1 + (e >= f1) + (e >= f2) : 1 + (e >= r1) + (e >= r2);
+        const int meta = lane < nt ? (left ? X.fmeta[e + 1] : X.bmeta[e + 1]) : X.bmeta[0];
+        const int64_t cost = left ? X.fcost[e + 1] : X.bcost[e + 1];
+        const int st = meta >> 4;
+        // label next to the inner pair, label next to the closing pair
+        const int in = left ? meta & 3 : (meta >> 2) & 3, out = left ? (meta >> 2) & 3 : meta & 3;
+        const int64_t v = (left ? I.RS() : I.LS())[rs_idx(st, m - l, l, in)];
+        const int64_t w = (left ? I.IDL() : I.JDL())[ring_idx(st, m - 5, 1, in)];
+        const bool x23 = left ? (l == 2 && pr != 2) || (l == 3 && rsep2) : (l == 2 && pl != 2) || (l == 3 && lsep2);
+        ta = bring + (lane == 63 ? fx(S.ml_closing + S.ml_intern, s)
+                                 : (bright ? rq->pb1 : ra->tail - rp->pa1) + fx(S.bulge[min(bl, kMaxLoop)], s));
+        if (lane != 63 && bl > cap) ta = kINF;
+        int64_t* ab = &X.AB[left ? 0 : 1][0][0];
+        if (lane < nt && v < kHalfINF) lds_min(ab + (l == 1 ? 4 : 0) + out, cost + v);
+        if (lane < nt && x23 && w < kHalfINF)
+            lds_min(ab + 8 + out, cost + w + fx(interior_base(S, 2, 3), s) + (left ? rq->pb2 : -rp->pa2));
+    }
     int B0, St, Sr;
     bool spl, half;
     // this lane's special loop closed by type t: byte address B0 + t St + rev(t') Sr, entries of 4 or
@@ -294,65 +308,57 @@ __device__ __forceinline__ void closed_pair(const IT& I, const SmallE& S, const 
         }
         return v;
     };
-    for (int idx = lane;; idx += 64) {
-        const bool in_list = idx < tot;
-        const int i = in_list ? (int)(((unsigned)idx * (unsigned)rcp) >> 16) : 0, j = in_list ? idx - i * nr : 0;
-        const int ef = f0 + i - 1, er = r0 + j - 1;
-        const int l1 = i == 0 ? 0 : 1 + (ef >= f1) + (ef >= f2), l2 = j == 0 ? 0 : 1 + (er >= r1) + (er >= r2);
-        const bool small = l1 <= 2 && l2 <= 2;
-        const bool ok = in_list && l1 + l2 <= max(cap, 0) &&
-                        (small || (l1 > 0 && l2 > 0 && !(l1 == 2 && lsep2) && !(l2 == 2 && rsep2)));
-        const int fm = i == 0 ? a1 << 4 : I.fwd_meta()[ef], bm = j == 0 ? b1 << 4 : I.bwd_meta()[er];
-        const int64_t fc = i == 0 ? 0 : I.fwd_cost()[ef], bc = j == 0 ? 0 : I.bwd_cost()[er];
-        const int64_t crow = i == 0 ? a1row : I.fwd_crow()[ef];
-        const int xi = (fm >> 2) & 3, xk = fm & 3, xl = (bm >> 2) & 3, xj = bm & 3;
-        const longlong2* vp = reinterpret_cast<const longlong2*>(I.V() + (ok ? crow + (bm >> 4) : a1row + b1) * 6);
-        const longlong2 v01 = vp[0], v23 = vp[1], v45 = vp[2];
-        vin[0] = v01.x, vin[1] = v01.y, vin[2] = v23.x, vin[3] = v23.y, vin[4] = v45.x, vin[5] = v45.y;
-        // type dependence of the loop: a special table (l1, l2 <= 2 except the 2-base bulge) or a
-        // boundary class (1 generic, 2 1xn, 3 2x3, 4 AU penalty only)
-        spl = small && (l1 + l2 != 2 || l1 == 1);
-        const int KK = small ? 4 : (l1 == 1 || l2 == 1) ? 2 : l1 + l2 == 5 ? 3 : 1;
-        const int32_t cst = !small ? interior_base(S, l1, l2) : l1 + l2 == 1 ? S.bulge[1] : spl ? 0 : S.bulge[2];
-        bs = (ok ? fc + bc : kBarred) + fx(cst, s);
-        // inner minimum over the inner pair's types for the boundary classes
-        {
-            const int32_t* tab = &S.mmH[0][0][0] + KK * 96 + xl * 4 + xk;
-            int64_t in = kINF;
+    if (paths)
+        for (int idx = lane;;) {
+            // type dependence of the loop: a special table (l1, l2 <= 2 except the 2-base bulge) or a
+            // boundary class (1 generic, 2 1xn, 3 2x3, 4 AU penalty only)
+            const bool small = l1 <= 2 && l2 <= 2;
+            spl = small && (l1 + l2 != 2 || l1 == 1);
+            const int KK = small ? 4 : (l1 == 1 || l2 == 1) ? 2 : l1 + l2 == 5 ? 3 : 1;
+            const int32_t cst = !small ? interior_base(S, l1, l2) : l1 + l2 == 1 ? S.bulge[1] : spl ? 0 : S.bulge[2];
+            bs += fx(cst, s);
+            // inner minimum over the inner pair's types for the boundary classes
+            {
+                const int32_t* tab = &S.mmH[0][0][0] + KK * 96 + xl * 4 + xk;
+                int64_t in = kINF;
 #pragma unroll
-            for (int tp = 0; tp < 6; tp++) in = mn(in, vin[tp] + fx(tab[type_rev(tp) * 16], s));
-            in += bs;
-            if (!spl) {
-                if (KK == 4) ta = mn(ta, in);
-                else if (in < kHalfINF) lds_min(&X.T[KK * 16 + xi * 4 + xj], in);
+                for (int tp = 0; tp < 6; tp++) in = mn(in, vin[tp] + fx(tab[type_rev(tp) * 16], s));
+                in += bs;
+                if (!spl) {
+                    if (KK == 4) ta = mn(ta, in);
+                    else if (in < kHalfINF) lds_min(&X.T[KK * 16 + xi * 4 + xj], in);
+                }
             }
-        }
-        half = l1 + l2 > 2;
-        if (l1 + l2 <= 1) {
-            B0 = offsetof(SmallE, stack), St = 24, Sr = 4;
-        } else if (l1 + l2 == 2) {
-            B0 = (int)offsetof(SmallE, int11) + (xi * 4 + xj) * 4, St = 384, Sr = 64;
-        } else if (l1 + l2 == 4) {
-            B0 = (int)offsetof(SmallE, int22) + (xi * 64 + xk * 16 + xl * 4 + xj) * 2, St = 3072, Sr = 512;
-        } else if (l1 == 1) {
-            B0 = (int)offsetof(SmallE, int21) + (xi * 16 + xl * 4 + xj) * 2, St = 768, Sr = 128;
-        } else {
-            B0 = (int)offsetof(SmallE, int21) + (xl * 16 + xi * 4 + xk) * 2, St = 128, Sr = 768;
-        }
-        if (!spl) B0 = 0, St = 0, Sr = 0, half = true;  // any valid entry: added to an infinite value
-        if (idx - lane + 64 >= tot) break;
+            half = l1 + l2 > 2;
+            if (l1 + l2 <= 1) {
+                B0 = offsetof(SmallE, stack), St = 24, Sr = 4;
+            } else if (l1 + l2 == 2) {
+                B0 = (int)offsetof(SmallE, int11) + (xi * 4 + xj) * 4, St = 384, Sr = 64;
+            } else if (l1 + l2 == 4) {
+                B0 = (int)offsetof(SmallE, int22) + (xi * 64 + xk * 16 + xl * 4 + xj) * 2, St = 3072, Sr = 512;
+            } else if (l1 == 1) {
+                B0 = (int)offsetof(SmallE, int21) + (xi * 16 + xl * 4 + xj) * 2, St = 768, Sr = 128;
+            } else {
+                B0 = (int)offsetof(SmallE, int21) + (xl * 16 + xi * 4 + xk) * 2, St = 128, Sr = 768;
+            }
+            if (!spl) B0 = 0, St = 0, Sr = 0, half = true;  // any valid entry: added to an infinite value
+            idx += 64;
+            if (idx - lane >= tot) break;
 #pragma unroll 1
-        for (int t = 0; t < 6; t++) {
-            if (!((tm >> t) & 1)) continue;
-            const int64_t v = wave_min(special(t));
-            if (lane == 0) wout[t] = mn(wout[t], v);
+            for (int t = 0; t < 6; t++) {
+                if (!((tm >> t) & 1)) continue;
+                const int64_t v = wave_min(special(t));
+                if (lane == 0) wout[t] = mn(wout[t], v);
+            }
+            read_cells(idx);
         }
-    }
     wave_lds_order();
     // T: explicit generic minima, hairpin / both-separable, one-sided
     int64_t T = X.T[lane];
-    {
-        const int64_t x = K == 0 ? hp : mini;
+    if (rings) {
+        // (MINI holds its pair's whole-codon terms)
+        const int64_t hp = m >= 5 && m != 6 ? fx(I.hp_init()[m], s) + rq->pb2 - rp->pa2 : kINF;
+        const int64_t x = K == 0 ? hp : (K & 1) && g >= 12 ? mini : kINF;
         if (al < kINF && be < kINF && x < kINF) T = mn(T, al + be + x);
         if (K > 0) {
             const int64_t A = X.AB[0][K - 1][xi4], B = X.AB[1][K - 1][xj4];
@@ -365,10 +371,11 @@ __device__ __forceinline__ void closed_pair(const IT& I, const SmallE& S, const 
 #pragma unroll 1
     for (int t = 0; t < 6; t++) {
         if (!((tm >> t) & 1)) continue;
-        const int64_t v = mn(wave_min(mn(special(t), T + fx(tab[t * 16], s))), ta + fx(au_pen(S, t), s));
+        const int64_t sv = paths ? special(t) : kINF;
+        const int64_t v = mn(wave_min(mn(sv, T + fx(tab[t * 16], s))), ta + fx(au_pen(S, t), s));
         if (lane == 0) wout[t] = norm_inf(mn(wout[t], v));
     }
-    if (m == 3 || m == 4 || m == 6) {
+    if (rings && (m == 3 || m == 4 || m == 6)) {
 #pragma unroll 1
         for (int t = 0; t < 6; t++) {
             if (!((tm >> t) & 1)) continue;
@@ -382,9 +389,17 @@ __device__ __forceinline__ void closed_pair(const IT& I, const SmallE& S, const 
 // The threads that work on one layer pair: the whole workgroup (ordered by workgroup barriers),
 // or a single wavefront of a workgroup whose waves each work on their own pair (ordered within the
 // wave; a workgroup barrier there would pair up unrelated points of different waves).
+// The lane index produced per call: teams run inside loops over their items, and lane predicates
+// derived from threadIdx would be hoisted to the kernel entry and held throughout, where they crowd
+// the scalar registers and are spilled to vector lanes.
+__device__ __forceinline__ int lane_id() {
+    int l;
+    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
+    return l;
+}
 struct BlockTeam {
-    __device__ int wave() const { return threadIdx.x >> 6; }
-    __device__ int lane() const { return threadIdx.x & 63; }
+    __device__ int wave() const { return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); }
+    __device__ int lane() const { return lane_id(); }
     __device__ int waves() const { return blockDim.x >> 6; }
     __device__ void sync() { __syncthreads(); }
 };
@@ -395,14 +410,7 @@ struct WaveTeam {
     int w = 0, n = 1;
     unsigned epoch = 0;
     __device__ int wave() const { return w; }
-    // The lane index produced per call: a wave team runs inside the persistent loop, and lane
-    // predicates derived from threadIdx would be hoisted to the kernel entry and held for the
-    // whole launch, where they crowd the scalar registers and are spilled to vector lanes.
-    __device__ int lane() const {
-        int l;
-        asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
-        return l;
-    }
+    __device__ int lane() const { return lane_id(); }
     __device__ int waves() const { return n; }
     __device__ void sync() {
         if (n == 1) {
@@ -419,47 +427,48 @@ struct WaveTeam {
 
 // LDS of one team; a wave's own scratch lies in the element of its own index, so that an array of
 // as many elements as waves serves teams of any size.
+constexpr int kTrieCells = kTrieWidth * kTrieWidth;
 struct GroupShared {
-    int64_t w[kMaxWidth * kMaxWidth][6];      // W_t(a1, b1) of the pair's inner boundary pairs
+    int64_t w[2][kTrieCells][6];      // W_t(a1, b1) of the pair's inner boundary pairs, in two parts
     union {
-        PairScratch scratch;                     // phase 1
-        int64_t vbuf[kMaxWidth * kMaxWidth][6];  // phase 2: typed closed values of the pair's cells
+        PairScratch scratch;          // phase 1
+        int64_t vbuf[kTrieCells][6];  // phase 2: typed closed values of the pair's cells
     };
-    int64_t s2[kMaxWidth * kMaxWidth];        // S2 of the cells
-    int64_t ps[kMaxWidth * kMaxWidth];        // P_S of the cells; once they are completed, B
-    int64_t aU[kMaxWidth][4], bU[kMaxWidth][4];  // edge costs out of the left states and of layer q - 1
-    int64_t boff[kMaxWidth];     // committed count, capacity and offset of each C_b
-    int bcnt[kMaxWidth], bcap[kMaxWidth];
-    // the edges' targets by label, counted from the first state of their layer (-1 none)
-    int8_t adst[kMaxWidth][4], bdst[kMaxWidth][4];
-    int8_t keep[kMaxWidth * kMaxWidth];       // 0 none, 1 strict, 2 retained non-strict
+    int64_t s2[kTrieCells];           // S2 of the cells
+    int64_t ps[kTrieCells];           // P_S of the cells; once they are completed, B
+    // the pair's records, as phase 2 needs them, read beside phase 1
+    int64_t aU[kTrieWidth][4], bU[kTrieWidth][4];        // edge costs out of the left states and of layer q - 1
+    int64_t abeta[kTrieWidth][4], balpha[kTrieWidth][4]; // beta of the left states, alpha of the right ones
+    int64_t btail[kTrieWidth], boff[kTrieWidth];         // right states: tail, candidate segment,
+    int bcnt[kTrieWidth], bcap[kTrieWidth];              //   committed count and capacity
+    int8_t adst[kTrieWidth][4], bdst[kTrieWidth][4];     // the edges' targets by slot (-1 none)
+    int8_t keep[kTrieCells];          // 0 none, 1 strict, 2 retained non-strict
 };
 
-// One-sided tables of state k of the pair for span g (left states c of layer p: RS, right states d of
+// One-sided tables of state st of the pair for span g (left states c of layer p: RS, right states d of
 // layer q: LS), by one wave: the minimum over the separable side's length of IDL / JDL of spans
 // <= g - 3 + loop energy + whole codons, per explicit length 1..3 and inner label.  They read nothing
 // this span writes.
-template <class IT>
-__device__ __forceinline__ void produce_one_sided(const IT& I, const SmallE& S, int p, int g, bool left, int st, int lane) {
-    const int s = I.shift;
+__device__ __forceinline__ void produce_one_sided(const Inst& I, const SmallE& S, int p, int q, bool left, int st, int lane) {
+    const int s = I.shift, g = q - p;
+    // the consumer closes (.., q + 1) around c, or (p - 1, ..) around d
+    if (left ? q == I.n : p == 0) return;
+    const int64_t cod = left ? slot_ptr(I)[2 * (q + 1)].pb2 : -slot_ptr(I)[2 * (p - 1)].pa2;
+    const int l0 = left ? (q - 1) % 3 + 2 : (p + 2) % 3 == 0 ? 3 : (p + 2) % 3 == 1 ? 2 : 4;  // shortest separable length
     // lane = 4 * grp + lab covers separable lengths 3 + grp and 19 + grp
     const int lab = lane & 3, grp = lane >> 2;
-    const int qc = p + g + 1, pc = p - 1;  // the consumer's closing layer of the separable side
-    int64_t o[3] = {kINF, kINF, kINF};
-    int64_t in0[2], in2[2], pt[2];
+    const int64_t* T = left ? I.IDL() : I.JDL();
+    int64_t in0[2], in2[2];
 #pragma unroll
     for (int h = 0; h < 2; h++) {
-        const int ls = 3 + grp + 16 * h, g2 = g - ls;
-        const bool ok = ls <= 29 && g2 >= 5 && (left ? sep_right(qc, ls) : pc >= 0 && sep_left(pc, ls));
-        const int l = ok ? ls : 3, gr = ok ? g2 : 0;
-        const int64_t* T = left ? I.IDL() : I.JDL();
+        const int ls = 3 + grp + 16 * h;
+        const bool ok = ls <= 29 && g - ls >= 5 && ls >= l0;
+        const int gr = ok ? g - ls : 0;
         in0[h] = T[ring_idx(st, gr, 0, lab)];
         in2[h] = T[ring_idx(st, gr, 2, lab)];
-        // P terms of the separable side, at clamped positions where it has none
-        const int hi = left ? (qc - 2) / 3 : (max(pc, 0) + l) / 3, lo = left ? (max(qc - l, 0)) / 3 + 1 : (max(pc, 0) + 2) / 3 + 1;
-        pt[h] = I.P()[min(hi, I.A)] - I.P()[min(lo, I.A)];
         if (!ok) in0[h] = in2[h] = kINF;
     }
+    int64_t o[3] = {kINF, kINF, kINF};
 #pragma unroll
     for (int h = 0; h < 2; h++) {
         const int ls = 3 + grp + 16 * h;
@@ -467,7 +476,7 @@ __device__ __forceinline__ void produce_one_sided(const IT& I, const SmallE& S, 
         for (int le = 1; le <= 3; le++) {
             if (le + ls > kMaxLoop || (le == 2 && ls == 3)) continue;
             // the energy depends on |l1 - l2| and l1 + l2 only
-            o[le - 1] = mn(o[le - 1], (le == 1 ? in2[h] : in0[h]) + pt[h] + fx(interior_base(S, le, ls), s));
+            o[le - 1] = mn(o[le - 1], (le == 1 ? in2[h] : in0[h]) + fx(interior_base(S, le, ls), s));
         }
     }
 #pragma unroll
@@ -478,90 +487,111 @@ __device__ __forceinline__ void produce_one_sided(const IT& I, const SmallE& S, 
         o[j] = mn(o[j], shfl_xor64(o[j], 16));
         o[j] = mn(o[j], shfl_xor64(o[j], 32));
     }
-    if (grp < 3) {
-        int64_t* T = left ? I.RS() : I.LS();
-        T[rs_idx(st, g, grp + 1, lab)] = norm_inf(grp == 0 ? o[0] : grp == 1 ? o[1] : o[2]);
-    }
+    if (grp < 3)
+        (left ? I.RS() : I.LS())[rs_idx(st, g, grp + 1, lab)] = norm_inf((grp == 0 ? o[0] : grp == 1 ? o[1] : o[2]) + cod);
 }
 
-// Inner minima of state k of the pair for span g from its typed values, by one wave: IDL (left
-// states, with their LM contribution) or JDL (right states), and the bulge rings BI / BJ.
-template <class IT>
-__device__ __forceinline__ void produce_inner(const IT& I, const SmallE& S, const GroupShared& G, int p, int g,
-                              bool left, int i, int a_lo, int b_lo, int wa, int wb, int lane, int64_t& lm0, int64_t& lm1) {
-    const int s = I.shift, st = left ? a_lo + i : b_lo + i, nother = left ? wb : wa;
-    // inner minima: lane = 16 * X + 4 * xx + z (48 lanes), minimised over z
-    {
-        const int X = lane >> 4, xx = (lane >> 2) & 3, z = lane & 3;
-        const int cls = X == 0 ? 1 : X == 1 ? 3 : 2;  // boundary class of X (row 3 repeats 1xn and is not stored)
-        const int32_t* tab = &S.mmH[0][0][0] + cls * 96 + (left ? z * 4 + xx : xx * 4 + z);
-        const int64_t be = I.betaU()[st * 4 + xx];
-        int64_t acc = kINF;
-        for (int o = 0; o < nother; o++) {
-            const int ci = left ? i * wb + o : o * wb + i;
-            // left: vary x_{l+1} = z with alpha(d); right: vary x_{k-1} = z with beta(c)
-            const int64_t w = left ? I.alphaU()[(b_lo + o) * 4 + z] : I.betaU()[(a_lo + o) * 4 + z];
-#pragma unroll
-            for (int tp = 0; tp < 6; tp++) {
-                const int64_t vin = uni(G.vbuf[ci][tp]);
-                if (vin >= kINF) continue;
-                const int64_t v = vin + w + fx(tab[type_rev(tp) * 16], s);
-                if (w < kINF) acc = mn(acc, v);
-            }
-        }
+// Inner minima of the pair's left or right states for span g, by one wave: IDL and BI (left states, and
+// LM) or JDL and BJ (right states).  v: lane 6 * cell + type holds the typed value; only the feasible
+// ones (about one per pair) are visited.
+__device__ __forceinline__ void produce_inner(const Inst& I, const SmallE& S, const GroupShared& G, int p, int q,
+                              bool left, int64_t v, int wa, int wb, int lane) {
+    const int s = I.shift, g = q - p;
+    const SlotPtr rp = slot_ptr(I) + 2 * p, rq = slot_ptr(I) + 2 * q;
+    // lane = 16 * X + 4 * xx + z (48 lanes), minimised over z; left: vary x_{l+1} = z with alpha(d),
+    // right: vary x_{k-1} = z with beta(c)
+    const int X = lane >> 4, xx = (lane >> 2) & 3, z = lane & 3;
+    const int cls = X == 0 ? 1 : X == 1 ? 3 : 2;  // boundary class of X (row 3 repeats 1xn and is not stored)
+    const int32_t* tab = &S.mmH[0][0][0] + cls * 96 + (left ? z * 4 + xx : xx * 4 + z);
+    const int64_t w0 = left ? G.balpha[0][z] : G.abeta[0][z], w1 = left ? G.balpha[1][z] : G.abeta[1][z];
+    int64_t acc0 = kINF, acc1 = kINF, bu0 = kINF, bu1 = kINF;  // the two states' minima, and their bulge rings'
+    for (unsigned long long m = __ballot(lane < wa * wb * 6 && v < kINF); m; m &= m - 1) {
+        const int k = __builtin_ctzll(m), ci = k / 6, t = k - 6 * ci, ia = ci / wb, ib = ci - wb * ia;
+        const int i = left ? ia : ib, o = left ? ib : ia;
+        const int64_t vin = readlane64(v, k), w = o ? w1 : w0;
+        const int64_t x = w < kINF ? vin + w + fx(tab[((0x305124 >> (4 * t)) & 7) * 16], s) : kINF;
+        const int64_t u = vin + (left ? G.btail[o] : 0) + fx(au_pen(S, t), s);
+        if (i) acc1 = mn(acc1, x), bu1 = mn(bu1, u);
+        else acc0 = mn(acc0, x), bu0 = mn(bu0, u);
+    }
+    int64_t lm = kINF;
+    for (int i = 0; i < (left ? wa : wb); i++) {
+        int64_t acc = i ? acc1 : acc0;
         acc = mn(acc, dpp64<kDppXor1>(acc));
         acc = mn(acc, dpp64<kDppXor2>(acc));
-        acc = norm_inf(acc);
-        if (X < 3 && z == 0) {
-            (left ? I.IDL() : I.JDL())[ring_idx(st, g, X, xx)] = acc;
-            if (left && acc < kINF && be < kINF) {
-                if (X == 0) lm0 = mn(lm0, acc + be);
-                if (X == 1) lm1 = mn(lm1, acc + be);
-            }
+        acc = norm_inf(acc + (left ? -rq->in2 : rp->ip1));
+        const int st = left ? rp[i].state : rq[i].state;
+        if (X < 3 && z == 0) (left ? I.IDL() : I.JDL())[ring_idx(st, g, X, xx)] = acc;
+        const int64_t bu = norm_inf((i ? bu1 : bu0) + (left ? -rq->in1 : rp->ip0));
+        if (lane == 63) (left ? I.BI() : I.BJ())[(int64_t)st * kLMRing + (g & (kLMRing - 1))] = bu;
+        if (left) {
+            const int64_t be = G.abeta[i][xx];
+            if (acc < kINF && be < kINF) lm = mn(lm, acc + be);
         }
     }
-    // bulge rings: lane = 6 * other + type (24 lanes)
-    {
-        const int o = lane / 6, tp = lane - 6 * o;
-        int64_t acc = kINF;
-        if (lane < 24 && o < nother) {
-            const int64_t vin = G.vbuf[left ? i * wb + o : o * wb + i][tp];
-            if (vin < kINF) acc = vin + (left ? I.tail()[b_lo + o] : 0) + fx(au_pen(S, tp), s);
-        }
-        acc = norm_inf(wave_min(acc));
-        if (lane == 0) (left ? I.BI() : I.BJ())[(int64_t)st * kLMRing + (g & (kLMRing - 1))] = acc;
+    if (left) {
+        // LM: layer-pair minimum of the both-separable form, over the row of class X (0 generic, 1 2x3)
+        lm = mn(lm, dpp64<kDppRor4>(lm));
+        lm = mn(lm, dpp64<kDppRor8>(lm));
+        if (X < 2 && (lane & 15) == 0) I.LM()[lm_idx(p, g, X)] = norm_inf(lm + rp->ip1);
     }
 }
 
 // Both-separable interior minima of layer pair (p, q), q - p >= 12, into the ring MINI, by one wave:
-// LM of the inner layer pairs (spans <= q - p - 8) + loop energy + whole codons.
-template <class IT>
-__device__ __forceinline__ void prepare_mini(const IT& I, const SmallE& S, int p, int q, int lane) {
-    const int s = I.shift, g = q - p, ph = (p % 3) * 3 + (q % 3), cap = min(g - 7, kMaxLoop);
-    const int cnt = kFastCnt[ph][cap];
+// LM of the inner layer pairs (spans <= q - p - 8) + loop energy + whole codons.  The lengths
+// (l1 >= L0, l2 >= R0, l1 + l2 <= cap) form a triangle of M rows (row a, l1 = L0 + a, holds M - a);
+// rows r and M - r hold M together, so four lanes take each such pair of rows in at most seven rounds.
+__device__ __forceinline__ void prepare_mini(const Inst& I, const SmallE& S, int p, int q, int lane) {
+    const int s = I.shift, g = q - p, cap = min(g - 7, kMaxLoop);
+    const int pl = p % 3, L0 = pl == 0 ? 3 : pl == 1 ? 2 : 4, R0 = (q - 2) % 3 + 2;  // shortest separable lengths
+    const int M = cap - L0 - R0 + 1;
+    const int64_t cod = slot_ptr(I)[2 * q].pb2 - slot_ptr(I)[2 * p].pa2;
+    const int r = lane >> 2;
     int64_t m0 = kINF, m1 = kINF;
-#pragma unroll 2
-    for (int k = lane; k < cnt; k += 64) {
-        const int code = kFastList[ph][k], l1 = code & 31, l2 = code >> 5;
+#pragma unroll 1
+    for (int it = 0; it < 7; it++) {
+        const int j = (lane & 3) + 4 * it;
+        const bool first = j < M - r;
+        const int a = first ? r : M - r, l1 = L0 + a, l2 = R0 + (first ? j : j - (M - r));
+        // 2x2 loops read their full table and are always enumerated
+        if (j >= M || 2 * r > M || (!first && 2 * r == M) || l1 + l2 == 4) continue;
         const int X = pair_class(l1, l2);
         const int64_t lm = I.LM()[lm_idx(p + 1 + l1, g - 2 - l1 - l2, X)];
-        const int64_t v = lm + fx(interior_base(S, l1, l2), s) + PLt(I, p, l1) + PRt(I, q, l2);
+        const int64_t v = lm + fx(interior_base(S, l1, l2), s);
         if (X) m1 = mn(m1, v);
         else m0 = mn(m0, v);
     }
     m0 = wave_min(m0);
     m1 = wave_min(m1);
-    if (lane < 2) I.MINI()[mini_idx(p, g, lane)] = norm_inf(lane ? m1 : m0);
+    if (lane < 2) I.MINI()[mini_idx(p, g, lane)] = norm_inf((lane ? m1 : m0) + cod);
 }
 
 struct GroupCounters {
     unsigned long long visits, feasible;
 };
 
+// The committed prefix of C_b with the gathered S1(a, c) (eq. 7), the lanes' minima.  Every entry was
+// committed by an earlier span, so its start state lies in a layer after a's.
+__device__ __forceinline__ int64_t scan_candidates(const int* __restrict__ cc, const int64_t* __restrict__ cB,
+                                                   const int64_t* __restrict__ S1r, int committed, int lane) {
+    int64_t s2 = kINF;
+    // four entries per lane and round, their loads issued together: the gathers of S1(a, c)
+    // depend on the start states, so one entry at a time would serialise two load latencies
+    // per 64 entries
+    int k = lane;
+    for (; k + 192 < committed; k += 256) {
+        const int c0 = cc[k] & 0x7fffffff, c1 = cc[k + 64] & 0x7fffffff;
+        const int c2 = cc[k + 128] & 0x7fffffff, c3 = cc[k + 192] & 0x7fffffff;
+        const int64_t b0 = cB[k], b1 = cB[k + 64], b2 = cB[k + 128], b3 = cB[k + 192];
+        const int64_t s0 = S1r[c0], s1v = S1r[c1], s2v = S1r[c2], s3 = S1r[c3];
+        s2 = mn(s2, mn(mn(s0 + b0, s1v + b1), mn(s2v + b2, s3 + b3)));
+    }
+    for (; k < committed; k += 64) s2 = mn(s2, S1r[cc[k] & 0x7fffffff] + cB[k]);
+    return s2;
+}
+
 // The split part of one cell (a, b) of layer pair (p, q), by one wave: S2 (eq. 7: in-edge
-// extensions, then the committed prefix of C_b with the gathered S1(a, c)) and P_S.  Every scan
-// reads only entries committed by earlier spans (their start states lie in layers after p, so the
-// guard of eq. 7 holds for each); neither value depends on the cell's direct cost.
+// extensions, then the committed prefix of C_b) and P_S; neither depends on the cell's direct cost.
 template <class IT>
 __device__ __forceinline__ void multiloop_scan(const IT& I, int a, int b, int p, int q, int64_t cell, int lane, int committed,
                                int64_t cbase, int64_t* s2_out, int64_t* ps_out) {
@@ -589,21 +619,35 @@ __device__ __forceinline__ void multiloop_scan(const IT& I, int a, int b, int p,
             if (ap >= 0) ps = mn(ps, I.S1()[I.rowoff()[ap] + (b - I.off()[p + 2])] + I.out_U()[a * 4 + lane] + I.mlbase_fx);
         }
     }
-    const int* __restrict__ cc = I.cc() + cbase;
-    const int64_t* __restrict__ cB = I.cB() + cbase;
-    // four entries per lane and round, their loads issued together: the gathers of S1(a, c)
-    // depend on the start states, so one entry at a time would serialise two load latencies
-    // per 64 entries
-    int k = lane;
-    for (; k + 192 < committed; k += 256) {
-        const int c0 = cc[k] & 0x7fffffff, c1 = cc[k + 64] & 0x7fffffff;
-        const int c2 = cc[k + 128] & 0x7fffffff, c3 = cc[k + 192] & 0x7fffffff;
-        const int64_t b0 = cB[k], b1 = cB[k + 64], b2 = cB[k + 128], b3 = cB[k + 192];
-        const int64_t s0 = S1r[c0], s1v = S1r[c1], s2v = S1r[c2], s3 = S1r[c3];
-        s2 = mn(s2, mn(mn(s0 + b0, s1v + b1), mn(s2v + b2, s3 + b3)));
+    s2 = norm_inf(wave_min(mn(s2, scan_candidates(I.cc() + cbase, I.cB() + cbase, S1r, committed, lane))));
+    *s2_out = s2;
+    *ps_out = norm_inf(mn(s2, wave_min(ps)));
+}
+
+// The same on the codon trie, from the slot records: ia / ib the slots of a and b in their layers.
+__device__ __forceinline__ void trie_scan(const Inst& I, int p, int q, int ia, int ib, int lane, int64_t* s2_out, int64_t* ps_out) {
+    const SlotPtr rp = slot_ptr(I) + 2 * p, rq = slot_ptr(I) + 2 * q;
+    const int b = rq[ib].state;
+    const int64_t arow = rp[ia].rowbase, cbase = rq[ib].coff;
+    const int committed = uni(I.ccnt()[b]);
+    const int64_t* __restrict__ S1r = I.S1() + arow;
+    const int64_t* __restrict__ S2r = I.S2() + arow;
+    int64_t s2 = kINF, ps = kINF;
+    if (q - p >= 2) {
+        // lanes 0-7 the edges of layer q - 1 (slot, label), lanes 8-11 a's out-edges by label
+        const int x = lane & 3;
+        const SlotPtr rb = rq - 2 + ((lane >> 2) & 1);
+        const bool in = lane < 8 && rb->state >= 0 && rb->dst[x] == ib;
+        const int d = lane >= 8 && lane < 12 ? rp[ia].dst[x] : -1;
+        const int64_t u = (in ? rb->outU[x] : rp[ia].outU[x]) + I.mlbase_fx;
+        if (in) {
+            s2 = S2r[rb->state] + u;
+            ps = S1r[rb->state] + u;
+        } else if (d >= 0) {
+            ps = I.S1()[rp[2 + d].rowbase + b] + u;
+        }
     }
-    for (; k < committed; k += 64) s2 = mn(s2, S1r[cc[k] & 0x7fffffff] + cB[k]);
-    s2 = norm_inf(wave_min(s2));
+    s2 = norm_inf(wave_min(mn(s2, scan_candidates(I.cc() + cbase, I.cB() + cbase, S1r, committed, lane))));
     *s2_out = s2;
     *ps_out = norm_inf(mn(s2, wave_min(ps)));
 }
@@ -666,95 +710,34 @@ __device__ void append_candidates(const IT& I, int a_lo, int wa, int b_lo, int w
                       mine ? I.ccap()[b_lo + lane] : 0, mine ? I.coff()[b_lo + lane] : 0);
 }
 
-// One layer pair of span step g.  Phase 1 is a list of tasks that read only earlier spans and are
-// dealt to the team's waves: the closed values W(a1, b1) of each inner boundary pair, the split
-// part of each cell, the one-sided tables of each state, and the next span's both-separable
-// minima.  After one barrier, the cells are completed (typed values, branch value, S1, retention,
-// appends) by one wave while others derive the inner minima for later two-loops.
-template <class IT, class Team>
-__device__ __forceinline__ GroupCounters span_group(const IT& I, const SmallE& S, const int32_t* __restrict__ spec, int p, int q,
-                                    GroupShared* Gs, Team& T) {
-    // Gs: the team's elements, one per wave; the first holds the pair's shared state
-    const int g = q - p, s = I.shift;
-    const int wave = T.wave(), lane = T.lane(), nw = T.waves();
-    GroupShared& G = Gs[0];
-    GroupCounters ctr{0, 0};
-    const int a_lo = I.off()[p], a1_lo = I.off()[p + 1], b_lo = I.off()[q], b_hi = I.off()[q + 1], b1_lo = I.off()[q - 1];
-    const int wa = a1_lo - a_lo, wb = b_hi - b_lo, ncell = wa * wb;
-    const int wa1 = I.off()[p + 2] - a1_lo, wb1 = b_lo - b1_lo;
-    // the pair's metadata: lanes 0-15 the out-edges of the left states, 16-31 those of layer q - 1,
-    // 32-35 the right states' candidate segments
-    if (wave == nw - 1) {
-        if (lane < 4 * wa) {
-            const int d = I.out_dst()[a_lo * 4 + lane];
-            (&G.adst[0][0])[lane] = d < 0 ? -1 : d - a1_lo;
-            (&G.aU[0][0])[lane] = I.out_U()[a_lo * 4 + lane];
-        } else if (lane >= 16 && lane < 16 + 4 * wb1) {
-            const int d = I.out_dst()[b1_lo * 4 + lane - 16];
-            (&G.bdst[0][0])[lane - 16] = d < 0 ? -1 : d - b_lo;
-            (&G.bU[0][0])[lane - 16] = I.out_U()[b1_lo * 4 + lane - 16];
-        } else if (lane >= 32 && lane < 32 + wb) {
-            const int b = b_lo + lane - 32;
-            G.bcnt[lane - 32] = I.ccnt()[b];
-            G.bcap[lane - 32] = I.ccap()[b];
-            G.boff[lane - 32] = I.coff()[b];
-        }
-    }
-    const int nclosed = g >= 5 ? wa1 * wb1 : 0, nstate = g >= 5 ? wa + wb : 0;
-    const int ntask = nclosed + ncell + nstate + (g + 1 >= 12 && q + 1 <= I.n ? 1 : 0);
-    for (int k0 = wave; k0 < ntask; k0 += nw) {
-        int k = k0;
-        if (k < nclosed) {
-            const int ia1 = k / wb1, ib1 = k - wb1 * ia1, a1 = a1_lo + ia1, b1 = b1_lo + ib1;
-            // types some edge pair around (a1, b1) has: first base entering a1, last base leaving b1
-            const IT J = rebased(I);
-            const int im = uni(J.inmask()[a1]), om = uni(J.inmask()[b1]) >> 4;
-            int tm = 0;
-#pragma unroll
-            for (int t = 0; t < 6; t++) tm |= ((im >> type_x(t)) & (om >> type_y(t)) & 1) << t;
-            if (tm) closed_pair(J, S, spec, p, q, a1, b1, tm, lane, Gs[wave].scratch, G.w[ia1 * kMaxWidth + ib1]);
-            continue;
-        }
-        k -= nclosed;
-        if (k < ncell) {
-            const int ia = k / wb, ib = k - wb * ia, a = a_lo + ia, b = b_lo + ib;
-            int64_t s2, ps;
-            const IT J = rebased(I);
-            multiloop_scan(J, a, b, p, q, uni(J.rowoff()[a]) + (b - a1_lo), lane, uni(J.ccnt()[b]), uni(J.coff()[b]), &s2, &ps);
-            if (lane == 0) {
-                G.s2[k] = s2;
-                G.ps[k] = ps;
-            }
-            continue;
-        }
-        k -= ncell;
-        if (k < nstate) {
-            produce_one_sided(rebased(I), S, p, g, k < wa, k < wa ? a_lo + k : b_lo + k - wa, lane);
-            continue;
-        }
-        prepare_mini(rebased(I), S, p, q + 1, lane);
-    }
-    T.sync();
-    // typed values of the cells: every wave that needs them completes all of them (each writes the
-    // same values)
-    const bool left_role = g >= 5 && (1 % nw) == wave, right_role = g >= 5 && (2 % nw) == wave;
-    if (wave != 0 && !left_role && !right_role) return ctr;
-    for (int k = lane; k < ncell * 6; k += 64) {
-        const int ci = k / 6, t = k - 6 * ci, ia = ci / wb, ib = ci - wb * ia;
-        int64_t v = kINF;
+// Phase 2 of a layer pair, by one wave: the typed values of its cells, and with `cells` their
+// completion (branch value, S1, retention, appends), with `left` / `right` the inner minima of its
+// left / right states.  Several waves may share the work; each completes the same typed values.
+__device__ __forceinline__ void complete_cells(const Inst& I, const SmallE& S, int p, int q, int wa, int wb, int wb1, int split, bool cells,
+                               bool left_role, bool right_role, int lane, GroupShared& G, GroupCounters& ctr) {
+    const int g = q - p, s = I.shift, ncell = wa * wb;
+    const SlotPtr rp = slot_ptr(I) + 2 * p, rq = slot_ptr(I) + 2 * q;
+    int64_t v = kINF;
+    if (lane < ncell * 6) {
+        const int ci = lane / 6, t = lane - 6 * ci, ia = ci / wb, ib = ci - wb * ia;
         if (g >= 5) {
             const int a1 = G.adst[ia][type_x(t)];
             if (a1 >= 0)
                 for (int j = 0; j < wb1; j++)
-                    if (G.bdst[j][type_y(t)] == ib)
-                        v = mn(v, G.aU[ia][type_x(t)] + G.bU[j][type_y(t)] + G.w[a1 * kMaxWidth + j][t]);
+                    if (G.bdst[j][type_y(t)] == ib) {
+                        int64_t w = G.w[0][a1 * kTrieWidth + j][t];
+                        if (split == 2) w = mn(w, G.w[1][a1 * kTrieWidth + j][t]);
+                        v = mn(v, G.aU[ia][type_x(t)] + G.bU[j][type_y(t)] + w);
+                    }
         }
         v = norm_inf(v);
-        G.vbuf[ci][t] = v;
-        if (wave == 0) I.V()[(I.rowoff()[a_lo + ia] + (b_lo + ib - a1_lo)) * 6 + t] = v;
+        if (cells) {
+            G.vbuf[ci][t] = v;
+            I.V()[(rp[ia].rowbase + rq[ib].state) * 6 + t] = v;
+        }
     }
-    wave_lds_order();
-    if (wave == 0) {
+    if (cells) {
+        wave_lds_order();
         // branch value (eq. 2), S1 and the retention test (eq. 6), one lane per cell
         bool feasible = false;
         if (lane < ncell) {
@@ -763,7 +746,7 @@ __device__ __forceinline__ GroupCounters span_group(const IT& I, const SmallE& S
 #pragma unroll
             for (int t = 0; t < 6; t++) Bv = mn(Bv, G.vbuf[lane][t] + fx(S.ml_intern + au_pen(S, t), s));
             Bv = norm_inf(Bv);
-            const int64_t cell = I.rowoff()[a_lo + ia] + (b_lo + ib - a1_lo), ps = G.ps[lane];
+            const int64_t cell = rp[ia].rowbase + rq[ib].state, ps = G.ps[lane];
             I.Bt()[cell] = Bv;
             I.S2()[cell] = G.s2[lane];
             I.S1()[cell] = mn(Bv, ps);
@@ -773,27 +756,96 @@ __device__ __forceinline__ GroupCounters span_group(const IT& I, const SmallE& S
             feasible = Bv < kINF;
         }
         ctr.feasible = __popcll(__ballot(feasible));
-        int vis = 0;
-        for (int j = 0; j < wb; j++) vis += G.bcnt[j];
-        ctr.visits = (unsigned long long)vis * wa;
+        ctr.visits = (unsigned long long)(G.bcnt[0] + (wb > 1 ? G.bcnt[1] : 0)) * wa;
         wave_lds_order();
         // appends in start-state order, one lane per right endpoint (this team owns C_b in this step)
         const bool mine = lane < wb;
-        append_candidates(I, a_lo, wa, b_lo, wb, G.keep, G.ps, g, lane, mine ? G.bcnt[lane] : 0,
+        append_candidates(I, rp[0].state, wa, rq[0].state, wb, G.keep, G.ps, g, lane, mine ? G.bcnt[lane] : 0,
                           mine ? G.bcap[lane] : 0, mine ? G.boff[lane] : (int64_t)0);
     }
-    if (left_role) {
-        int64_t lm0 = kINF, lm1 = kINF;
-        for (int i = 0; i < wa; i++) produce_inner(I, S, G, p, g, true, i, a_lo, b_lo, wa, wb, lane, lm0, lm1);
-        // LM: layer-pair minimum of the both-separable form
-        lm0 = wave_min(lm0);
-        lm1 = wave_min(lm1);
-        if (lane < 2) I.LM()[lm_idx(p, g, lane)] = norm_inf(lane ? lm1 : lm0);
+    if (left_role) produce_inner(I, S, G, p, q, true, v, wa, wb, lane);
+    if (right_role) produce_inner(I, S, G, p, q, false, v, wa, wb, lane);
+}
+
+// One layer pair of span step g on the codon trie.  Phase 1 is a list of tasks that read only earlier
+// spans and are dealt to the team's waves (everything they need of the pair's states is one level of
+// loads away, in the slot records): the closed values W(a1, b1) of each inner boundary pair,
+// the split part of each cell, the one-sided tables of each state, and the next span's
+// both-separable minima.  After one barrier, the cells are completed (typed values, branch value, S1,
+// retention, appends) by one wave while others derive the inner minima for later two-loops.
+template <class Team>
+__device__ __forceinline__ GroupCounters span_group(const Inst& I, const SmallE& S, const int32_t* __restrict__ spec, int p, int q,
+                                    GroupShared* Gs, Team& T) {
+    // Gs: the team's elements, one per wave; the first holds the pair's shared state
+    const int g = q - p, s = I.shift;
+    const int wave = T.wave(), lane = T.lane(), nw = T.waves();
+    GroupShared& G = Gs[0];
+    GroupCounters ctr{0, 0};
+    const SlotPtr rp1 = slot_ptr(I) + 2 * p, rq1 = slot_ptr(I) + 2 * q;
+    const int wa = 1 + (rp1[1].state >= 0), wb = 1 + (rq1[1].state >= 0), ncell = wa * wb;
+    const int wa1 = 1 + (rp1[3].state >= 0), wb1 = 1 + (rq1[-1].state >= 0);
+    if (wave == nw - 1) {
+        const SlotPtr rp = rp1, rq = rq1;
+        // lanes 0-7 the left states' out-edges (slot, label) and beta, 8-15 the edges out of layer q - 1,
+        // 16-23 the right states' alpha, 24-25 their candidate segments
+        const int i = (lane >> 2) & 1, x = lane & 3;
+        if (lane < 8) {
+            G.adst[i][x] = rp[i].dst[x];
+            G.aU[i][x] = rp[i].outU[x];
+            G.abeta[i][x] = rp[i].beta[x];
+        } else if (lane < 16) {
+            G.bdst[i][x] = rq[i - 2].state >= 0 ? rq[i - 2].dst[x] : -1;
+            G.bU[i][x] = rq[i - 2].outU[x];
+        } else if (lane < 24) {
+            G.balpha[i][x] = rq[i].alpha[x];
+        } else if (lane < 24 + wb) {
+            G.btail[x] = rq[x].tail;
+            G.boff[x] = rq[x].coff;
+            G.bcap[x] = rq[x].ccap;
+            G.bcnt[x] = I.ccnt()[rq[x].state];
+        }
     }
-    if (right_role) {
-        int64_t u0 = kINF, u1 = kINF;
-        for (int i = 0; i < wb; i++) produce_inner(I, S, G, p, g, false, i, a_lo, b_lo, wa, wb, lane, u0, u1);
+    // teams of eight waves or more give the two parts of a closed value to different waves
+    const int split = nw >= 8 ? 2 : 1, nclosed = g >= 5 ? wa1 * wb1 * split : 0, nstate = g >= 5 ? wa + wb : 0;
+    const int ntask = nclosed + ncell + nstate + (g + 1 >= 12 && q + 1 <= I.n ? 1 : 0);
+    for (int k0 = wave; k0 < ntask; k0 += nw) {
+        int k = k0;
+        const Inst J = rebased(I);
+        if (k < nclosed) {
+            const int kk = k / split, part = k - kk * split, ia1 = kk / wb1, ib1 = kk - wb1 * ia1;
+            const SlotPtr ra = slot_ptr(J) + 2 * (p + 1) + ia1, rb = slot_ptr(J) + 2 * (q - 1) + ib1;
+            // types some edge pair around (a1, b1) has: first base entering a1, last base leaving b1
+            const int im = ra->inmask, om = rb->outmask;
+            int tm = 0;
+#pragma unroll
+            for (int t = 0; t < 6; t++) tm |= ((im >> type_x(t)) & (om >> type_y(t)) & 1) << t;
+            if (tm)
+                closed_pair(J, S, spec, p, q, ra, rb, tm, split == 2 ? 1 + part : 3, lane, Gs[wave].scratch,
+                            G.w[part][ia1 * kTrieWidth + ib1]);
+            continue;
+        }
+        k -= nclosed;
+        if (k < ncell) {
+            int64_t s2, ps;
+            trie_scan(J, p, q, k / wb, k - wb * (k / wb), lane, &s2, &ps);
+            if (lane == 0) {
+                G.s2[k] = s2;
+                G.ps[k] = ps;
+            }
+            continue;
+        }
+        k -= ncell;
+        if (k < nstate) {
+            const bool left = k < wa;
+            produce_one_sided(J, S, p, q, left, left ? slot_ptr(J)[2 * p + k].state : slot_ptr(J)[2 * q + k - wa].state, lane);
+            continue;
+        }
+        prepare_mini(J, S, p, q + 1, lane);
     }
+    T.sync();
+    const bool left_role = g >= 5 && (1 % nw) == wave, right_role = g >= 5 && (2 % nw) == wave;
+    if (wave != 0 && !left_role && !right_role) return ctr;
+    complete_cells(rebased(I), S, p, q, wa, wb, wb1, split, wave == 0, left_role, right_role, lane, G, ctr);
     return ctr;
 }
 
@@ -845,47 +897,64 @@ __device__ __forceinline__ int xcd_band(int i, int nb) {
     return base + k;
 }
 
-// ---- the span step (plain mode): layer pair xcd_band(x) for block x < layer pairs ---------------
-// The 512-thread instantiation is held to 80 VGPRs so that three of its workgroups fit a CU.
-template <int NT>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT == 512 ? 6 : 1)))
-void k_span(Inst I, const EnergyTables* __restrict__ E, const int32_t* __restrict__ spec, int g,
-            int ext_layer, int nblk_cells) {
-    __shared__ SmallE S;
-    __shared__ GroupShared G[NT / 64];
-    stage_tables(S, E);
-    __syncthreads();
-    BlockTeam T;
-    if ((int)blockIdx.x >= nblk_cells) {
-        if (ext_layer >= 0) ext_column(I, S, ext_layer, G, T);
-        return;
-    }
-    const int p = xcd_band(blockIdx.x, nblk_cells), q = p + g;
-    flush_counters(I, span_group(I, S, spec, p, q, G, T), p, threadIdx.x & 63);
+// Brings the records of a pair's four layers to this XCD's L2 while the tables are staged: one word of
+// each of their lines, by the first wave.
+__device__ __forceinline__ void prefetch_records(const Inst& I, int p, int g) {
+    if (threadIdx.x >= 64) return;
+    constexpr int kLines = 4 * sizeof(SlotRec) / 128;  // two layers
+    const int lane = threadIdx.x;
+    const char* base = reinterpret_cast<const char*>(I.recs() + (lane < kLines ? 2 * p : 2 * (p + g - 1)));
+    const int w = *reinterpret_cast<const int*>(base + (lane < kLines ? lane : min(lane - kLines, kLines - 1)) * 128);
+    asm volatile("" ::"v"(w));
 }
 
-// The span step with every wave on its own layer pair: four pairs per workgroup and one staging of
-// the energy tables, for spans with many more layer pairs than the chip holds workgroups.  Items
-// are the span's layer pairs, then the external column; workgroup x takes the four consecutive
-// items of band xcd_band(x).  No workgroup barrier follows the staging: the waves' items are
-// independent and some waves have none.
+// ---- the span step (plain mode) ----------------------------------------------------------------
+// Items are the span's layer pairs (item x is pair xcd_band(x)), then the external column.  A span
+// with more items than the chip holds workgroups runs as many workgroups as it holds, each taking
+// every gridDim.x-th item with one staging of the energy tables.  Held to 128 VGPRs, without spills: four
+// workgroups of 256 threads fit a CU, two of 512.  With 148 VGPRs (three) the 1,976-aa fill took 384 ms
+// instead of 324; one staging per resident workgroup, direct copies to LDS and the records brought
+// to L2 beside them made it 279 ms (300 aa 17.7 -> 16.7 ms).
 template <int NT>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_span_waves(
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT == 64 ? 1 : 4)))
+void k_span(Inst I, const EnergyTables* __restrict__ E, const int32_t* __restrict__ spec, int g,
+            int ext_layer, int npairs) {
+    __shared__ SmallE S;
+    __shared__ GroupShared G[NT / 64];
+    stage_begin(S, E);
+    if ((int)blockIdx.x < npairs) prefetch_records(I, xcd_band(blockIdx.x, npairs), g);
+    stage_wait();
+    BlockTeam T;
+    const int items = npairs + (ext_layer >= 0 ? 1 : 0);
+    for (int i = blockIdx.x; i < items; i += gridDim.x) {
+        if (i < npairs) {
+            const int p = xcd_band(i, npairs);
+            const Inst J = rebased(I);
+            flush_counters(J, span_group(J, S, spec, p, p + g, G, T), p, T.lane());
+        } else {
+            ext_column(I, S, ext_layer, G, T);
+        }
+        __syncthreads();  // the team's shared state is free for its next item
+    }
+}
+
+// The span step with every wave on its own layer pair, sixteen pairs per workgroup and one staging of
+// the energy tables: the waves' items are independent and no workgroup barrier follows the staging.
+template <int NT>
+__global__ __launch_bounds__(NT) void k_span_waves(
     Inst I, const EnergyTables* __restrict__ E, const int32_t* __restrict__ spec, int g, int ext_layer, int npairs) {
     constexpr int NWV = NT / 64;
     __shared__ SmallE S;
     __shared__ GroupShared G[NWV];
     stage_tables(S, E);
-    __syncthreads();
-    const int wave = threadIdx.x >> 6;
-    const int items = npairs + (ext_layer >= 0 ? 1 : 0);
-    const int nblk = (items + NWV - 1) / NWV;
-    const int item = xcd_band(blockIdx.x, nblk) * NWV + wave;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int items = npairs + (ext_layer >= 0 ? 1 : 0), nblk = (items + NWV - 1) / NWV;
     WaveTeam T;
-    if (item < npairs) {
-        flush_counters(I, span_group(I, S, spec, item, item + g, &G[wave], T), item, T.lane());
-    } else if (item == npairs && ext_layer >= 0) {
-        ext_column(I, S, ext_layer, &G[wave], T);
+    for (int i = blockIdx.x; i < nblk; i += gridDim.x) {
+        const int item = xcd_band(i, nblk) * NWV + wave;
+        const Inst J = rebased(I);
+        if (item < npairs) flush_counters(J, span_group(J, S, spec, item, item + g, &G[wave], T), item, T.lane());
+        else if (item < items) ext_column(J, S, ext_layer, &G[wave], T);
     }
 }
 
@@ -893,7 +962,6 @@ __global__ __launch_bounds__(256) void k_ext(Inst I, const EnergyTables* __restr
     __shared__ SmallE S;
     __shared__ GroupShared G[4];
     stage_tables(S, E);
-    __syncthreads();
     BlockTeam T;
     ext_column(I, S, L, G, T);
 }
@@ -1353,7 +1421,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
                                                     const int32_t* __restrict__ spec, int g) {
     __shared__ SmallE S;
     stage_tables(S, E);
-    __syncthreads();
     const int lane = threadIdx.x & 63;
     const int64_t j0 = I.gjob_off()[g], total = (I.gjob_off()[g + 1] - j0) * kGenParts;
     for (;;) {
@@ -1378,7 +1445,6 @@ __global__ __launch_bounds__(256) void k_span_gen(Inst I, const EnergyTables* __
     __shared__ GroupShared X[4];
     __shared__ GenShared G;
     stage_tables(S, E);
-    __syncthreads();
     if ((int)blockIdx.x >= nblk_cells) {
         BlockTeam T;
         if (ext_layer >= 0) ext_column(I, S, ext_layer, X, T);
@@ -1546,8 +1612,7 @@ __device__ __forceinline__ int item_instance(const int* pref, int ninst, int ite
 // items' costs differ); with fewer items the teams grow (to the whole workgroup when there is at
 // most one item per workgroup), since a step then takes its longest item's time, and each team's
 // items follow from its index.  min_team is the schedule's waves per item (1, or all of a 256- or
-// 512-thread workgroup's).  With the barrier above: 7 proteins of 50-150 aa 21.0 -> 12.6 ms, 64 of
-// 50-1,000 aa 0.71 -> 0.55 s per launch.
+// 512-thread workgroup's).
 template <int NT>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_persistent(
     const Inst* __restrict__ insts, int ninst, int nsteps, const EnergyTables* __restrict__ E,
@@ -1601,7 +1666,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
             if (k >= band) break;
             const int item = (int)(lo_item + k);
             const int inst = __builtin_amdgcn_readfirstlane(item_instance(pref, ninst, item));
-            const Inst I = rebased(insts[inst]);  // a few scalar registers: bases and sizes
+            const Inst I = load_inst(insts + inst);  // a few scalar registers: bases and sizes
             const int local = __builtin_amdgcn_readfirstlane(item - pref[inst]), g = I.g0 + step;
             const int n = I.n, ncell_items = g <= n ? n - g + 1 : 0;
             if (local < ncell_items) flush_counters(I, span_group(I, S, spec, local, local + g, Gs, T), local, T.lane());
@@ -1618,7 +1683,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
 
 // Resets the barrier state and initialises every instance whose g0 is 1 (new instances).
 __global__ void k_batch_init(const Inst* __restrict__ insts, int ninst, BatchCtl* ctl) {
-    const Inst I = rebased(insts[blockIdx.x]);
+    const Inst I = load_inst(insts + blockIdx.x);
     const int tid = threadIdx.x, nt = blockDim.x;
     if (blockIdx.x == 0 && tid < kMaxXcd) {
         ctl->arrive[tid].v = 0;
@@ -1663,29 +1728,6 @@ __global__ void k_batch_init(const Inst* __restrict__ insts, int ninst, BatchCtl
 // ---- host launch wrappers ----------------------------------------------------------------------
 namespace sd {
 
-hipError_t upload_pair_order() {
-    static unsigned short list[9][kNumPairs];
-    static unsigned short cnt[9][31];
-    memset(list, 0, sizeof(list));
-    memset(cnt, 0, sizeof(cnt));
-    for (int pm = 0; pm < 3; pm++)
-        for (int qm = 0; qm < 3; qm++) {
-            const int ph = pm * 3 + qm, p = 3 + pm, q = 300 + qm;  // representatives of the phases
-            int len = 0;
-            for (int sum = 0; sum <= kMaxLoop; sum++) {
-                for (int a = 2; a + 2 <= sum; a++) {
-                    const int b = sum - a;
-                    // 2x2 loops read their full table and are always enumerated
-                    if (sum > 4 && sep_left(p, a) && sep_right(q, b)) list[ph][len++] = (unsigned short)(a | b << 5);
-                }
-                cnt[ph][sum] = (unsigned short)len;
-            }
-        }
-    hipError_t e = hipMemcpyToSymbol(HIP_SYMBOL(kFastList), list, sizeof(list));
-    if (e != hipSuccess) return e;
-    return hipMemcpyToSymbol(HIP_SYMBOL(kFastCnt), cnt, sizeof(cnt));
-}
-
 hipError_t launch_init(const Inst& I, hipStream_t st) {
     hipLaunchKernelGGL(k_init, dim3(64), dim3(256), 0, st, I);
     return hipGetLastError();
@@ -1693,23 +1735,27 @@ hipError_t launch_init(const Inst& I, hipStream_t st) {
 
 // one span step: cells of span g plus the external column of layer ext_layer (or -1)
 hipError_t launch_span(const Inst& I, const EnergyTables* E, const int32_t* spec, int g,
-                       int ext_layer, int threads, int item_waves, hipStream_t st) {
+                       int ext_layer, int threads, int item_waves, int num_cu, hipStream_t st) {
     const int layers = I.n - g + 1;
     const int nblk = layers > 0 ? layers : 0;
     const int total = nblk + (ext_layer >= 0 ? 1 : 0);
     if (total == 0) return hipSuccess;
-    if (item_waves == 1 && threads == 256) {  // every wave on its own pair, four per workgroup
-        hipLaunchKernelGGL(k_span_waves<256>, dim3((total + 3) / 4), dim3(256), 0, st, I, E, spec, g, ext_layer, nblk);
+    if (item_waves == 1 && threads == 256) {  // every wave on its own pair, sixteen per workgroup
+        hipLaunchKernelGGL(k_span_waves<1024>, dim3(std::min((total + 15) / 16, num_cu)), dim3(1024), 0, st, I, E, spec, g,
+                           ext_layer, nblk);
         return hipGetLastError();
     }
     if (item_waves != threads / 64) return hipErrorInvalidValue;
+#define SD_LAUNCH(NT, PER_CU)                                                                                      \
+    hipLaunchKernelGGL(k_span<NT>, dim3(std::min(total, (PER_CU) * num_cu)), dim3(NT), 0, st, I, E, spec, g, ext_layer, nblk)
     switch (threads) {
-    case 64: hipLaunchKernelGGL(k_span<64>, dim3(total), dim3(64), 0, st, I, E, spec, g, ext_layer, nblk); break;
-    case 256: hipLaunchKernelGGL(k_span<256>, dim3(total), dim3(256), 0, st, I, E, spec, g, ext_layer, nblk); break;
-    case 512: hipLaunchKernelGGL(k_span<512>, dim3(total), dim3(512), 0, st, I, E, spec, g, ext_layer, nblk); break;
-    case 1024: hipLaunchKernelGGL(k_span<1024>, dim3(total), dim3(1024), 0, st, I, E, spec, g, ext_layer, nblk); break;
+    case 64: SD_LAUNCH(64, 4); break;
+    case 256: SD_LAUNCH(256, 4); break;
+    case 512: SD_LAUNCH(512, 2); break;
+    case 1024: SD_LAUNCH(1024, 1); break;
     default: return hipErrorInvalidValue;
     }
+#undef SD_LAUNCH
     return hipGetLastError();
 }
 

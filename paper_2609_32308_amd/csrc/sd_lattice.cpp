@@ -207,7 +207,7 @@ int parse_params(const std::string& text, Params& P, std::string& err) {
             err = "[int21] entry outside the 16-bit range the kernels stage";
             return SD_E_PARAMS;
         }
-        (&P.E.int21h[0][0][0][0][0])[j] = (int16_t)v;
+        (&P.E.small.int21[0][0][0][0][0])[j] = (int16_t)v;
     }
     for (int j = 0; j < 9216; j++) {
         const int32_t v = (&P.E.int22[0][0][0][0][0][0])[j];
@@ -215,8 +215,25 @@ int parse_params(const std::string& text, Params& P, std::string& err) {
             err = "[int22] entry outside the 16-bit range the kernels stage";
             return SD_E_PARAMS;
         }
-        (&P.E.int22h[0][0][0][0][0][0])[j] = (int16_t)v;
+        (&P.E.small.int22[0][0][0][0][0][0])[j] = (int16_t)v;
     }
+    SmallE& M = P.E.small;
+    memcpy(M.stack, P.E.stack, sizeof(M.stack));
+    memcpy(M.mmH, P.E.mmH, sizeof(M.mmH));
+    memcpy(M.mmI, P.E.mmI, sizeof(M.mmI));
+    memcpy(M.mm1n, P.E.mm1n, sizeof(M.mm1n));
+    memcpy(M.mm23, P.E.mm23, sizeof(M.mm23));
+    for (int j = 0; j < 96; j++) (&M.mmA[0][0][0])[j] = j >> 4 == 1 || j >> 4 == 2 ? 0 : P.E.terminal_au;
+    memcpy(M.int11, P.E.int11, sizeof(M.int11));
+    memcpy(M.hairpin, P.E.hairpin, sizeof(M.hairpin));
+    memcpy(M.bulge, P.E.bulge, sizeof(M.bulge));
+    memcpy(M.interior, P.E.interior, sizeof(M.interior));
+    M.ml_closing = P.E.ml_closing;
+    M.ml_intern = P.E.ml_intern;
+    M.ml_base = P.E.ml_base;
+    M.terminal_au = P.E.terminal_au;
+    M.ninio = P.E.ninio;
+    M.ninio_max = P.E.ninio_max;
     // special-loop lookup table keyed by the base-4 value of the loop sequence
     P.spec_table.assign(kSpecSize, kNoSpecial);
     const int offs[3] = {kSpecOff5, kSpecOff6, kSpecOff8};
@@ -375,6 +392,87 @@ static int64_t energy_bound(const Params& P, int n) {
     return std::max(-elo, ehi);
 }
 
+// The slot records of the codon trie (see SlotRec); false if a path list does not fit.
+static bool build_slots(Lattice& L) {
+    const int n = L.n, A = L.A;
+    L.recs.assign(2 * (size_t)(n + 1), SlotRec());
+    auto Pc = [&](int k) { return L.P[std::min(std::max(k, 0), A)]; };
+    for (int l = 0; l <= n; l++)
+        for (int i = 0; i < kTrieWidth; i++) {
+            SlotRec& r = L.recs[2 * (size_t)l + i];
+            memset(&r, 0, sizeof(r));
+            const int s = L.off[l] + i;
+            r.state = s < L.off[l + 1] ? s : -1;
+            r.pa1 = Pc((l + 1) / 3 + 1);
+            r.pa2 = Pc((l + 2) / 3 + 1);
+            r.pb1 = Pc((std::max(l, 1) - 1) / 3);
+            r.pb2 = Pc((std::max(l, 2) - 2) / 3);
+            r.in1 = Pc(l / 3 + 1);
+            r.in2 = Pc((l + 1) / 3 + 1);
+            r.ip0 = Pc(l / 3);
+            r.ip1 = Pc((std::max(l, 1) - 1) / 3);
+            for (int x = 0; x < 4; x++) {
+                r.dst[x] = -1;
+                r.alpha[x] = r.beta[x] = kINF;
+            }
+            if (r.state < 0) continue;
+            r.inmask = L.inmask[s] & 15;
+            r.outmask = L.inmask[s] >> 4;
+            r.rowbase = L.rowoff[s] - L.off[l + 1];
+            r.tail = L.tail[s];
+            r.coff = L.coff[s];
+            r.ccap = L.ccap[s];
+            for (int x = 0; x < 4; x++) {
+                const int d = L.out_dst[4 * s + x];
+                r.outU[x] = L.out_U[4 * s + x];
+                if (d < 0) continue;
+                r.dst[x] = (int8_t)(d - L.off[l + 1]);
+                r.alpha[x] = L.out_U[4 * s + x] + L.tail[d];
+            }
+            for (int j = L.in_start[s]; j < L.in_start[s + 1]; j++)
+                r.beta[L.in_lab[j]] = std::min(r.beta[L.in_lab[j]], L.in_U[j]);
+            // label paths: walks of up to 3 edges (2 unless the state is a codon boundary)
+            struct Fr { int state, first, last; int64_t cost; };
+            const int lmax = l % 3 == 0 ? 3 : 2;
+            std::vector<Fr> cur{{s, -1, -1, 0}}, nxt;
+            int k = 0;
+            for (int len = 1; len <= 3; len++) {
+                nxt.clear();
+                for (const Fr& f : cur)
+                    for (int x = 0; x < 4 && len <= lmax; x++) {
+                        const int d = L.out_dst[4 * f.state + x];
+                        if (d >= 0) nxt.push_back({d, len == 1 ? x : f.first, x, f.cost + L.out_U[4 * f.state + x]});
+                    }
+                for (const Fr& f : nxt) {
+                    if (k >= kFwdPaths) return false;
+                    r.fmeta[k] = f.state << 4 | f.first << 2 | f.last;
+                    r.fcost[k] = f.cost;
+                    r.fcrow[k] = L.rowoff[f.state] - L.off[L.layer[f.state] + 1];
+                    k++;
+                }
+                r.nf[len - 1] = (uint8_t)k;
+                cur.swap(nxt);
+            }
+            cur.assign(1, {s, -1, -1, 0});
+            k = 0;
+            for (int len = 1; len <= 3; len++) {
+                nxt.clear();
+                for (const Fr& f : cur)
+                    for (int j = L.in_start[f.state]; j < L.in_start[f.state + 1] && len <= lmax; j++)
+                        nxt.push_back({L.in_src[j], L.in_lab[j], len == 1 ? L.in_lab[j] : f.last, f.cost + L.in_U[j]});
+                for (const Fr& f : nxt) {
+                    if (k >= kBwdPaths) return false;
+                    r.bmeta[k] = f.state << 4 | f.first << 2 | f.last;
+                    r.bcost[k] = f.cost;
+                    k++;
+                }
+                r.nb[len - 1] = (uint8_t)k;
+                cur.swap(nxt);
+            }
+        }
+    return true;
+}
+
 int build_lattice(const char* protein, const CodonTable& T, const Params& P, double lambda,
                   const CapPolicy& cp, Lattice& L, std::string& err) {
     int rc = check_protein(protein);
@@ -432,8 +530,8 @@ int build_lattice(const char* protein, const CodonTable& T, const Params& P, dou
     L.off[n + 1] = (int)L.layer.size();
     const int N = L.N = (int)L.layer.size();
     for (int p = 0; p <= n; p++) {
-        if (L.off[p + 1] - L.off[p] > 4) {  // kernels buffer at most 4 x 4 cells per layer pair
-            err = "automaton layer wider than 4 states";
+        if (L.off[p + 1] - L.off[p] > kTrieWidth) {  // the genetic code's families have at most two prefixes
+            err = "automaton layer wider than 2 states";
             return SD_E_INTERNAL;
         }
         L.wmax = std::max(L.wmax, L.off[p + 1] - L.off[p]);
@@ -503,71 +601,11 @@ int build_lattice(const char* protein, const CodonTable& T, const Params& P, dou
             }
     L.tail[beta[A]] = 0;
     for (int k = 0; k < A; k++) L.P[k + 1] = L.P[k] + cmin[k];
-    // segment ends: alpha(d,x) = U(d -x-> d2) + tail(d2); beta(c,x) = min U over in-edges labelled x
-    L.alphaU.assign((size_t)4 * N, kINF);
-    L.betaU.assign((size_t)4 * N, kINF);
-    for (int v = 0; v < N; v++)
-        for (int x = 0; x < 4; x++) {
-            int d = L.out_dst[4 * v + x];
-            if (d >= 0) L.alphaU[4 * v + x] = L.out_U[4 * v + x] + L.tail[d];
-        }
-    for (int v = 0; v < N; v++)
-        for (int j = L.in_start[v]; j < L.in_start[v + 1]; j++)
-            L.betaU[4 * v + L.in_lab[j]] = std::min(L.betaU[4 * v + L.in_lab[j]], L.in_U[j]);
-    // label paths of 1..3 edges out of / into every state (explicit short loop segments); the fourth
-    // offset of a state ends its list
-    L.fwd_off.assign((size_t)4 * N + 1, 0);
-    L.bwd_off.assign((size_t)4 * N + 1, 0);
-    L.fwd_meta.clear(); L.fwd_cost.clear(); L.bwd_meta.clear(); L.bwd_cost.clear();
-    for (int u = 0; u < N; u++)
-        for (int len = 1; len <= 4; len++) {
-            L.fwd_off[4 * u + len - 1] = (int)L.fwd_meta.size();
-            if (len == 4) break;
-            struct Fr { int state, first_lab, last_lab; int64_t cost; int depth; };
-            std::vector<Fr> stack{{u, -1, -1, 0, 0}};
-            while (!stack.empty()) {
-                Fr f = stack.back();
-                stack.pop_back();
-                if (f.depth == len) {
-                    L.fwd_meta.push_back(f.state << 4 | f.first_lab << 2 | f.last_lab);
-                    L.fwd_cost.push_back(f.cost);
-                    continue;
-                }
-                for (int x = 0; x < 4; x++) {
-                    int e = 4 * f.state + x, d = L.out_dst[e];
-                    if (d < 0) continue;
-                    stack.push_back({d, f.depth == 0 ? x : f.first_lab, x, f.cost + L.out_U[e], f.depth + 1});
-                }
-            }
-        }
-    L.fwd_off[4 * N] = (int)L.fwd_meta.size();
-    for (int v = 0; v < N; v++)
-        for (int len = 1; len <= 4; len++) {
-            L.bwd_off[4 * v + len - 1] = (int)L.bwd_meta.size();
-            if (len == 4) break;
-            // backward walk over in-edge sequences; record (start, first label, last label)
-            struct Fr { int state, first_lab, last_lab; int64_t cost; int depth; };
-            std::vector<Fr> stack{{v, -1, -1, 0, 0}};
-            while (!stack.empty()) {
-                Fr f = stack.back();
-                stack.pop_back();
-                if (f.depth == len) {
-                    L.bwd_meta.push_back(f.state << 4 | f.first_lab << 2 | f.last_lab);
-                    L.bwd_cost.push_back(f.cost);
-                    continue;
-                }
-                for (int j = L.in_start[f.state]; j < L.in_start[f.state + 1]; j++)
-                    stack.push_back({L.in_src[j], L.in_lab[j], f.depth == 0 ? L.in_lab[j] : f.last_lab,
-                                     f.cost + L.in_U[j], f.depth + 1});
-            }
-        }
-    L.bwd_off[4 * N] = (int)L.bwd_meta.size();
     hairpin_init(L, P);
     layout_rows(L, cp);
-    L.fwd_crow.resize(L.fwd_meta.size());
-    for (size_t e = 0; e < L.fwd_meta.size(); e++) {
-        const int c = L.fwd_meta[e] >> 4;
-        L.fwd_crow[e] = L.rowoff[c] - L.off[L.layer[c] + 1];
+    if (!build_slots(L)) {
+        err = "a state has more short label paths than a slot record holds";
+        return SD_E_INTERNAL;
     }
     return SD_OK;
 }
@@ -710,10 +748,6 @@ int build_motif_lattice(const char* protein, const CodonTable& T, const Params& 
     L.tail.assign(N, 0);
     L.pfx.assign(N, 0);
     L.P.assign(L.A + 1, 0);
-    L.alphaU.assign((size_t)4 * N, kINF);
-    L.betaU.assign((size_t)4 * N, kINF);
-    L.fwd_off.assign((size_t)4 * N + 1, 0);
-    L.bwd_off.assign((size_t)4 * N + 1, 0);
     L.generic = true;
     L.motifs = motifs;
     for (int p = 0; p <= n; p++)

@@ -35,10 +35,7 @@ struct Lattice {
     std::vector<int> in_start, in_src, in_lab, in_cod;
     std::vector<int64_t> in_U;
     std::vector<int64_t> tail, P;
-    std::vector<int64_t> alphaU, betaU;  // [N*4] separable segment ends (see sd_kernels.hip)
-    std::vector<int> fwd_off, fwd_meta, bwd_off, bwd_meta;  // label paths of 1..3 edges
-    std::vector<int64_t> fwd_cost, bwd_cost;
-    std::vector<int64_t> fwd_crow;  // per forward path: rowoff[end] - off[layer(end) + 1]
+    std::vector<SlotRec> recs;  // two per layer (codon trie only)
     std::vector<int> pfx, hp_init;
     std::vector<int> inmask;  // [N] bit y: in-edge labelled y, bit 4 + x: out-edge labelled x
     std::vector<int64_t> rowoff, coff;
