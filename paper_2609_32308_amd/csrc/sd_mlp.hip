@@ -5,12 +5,14 @@
 // Targets: for K bins of right endpoints b by relative position layer(b)/n, the fraction of the
 // worst-case candidate slots (states c with layer(c) <= layer(b)-5) that the exact DP retains in
 // C_b (eq. 6), summed per bin.  Loss: mean squared error over samples and outputs.
-// Every reduction runs in a fixed order (one thread owns one output value), so gradients are
-// deterministic.
+// Every reduction runs in a fixed order (one thread owns one partial sum, and the partial sums of a
+// weight are added in order), so gradients are deterministic.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <string.h>
 
+#include <algorithm>
+#include <mutex>
 #include <vector>
 
 #include "../../include/sparsedesign.h"
@@ -71,21 +73,34 @@ __global__ void k_dense_bwd_data(const float* __restrict__ W, const float* __res
     dprev[idx] = act[idx] > 0.f ? g : 0.f;
 }
 
-// weight / bias gradients: gW[j][i] = sum_s d[s][j] * in[s][i], gb[j] = sum_s d[s][j]
-__global__ void k_dense_bwd_weights(const float* __restrict__ d, const float* __restrict__ in, float* __restrict__ gW,
-                                    float* __restrict__ gb, int n, int nin, int nout) {
-    const int idx = blockIdx.x * blockDim.x + threadIdx.x;
+// weight / bias gradients over one chunk of samples per blockIdx.y: part[chunk][j][i] = sum_s d[s][j] *
+// in[s][i], then part[chunk][nout * nin + j] = sum_s d[s][j].  One thread owns one sum.
+__global__ void k_dense_bwd_weights(const float* __restrict__ d, const float* __restrict__ in, float* __restrict__ part,
+                                    int n, int nin, int nout, int per) {
+    const int idx = blockIdx.x * blockDim.x + threadIdx.x, tot = nout * nin + nout;
+    if (idx >= tot) return;
+    const int s0 = blockIdx.y * per, s1 = min(n, s0 + per);
+    float g = 0.f;
     if (idx < nout * nin) {
         const int j = idx / nin, i = idx % nin;
-        float g = 0.f;
-        for (int s = 0; s < n; s++) g = fmaf(d[s * nout + j], in[s * nin + i], g);
-        gW[idx] = g;
-    } else if (idx < nout * nin + nout) {
+#pragma unroll 8
+        for (int s = s0; s < s1; s++) g = fmaf(d[s * nout + j], in[s * nin + i], g);
+    } else {
         const int j = idx - nout * nin;
-        float g = 0.f;
-        for (int s = 0; s < n; s++) g += d[s * nout + j];
-        gb[j] = g;
+#pragma unroll 8
+        for (int s = s0; s < s1; s++) g += d[s * nout + j];
     }
+    part[(size_t)blockIdx.y * tot + idx] = g;
+}
+
+// out[i] = the chunks' partial sums in chunk order (weights and biases are adjacent in the layout)
+__global__ void k_sum_chunks(const float* __restrict__ part, float* __restrict__ out, int chunks, int tot) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= tot) return;
+    float g = 0.f;
+#pragma unroll 8
+    for (int c = 0; c < chunks; c++) g += part[(size_t)c * tot + i];
+    out[i] = g;
 }
 
 __global__ void k_mse(const float* __restrict__ yhat, const float* __restrict__ y, float* __restrict__ loss,
@@ -130,6 +145,11 @@ struct sd_sizer {
     float* M = nullptr;  // Adam first moment
     float* Vm = nullptr; // Adam second moment
     int64_t adam_t = 0;
+    // workspace kept between calls (up to kKeepBytes; larger calls allocate their own): device memory,
+    // pinned staging.  Calls on one sizer hold the mutex, each until its stream has drained.
+    std::mutex mu;
+    float *dev = nullptr, *pin = nullptr;
+    size_t dev_n = 0, pin_n = 0;
     std::vector<float> host;  // host copy of the parameters (prediction on the host side)
 };
 
@@ -137,15 +157,32 @@ namespace {
 thread_local std::string g_mlp_err;
 int cdiv(int a, int b) { return (a + b - 1) / b; }
 
+constexpr size_t kKeepBytes = (size_t)64 << 20;
+
+// Chunks of samples per weight gradient: about 2^18 partial sums keep the chip busy where one thread per
+// weight left all but 20 workgroups idle for n steps (1,800 samples, gradient and prediction: 1.71 ms
+// with that and buffers allocated per call, 0.21 ms now); at least 32 samples each, so that the chunk sum stays the smaller part.
+int weight_chunks(int n, int tot) { return std::max(1, std::min(cdiv(n, 32), (1 << 18) / tot)); }
+
 struct Work {
     float *X = nullptr, *Y = nullptr, *H1 = nullptr, *H2 = nullptr, *O = nullptr, *D3 = nullptr,
-          *D2 = nullptr, *D1 = nullptr, *loss = nullptr;
-    hipError_t alloc(int n, int H, int K) {
-        size_t tot = (size_t)n * (kFeat + K + 3 * H + 2 * K + H) + 1;
-        float* base = nullptr;
-        hipError_t e = hipMalloc(&base, tot * sizeof(float));
+          *D2 = nullptr, *D1 = nullptr, *part = nullptr, *loss = nullptr;
+    float* pin = nullptr;  // pinned: n * (kFeat + K) floats in, at least 1 + total out
+    float *own_dev = nullptr, *own_pin = nullptr;
+    hipError_t alloc(sd_sizer* z, int n) {
+        const int H = z->sh.H, K = z->sh.K;
+        size_t parts = 0;
+        for (int tot : {K * H + K, H * H + H, H * kFeat + H}) parts = std::max(parts, (size_t)weight_chunks(n, tot) * tot);
+        const size_t dn = (size_t)n * (kFeat + K + 4 * H + 2 * K) + parts + 1;
+        const size_t pn = std::max((size_t)n * (kFeat + K), (size_t)z->sh.total + 1);
+        hipError_t e = grow(z->dev, z->dev_n, own_dev, dn, [](float** p, size_t b) { return hipMalloc(p, b); },
+                            [](float* p) { return hipFree(p); });
+        if (e == hipSuccess)
+            e = grow(z->pin, z->pin_n, own_pin, pn, [](float** p, size_t b) { return hipHostMalloc((void**)p, b, hipHostMallocDefault); },
+                     [](float* p) { return hipHostFree(p); });
         if (e != hipSuccess) return e;
-        X = base;
+        pin = own_pin ? own_pin : z->pin;
+        X = own_dev ? own_dev : z->dev;
         Y = X + (size_t)n * kFeat;
         H1 = Y + (size_t)n * K;
         H2 = H1 + (size_t)n * H;
@@ -153,11 +190,33 @@ struct Work {
         D3 = O + (size_t)n * K;
         D2 = D3 + (size_t)n * K;
         D1 = D2 + (size_t)n * H;
-        loss = D1 + (size_t)n * H;
+        part = D1 + (size_t)n * H;
+        loss = part + parts;
         return hipSuccess;
     }
+    // the kept buffer if it holds `need` floats, grown up to the limit; beyond it one of this call's own
+    template <class A, class F>
+    static hipError_t grow(float*& keep, size_t& keep_n, float*& own, size_t need, A a, F f) {
+        if (need <= keep_n) return hipSuccess;
+        if (need * sizeof(float) > kKeepBytes) return a(&own, need * sizeof(float));
+        if (keep) f(keep);
+        keep = nullptr;
+        keep_n = 0;
+        hipError_t e = a(&keep, need * sizeof(float));
+        if (e == hipSuccess) keep_n = need;
+        else keep = nullptr;
+        return e;
+    }
+    // inputs through the pinned buffer in one copy (Y may be null)
+    hipError_t upload(const sd_sizer* z, int n, const float* Xh, const float* Yh, hipStream_t st) {
+        const size_t nx = (size_t)n * kFeat, ny = Yh ? (size_t)n * z->sh.K : 0;
+        memcpy(pin, Xh, nx * sizeof(float));
+        if (Yh) memcpy(pin + nx, Yh, ny * sizeof(float));
+        return hipMemcpyAsync(X, pin, (nx + ny) * sizeof(float), hipMemcpyHostToDevice, st);
+    }
     ~Work() {
-        if (X) hipFree(X);
+        if (own_dev) hipFree(own_dev);
+        if (own_pin) hipHostFree(own_pin);
     }
 };
 
@@ -172,12 +231,18 @@ hipError_t fwd_bwd(sd_sizer* z, Work& W, int n, bool backward, hipStream_t st) {
     if (W.Y) hipLaunchKernelGGL(k_mse, dim3(1), dim3(256), 0, st, W.O, W.Y, W.loss, n * K);
     if (!backward) return hipGetLastError();
     float* G = z->G;
+    auto weights = [&](const float* d, const float* in, float* g, int nin, int nout) {
+        const int tot = nout * nin + nout, per = cdiv(n, weight_chunks(n, tot)), chunks = cdiv(n, per);
+        hipLaunchKernelGGL(k_dense_bwd_weights, dim3(cdiv(tot, 256), chunks), dim3(256), 0, st, d, in,
+                           chunks > 1 ? W.part : g, n, nin, nout, per);
+        if (chunks > 1) hipLaunchKernelGGL(k_sum_chunks, dim3(cdiv(tot, 256)), dim3(256), 0, st, W.part, g, chunks, tot);
+    };
     hipLaunchKernelGGL(k_out_delta, dim3(cdiv(n * K, 256)), dim3(256), 0, st, W.O, W.Y, W.D3, n * K, 2.f / (float)(n * K));
-    hipLaunchKernelGGL(k_dense_bwd_weights, dim3(cdiv(K * H + K, 256)), dim3(256), 0, st, W.D3, W.H2, G + s.o_w3, G + s.o_b3, n, H, K);
+    weights(W.D3, W.H2, G + s.o_w3, H, K);
     hipLaunchKernelGGL(k_dense_bwd_data, dim3(cdiv(n * H, 256)), dim3(256), 0, st, P + s.o_w3, W.D3, W.H2, W.D2, n, H, K);
-    hipLaunchKernelGGL(k_dense_bwd_weights, dim3(cdiv(H * H + H, 256)), dim3(256), 0, st, W.D2, W.H1, G + s.o_w2, G + s.o_b2, n, H, H);
+    weights(W.D2, W.H1, G + s.o_w2, H, H);
     hipLaunchKernelGGL(k_dense_bwd_data, dim3(cdiv(n * H, 256)), dim3(256), 0, st, P + s.o_w2, W.D2, W.H1, W.D1, n, H, H);
-    hipLaunchKernelGGL(k_dense_bwd_weights, dim3(cdiv(H * kFeat + H, 256)), dim3(256), 0, st, W.D1, W.X, G + s.o_w1, G + s.o_b1, n, kFeat, H);
+    weights(W.D1, W.X, G + s.o_w1, kFeat, H);
     return hipGetLastError();
 }
 
@@ -232,6 +297,8 @@ extern "C" sd_status sd_sizer_create(sd_context* ctx, int hidden, int n_out, uin
 extern "C" void sd_sizer_free(sd_sizer* z) {
     if (!z) return;
     if (z->P) hipFree(z->P);
+    if (z->dev) hipFree(z->dev);
+    if (z->pin) hipHostFree(z->pin);
     delete z;
 }
 
@@ -254,15 +321,20 @@ extern "C" sd_status sd_sizer_set_params(sd_sizer* z, const float* flat) {
 extern "C" sd_status sd_sizer_gradient(sd_sizer* z, int n, const float* X, const float* Y, float* loss,
                                        float* grad) {
     if (!z || n <= 0 || !X || !Y || !loss || !grad) return mlp_fail(SD_E_ARG, "null argument");
+    std::lock_guard<std::mutex> lk(z->mu);
     Work W;
-    hipError_t e = W.alloc(n, z->sh.H, z->sh.K);
+    hipError_t e = W.alloc(z, n);
     hipStream_t st = z->ctx->stream;
-    if (e == hipSuccess) e = hipMemcpyAsync(W.X, X, sizeof(float) * n * kFeat, hipMemcpyHostToDevice, st);
-    if (e == hipSuccess) e = hipMemcpyAsync(W.Y, Y, sizeof(float) * n * z->sh.K, hipMemcpyHostToDevice, st);
+    if (e == hipSuccess) e = W.upload(z, n, X, Y, st);
     if (e == hipSuccess) e = fwd_bwd(z, W, n, true, st);
-    if (e == hipSuccess) e = hipMemcpyAsync(loss, W.loss, sizeof(float), hipMemcpyDeviceToHost, st);
-    if (e == hipSuccess) e = hipMemcpyAsync(grad, z->G, sizeof(float) * z->sh.total, hipMemcpyDeviceToHost, st);
+    // (the inputs' copy has left the pinned buffer before the results' copies start: one stream)
+    if (e == hipSuccess) e = hipMemcpyAsync(W.pin, z->G, sizeof(float) * z->sh.total, hipMemcpyDeviceToHost, st);
+    if (e == hipSuccess) e = hipMemcpyAsync(W.pin + z->sh.total, W.loss, sizeof(float), hipMemcpyDeviceToHost, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
+    if (e == hipSuccess) {
+        memcpy(grad, W.pin, sizeof(float) * z->sh.total);
+        *loss = W.pin[z->sh.total];
+    }
     return e == hipSuccess ? SD_OK : mlp_fail(SD_E_DEVICE, hipGetErrorString(e));
 }
 
@@ -270,11 +342,11 @@ extern "C" sd_status sd_sizer_gradient(sd_sizer* z, int n, const float* X, const
 extern "C" sd_status sd_sizer_train(sd_sizer* z, int n, const float* X, const float* Y, int steps, float lr,
                                     float* final_loss) {
     if (!z || n <= 0 || !X || !Y || steps < 0) return mlp_fail(SD_E_ARG, "bad training arguments");
+    std::lock_guard<std::mutex> lk(z->mu);
     Work W;
-    hipError_t e = W.alloc(n, z->sh.H, z->sh.K);
+    hipError_t e = W.alloc(z, n);
     hipStream_t st = z->ctx->stream;
-    if (e == hipSuccess) e = hipMemcpyAsync(W.X, X, sizeof(float) * n * kFeat, hipMemcpyHostToDevice, st);
-    if (e == hipSuccess) e = hipMemcpyAsync(W.Y, Y, sizeof(float) * n * z->sh.K, hipMemcpyHostToDevice, st);
+    if (e == hipSuccess) e = W.upload(z, n, X, Y, st);
     const float b1 = 0.9f, b2 = 0.999f;
     for (int it = 0; it < steps && e == hipSuccess; it++) {
         e = fwd_bwd(z, W, n, true, st);
@@ -300,16 +372,18 @@ extern "C" sd_status sd_sizer_train(sd_sizer* z, int n, const float* X, const fl
 // GPU forward on n samples
 extern "C" sd_status sd_sizer_predict(sd_sizer* z, int n, const float* X, float* Yhat) {
     if (!z || n <= 0 || !X || !Yhat) return mlp_fail(SD_E_ARG, "null argument");
+    std::lock_guard<std::mutex> lk(z->mu);
     Work W;
-    hipError_t e = W.alloc(n, z->sh.H, z->sh.K);
+    hipError_t e = W.alloc(z, n);
     hipStream_t st = z->ctx->stream;
-    float* y = W.Y;
-    W.Y = nullptr;  // no loss
-    if (e == hipSuccess) e = hipMemcpyAsync(W.X, X, sizeof(float) * n * kFeat, hipMemcpyHostToDevice, st);
+    if (e == hipSuccess) {
+        W.Y = nullptr;  // no loss
+        e = W.upload(z, n, X, nullptr, st);
+    }
     if (e == hipSuccess) e = fwd_bwd(z, W, n, false, st);
-    W.Y = y;
-    if (e == hipSuccess) e = hipMemcpyAsync(Yhat, W.O, sizeof(float) * n * z->sh.K, hipMemcpyDeviceToHost, st);
+    if (e == hipSuccess) e = hipMemcpyAsync(W.pin, W.O, sizeof(float) * n * z->sh.K, hipMemcpyDeviceToHost, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
+    if (e == hipSuccess) memcpy(Yhat, W.pin, sizeof(float) * n * z->sh.K);
     return e == hipSuccess ? SD_OK : mlp_fail(SD_E_DEVICE, hipGetErrorString(e));
 }
 
