@@ -22,6 +22,14 @@ constexpr int64_t kHalfINF = int64_t(1) << 61;  // anything above is infeasible
 constexpr int kMaxLoop = 30;                    // bulge / interior unpaired cap (Sec. 3)
 constexpr int kNumPairs = 496;                  // (l1,l2) with l1 + l2 <= 30
 
+// Lower bounds of two-loop energies per closing type over boundary bases and inner types (traceback).
+struct LoopMin {
+    int32_t stack[6], int11[6], int12[6], int21[6], int22[6];
+    int32_t mm_out[3][6];  // min over (x_{i+1}, x_{j-1}) of mm_X[t], X = 0 generic, 1 2x3, 2 1xn
+    int32_t mm_in[3];      // min over inner types and boundary bases of mm_X
+    int32_t au_min;
+};
+
 // Loop tables as the kernels stage them in LDS, a multiple of 1 KiB (the 1x2 and 2x2 full-loop tables as
 // 16-bit copies; the parser requires entries in [-32768, 32767]).
 struct SmallE {
@@ -34,7 +42,8 @@ struct SmallE {
     int32_t int11[6][6][4][4];
     int32_t hairpin[31], bulge[31], interior[31];
     int32_t ml_closing, ml_intern, ml_base, terminal_au, ninio, ninio_max;
-    int32_t pad[217];
+    LoopMin lmin;
+    int32_t pad[165];
 };
 static_assert(sizeof(SmallE) % 1024 == 0, "staged in pieces of 1 KiB");
 

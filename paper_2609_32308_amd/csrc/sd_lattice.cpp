@@ -234,6 +234,20 @@ int parse_params(const std::string& text, Params& P, std::string& err) {
     M.terminal_au = P.E.terminal_au;
     M.ninio = P.E.ninio;
     M.ninio_max = P.E.ninio_max;
+    LoopMin& B = M.lmin;
+    const int32_t(*mm[3])[4][4] = {P.E.mmI, P.E.mm23, P.E.mm1n};
+    auto low = [](const int32_t* p, int cnt) { return *std::min_element(p, p + cnt); };
+    for (int t = 0; t < 6; t++) {
+        B.stack[t] = low(P.E.stack[t], 6);
+        B.int11[t] = low(&P.E.int11[t][0][0][0], 96);
+        B.int12[t] = low(&P.E.int21[t][0][0][0][0], 384);
+        B.int21[t] = INT32_MAX;  // 2x1 loops read the table from the inner pair's side
+        for (int u = 0; u < 6; u++) B.int21[t] = std::min(B.int21[t], low(&P.E.int21[u][t][0][0][0], 64));
+        B.int22[t] = low(&P.E.int22[t][0][0][0][0][0], 1536);
+        for (int X = 0; X < 3; X++) B.mm_out[X][t] = low(&mm[X][t][0][0], 16);
+    }
+    for (int X = 0; X < 3; X++) B.mm_in[X] = low(&mm[X][0][0][0], 96);
+    B.au_min = std::min(0, P.E.terminal_au);
     // special-loop lookup table keyed by the base-4 value of the loop sequence
     P.spec_table.assign(kSpecSize, kNoSpecial);
     const int offs[3] = {kSpecOff5, kSpecOff6, kSpecOff8};

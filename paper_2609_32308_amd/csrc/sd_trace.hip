@@ -77,50 +77,9 @@ __device__ __forceinline__ int32_t two_loop_e(const SmallE& S, int t, int tr, in
     return interior_e(S, nullptr, t, tr, l1, l2, xi, xk, xl, xj);
 }
 
-// lower bounds of two-loop energies per closing type over boundary bases and inner types
-struct LoopMin {
-    int32_t stack[6], int11[6], int12[6], int21[6], int22[6];
-    int32_t mm_out[3][6];  // min over (x_{i+1}, x_{j-1}) of mm_X[t]
-    int32_t mm_in[3];      // min over inner types and boundary bases of mm_X
-    int32_t au_min;
-};
-
-__device__ void loop_minima(const SmallE& S, LoopMin& M, int lane) {
-    for (int t = 0; t < 6; t++) {
-        int64_t st = lane < 6 ? S.stack[t][lane] : kINF, i11 = kINF, i12 = kINF, i21 = kINF, i22 = kINF;
-        for (int k = lane; k < 96; k += 64) i11 = mn(i11, (&S.int11[t][0][0][0])[k]);
-        for (int k = lane; k < 384; k += 64) {
-            i12 = mn(i12, (&S.int21[t][0][0][0][0])[k]);
-            i21 = mn(i21, (&S.int21[k >> 6][t][0][0][0])[k & 63]);
-        }
-        for (int k = lane; k < 1536; k += 64) i22 = mn(i22, (&S.int22[t][0][0][0][0][0])[k]);
-        st = wave_min(st);
-        i11 = wave_min(i11);
-        i12 = wave_min(i12);
-        i21 = wave_min(i21);
-        i22 = wave_min(i22);
-        int64_t mo[3];
-        for (int X = 0; X < 3; X++) mo[X] = wave_min(lane < 16 ? (int64_t)mmx(S, X, t, lane >> 2, lane & 3) : kINF);
-        if (lane == 0) {
-            M.stack[t] = (int32_t)st;
-            M.int11[t] = (int32_t)i11;
-            M.int12[t] = (int32_t)i12;
-            M.int21[t] = (int32_t)i21;
-            M.int22[t] = (int32_t)i22;
-            for (int X = 0; X < 3; X++) M.mm_out[X][t] = (int32_t)mo[X];
-        }
-    }
-    for (int X = 0; X < 3; X++) {
-        int64_t v = kINF;
-        for (int k = lane; k < 96; k += 64) v = mn(v, mmx(S, X, k >> 4, (k >> 2) & 3, k & 3));
-        v = wave_min(v);
-        if (lane == 0) M.mm_in[X] = (int32_t)v;
-    }
-    if (lane == 0) M.au_min = S.terminal_au < 0 ? S.terminal_au : 0;
-}
-
 // lower bound of two_loop_e(t, *, l1, l2, *) over inner types and boundary bases
-__device__ __forceinline__ int32_t two_loop_lb(const SmallE& S, const LoopMin& M, int t, int l1, int l2) {
+__device__ __forceinline__ int32_t two_loop_lb(const SmallE& S, int t, int l1, int l2) {
+    const LoopMin& M = S.lmin;
     if (l1 == 0 && l2 == 0) return M.stack[t];
     if (l1 == 0 || l2 == 0) {
         const int l = l1 + l2;
@@ -236,15 +195,18 @@ struct TraceScratch {
     int pre[kNumPairs + 1];  // tuples of the two-loop pairs before pair k
     int jl[64];              // in-edges of b labelled y (closing edge of a pair)
     int hpre[65];            // generic hairpins: prefix of in-degrees of the b1 of jl
+    // codon trie: the inner states at every distance l from the closing pair, index 2 l + slot
+    int64_t gl[64], row[64];  // gap a1 ~> c (infinite: no such state or path), row base of c
+    int64_t gr[2][64];        // gap d ~> b1 for each slot of b1
+    int st[64];               // state of d
 };
 
 struct TraceLds {
     SmallE S;
-    LoopMin M;
     unsigned char pl1[kNumPairs], pl2[kNumPairs];
     TraceScratch w[kTraceWaves];
     // the shared stack of deferred frames (frames in region A, its top here), guarded by `lock`
-    int lock, sp, busy, failed, dup;
+    int lock, sp, busy, failed, emitted;
     unsigned long long E, U;  // sums over the waves (two's complement)
 };
 
@@ -257,9 +219,13 @@ struct Tracer {
     int lane;
     int64_t E = 0, U = 0;
     bool fail = false;
-    bool dup = false;  // a position emitted twice (lane 0's view, broadcast at the end)
+    int emitted = 0;   // bases this wave emitted (over all waves n, or one was emitted twice)
     TFrame next;
     bool have_next = false;
+    // what is known of the next closed value beside its frame (codon trie): layers, slots, value
+    bool known = false;
+    int kp = 0, kq = 0, kia = 0, kib = 0;
+    int64_t kv = 0;
 
     __device__ Tracer(const Inst& I_, TraceLds& L_, TraceScratch& W_, const int32_t* sp_, int ln)
         : I(I_), L(L_), W(W_), spec(sp_), lane(ln) {}
@@ -389,12 +355,11 @@ struct Tracer {
     __device__ void go(int kind, int a, int b, int t) {
         next = TFrame{kind, a, b, t};
         have_next = true;
+        known = false;
     }
     __device__ void emit_at(int pos, int lab, int64_t cost) {
-        if (lane == 0) {
-            if (I.tr_seq()[pos] >= 0) dup = true;
-            I.tr_seq()[pos] = lab;
-        }
+        if (lane == 0) I.tr_seq()[pos] = lab;
+        emitted++;
         U += cost;
     }
     __device__ void emit_out(int e) { emit_at(I.layer()[e >> 2], e & 3, I.out_U()[e]); }
@@ -432,6 +397,7 @@ struct Tracer {
     __device__ void closed(int a, int b, int t);
     __device__ bool hairpin(int a, int b, int t, int64_t v, int ea, int a1);
     __device__ bool twoloop(int a, int b, int t, int64_t v, int ea, int a1);
+    __device__ void closed_trie(int a, int b, int t, int p, int q, int ia, int ib, int64_t v);
     __device__ void s1(int a, int b);
     __device__ void s2(int a, int b);
     __device__ void branch(int a, int b);
@@ -455,21 +421,21 @@ __device__ void Tracer::ext(int a) {
     // branches b (state order), pair types in order; one state per lane
     const int la = I.layer()[a];
     const int b0 = la + 5 <= I.n ? I.off()[la + 5] : I.N;
+    const int64_t* Br = I.Bt() + I.rowoff()[a] - I.off()[la + 1];
     for (int base = b0; base < I.N; base += 64) {
         const int bb = base + lane;
-        int hit = INT_MAX;
-        if (bb < I.N) {
-            const int64_t* vr = I.V() + tcell(I, a, bb) * 6;
-            const int64_t xb = I.X()[bb];
-            for (int t = 0; t < 6; t++)
-                if (sadd(sadd(vr[t], fxe(au_pen(L.S, t))), xb) == x) {
-                    hit = bb * 8 + t;
-                    break;
-                }
-        }
-        hit = wmin_int(hit);
-        if (hit != INT_MAX) {
-            const int b = hit >> 3, t = hit & 7;
+        // the branch value holds min over t of V_t + ML_intern + AU, and no branch lies below X(a): a
+        // state matches exactly if its branch value does
+        const bool hit = bb < I.N && sadd(sadd(Br[bb], -fxe(L.S.ml_intern)), I.X()[bb]) == x;
+        const unsigned long long hm = __ballot(hit);
+        if (hm) {
+            const int b = base + first_lane(hm);
+            const int64_t xb = I.X()[b];
+            bool th = false;
+            if (lane < 6) th = sadd(sadd(tV(I, lane, a, b), fxe(au_pen(L.S, lane))), xb) == x;
+            const unsigned long long tmk = __ballot(th);
+            if (!tmk) break;
+            const int t = first_lane(tmk);
             E += au_pen(L.S, t);
             push(kFX, b, -1, -1);
             go(kFV, a, b, t);
@@ -706,7 +672,7 @@ __device__ bool Tracer::twoloop(int a, int b, int t, int64_t v, int ea, int a1) 
             int64_t vmin = kINF;
             for (int tp = 0; tp < 6; tp++) vmin = mn(vmin, vr[tp]);
             // exact lower bound of every alternative of the group
-            const int64_t lb0 = Ua + tgl[k] + tgr[k] + tU[k] + fxe(two_loop_lb(L.S, L.M, t, l1, l2));
+            const int64_t lb0 = Ua + tgl[k] + tgr[k] + tU[k] + fxe(two_loop_lb(L.S, t, l1, l2));
             if (vmin >= kINF || lb0 + vmin > v) continue;
             // enumerate (inner type, left segment, right segment) in order
             for (int tp = 0; tp < 6 && code == INT_MAX; tp++) {
@@ -760,7 +726,238 @@ __device__ bool Tracer::twoloop(int a, int b, int t, int64_t v, int ea, int a1) 
     return false;
 }
 
+// A closed value on the codon trie, inner span >= 5.  A replay is one chain of decisions, so what bounds
+// it is the dependent loads of each: the general functions look states, layers, edges and gaps up one
+// after another (two-loop decision 17 us, hairpin test 3 us at 300 residues).  Here one level of loads
+// brings the slot records of every layer a two-loop can reach, the next one the inner cells, and a helix
+// carries layers, slots and the closed value from pair to pair.  The hairpin is enumerated only if its
+// separable minimum equals v: the value is the minimum over all loops, so nothing else can match.
+// 17 -> 8 us per decision; 50 residues 1.00 -> 0.73 ms between the fill and the result, 300 residues
+// 2.44 -> 2.31, 1,976 residues 19.9 -> 17.8 (there the cells themselves come from beyond the caches).
+__device__ void Tracer::closed_trie(int a, int b, int t, int p, int q, int ia, int ib, int64_t v) {
+    const int g = q - p, m = g - 2, x = kTX[t], y = kTY[t];
+    const SlotRec* R = I.recs();
+    if (lane == 0) {
+        I.tr_pair()[p] = q - 1;
+        I.tr_pair()[q - 1] = p;
+    }
+    // closing edges: a -x-> a1, and b1 -y-> b from either slot of layer q - 1 (in CSR order)
+    const int ia1 = bcast(R[2 * p + ia].dst[x]);
+    if (ia1 < 0 || v >= kINF) {
+        fail = true;
+        return;
+    }
+    const int64_t Ua = R[2 * p + ia].outU[x];
+    const SlotRec &r1 = R[2 * (p + 1) + ia1], &rb0 = R[2 * (q - 1)], &rb1 = R[2 * (q - 1) + 1];
+    const int a1 = bcast(r1.state);
+    const bool e0 = rb0.dst[y] == ib, e1 = rb1.state >= 0 && rb1.dst[y] == ib;
+    const int nj = (int)e0 + (int)e1, s0 = e0 ? 0 : 1;  // slots of the nj sources: s0 (then 1)
+    if (nj == 0) {
+        fail = true;
+        return;
+    }
+    const int64_t U0 = R[2 * (q - 1) + s0].outU[y], U1 = rb1.outU[y];
+    // the states at every distance: lane 2 l + slot, left c of layer p + 1 + l, right d of layer q - 1 - l
+    {
+        const int l = lane >> 1, sl = lane & 1, maxl = min(g - 7, kMaxLoop);
+        const bool in = l <= maxl;
+        const SlotRec& rc = R[2 * (p + 1 + (in ? l : 0)) + sl];
+        const SlotRec& rd = R[2 * (q - 1 - (in ? l : 0)) + sl];
+        const int cs = rc.state, ds = rd.state;
+        int64_t gl = kINF, g0 = kINF, g1 = kINF;
+        if (in && cs >= 0) {
+            const int cl = p + 1 + l;
+            if (l == 0) gl = sl == ia1 ? 0 : kINF;
+            else if (cl / 3 != (p + 1) / 3) gl = r1.tail + rc.ip0 - R[2 * p].pa1;
+            else if ((p + 1) % 3 == 0) gl = 0;
+            else gl = r1.dst[0] == sl || r1.dst[1] == sl || r1.dst[2] == sl || r1.dst[3] == sl ? 0 : kINF;
+        }
+        if (in && ds >= 0) {
+            const int dl = q - 1 - l;
+            if (l == 0) {
+                g0 = sl == 0 ? 0 : kINF;
+                g1 = sl == 1 ? 0 : kINF;
+            } else if (dl / 3 != (q - 1) / 3) {
+                g0 = g1 = rd.tail + R[2 * q].pb1 - rd.in1;
+            } else if (dl % 3 == 0) {
+                g0 = g1 = 0;
+            } else {
+                g0 = rd.dst[0] == 0 || rd.dst[1] == 0 || rd.dst[2] == 0 || rd.dst[3] == 0 ? 0 : kINF;
+                g1 = rd.dst[0] == 1 || rd.dst[1] == 1 || rd.dst[2] == 1 || rd.dst[3] == 1 ? 0 : kINF;
+            }
+        }
+        W.gl[lane] = gl;
+        W.row[lane] = rc.rowbase;
+        W.st[lane] = ds;
+        W.gr[0][lane] = g0;
+        W.gr[1][lane] = g1;
+    }
+    // hairpin: sizes 3, 4 and 6 (listed loops) are enumerated, the others only if their minimum is v
+    {
+        bool hit = m == 3 || m == 4 || m == 6;
+        if (!hit) {
+            const int k = lane >> 4, x2 = (lane >> 2) & 3, z = lane & 3;
+            const int64_t al = r1.alpha[x2], be = (k && e1 ? rb1 : R[2 * (q - 1) + s0]).beta[z];
+            const int64_t w = al >= kINF || be >= kINF ? kINF
+                              : Ua + (k && e1 ? U1 : U0) + al + be + R[2 * q].pb2 - R[2 * p].pa2 +
+                                    fxe(I.hp_init()[m] + L.S.mmH[t][x2][z]);
+            hit = __ballot(lane < 32 && w == v) != 0;
+        }
+        if (hit && hairpin(a, b, t, v, a * 4 + x, a1)) return;
+    }
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    // two-loops: tuple = pair (l1, l2), source of the closing edge, slot of c, slot of d, in canonical
+    // order; two tuples per lane and round
+    const int sh = nj == 2 ? 3 : 2, total = kNumPairs << sh;
+    constexpr int kPer = 2;
+    for (int base = 0; base < total; base += 64 * kPer) {
+        int code = INT_MAX, wtp = 0, wp = 0, wq = 0;
+        int64_t wv = 0;
+        int tl1[kPer], tl2[kPer], tjj[kPer];
+        int64_t tg[kPer];
+        longlong2 tv[kPer][3];
+        bool ok[kPer];
+#pragma unroll
+        for (int k = 0; k < kPer; k++) {
+            const int T = base + lane + 64 * k, pk = min(T >> sh, kNumPairs - 1);
+            tl1[k] = L.pl1[pk];
+            tl2[k] = L.pl2[pk];
+            tjj[k] = nj == 2 ? (T >> 2) & 1 : s0;
+            const int il = 2 * tl1[k] + ((T >> 1) & 1), ir = 2 * tl2[k] + (T & 1);
+            const int64_t gl = W.gl[il], gr = W.gr[tjj[k]][ir];
+            ok[k] = T < total && tl1[k] + tl2[k] <= g - 7 && gl < kINF && gr < kINF;
+            tg[k] = gl + gr;
+            const longlong2* vp = reinterpret_cast<const longlong2*>(I.V() + (ok[k] ? W.row[il] + W.st[ir] : r1.rowbase + rb0.state) * 6);
+            tv[k][0] = vp[0];
+            tv[k][1] = vp[1];
+            tv[k][2] = vp[2];
+        }
+#pragma unroll
+        for (int k = 0; k < kPer; k++) {
+            if (!ok[k] || code != INT_MAX) continue;
+            const int l1 = tl1[k], l2 = tl2[k];
+            const int64_t vin[6] = {tv[k][0].x, tv[k][0].y, tv[k][1].x, tv[k][1].y, tv[k][2].x, tv[k][2].y};
+            const int64_t Uj = nj == 2 && tjj[k] ? U1 : U0;
+            const int64_t lb0 = Ua + tg[k] + Uj + fxe(two_loop_lb(L.S, t, l1, l2));
+            int64_t vmin = kINF;
+#pragma unroll
+            for (int tp = 0; tp < 6; tp++) vmin = mn(vmin, vin[tp]);
+            if (vmin >= kINF || lb0 + vmin > v) continue;
+            const int T = base + lane + 64 * k;
+#pragma unroll
+            for (int tp = 0; tp < 6; tp++) {
+                if (code != INT_MAX || vin[tp] >= kINF || lb0 + vin[tp] > v) continue;
+                const int tr = kRev[tp];
+                if (l1 == 0 || l2 == 0) {
+                    // no boundary base enters the energy: the segment's minimum decides
+                    const int32_t e2 = l1 + l2 == 0 ? L.S.stack[t][tr] : bulge_e(L.S, t, tr, l1 + l2);
+                    if (Ua + tg[k] + vin[tp] + Uj + fxe(e2) == v) {
+                        code = T;
+                        wtp = tp;
+                        wp = wq = -1;
+                        wv = vin[tp];
+                    }
+                    continue;
+                }
+                const int c = R[2 * (p + 1 + l1) + ((T >> 1) & 1)].state, d = W.st[2 * l2 + (T & 1)];
+                const int b1 = R[2 * (q - 1) + tjj[k]].state;
+                Seg sl, sr;
+                SegIter li(I, a1, c, l1);
+                for (int pp = 0; code == INT_MAX && li.next(I, sl); pp++) {
+                    SegIter ri(I, d, b1, l2);
+                    for (int qq = 0; code == INT_MAX && ri.next(I, sr); qq++) {
+                        const int32_t e2 = interior_e(L.S, nullptr, t, tr, l1, l2, sl.xa, sl.xb, sr.xa, sr.xb);
+                        if (Ua + sl.cost + vin[tp] + sr.cost + Uj + fxe(e2) == v) {
+                            code = T;
+                            wtp = tp;
+                            wp = pp;
+                            wq = qq;
+                            wv = vin[tp];
+                        }
+                    }
+                }
+            }
+        }
+        const int best = wmin_int(code);
+        if (best == INT_MAX) {
+            if (L.pl1[min((base + 64 * kPer) >> sh, kNumPairs - 1)] > g - 7) break;  // no further pair fits
+            continue;
+        }
+        const int wl = first_lane(__ballot(code == best));
+        const int tp = bcast(__shfl(wtp, wl, 64)), pp = bcast(__shfl(wp, wl, 64)), qq = bcast(__shfl(wq, wl, 64));
+        const int64_t vn = readlane64(wv, wl);
+        const int l1 = L.pl1[best >> sh], l2 = L.pl2[best >> sh], ci = (best >> 1) & 1, di = best & 1;
+        const int jj = nj == 2 ? (best >> 2) & 1 : s0;
+        const int c = R[2 * (p + 1 + l1) + ci].state, d = R[2 * (q - 1 - l2) + di].state, b1 = R[2 * (q - 1) + jj].state;
+        emit_at(p, x, Ua);
+        if (pp < 0) {  // stack or bulge: the first path at the segment's minimum, if there is a segment
+            E += l1 + l2 == 0 ? L.S.stack[t][kRev[tp]] : bulge_e(L.S, t, kRev[tp], l1 + l2);
+            Seg s;
+            for (int side = 0; side < 2; side++) {
+                const int l = side ? l2 : l1, u = side ? d : a1, w = side ? b1 : c;
+                const int64_t want = side ? W.gr[jj][2 * l2 + di] : W.gl[2 * l1 + ci];
+                if (l == 0) continue;
+                int k = 0;
+                bool got;
+                while ((got = seg_at(I, u, w, l, k, s)) && s.cost != want) k++;
+                if (!got) {
+                    fail = true;
+                    return;
+                }
+                emit_seg(s);
+            }
+        } else {
+            Seg sl, sr;
+            seg_at(I, a1, c, l1, pp, sl);
+            seg_at(I, d, b1, l2, qq, sr);
+            E += interior_e(L.S, nullptr, t, kRev[tp], l1, l2, sl.xa, sl.xb, sr.xa, sr.xb);
+            emit_seg(sl);
+            emit_seg(sr);
+        }
+        emit_at(q - 1, y, nj == 2 && jj ? U1 : U0);
+        go(kFV, c, d, tp);
+        known = true;
+        kp = p + 1 + l1;
+        kq = q - 1 - l2;
+        kia = ci;
+        kib = di;
+        kv = vn;
+        return;
+    }
+    // multiloop: closing in-edge of b labelled y, in CSR order
+    const int32_t mlc = L.S.ml_closing + L.S.ml_intern + au_pen(L.S, t);
+    for (int k = 0; k < nj; k++) {
+        const int sl = k ? 1 : s0, b1 = R[2 * (q - 1) + sl].state;
+        const int64_t Uj = k ? U1 : U0;
+        if (g >= 12 && sadd(Ua + Uj + fxe(mlc), I.S2()[r1.rowbase + b1]) == v) {
+            emit_at(p, x, Ua);
+            emit_at(q - 1, y, Uj);
+            E += mlc;
+            go(kFS2, a1, b1, -1);
+            return;
+        }
+    }
+    fail = true;
+}
+
 __device__ void Tracer::closed(int a, int b, int t) {
+    if (!I.gwin) {
+        int p = kp, q = kq, ia = kia, ib = kib;
+        int64_t v = kv;
+        if (!known) {
+            p = bcast(I.layer()[a]);
+            q = bcast(I.layer()[b]);
+            ia = a - bcast(I.off()[p]);
+            ib = b - bcast(I.off()[q]);
+            v = tV(I, t, a, b);
+        }
+        known = false;
+        if (q - p >= 7) {
+            closed_trie(a, b, t, p, q, ia, ib, v);
+            return;
+        }
+    }
     const int64_t v = tV(I, t, a, b);
     const int i = I.layer()[a], j = I.layer()[b] - 1;
     if (lane == 0) {
@@ -913,12 +1110,11 @@ __device__ void trace_instance(const Inst& I, const EnergyTables* __restrict__ E
         L.sp = 0;
         L.busy = 1;  // wave 0 starts busy with X(s)
         L.failed = 0;
-        L.dup = 0;
+        L.emitted = 0;
         L.E = 0;
         L.U = 0;
     }
     __syncthreads();  // every wave's share of the energy tables is staged
-    if (wave == 0) loop_minima(L.S, L.M, lane);
     // A position is initialised by one wave and later written by whichever wave emits it: every
     // wave waits for its initialising stores before the barrier (which by itself waits only for
     // LDS operations), so that no -1 can land after an emitted value.
@@ -955,17 +1151,16 @@ __device__ void trace_instance(const Inst& I, const EnergyTables* __restrict__ E
             default: tr.branch(f.a, f.b); break;
         }
     }
-    const int dup = bcast(tr.dup ? 1 : 0);
     if (lane == 0) {
         atomicAdd(&L.E, (unsigned long long)tr.E);
         atomicAdd(&L.U, (unsigned long long)tr.U);
-        if (dup) atomicOr(&L.dup, 1);
+        atomicAdd(&L.emitted, tr.emitted);
     }
     __syncthreads();
     if (tid == 0) {
         I.tr_res()[0] = (long long)L.E;
         I.tr_res()[1] = (long long)L.U;
-        I.tr_res()[2] = L.failed ? L.failed : L.dup ? kTrDup : kTrOk;
+        I.tr_res()[2] = L.failed ? L.failed : L.emitted > I.n ? kTrDup : kTrOk;
         I.tr_res()[3] = xs;
     }
 }
@@ -980,7 +1175,7 @@ __global__ __launch_bounds__(64 * kTraceWaves) void k_trace_many(const Inst* __r
                                                                  const EnergyTables* __restrict__ E,
                                                                  const int32_t* __restrict__ spec) {
     __shared__ TraceLds L;
-    const Inst I = insts[blockIdx.x];
+    const Inst I = load_inst(insts + blockIdx.x);
     trace_instance(I, E, spec, L);
 }
 
