@@ -306,9 +306,12 @@ InstLayout layout_instance(const Lattice& L, char* A, char* B, Inst& I) {
     I.mlbase_fx = L.mlbase_fx;
     I.retain_all = 0;
     I.g0 = 1;
-    I.gwin = L.generic ? L.gwin : 0;
+    I.gwin = L.generic ? 1 : 0;
     I.wmax = L.wmax;
-    I.njobs = L.generic ? (int64_t)L.gjobs.size() / 2 : 0;
+    I.nwalk = (int64_t)L.gwalks.size();
+    I.nil = (int)L.grows.size();
+    I.lgsize = L.lgsize;
+    I.win = L.win;
     // extents against slots (units of U in region A, of R in region B)
     struct Ext { const void* p; int64_t bytes; int64_t slot; };
     const int64_t U = I.U, R = I.R();
@@ -369,8 +372,11 @@ void stage_inputs(const Lattice& L, const Inst& I, const char* devA, char* image
     put(I.ccap(), L.ccap.data(), L.ccap.size() * 4);
     put(I.recs(), L.recs.data(), L.recs.size() * sizeof(SlotRec));
     if (L.generic) {
-        put(I.gjob_off(), L.gjob_off.data(), L.gjob_off.size() * 8);
-        put(I.gjobs(), L.gjobs.data(), L.gjobs.size() * 4);
+        put(I.gedges(), L.gedges.data(), L.gedges.size() * sizeof(GenEdge));
+        put(I.gwalks(), L.gwalks.data(), L.gwalks.size() * sizeof(GenEdge));
+        put(I.grows(), L.grows.data(), L.grows.size() * sizeof(GenRow));
+        put(I.growedge(), L.growedge.data(), L.growedge.size() * 4);
+        put(I.geoff(), L.goff.data(), L.goff.size() * 4);
     }
 }
 

@@ -88,9 +88,7 @@ struct TFrame {
 // Region B (DP tables) is cut into ring units of R = 512 * N bytes (N states x 64 spans x 8 B):
 //   0-1 LM  2-13 IDL  14-25 JDL  26 BI  27 BJ  28-43 RS  44-59 LS  60-61 MINI, then from 62 R:
 //   V[cells][6], Bt[cells], S1[cells], S2[cells], cc[slots], cB[slots], and for generic lattices
-//   G[cells] (minimum path cost a -> b) and LG[state][gwin][4][4] (minimum cost of a path u -> v
-//   of 1..30 edges with first label x and last label y; v indexed from the first state of the
-//   layer after u's).
+//   G[cells] (minimum path cost a -> b), LG[row][wl] and IN[class 3][row][win] (see GenRow).
 // Meaning of the arrays:
 //   layer/off: layer of a state, first state of a layer; out_dst/out_U: out-edge by label
 //   (-1 / cost); in_start/in_src/in_lab/in_U: in-edges (CSR, sorted by source and label);
@@ -142,17 +140,33 @@ struct alignas(64) SlotRec {
     int32_t fmeta[kFwdPaths], bmeta[kBwdPaths];
 };
 
+// Generic lattices.  Out-edges in order of state and label, walks of two edges in order of their edges,
+// and rows: one per state and label of its in-edges, in order of state and label.
+struct GenEdge {
+    int32_t src, dst, lab, layer;  // of a walk: lab = first label | last label << 2; layer of src
+    int64_t U;
+    int32_t row, pad;              // row of (dst, lab)
+};
+// LG(e, row) lies at lgbase + e, e an out-edge of the 30 layers before the row's; IN_X(row, f) in column
+// f mod win, a ring over the out-edges of 33 layers.
+struct GenRow {
+    int32_t state, lab, layer, cnt;  // cnt edges enter the state with the label:
+    int32_t first, pad;              // growedge()[first..]
+    int64_t lgbase;
+};
+
 struct Inst {
     char *ra, *rb;         // region bases
     int64_t U;             // region-A unit in bytes
     int64_t nE, nrec;      // in-edges, slot records (0 for generic lattices)
     int64_t cells, slots;  // DP cells, candidate slots
     int64_t mlbase_fx;     // ML_base * 2^s
-    int64_t njobs;         // generic lattices: typed-value jobs over all spans
+    int64_t nwalk, lgsize;  // generic lattices: walks of two edges, words of LG
     int n, N, A, shift;
     int retain_all;
     int g0;  // persistent launches: first span this launch processes for the instance
-    int gwin;  // generic lattices: states in the 30 layers after any layer (0 for the codon trie)
+    int gwin;  // 1 for generic lattices (0 for the codon trie)
+    int nil, win;  // generic lattices: rows, ring width of IN
     int wmax;  // widest layer
 
     __host__ __device__ static int64_t al8(int64_t x) { return (x + 7) & ~(int64_t)7; }
@@ -189,13 +203,17 @@ struct Inst {
     __host__ __device__ const SlotRec* recs() const {
         return (const SlotRec*)(ra + ((ua(27) + 2 * al8(4 * nE) + 8 * nE - ra + 63) & ~(int64_t)63));
     }
-    // generic lattices: per span g the typed-value jobs [gjob_off[g], gjob_off[g+1]) of gjobs
-    // (pairs a, b * 8 + type), and one work-ticket counter per span
-    __host__ __device__ int64_t* gjob_off() const { return (int64_t*)(recs() + nrec); }
-    __host__ __device__ int* gjobs() const { return (int*)(gjob_off() + (gwin ? n + 2 : 0)); }
-    __host__ __device__ unsigned* gtickets() const { return (unsigned*)(gjobs() + 2 * njobs); }
+    // generic lattices: edges, rows, walks, the edges of each row, and the first edge, row and walk of
+    // every layer
+    __host__ __device__ const GenEdge* gedges() const { return (const GenEdge*)(recs() + nrec); }
+    __host__ __device__ const GenEdge* gwalks() const { return gedges() + (gwin ? nE : 0); }
+    __host__ __device__ const GenRow* grows() const { return (const GenRow*)(gwalks() + nwalk); }
+    __host__ __device__ const int* growedge() const { return (const int*)(grows() + nil); }
+    __host__ __device__ const int* geoff() const { return growedge() + (gwin ? nE : 0); }
+    __host__ __device__ const int* groff() const { return geoff() + n + 2; }
+    __host__ __device__ const int* gwoff() const { return groff() + n + 2; }
     __host__ __device__ int64_t a_bytes() const {
-        return (int64_t)((char*)gtickets() - ra) + (gwin ? al8(4 * ((int64_t)n + 1)) : 0);
+        return (int64_t)((char*)geoff() - ra) + (gwin ? 12 * ((int64_t)n + 2) : 0);
     }
 
     __host__ __device__ int64_t* LM() const { return (int64_t*)ub(0); }
@@ -212,11 +230,13 @@ struct Inst {
     __host__ __device__ int64_t* S2() const { return (int64_t*)(ub(62) + 64 * cells); }
     __host__ __device__ int* cc() const { return (int*)(ub(62) + 72 * cells); }
     __host__ __device__ int64_t* cB() const { return (int64_t*)(ub(62) + 72 * cells + al8(4 * slots)); }
-    // generic lattices only: gap table G[cells] and labelled gap table LG[N][gwin][16]
+    // generic lattices only: gap table G[cells], labelled gaps LG and inner loop parts IN
     __host__ __device__ int64_t* Gt() const { return (int64_t*)(ub(62) + 72 * cells + al8(4 * slots) + 8 * slots); }
     __host__ __device__ int64_t* LG() const { return Gt() + cells; }
+    __host__ __device__ int64_t* IN() const { return LG() + lgsize; }
     __host__ __device__ int64_t b_bytes() const {
-        return 62 * R() + 72 * cells + al8(4 * slots) + 8 * slots + (gwin ? 8 * cells + 128 * (int64_t)N * gwin : 0);
+        return 62 * R() + 72 * cells + al8(4 * slots) + 8 * slots +
+               (gwin ? 8 * (cells + lgsize + 3 * (int64_t)nil * win) : 0);
     }
 };
 

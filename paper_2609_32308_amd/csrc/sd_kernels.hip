@@ -972,6 +972,11 @@ __global__ void k_init(Inst I) {
         I.ccnt()[i] = 0;
         I.X()[i] = I.layer()[i] == I.n ? 0 : kINF;  // every state of the last layer is a sink
     }
+    if (I.gwin) {  // no rings on a generic lattice
+        if (tid < 4) I.stats()[tid] = tid == 2 ? ~0ull : 0ull;
+        for (int i = tid; i <= I.n; i += nt) I.visits()[i] = I.feasible()[i] = 0;
+        return;
+    }
     for (size_t i = tid; i < (size_t)(I.n + 1) * 2 * kLMRing; i += nt) I.LM()[i] = kINF;
     for (size_t i = tid; i < (size_t)I.N * kLMRing * 12; i += nt) {
         I.IDL()[i] = kINF;
@@ -989,10 +994,6 @@ __global__ void k_init(Inst I) {
     for (int i = tid; i <= I.n; i += nt) {
         I.visits()[i] = 0;
         I.feasible()[i] = 0;
-    }
-    if (I.gwin) {  // generic lattices: typed values are folded in with atomic minima
-        for (int64_t i = tid; i < I.cells * 6; i += nt) I.V()[i] = kINF;
-        for (int i = tid; i <= I.n; i += nt) I.gtickets()[i] = 0;
     }
 }
 
@@ -1088,371 +1089,463 @@ __global__ void k_checksum(Inst I, int g, unsigned long long* out) {
 }
 
 // ---- generic lattice: the codon automaton intersected with a forbidden-motif matcher --------------
-// Nothing below relies on the codon trie.  Minimum path costs come from two tables that the span
-// step fills for its own cells and that later spans read:
-//   G(a, b)        minimum path cost a -> b (cell layout);
-//   LG(u, v, x, y) minimum cost of a path u -> v whose first edge is labelled x and last edge y,
-//                  for layer distances 1..30 (the unpaired segments of a two-loop).
-// A generic interior loop couples its segments only through the four bases next to the two
-// pairs (outer mismatch: x_{i+1}, x_{j-1}; inner mismatch: x_{l+1}, x_{k-1}), so for an inner
-// cell (c, d) the minimum over those bases is a min-plus product over a 4-cycle: eliminate x_{j-1}
-// with the right segment and the outer mismatch, x_{k-1} with the left segment and the inner
-// mismatch, then take the minimum over (x_{i+1}, x_{l+1}).  Loops with both sides of <= 2 bases
-// (the 1x1, 1x2, 2x2 tables) enumerate all boundary bases.
-// per (cell, type): part 0 hairpin, stack, bulges, multiloop; part l1 = 1..29 the interior loops
-// whose left segment has l1 bases (one ticket each, so that a span's work balances finely)
-constexpr int kGenParts = 30;
+// Nothing below relies on the codon trie.  With e = (a, x) an out-edge (state and label), i = (v, y) a
+// row (state and the label of an in-edge), the span step fills for its own cells and later spans read
+//   G(a, b)    minimum path cost a -> b (cell layout);
+//   LG(e, i)   minimum cost of a path that starts with edge e and ends in v through an edge labelled
+//              y, for layer distances 1..30: the unpaired segments of a two-loop;
+//   IN_X(i, f) for row i = (c, xk) and out-edge f = (d, xl): min over types t' of V_t'(c, d) + mm_X[t'
+//              reversed][xl][xk], the inner part of an interior loop of mismatch class X.
+// An interior loop couples its segments only through the four bases next to its pairs, so the closed
+// value of an inner boundary pair (a1, b1) of layers p1, q1 is the minimum over e out of a1 and rows j
+// of b1 of T_X(e, j) + mm_X[t][x(e)][y(j)], with
+//   Q(e, f) = min over l1 and rows i of layer p1 + l1 of LG(e, i) + IN(i, f) + size(l1, l2)
+//   T(e, j) = min over l2 and out-edges f of layer q1 - l2 of Q(e, f) + LG(f, j)
+// two min-plus products that serve every closing type and every pair of states of the two layers: per
+// layer pair about 465 * rows * edges * edges sums, where one evaluation per (a, b, type) took states^3 *
+// edges * 160.  Loops with a side of one base (class 1xn) need only one of the products and 2x3 loops are
+// a handful of rows; stacks, bulges of one base and the tabulated 1x1, 1x2, 2x2 loops enumerate the
+// label walks of up to two edges on both sides.
+// What bounds the step is its chain of loads (offsets, records, tables) and the issue of 64-bit sums;
+// 315 layer pairs give every CU one workgroup.
+// Infinite operands: LG is kINF, IN and the accumulators kHalfINF, finite values lie within 2^60, so a
+// sum of all three neither overflows nor falls below kGenBig.
+constexpr int64_t kGenBig = kHalfINF >> 1;
+constexpr int kGenGroup = 4;   // left edges per accumulator set
+constexpr int kGenTasks = 8;   // (edge group, 64 right edges) accumulator sets per round
 
-template <class IT>
-__device__ __forceinline__ int64_t gen_gap(const IT& I, int a, int la, int b, int lb) {
-    if (la == lb) return a == b ? 0 : kINF;
-    return I.Gt()[I.rowoff()[a] + (b - I.off()[la + 1])];
-}
-template <class IT>
-__device__ __forceinline__ const int64_t* gen_lg(const IT& I, int u, int lu, int v) {
-    return I.LG() + ((int64_t)u * I.gwin + (v - I.off()[lu + 1])) * 16;
-}
+typedef const __attribute__((address_space(4))) GenEdge* GenEdgePtr;
+typedef const __attribute__((address_space(4))) GenRow* GenRowPtr;
+typedef const __attribute__((address_space(4))) int* IntPtr;
+typedef const __attribute__((address_space(4))) int64_t* LongPtr;
 
 struct GenShared {
-    int64_t cellB[kGenMaxWidth * kGenMaxWidth];
+    int64_t w[kGenMaxWidth * kGenMaxWidth * 6];  // W_t(a1, b1)
+    int64_t v[kGenMaxWidth * kGenMaxWidth * 6];  // hairpins of 3, 4, 6 bases, then V of the cells
+    int64_t s2[kGenMaxWidth * kGenMaxWidth], ps[kGenMaxWidth * kGenMaxWidth], cellB[kGenMaxWidth * kGenMaxWidth];
+    int committed[kGenMaxWidth * kGenMaxWidth];
     int8_t keep[kGenMaxWidth * kGenMaxWidth];
+    int64_t q[kGenTasks][kGenGroup][64];         // Q of one round
 };
 
-// interior loop (l1, l2 >= 1) closed by type t around inner cell values vin[6], with the left
-// and right segment tables L = LG(a1, c), R = LG(d, b1)
-__device__ int64_t gen_interior(const SmallE& S, const EnergyTables* __restrict__ E, int t, int l1, int l2,
-                                const int64_t* __restrict__ Lp, const int64_t* __restrict__ Rp,
-                                const int64_t vin[6], int s) {
-    int64_t best = kINF;
-    if (l1 <= 2 && l2 <= 2) {
-        for (int i = 0; i < 16; i++) {
-            const int64_t li = Lp[i];
-            if (li >= kINF) continue;
-            for (int j = 0; j < 16; j++) {
-                const int64_t rj = Rp[j];
-                if (rj >= kINF) continue;
-#pragma unroll
-                for (int tp = 0; tp < 6; tp++) {
-                    if (vin[tp] >= kINF) continue;
-                    const int32_t e2 = interior_e(S, E, t, kRev[tp], l1, l2, i >> 2, i & 3, j >> 2, j & 3);
-                    best = mn(best, li + rj + vin[tp] + fx(e2, s));
-                }
-            }
-        }
-        return best;
-    }
-    const int X = mm_class(l1, l2);
-    // T2[xl][xi] = min over xj of R[xl][xj] + mm_X[t][xi][xj]
-    int64_t T2[16];
-#pragma unroll
-    for (int k = 0; k < 16; k++) {
-        const int xl = k >> 2, xi = k & 3;
-        int64_t acc = kINF;
-#pragma unroll
-        for (int xj = 0; xj < 4; xj++) {
-            const int64_t r = Rp[xl * 4 + xj];
-            if (r < kINF) acc = mn(acc, r + fx(mmx(S, X, t, xi, xj), s));
-        }
-        T2[k] = acc;
-    }
-    for (int tp = 0; tp < 6; tp++) {
-        if (vin[tp] >= kINF) continue;
-        const int tr = kRev[tp];
-        for (int xi = 0; xi < 4; xi++)
-            for (int xl = 0; xl < 4; xl++) {
-                const int64_t t2 = T2[xl * 4 + xi];
-                if (t2 >= kINF) continue;
-                int64_t t1 = kINF;  // min over xk of L[xi][xk] + mm_X[tr][xl][xk]
-#pragma unroll
-                for (int xk = 0; xk < 4; xk++) {
-                    const int64_t l = Lp[xi * 4 + xk];
-                    if (l < kINF) t1 = mn(t1, l + fx(mmx(S, X, tr, xl, xk), s));
-                }
-                if (t1 < kINF) best = mn(best, t1 + t2 + vin[tp]);
-            }
-    }
-    return best >= kINF ? kINF : best + fx(interior_base(S, l1, l2), s);
+// minimum into a shared word; values that hold an infinite operand are left out
+__device__ __forceinline__ void gen_min(int64_t* w, int64_t v) {
+    if (v < kGenBig) __hip_atomic_fetch_min(w, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
-// Interior loop of mismatch class X with both segment tables known, when the left segment's
-// part is pre-reduced: A[xk][xj] = min over xi of L[xi][xk] + mm_X[t][xi][xj] (per inner left
-// state c).  Then min over (xk, xl) of [min over xj of A[xk][xj] + R[xl][xj]] + IN(xk, xl), with
-// IN(xk, xl) = min over inner types of V + mm_X[reversed type][xl][xk].
-__device__ __forceinline__ int64_t gen_interior_fast(const SmallE& S, int X, const int64_t A[16],
-                                                     const int64_t* __restrict__ Rp, const int64_t vin[6],
-                                                     int l1, int l2, int s) {
-    int64_t R[16];
-#pragma unroll
-    for (int k = 0; k < 16; k++) R[k] = Rp[k];
-    // the class's table through an offset the compiler cannot hoist: keeping the 96 scaled entries in
-    // registers across the inner states' loop spills them (1.6 KB of scratch per lane)
-    int off = (X == 0 ? 1 : X == 2 ? 2 : 3) * 96;
-    asm volatile("" : "+v"(off));
-    const int32_t* tab = &S.mmH[0][0][0] + off;
-    int64_t best = kINF;
-#pragma unroll
-    for (int xk = 0; xk < 4; xk++)
-#pragma unroll
-        for (int xl = 0; xl < 4; xl++) {
-            int64_t out = kINF;
-#pragma unroll
-            for (int xj = 0; xj < 4; xj++) {
-                const int64_t a = A[xk * 4 + xj], r = R[xl * 4 + xj];
-                if (a < kINF && r < kINF) out = mn(out, a + r);
-            }
-            if (out >= kINF) continue;
-            int64_t in = kINF;
-#pragma unroll
-            for (int tp = 0; tp < 6; tp++)
-                if (vin[tp] < kINF) in = mn(in, vin[tp] + fx(tab[type_rev(tp) * 16 + xl * 4 + xk], s));
-            if (in < kINF) best = mn(best, out + in);
-        }
-    return best >= kINF ? kINF : best + fx(interior_base(S, l1, l2), s);
-}
+// The sums of one layer pair that a two-loop of layers p1 = p + 1, q1 = q - 1 needs.
+struct GenPair {
+    int p, q, p1, q1, g, a1lo, wa1, b1lo, wb1;
+    int e0, ne, j0, nj;  // out-edges of layer p1, rows of layer q1
+};
 
-// One part of V_t(a, b) on a generic lattice, with the lanes of one wave (min over lanes).
-template <class IT>
-__device__ int64_t gen_closed_part(const IT& I, const SmallE& S, const EnergyTables* __restrict__ E,
-                                   const int32_t* __restrict__ spec, int a, int b, int t, int p, int q,
-                                   int part, int lane) {
-    const int g = q - p, s = I.shift;
-    const int a1 = I.out_dst()[a * 4 + kTX[t]];
-    const int64_t Ua = I.out_U()[a * 4 + kTX[t]];
-    const int y = kTY[t];
-    const int ib0 = I.in_start()[b], ib1 = I.in_start()[b + 1];
-    int64_t v = kINF;
-    if (part == 0) {
-        const int m = g - 2;
-        if (m == 3 || m == 4 || m == 6) {
-            v = hairpin_lane(I, S, spec, a, b, t, a1, Ua, p, g, lane);  // path enumeration only
-        } else if (m >= 5) {
-            // a -x-> a1 -x2-> a2 ~~> b2 -z-> b1 -y-> b: lanes over (x2, in-edge of b1)
-            for (int eb = ib0; eb < ib1; eb++) {
-                if (I.in_lab()[eb] != y) continue;
-                const int b1 = I.in_src()[eb];
-                const int j0 = I.in_start()[b1], nj = I.in_start()[b1 + 1] - j0;
-                for (int k = lane; k < 4 * nj; k += 64) {
-                    const int x2 = k & 3, j = j0 + (k >> 2);
-                    const int a2 = I.out_dst()[a1 * 4 + x2];
-                    if (a2 < 0) continue;
-                    const int64_t gg = gen_gap(I, a2, p + 2, I.in_src()[j], q - 2);
-                    if (gg >= kINF) continue;
-                    v = mn(v, Ua + I.out_U()[a1 * 4 + x2] + gg + I.in_U()[j] + I.in_U()[eb] +
-                                  fx(I.hp_init()[m] + S.mmH[t][x2][I.in_lab()[j]], s));
-                }
-            }
+// T(e, j) of classes 1xn and 2x3, by one wave.
+__device__ __forceinline__ void gen_thin(const Inst& I, const SmallE& S, const GenPair& P, int e, int j, int64_t* w6, int lane) {
+    const GenEdgePtr E = (GenEdgePtr)(uintptr_t)I.gedges();
+    const GenRowPtr R = (GenRowPtr)(uintptr_t)I.grows();
+    const IntPtr eo = (IntPtr)(uintptr_t)I.geoff(), io = (IntPtr)(uintptr_t)I.groff(), re = (IntPtr)(uintptr_t)I.growedge();
+    const int s = I.shift, g1 = P.g - 2, win = I.win;
+    const int64_t* LG = I.LG();
+    const int64_t* LGj = LG + R[j].lgbase;
+    const int64_t* IN2 = I.IN() + 2 * (int64_t)I.nil * win;
+    const int64_t* IN1 = I.IN() + (int64_t)I.nil * win;
+    int64_t c2 = kHalfINF, c1 = kHalfINF;
+    if (g1 >= 9) {
+        // l1 = 1, l2 = 3..29: the inner left state is e's target
+        const int f0 = eo[max(P.q1 - 29, P.p1 + 6)], f1 = eo[P.q1 - 2];
+        const int64_t* inr = IN2 + (int64_t)E[e].row * win;
+        const int64_t Ue = E[e].U;
+        const int col0 = f0 % win;
+        for (int k = lane; k < f1 - f0; k += 64) {
+            const int f = f0 + k, l2 = P.q1 - I.gedges()[f].layer;
+            int col = col0 + k;
+            col -= col >= win ? win : 0;
+            c2 = mn(c2, inr[col] + Ue + LGj[f] + fx(interior_base(S, 1, l2), s));
         }
-        if (g >= 7) {
-            // stack (item 0), left bulges (inner c of layer p+1+l, d = b1), right bulges (c = a1,
-            // inner d of layer q-1-l); inner span >= 5 and l <= 30
-            const int cl_hi = min(p + 31, q - 6), dl_lo = max(q - 31, p + 6);
-            const int c0 = I.off()[p + 2], c1 = cl_hi >= p + 2 ? I.off()[cl_hi + 1] : c0;
-            const int d1 = I.off()[q - 1], d0 = dl_lo <= q - 2 ? I.off()[dl_lo] : d1;
-            const int nc = c1 - c0, nd = d1 - d0;
-            for (int eb = ib0; eb < ib1; eb++) {
-                if (I.in_lab()[eb] != y) continue;
-                const int b1 = I.in_src()[eb];
-                const int64_t Uab = Ua + I.in_U()[eb];
-                for (int k = lane; k < 1 + nc + nd; k += 64) {
-                    int c = a1, d = b1, lc = p + 1, l = 0;
-                    int64_t gl = 0;
-                    if (k >= 1 && k <= nc) {
-                        c = c0 + k - 1;
-                        lc = I.layer()[c];
-                        l = lc - (p + 1);
-                        gl = gen_gap(I, a1, p + 1, c, lc);
-                    } else if (k > nc) {
-                        d = d0 + k - 1 - nc;
-                        const int ld = I.layer()[d];
-                        l = (q - 1) - ld;
-                        gl = gen_gap(I, d, ld, b1, q - 1);
-                    }
-                    if (gl >= kINF) continue;
-                    const int64_t* vv = I.V() + (I.rowoff()[c] - I.off()[lc + 1] + d) * 6;
-#pragma unroll
-                    for (int tp = 0; tp < 6; tp++) {
-                        const int64_t vin = vv[tp];
-                        if (vin >= kINF) continue;
-                        const int32_t e2 = l == 0 ? S.stack[t][kRev[tp]] : bulge_e(S, t, kRev[tp], l);
-                        v = mn(v, Uab + gl + vin + fx(e2, s));
-                    }
-                }
+        // l2 = 1, l1 = 3..29: the inner right states are the sources of row j's edges
+        const int i0 = io[P.p1 + 3], i1 = io[min(P.p1 + 29, P.q1 - 6) + 1];
+        for (int i = i0 + lane; i < i1; i += 64) {
+            const GenRow& row = I.grows()[i];
+            const int l1 = row.layer - P.p1;
+            int64_t r = kHalfINF;
+            for (int m = 0; m < R[j].cnt; m++) {
+                const int f = re[R[j].first + m];
+                r = mn(r, IN2[(int64_t)i * win + f % win] + E[f].U);
             }
-        }
-        if (g >= 12) {
-            // multiloop closure (ML_closing + ML_intern + AU) + S2 of the interior
-            const int32_t mlc = S.ml_closing + S.ml_intern + au_pen(S, t);
-            for (int eb = ib0 + lane; eb < ib1; eb += 64) {
-                if (I.in_lab()[eb] != y) continue;
-                const int b1 = I.in_src()[eb];
-                if (I.layer()[b1] - (p + 1) < 10) continue;
-                v = mn(v, I.S2()[cell_of(I, a1, b1)] + Ua + I.in_U()[eb] + fx(mlc, s));
-            }
-        }
-    } else if (g >= 9) {
-        // interior loops with l1 = part (29 parts cover every l1): the inner left state c runs
-        // over the layer of l1, the lanes over every inner right state d with 1 <= l2 <= 30 - l1
-        // and inner span >= 5 (one contiguous state range).  Pairs of the class that dominates
-        // the row (1xn for l1 = 1, generic otherwise) take the pre-reduced form; 1x1/1x2/2x2,
-        // 2x3 and 1xn with l1 > 1 the full one.
-        for (int eb = ib0; eb < ib1; eb++) {
-            if (I.in_lab()[eb] != y) continue;
-            const int b1 = I.in_src()[eb];
-            const int64_t Uab = Ua + I.in_U()[eb];
-            for (int l1 = part; l1 <= kGenLoopWin - 1; l1 += kGenParts - 1) {
-                const int lc = p + 1 + l1;
-                const int dl_lo = max(q - 1 - (kGenLoopWin - l1), lc + 5), dl_hi = q - 2;
-                if (dl_lo > dl_hi) break;
-                const int d0 = I.off()[dl_lo], d1 = I.off()[dl_hi + 1];
-                const int Xc = l1 == 1 ? 2 : 0;
-                for (int c = I.off()[lc]; c < I.off()[lc + 1]; c++) {
-                    const int64_t* lgl = gen_lg(I, a1, p + 1, c);
-                    const int64_t crow = I.rowoff()[c] - I.off()[lc + 1];
-                    int64_t A[16];
-                    bool anyA = false;
-#pragma unroll
-                    for (int k = 0; k < 16; k++) {
-                        const int xk = k >> 2, xj = k & 3;
-                        int64_t acc = kINF;
-#pragma unroll
-                        for (int xi = 0; xi < 4; xi++) {
-                            const int64_t l = lgl[xi * 4 + xk];
-                            if (l < kINF) acc = mn(acc, l + fx(mmx(S, Xc, t, xi, xj), s));
-                        }
-                        A[k] = acc;
-                        anyA = anyA || acc < kINF;
-                    }
-                    if (!anyA) continue;  // no path a1 -> c of l1 edges
-                    for (int d = d0 + lane; d < d1; d += 64) {
-                        const int64_t* vv = I.V() + (crow + d) * 6;
-                        int64_t vin[6];
-                        bool any = false;
-#pragma unroll
-                        for (int tp = 0; tp < 6; tp++) {
-                            vin[tp] = vv[tp];
-                            any = any || vin[tp] < kINF;
-                        }
-                        if (!any) continue;
-                        const int ld = I.layer()[d], l2 = q - 1 - ld;
-                        const int64_t* lgr = gen_lg(I, d, ld, b1);
-                        const bool fast = !(l1 <= 2 && l2 <= 2) && mm_class(l1, l2) == Xc;
-                        const int64_t w = fast ? gen_interior_fast(S, Xc, A, lgr, vin, l1, l2, s)
-                                               : gen_interior(S, E, t, l1, l2, lgl, lgr, vin, s);
-                        if (w < kINF) v = mn(v, Uab + w);
-                    }
-                }
-            }
+            c2 = mn(c2, r + LG[row.lgbase + e] + fx(interior_base(S, l1, 1), s));
         }
     }
-    return norm_inf(wave_min(v));
+    if (g1 >= 10) {
+#pragma unroll 1
+        for (int l1 = 2; l1 <= 3; l1++) {
+            const int l2 = 5 - l1, i0 = io[P.p1 + l1], ni = io[P.p1 + l1 + 1] - i0;
+            const int f0 = eo[P.q1 - l2], nf = eo[P.q1 - l2 + 1] - f0;
+            for (int k = lane; k < ni * nf; k += 64) {
+                const int i = i0 + k / nf, f = f0 + k % nf;
+                c1 = mn(c1, mn(LG[I.grows()[i].lgbase + e], kHalfINF) + IN1[(int64_t)i * win + f % win] + mn(LGj[f], kHalfINF));
+            }
+        }
+        c1 += fx(interior_base(S, 2, 3), s);
+    }
+    c2 = wave_min(c2);
+    c1 = wave_min(c1);
+    if (lane < 6) {
+        const int xi = E[e].lab, xj = R[j].lab;
+        gen_min(w6 + lane, mn(c2 + fx(S.mm1n[lane][xi][xj], s), c1 + fx(S.mm23[lane][xi][xj], s)));
+    }
 }
 
-template <int NW, class IT>
-__device__ GroupCounters gen_span_group(const IT& I, const SmallE& S, const EnergyTables* __restrict__ E,
-                                        const int32_t* __restrict__ spec, int p, int q, GenShared& G) {
-    const int g = q - p, s = I.shift;
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, nw = blockDim.x >> 6;
+// Hairpins of listless sizes, bulges of two bases and more, and the multiloop around (a1, b1), by one wave.
+__device__ __forceinline__ void gen_around(const Inst& I, const SmallE& S, const GenPair& P, int a1, int b1, int64_t* w6, int lane) {
+    const IntPtr off = (IntPtr)(uintptr_t)I.off();
+    const int s = I.shift, g1 = P.g - 2, m = g1;
+    if (m == 5 || m >= 7) {
+        // a1 -x2-> a2 ~~> b2 -z-> b1: lanes over (x2, in-edge of b1)
+        const int j0 = I.in_start()[b1], nj = I.in_start()[b1 + 1] - j0;
+        for (int k = lane; k < 4 * nj; k += 64) {
+            const int x2 = k & 3, j = j0 + (k >> 2), a2 = I.out_dst()[a1 * 4 + x2];
+            if (a2 < 0) continue;
+            const int64_t gg = I.Gt()[I.rowoff()[a2] + (I.in_src()[j] - off[P.p1 + 2])];
+            if (gg >= kINF) continue;
+            const int64_t h = I.out_U()[a1 * 4 + x2] + gg + I.in_U()[j] + fx(I.hp_init()[m], s);
+            const int z = I.in_lab()[j];
+#pragma unroll
+            for (int t = 0; t < 6; t++) gen_min(w6 + t, h + fx(S.mmH[t][x2][z], s));
+        }
+    }
+    if (g1 >= 7) {
+        int64_t v = kHalfINF;
+        const int64_t arow = I.rowoff()[a1] - off[P.p1 + 1];
+        const int mi = S.ml_intern;
+        const int c0 = off[P.p1 + 2], c1 = off[min(P.p1 + 30, P.q1 - 5) + 1];
+        for (int c = c0 + lane; c < c1; c += 64) {
+            const int lc = I.layer()[c];
+            const int64_t x = mn(I.Gt()[arow + c], kHalfINF) + I.Bt()[I.rowoff()[c] + (b1 - I.off()[lc + 1])];
+            v = mn(v, x + fx(S.bulge[lc - P.p1] - mi, s));
+        }
+        const int d0 = off[max(P.q1 - 30, P.p1 + 5)], d1 = off[P.q1 - 1];
+        for (int d = d0 + lane; d < d1; d += 64) {
+            const int ld = I.layer()[d];
+            const int64_t x = mn(I.Gt()[I.rowoff()[d] + (b1 - I.off()[ld + 1])], kHalfINF) + I.Bt()[arow + d];
+            v = mn(v, x + fx(S.bulge[P.q1 - ld] - mi, s));
+        }
+        v = wave_min(v);
+        if (lane < 6) gen_min(w6 + lane, v + fx(au_pen(S, lane), s));
+    }
+    if (g1 >= 10 && lane < 6)
+        gen_min(w6 + lane, I.S2()[I.rowoff()[a1] + (b1 - off[P.p1 + 1])] + fx(S.ml_closing + S.ml_intern + au_pen(S, lane), s));
+}
+
+// Stacks, bulges of one base and the loops of the 1x1, 1x2, 2x2 tables: one (left walk, right walk,
+// closing type) per thread.  Walks of 0, 1, 2 edges: states, out-edges, entries of the walk list.
+__device__ __forceinline__ void gen_small(const Inst& I, const SmallE& S, const GenPair& P, int64_t* w, int tid, int nt) {
+    const IntPtr eo = (IntPtr)(uintptr_t)I.geoff(), wo = (IntPtr)(uintptr_t)I.gwoff();
+    const int s = I.shift, g1 = P.g - 2;
+    int nl[3], nr[3], cum[7], total = 0;
+    nl[0] = P.wa1;
+    nl[1] = P.ne;
+    const int lw = wo[P.p1];
+    nl[2] = wo[P.p1 + 1] - lw;
+    nr[0] = P.wb1;
+    const int rf = eo[P.q1 - 1];
+    nr[1] = eo[P.q1] - rf;
+    const int rw = wo[P.q1 - 2];
+    nr[2] = wo[P.q1 - 1] - rw;
+#pragma unroll
+    for (int k = 0; k < 7; k++) {
+        constexpr int L1[7] = {0, 0, 1, 1, 1, 2, 2}, L2[7] = {0, 1, 0, 1, 2, 1, 2};
+        cum[k] = total;
+        if (g1 - L1[k] - L2[k] >= 5) total += nl[L1[k]] * nr[L2[k]];
+    }
+    for (int it = tid; it < 6 * total; it += nt) {
+        const int t = it % 6, k = it / 6;
+        int cls = 0, base = 0;
+#pragma unroll
+        for (int c = 1; c < 7; c++)
+            if (k >= cum[c]) {
+                cls = c;
+                base = cum[c];
+            }
+        const int l1 = cls < 2 ? 0 : cls < 5 ? 1 : 2, l2 = cls == 0 || cls == 2 ? 0 : cls == 1 || cls == 3 || cls == 5 ? 1 : 2;
+        const int n2 = l2 == 0 ? nr[0] : l2 == 1 ? nr[1] : nr[2], kl = (k - base) / n2, kr = (k - base) - kl * n2;
+        int a1 = P.a1lo + kl, c = a1, xi = 0, xk = 0, d = P.b1lo + kr, b1 = d, xl = 0, xj = 0;
+        int64_t U = 0;
+        if (l1 > 0) {
+            const GenEdge& e = l1 == 1 ? I.gedges()[P.e0 + kl] : I.gwalks()[lw + kl];
+            a1 = e.src;
+            c = e.dst;
+            xi = e.lab & 3;
+            xk = e.lab >> 2;
+            U = e.U;
+            if (l1 == 1) xk = xi;
+        }
+        if (l2 > 0) {
+            const GenEdge& e = l2 == 1 ? I.gedges()[rf + kr] : I.gwalks()[rw + kr];
+            d = e.src;
+            b1 = e.dst;
+            xl = e.lab & 3;
+            xj = e.lab >> 2;
+            U += e.U;
+            if (l2 == 1) xj = xl;
+        }
+        const int64_t* vv = I.V() + (I.rowoff()[c] + (d - I.off()[P.p1 + l1 + 1])) * 6;
+        int64_t best = kINF;
+#pragma unroll
+        for (int tp = 0; tp < 6; tp++) {
+            const int tr = type_rev(tp);
+            const int32_t e2 = l1 + l2 == 0 ? S.stack[t][tr]
+                               : l1 * l2 == 0 ? bulge_e(S, t, tr, 1) : interior_e(S, nullptr, t, tr, l1, l2, xi, xk, xl, xj);
+            best = mn(best, vv[tp] + fx(e2, s));
+        }
+        gen_min(w + ((a1 - P.a1lo) * P.wb1 + (b1 - P.b1lo)) * 6 + t, best + U);
+    }
+}
+
+// Interior loops with both sides of two bases or more except 2x2 and 2x3: the two products.  Rounds of
+// up to kGenTasks accumulator sets; a set's rows are dealt to the waves that share it.  `rest` is the other
+// work of the step, done by each wave between its share of the first round's left product and the barrier.
+template <class F>
+__device__ __forceinline__ void gen_products(const Inst& I, const SmallE& S, const GenPair& P, GenShared& G, int wave, int nw,
+                                             int lane, F rest) {
+    const GenEdgePtr E = (GenEdgePtr)(uintptr_t)I.gedges();
+    const GenRowPtr R = (GenRowPtr)(uintptr_t)I.grows();
+    const IntPtr eo = (IntPtr)(uintptr_t)I.geoff(), io = (IntPtr)(uintptr_t)I.groff();
+    const LongPtr LG4 = (LongPtr)(uintptr_t)I.LG();
+    const int s = I.shift, g1 = P.g - 2, win = I.win, smax = min(kGenLoopWin, g1 - 5);
+    // right edges with l2 = 2..28, rows with l1 = 2..28, inner span >= 5
+    const int f0 = g1 >= 9 ? eo[max(P.q1 - 28, P.p1 + 7)] : 0, f1 = g1 >= 9 ? eo[P.q1 - 1] : 0;
+    const int i0 = g1 >= 9 ? io[P.p1 + 2] : 0, i1 = g1 >= 9 ? io[min(P.p1 + 28, P.q1 - 7) + 1] : 0;
+    const int nblk = (f1 - f0 + 63) / 64, ngrp = (P.ne + kGenGroup - 1) / kGenGroup;
+    const int rb = min(nblk, kGenTasks), rg = rb ? kGenTasks / rb : 1;  // blocks and edge groups per round
+    bool first = true;
+    for (int grp0 = 0; grp0 < ngrp || first; grp0 += rg)
+        for (int blk0 = 0; blk0 < nblk || first; blk0 += rb) {
+            const int cb = min(rb, nblk - blk0), cg = min(rg, ngrp - grp0), ntask = g1 >= 11 ? cb * cg : 0;
+            if (!first) {
+                for (int k = wave * 64 + lane; k < kGenTasks * kGenGroup * 64; k += nw * 64) (&G.q[0][0][0])[k] = kHalfINF;
+                __syncthreads();
+            }
+            const int share = ntask ? max(1, nw / ntask) : 1;  // waves per set
+            for (int k = wave; k < ntask * share; k += nw) {
+                const int task = k % ntask, part = k / ntask, e = P.e0 + (grp0 + task / cb) * kGenGroup;
+                const int f = min(f0 + (blk0 + task % cb) * 64 + lane, f1 - 1);
+                const int l2 = P.q1 - I.gedges()[f].layer, col = f % win;
+                const int64_t* IN0 = I.IN() + col;
+                int64_t acc[kGenGroup];
+#pragma unroll
+                for (int x = 0; x < kGenGroup; x++) acc[x] = kHalfINF;
+#pragma unroll 4
+                for (int i = i0 + part; i < i1; i += share) {
+                    const int l1 = R[i].layer - P.p1, sum = l1 + l2;
+                    const LongPtr lg = LG4 + (R[i].lgbase + e);
+                    const int64_t in = IN0[(int64_t)i * win];
+                    const int dd = l1 > l2 ? l1 - l2 : l2 - l1;
+                    const int32_t base = S.interior[min(sum, kGenLoopWin)] + min(S.ninio * dd, S.ninio_max);
+                    const int64_t x = sum >= 6 && sum <= smax ? in + fx(base, s) : kHalfINF;
+#pragma unroll
+                    for (int y = 0; y < kGenGroup; y++) acc[y] = mn(acc[y], lg[y] + x);
+                }
+#pragma unroll
+                for (int y = 0; y < kGenGroup; y++) gen_min(&G.q[task][y][lane], acc[y]);
+            }
+            if (first) rest();
+            first = false;
+            __syncthreads();
+            const int items = ntask ? min(cg * kGenGroup, P.ne - grp0 * kGenGroup) * P.nj : 0;
+            for (int it = wave; it < items; it += nw) {
+                const int k = it / P.nj, j = P.j0 + it % P.nj, e = P.e0 + grp0 * kGenGroup + k;
+                const int64_t* LGj = I.LG() + R[j].lgbase;
+                int64_t v = kHalfINF;
+                for (int b = 0; b < cb; b++) {
+                    const int f = f0 + (blk0 + b) * 64 + lane;
+                    if (f < f1) v = mn(v, G.q[(k / kGenGroup) * cb + b][k % kGenGroup][lane] + LGj[f]);
+                }
+                v = wave_min(v);
+                const int xi = E[e].lab, xj = R[j].lab;
+                if (lane < 6)
+                    gen_min(G.w + ((E[e].src - P.a1lo) * P.wb1 + (R[j].state - P.b1lo)) * 6 + lane,
+                            v + fx(S.mmI[lane][xi][xj], s));
+            }
+            __syncthreads();
+        }
+}
+
+// One layer pair of span step g by one workgroup.  Between the first barriers every wave takes its share
+// of the tasks that read only earlier spans; then typed values, cells and the tables of the span.
+template <int NT>
+__device__ __forceinline__ void gen_span_group(const Inst& I, const SmallE& S, const int32_t* __restrict__ spec, int p, int q,
+                                               GenShared& G) {
+    const int g = q - p, s = I.shift, tid = threadIdx.x, lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    constexpr int NW = NT / 64;
+    const IntPtr off = (IntPtr)(uintptr_t)I.off(), eo = (IntPtr)(uintptr_t)I.geoff(), io = (IntPtr)(uintptr_t)I.groff(),
+                 re = (IntPtr)(uintptr_t)I.growedge();
+    const GenEdgePtr E = (GenEdgePtr)(uintptr_t)I.gedges();
+    const GenRowPtr R = (GenRowPtr)(uintptr_t)I.grows();
+    const int a_lo = off[p], wa = off[p + 1] - a_lo, b_lo = off[q], wb = off[q + 1] - b_lo, ncell = wa * wb;
+    GenPair P;
+    P.p = p;
+    P.q = q;
+    P.p1 = p + 1;
+    P.q1 = q - 1;
+    P.g = g;
+    P.a1lo = off[p + 1];
+    P.wa1 = off[p + 2] - P.a1lo;  // off has n + 2 entries and p + 1 <= n
+    P.b1lo = off[q - 1];
+    P.wb1 = off[q] - P.b1lo;
+    P.e0 = eo[p + 1];
+    P.ne = eo[p + 2] - P.e0;
+    P.j0 = io[q - 1];
+    P.nj = io[q] - P.j0;
+    for (int k = tid; k < kGenMaxWidth * kGenMaxWidth * 6; k += NT) {
+        G.w[k] = kHalfINF;
+        G.v[k] = kINF;
+    }
+    for (int k = tid; k < kGenTasks * kGenGroup * 64; k += NT) (&G.q[0][0][0])[k] = kHalfINF;
     GroupCounters ctr{0, 0};
-    const int a_lo = I.off()[p], a_hi = I.off()[p + 1], b_lo = I.off()[q], b_hi = I.off()[q + 1];
-    const int wa = a_hi - a_lo, wb = b_hi - b_lo, ncell = wa * wb;
-    // gap tables of this span's cells (only later spans read them)
-    for (int ci = tid; ci < ncell; ci += blockDim.x) {
-        const int a = a_lo + ci / wb, b = b_lo + ci % wb;
-        int64_t gv = kINF;
-        for (int eb = I.in_start()[b]; eb < I.in_start()[b + 1]; eb++) {
-            const int bp = I.in_src()[eb];
-            const int64_t gp = g == 1 ? (bp == a ? 0 : kINF) : I.Gt()[cell_of(I, a, bp)];
-            if (gp < kINF) gv = mn(gv, gp + I.in_U()[eb]);
+    __syncthreads();
+    auto rest = [&]() {
+        const int nthin = g >= 11 ? P.ne * P.nj : 0, naround = g >= 5 ? P.wa1 * P.wb1 : 0;
+        const int nspec = g == 5 || g == 6 || g == 8 ? ncell * 6 : 0, ntask = nthin + naround + ncell + nspec;
+        for (int k0 = NW - 1 - wave; k0 < ntask; k0 += NW) {
+            int k = k0;
+            if (k < nthin) {
+                const int e = P.e0 + k / P.nj, j = P.j0 + k % P.nj;
+                gen_thin(I, S, P, e, j, G.w + ((E[e].src - P.a1lo) * P.wb1 + (R[j].state - P.b1lo)) * 6, lane);
+                continue;
+            }
+            k -= nthin;
+            if (k < ncell) {
+                const int a = a_lo + k / wb, b = b_lo + k % wb, committed = uni(I.ccnt()[b]);
+                int64_t s2, ps;
+                multiloop_scan(I, a, b, p, q, I.rowoff()[a] + (b - off[p + 1]), lane, committed, I.coff()[b], &s2, &ps);
+                if (lane == 0) {
+                    G.s2[k] = s2;
+                    G.ps[k] = ps;
+                    G.committed[k] = committed;
+                }
+                continue;
+            }
+            k -= ncell;
+            if (k < naround) {
+                gen_around(I, S, P, P.a1lo + k / P.wb1, P.b1lo + k % P.wb1, G.w + k * 6, lane);
+                continue;
+            }
+            // hairpins of 3, 4 and 6 bases, whose listed loops depend on the whole label path
+            k -= naround;
+            const int t = k % 6, ci = k / 6, a = a_lo + ci / wb, b = b_lo + ci % wb, a1 = I.out_dst()[a * 4 + type_x(t)];
+            if (a1 < 0) continue;
+            const int64_t v = wave_min(hairpin_lane(I, S, spec, a, b, t, a1, I.out_U()[a * 4 + type_x(t)], p, g, lane));
+            if (lane == 0) G.v[k] = v;
         }
-        I.Gt()[cell_of(I, a, b)] = gv;
-    }
-    if (g <= kGenLoopWin) {
-        for (int k = tid; k < ncell * 16; k += blockDim.x) {
-            const int ci = k >> 4, x = (k >> 2) & 3, yy = k & 3;
+        if (g >= 7) gen_small(I, S, P, G.w, tid, NT);
+        // gap table of this span's cells and labelled gaps (later spans read them)
+        for (int ci = tid; ci < ncell; ci += NT) {
             const int a = a_lo + ci / wb, b = b_lo + ci % wb;
-            const int u1 = I.out_dst()[a * 4 + x];
-            int64_t lv = kINF;
-            if (u1 >= 0) {
+            int64_t gv = kINF;
+            for (int eb = I.in_start()[b]; eb < I.in_start()[b + 1]; eb++) {
+                const int bp = I.in_src()[eb];
+                const int64_t gp = g == 1 ? (bp == a ? 0 : kINF) : I.Gt()[I.rowoff()[a] + (bp - off[p + 1])];
+                if (gp < kINF) gv = mn(gv, gp + I.in_U()[eb]);
+            }
+            I.Gt()[I.rowoff()[a] + (b - off[p + 1])] = gv;
+        }
+        if (g <= kGenLoopWin) {
+            const int f0 = eo[p], nf = eo[p + 1] - f0, i0 = io[q], ni = io[q + 1] - i0;
+            for (int k = tid; k < nf * ni; k += NT) {
+                const int f = f0 + k % nf, i = i0 + k / nf;
+                const GenEdge& e = I.gedges()[f];
+                const GenRow& row = I.grows()[i];
+                int64_t lv = kINF;
                 if (g == 1) {
-                    if (u1 == b && x == yy) lv = I.out_U()[a * 4 + x];
+                    if (e.row == i) lv = e.U;
                 } else {
-                    for (int eb = I.in_start()[b]; eb < I.in_start()[b + 1]; eb++) {
-                        if (I.in_lab()[eb] != yy) continue;
-                        const int v1 = I.in_src()[eb];
-                        const int64_t gg = g == 2 ? (u1 == v1 ? 0 : kINF) : I.Gt()[cell_of(I, u1, v1)];
-                        if (gg < kINF) lv = mn(lv, I.out_U()[a * 4 + x] + gg + I.in_U()[eb]);
+                    for (int m = 0; m < row.cnt; m++) {
+                        const GenEdge& l = I.gedges()[re[row.first + m]];
+                        const int64_t gg = g == 2 ? (e.dst == l.src ? 0 : kINF) : I.Gt()[I.rowoff()[e.dst] + (l.src - off[p + 2])];
+                        if (gg < kINF) lv = mn(lv, e.U + gg + l.U);
                     }
                 }
+                I.LG()[row.lgbase + f] = lv;
             }
-            I.LG()[((int64_t)a * I.gwin + (b - I.off()[p + 1])) * 16 + x * 4 + yy] = lv;
         }
-    }
-    // typed values of this span were filled by k_gen_closed
-    // branch value, S2 (eq. 7), P_S, S1 and the retention test, one cell per wave
-    for (int ci = wave; ci < ncell; ci += nw) {
-        const int a = a_lo + ci / wb, b = b_lo + ci % wb;
-        const int64_t cell = I.rowoff()[a] + (b - I.off()[p + 1]);
-        int64_t Bv = kINF;
-        {
-            const int64_t v = lane < 6 ? I.V()[cell * 6 + lane] : kINF;
-            if (v < kINF) Bv = v + fx(S.ml_intern + au_pen(S, lane), s);
-            Bv = wave_min(Bv);
+    };
+    gen_products(I, S, P, G, wave, NW, lane, rest);
+    // typed values, branch value, S1 and the retention test: eight lanes per cell, one per type
+    for (int k = tid; k < ncell * 8; k += NT) {
+        const int ci = k >> 3, t = k & 7, a = a_lo + ci / wb, b = b_lo + ci % wb;
+        const int64_t cell = I.rowoff()[a] + (b - off[p + 1]);
+        int64_t v = kINF, Bv = kINF;
+        if (t < 6) {
+            const int x = type_x(t), y = type_y(t), a1 = g >= 5 ? I.out_dst()[a * 4 + x] : -1;
+            if (a1 >= 0) {
+                for (int eb = I.in_start()[b]; eb < I.in_start()[b + 1]; eb++)
+                    if (I.in_lab()[eb] == y)
+                        v = mn(v, G.w[((a1 - P.a1lo) * P.wb1 + (I.in_src()[eb] - P.b1lo)) * 6 + t] + I.in_U()[eb]);
+                v = mn(v + I.out_U()[a * 4 + x], G.v[ci * 6 + t]);
+                if (v >= kGenBig) v = kINF;
+            }
+            I.V()[cell * 6 + t] = v;
+            if (v < kINF) Bv = v + fx(S.ml_intern + au_pen(S, t), s);
         }
-        const int keep = multiloop_cell(I, a, b, p, q, cell, Bv, lane, ctr);
-        if (lane == 0) {
-            G.keep[ci] = keep;
+        Bv = mn(Bv, shfl_xor64(Bv, 1));
+        Bv = mn(Bv, shfl_xor64(Bv, 2));
+        Bv = mn(Bv, shfl_xor64(Bv, 4));
+        if (t < 6) G.v[ci * 6 + t] = v;
+        if (t == 0) {
+            const int64_t ps = G.ps[ci];
+            I.Bt()[cell] = Bv;
+            I.S2()[cell] = G.s2[ci];
+            I.S1()[cell] = mn(Bv, ps);
+            const bool strict = Bv < ps;
+            G.keep[ci] = I.retain_all ? (Bv < kINF ? (strict ? 1 : 2) : 0) : (strict ? 1 : 0);
             G.cellB[ci] = Bv;
         }
     }
     __syncthreads();
-    // appends in start-state order, one lane per right endpoint
     if (wave == 0) {
+        // appends in start-state order, one lane per right endpoint; candidates visited, feasible cells
         append_candidates(I, a_lo, wa, b_lo, wb, G.keep, G.cellB, g, lane);
+        for (int ci = lane; ci < ncell; ci += 64) {
+            ctr.visits += (unsigned long long)G.committed[ci];
+            ctr.feasible += G.cellB[ci] < kINF;
+        }
+        if (ctr.visits) atomicAdd(&I.visits()[p], ctr.visits);
+        if (ctr.feasible) atomicAdd(&I.feasible()[p], ctr.feasible);
     }
-    return ctr;
-}
-
-// typed closed values of span g on a generic lattice: every wave draws (job, part) tickets of the
-// span's job list (host-built: cells and types that can close) and folds its part into V with an
-// atomic minimum (V starts at infinity, set by k_init).  Occupancy is hinted to 3 waves per SIMD
-// (168 VGPRs, a few spilled): 11 % faster on a 300-aa design than the unhinted 2 waves; 4 waves
-// spill too much.
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_gen_closed(Inst I, const EnergyTables* __restrict__ E,
-                                                    const int32_t* __restrict__ spec, int g) {
-    __shared__ SmallE S;
-    stage_tables(S, E);
-    const int lane = threadIdx.x & 63;
-    const int64_t j0 = I.gjob_off()[g], total = (I.gjob_off()[g + 1] - j0) * kGenParts;
-    for (;;) {
-        unsigned k = 0;
-        if (lane == 0) k = atomicAdd(&I.gtickets()[g], 1u);
-        k = __shfl(k, 0, 64);
-        if ((int64_t)k >= total) break;
-        const int64_t j = j0 + k / kGenParts;
-        const int a = I.gjobs()[2 * j], bt = I.gjobs()[2 * j + 1], b = bt >> 3, t = bt & 7;
-        const int64_t v = gen_closed_part(I, S, E, spec, a, b, t, I.layer()[a], I.layer()[b], (int)(k % kGenParts), lane);
-        if (lane == 0 && v < kINF)
-            __hip_atomic_fetch_min(&I.V()[cell_of(I, a, b) * 6 + t], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (g >= 5) {
+        // the inner parts of interior loops around this span's cells, per class, row of a, out-edge of b
+        const int f0 = eo[q], nf = eo[q + 1] - f0, i0 = io[p], ni = io[p + 1] - i0, tot = nf * ni;
+        for (int k = tid; k < 3 * tot; k += NT) {
+            const int X = k / tot, r = k - X * tot, f = f0 + r % nf, i = i0 + r / nf;
+            const GenEdge& e = I.gedges()[f];
+            const GenRow& row = I.grows()[i];
+            const int64_t* vv = G.v + ((row.state - a_lo) * wb + (e.src - b_lo)) * 6;
+            int64_t v = kINF;
+#pragma unroll
+            for (int tp = 0; tp < 6; tp++) v = mn(v, vv[tp] + fx(mmx(S, X, type_rev(tp), e.lab, row.lab), s));
+            I.IN()[((int64_t)X * I.nil + i) * I.win + f % I.win] = v >= kGenBig ? kHalfINF : v;
+        }
     }
 }
 
 // span step on a generic lattice: layer pair xcd_band(x) for block x < layer pairs, then the
 // external column one layer behind
-__global__ __launch_bounds__(256) void k_span_gen(Inst I, const EnergyTables* __restrict__ E,
-                                                  const int32_t* __restrict__ spec, int g,
-                                                  int ext_layer, int nblk_cells) {
+template <int NT>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_span_gen(
+    Inst I, const EnergyTables* __restrict__ E, const int32_t* __restrict__ spec, int g, int ext_layer, int npairs) {
     __shared__ SmallE S;
-    __shared__ GroupShared X[4];
-    __shared__ GenShared G;
+    __shared__ union {
+        GenShared g;
+        GroupShared x[NT / 64];
+    } G;
     stage_tables(S, E);
-    if ((int)blockIdx.x >= nblk_cells) {
+    if ((int)blockIdx.x >= npairs) {
         BlockTeam T;
-        if (ext_layer >= 0) ext_column(I, S, ext_layer, X, T);
+        if (ext_layer >= 0) ext_column(I, S, ext_layer, G.x, T);
         return;
     }
-    const int p = xcd_band(blockIdx.x, nblk_cells), q = p + g;
-    GroupCounters c = gen_span_group<4>(I, S, E, spec, p, q, G);
-    flush_counters(I, c, p, threadIdx.x & 63);
+    const int p = xcd_band(blockIdx.x, npairs);
+    gen_span_group<NT>(rebased(I), S, spec, p, p + g, G.g);
 }
 
 // ---- batched persistent kernel ------------------------------------------------------------------
@@ -1766,12 +1859,7 @@ hipError_t launch_span_gen(const Inst& I, const EnergyTables* E, const int32_t* 
     const int nblk = layers > 0 ? layers : 0;
     const int total = nblk + (ext_layer >= 0 ? 1 : 0);
     if (total == 0) return hipSuccess;
-    if (g >= 5 && nblk > 0) {
-        hipLaunchKernelGGL(k_gen_closed, dim3(4 * num_cu), dim3(256), 0, st, I, E, spec, g);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    hipLaunchKernelGGL(k_span_gen, dim3(total), dim3(256), 0, st, I, E, spec, g, ext_layer, nblk);
+    hipLaunchKernelGGL(k_span_gen<512>, dim3(total), dim3(512), 0, st, I, E, spec, g, ext_layer, nblk);
     return hipGetLastError();
 }
 

@@ -624,6 +624,76 @@ int build_lattice(const char* protein, const CodonTable& T, const Params& P, dou
     return SD_OK;
 }
 
+// Edge, walk and row lists of a generic lattice, and the extents of its LG and IN tables.
+static void build_generic_tables(Lattice& L) {
+    const int n = L.n, N = L.N;
+    std::vector<int> row4((size_t)4 * N, -1), first_edge((size_t)4 * N, -1);
+    L.goff.assign(3 * (size_t)(n + 2), 0);
+    int* eo = L.goff.data();
+    int* io = eo + n + 2;
+    int* wo = io + n + 2;
+    for (int l = 0; l <= n; l++) {
+        io[l] = (int)L.grows.size();
+        for (int v = L.off[l]; v < L.off[l + 1]; v++)
+            for (int y = 0; y < 4; y++) {
+                if (!((L.inmask[v] >> y) & 1)) continue;
+                row4[(size_t)4 * v + y] = (int)L.grows.size();
+                L.grows.push_back(GenRow{v, y, l, 0, 0, 0, 0});
+            }
+    }
+    io[n + 1] = (int)L.grows.size();
+    for (int l = 0; l <= n; l++) {
+        eo[l] = (int)L.gedges.size();
+        for (int u = L.off[l]; u < L.off[l + 1]; u++)
+            for (int x = 0; x < 4; x++) {
+                const int d = L.out_dst[(size_t)4 * u + x];
+                if (d < 0) continue;
+                first_edge[(size_t)4 * u + x] = (int)L.gedges.size();
+                const int r = row4[(size_t)4 * d + x];
+                L.gedges.push_back(GenEdge{u, d, x, l, L.out_U[(size_t)4 * u + x], r, 0});
+                L.grows[r].cnt++;
+            }
+    }
+    eo[n + 1] = (int)L.gedges.size();
+    int at = 0;
+    for (GenRow& r : L.grows) {
+        r.first = at;
+        at += r.cnt;
+        r.cnt = 0;
+    }
+    L.growedge.assign(L.gedges.size(), 0);
+    for (size_t k = 0; k < L.gedges.size(); k++) {
+        GenRow& r = L.grows[L.gedges[k].row];
+        L.growedge[r.first + r.cnt++] = (int)k;
+    }
+    for (int l = 0; l <= n; l++) {
+        wo[l] = (int)L.gwalks.size();
+        for (int k = eo[l]; k < eo[l + 1]; k++) {
+            const GenEdge& e = L.gedges[k];
+            for (int x = 0; x < 4; x++) {
+                const int d = L.out_dst[(size_t)4 * e.dst + x];
+                if (d < 0) continue;
+                L.gwalks.push_back(GenEdge{e.src, d, e.lab | x << 2, l, e.U + L.out_U[(size_t)4 * e.dst + x],
+                                           row4[(size_t)4 * d + x], 0});
+            }
+        }
+    }
+    wo[n + 1] = (int)L.gwalks.size();
+    // a row's LG words: the edges of the kGenLoopWin layers before it, and three more that a group of
+    // four edges reaches past the last layer's end
+    int64_t words = 0;
+    for (GenRow& r : L.grows) {
+        const int lo = eo[std::max(r.layer - kGenLoopWin, 0)];
+        r.lgbase = words - lo;
+        words += eo[r.layer] - lo + 3;
+    }
+    L.lgsize = words;
+    // a span reads right layers down to kGenLoopWin + 2 behind the one it writes
+    L.win = 1;
+    for (int l = 0; l <= n; l++)
+        L.win = std::max(L.win, eo[std::min(l + kGenLoopWin + 3, n + 1)] - eo[l]);
+}
+
 // ------------------------------------------------------------------------------------------------
 // Forbidden motifs (Sec. 3): the codon trie intersected with a deterministic motif matcher.
 // Matcher states are the distinct motif prefixes (the empty one included), ranked by length and
@@ -764,27 +834,7 @@ int build_motif_lattice(const char* protein, const CodonTable& T, const Params& 
     L.P.assign(L.A + 1, 0);
     L.generic = true;
     L.motifs = motifs;
-    for (int p = 0; p <= n; p++)
-        L.gwin = std::max(L.gwin, L.off[std::min(p + 1 + kGenLoopWin, n + 1)] - L.off[std::min(p + 1, n + 1)]);
-    L.gwin = std::max(L.gwin, 1);
-    // typed-value jobs per span: (a, b, t) with an out-edge of a labelled t's 5' base, an in-edge
-    // of b labelled its 3' base and span >= 5 (no other type can close the cell)
-    L.gjob_off.assign(n + 2, 0);
-    L.gjobs.clear();
-    for (int g = 0; g <= n; g++) {
-        L.gjob_off[g] = (int64_t)L.gjobs.size() / 2;
-        if (g < 5) continue;
-        for (int p = 0; p + g <= n; p++)
-            for (int a = L.off[p]; a < L.off[p + 1]; a++)
-                for (int b = L.off[p + g]; b < L.off[p + g + 1]; b++)
-                    for (int t = 0; t < 6; t++) {
-                        static const int tx[6] = {0, 1, 2, 2, 3, 3}, ty[6] = {3, 2, 1, 3, 0, 2};
-                        if (L.out_dst[(size_t)4 * a + tx[t]] < 0 || !((L.inmask[b] >> ty[t]) & 1)) continue;
-                        L.gjobs.push_back(a);
-                        L.gjobs.push_back(b * 8 + t);
-                    }
-    }
-    L.gjob_off[n + 1] = (int64_t)L.gjobs.size() / 2;
+    build_generic_tables(L);
     return SD_OK;
 }
 

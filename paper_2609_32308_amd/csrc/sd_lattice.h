@@ -45,10 +45,14 @@ struct Lattice {
     // generic lattice (codon automaton x forbidden-motif matcher): the kernels use gap tables
     // instead of the trie's closed form
     bool generic = false;
-    int gwin = 0, wmax = 0;
+    int wmax = 0;
     std::vector<std::string> motifs;
-    std::vector<int64_t> gjob_off;  // [n+2]: jobs of span g are [gjob_off[g], gjob_off[g+1])
-    std::vector<int32_t> gjobs;     // pairs (a, b*8 + type) of typed-value jobs
+    std::vector<GenEdge> gedges, gwalks;  // out-edges, walks of two edges
+    std::vector<GenRow> grows;
+    std::vector<int> growedge;
+    std::vector<int> goff;                // [3][n+2]: first edge, row and walk of every layer
+    int64_t lgsize = 0;
+    int win = 0;
 };
 
 // validation and construction; return sd_status values
