@@ -92,13 +92,17 @@ __device__ __forceinline__ int64_t readlane64(int64_t v, int l) {
     const int hi = __builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)v >> 32), l);
     return (int64_t)(((uint64_t)(uint32_t)hi << 32) | (uint64_t)(uint32_t)lo);
 }
-// minimum over the whole wave (every lane active): DPP within each row of 16 lanes, then the
-// four row minima on the scalar unit
-__device__ __forceinline__ int64_t wave_min(int64_t v) {
+// minimum over each row of 16 lanes (every lane of the wave active)
+__device__ __forceinline__ int64_t row_min(int64_t v) {
     v = mn(v, dpp64<kDppXor1>(v));
     v = mn(v, dpp64<kDppXor2>(v));
     v = mn(v, dpp64<kDppHalfMirror>(v));
-    v = mn(v, dpp64<kDppMirror>(v));
+    return mn(v, dpp64<kDppMirror>(v));
+}
+// minimum over the whole wave (every lane active): DPP within each row of 16 lanes, then the
+// four row minima on the scalar unit
+__device__ __forceinline__ int64_t wave_min(int64_t v) {
+    v = row_min(v);
     return mn(mn(readlane64(v, 0), readlane64(v, 16)), mn(readlane64(v, 32), readlane64(v, 48)));
 }
 

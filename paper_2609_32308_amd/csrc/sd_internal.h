@@ -178,6 +178,8 @@ struct Inst {
     __host__ __device__ const int* off() const { return (const int*)ua(1); }
     __host__ __device__ const int* in_start() const { return (const int*)ua(2); }
     __host__ __device__ const int64_t* tail() const { return (const int64_t*)ua(3); }
+    // generic lattices (which have no tail): cell(a, b) = rowbase[a] + b
+    __host__ __device__ const int64_t* rowbase() const { return tail(); }
     __host__ __device__ const int* pfx() const { return (const int*)ua(4); }
     __host__ __device__ const int64_t* P() const { return (const int64_t*)ua(5); }
     __host__ __device__ const int* hp_init() const { return (const int*)ua(6); }

@@ -66,7 +66,11 @@ __device__ int64_t hairpin_lane(const IT& I, const SmallE& S, const int32_t* __r
             int64_t c2 = cost;
             for (int i = nfree - 1; i >= 0; i--) {
                 const int lab = (k >> (2 * i)) & 3, e = st2 * 4 + lab, d = I.out_dst()[e];
-                if (d < 0) { ok = 0; break; }
+                if (d < 0) {  // no path spells these labels: on to the next label here
+                    ok = 0;
+                    k |= (1 << (2 * i)) - 1;
+                    break;
+                }
                 c2 += I.out_U()[e];
                 key2 = key2 * 4 + lab;
                 st2 = d;
@@ -1111,21 +1115,38 @@ __global__ void k_checksum(Inst I, int g, unsigned long long* out) {
 // Infinite operands: LG is kINF, IN and the accumulators kHalfINF, finite values lie within 2^60, so a
 // sum of all three neither overflows nor falls below kGenBig.
 constexpr int64_t kGenBig = kHalfINF >> 1;
-constexpr int kGenGroup = 4;   // left edges per accumulator set
-constexpr int kGenTasks = 8;   // (edge group, 64 right edges) accumulator sets per round
+constexpr int64_t kGenBias = kHalfINF >> 1;  // makes finite sums positive (see min_positive)
+constexpr int kGenGroup = 8;   // left edges per task
+constexpr int kGenRows = 16;   // rows per unit
+constexpr int kGenTasks = 16;  // (eight left edges, 64 right edges) per round
+
+// Minimum of two int64 in [2^52, 2^63 - 2^53): positive patterns of finite doubles order as the integers do,
+// so one instruction replaces a compare and two selects.
+__device__ __forceinline__ int64_t min_positive(int64_t a, int64_t b) {
+    int64_t r;
+    asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
 
 typedef const __attribute__((address_space(4))) GenEdge* GenEdgePtr;
 typedef const __attribute__((address_space(4))) GenRow* GenRowPtr;
 typedef const __attribute__((address_space(4))) int* IntPtr;
 typedef const __attribute__((address_space(4))) int64_t* LongPtr;
 
+// The states of an inner layer and the row base of its first state; every state's row has len cells.
+struct GenLayer {
+    int first, cnt;
+    int64_t row, len;
+};
 struct GenShared {
     int64_t w[kGenMaxWidth * kGenMaxWidth * 6];  // W_t(a1, b1)
     int64_t v[kGenMaxWidth * kGenMaxWidth * 6];  // hairpins of 3, 4, 6 bases, then V of the cells
     int64_t s2[kGenMaxWidth * kGenMaxWidth], ps[kGenMaxWidth * kGenMaxWidth], cellB[kGenMaxWidth * kGenMaxWidth];
     int committed[kGenMaxWidth * kGenMaxWidth];
     int8_t keep[kGenMaxWidth * kGenMaxWidth];
-    int64_t q[kGenTasks][kGenGroup][64];         // Q of one round
+    GenLayer left[kGenLoopWin + 1], right[kGenLoopWin + 1];  // layers p1 + l, q1 - l
+    int64_t size[kGenLoopWin][32];               // size(l1, l2) + kGenBias in fixed point
+    int64_t q[kGenTasks][64][kGenGroup + 1];     // Q + kGenBias of one round
 };
 
 // minimum into a shared word; values that hold an infinite operand are left out
@@ -1139,101 +1160,96 @@ struct GenPair {
     int e0, ne, j0, nj;  // out-edges of layer p1, rows of layer q1
 };
 
-// T(e, j) of classes 1xn and 2x3, by one wave.
-__device__ __forceinline__ void gen_thin(const Inst& I, const SmallE& S, const GenPair& P, int e, int j, int64_t* w6, int lane) {
-    const GenEdgePtr E = (GenEdgePtr)(uintptr_t)I.gedges();
-    const GenRowPtr R = (GenRowPtr)(uintptr_t)I.grows();
-    const IntPtr eo = (IntPtr)(uintptr_t)I.geoff(), io = (IntPtr)(uintptr_t)I.groff(), re = (IntPtr)(uintptr_t)I.growedge();
-    const int s = I.shift, g1 = P.g - 2, win = I.win;
-    const int64_t* LG = I.LG();
-    const int64_t* LGj = LG + R[j].lgbase;
-    const int64_t* IN2 = I.IN() + 2 * (int64_t)I.nil * win;
-    const int64_t* IN1 = I.IN() + (int64_t)I.nil * win;
-    int64_t c2 = kHalfINF, c1 = kHalfINF;
-    if (g1 >= 9) {
-        // l1 = 1, l2 = 3..29: the inner left state is e's target
-        const int f0 = eo[max(P.q1 - 29, P.p1 + 6)], f1 = eo[P.q1 - 2];
-        const int64_t* inr = IN2 + (int64_t)E[e].row * win;
-        const int64_t Ue = E[e].U;
-        const int col0 = f0 % win;
-        for (int k = lane; k < f1 - f0; k += 64) {
-            const int f = f0 + k, l2 = P.q1 - I.gedges()[f].layer;
-            int col = col0 + k;
-            col -= col >= win ? win : 0;
-            c2 = mn(c2, inr[col] + Ue + LGj[f] + fx(interior_base(S, 1, l2), s));
+// Bulges of two bases and more around every (a1, b1): one thread per (a1, b1, share of the sizes).  The branch
+// value of the inner pair holds the minimum over its types; the rows of a layer's states are equally long.
+__device__ __forceinline__ void gen_bulges(const Inst& I, const SmallE& S, const GenPair& P, GenShared& G, int tid, int nt) {
+    const int s = I.shift, outs = P.wa1 * P.wb1, parts = max(1, min(kGenLoopWin - 1, nt / outs));
+    const int lmax = min(kGenLoopWin, P.g - 7);
+    const int64_t* Gt = I.Gt();
+    const int64_t* Bt = I.Bt();
+    for (int k = tid; k < outs * parts; k += nt) {
+        const int ib = k % P.wb1, r = k / P.wb1, ia = r % P.wa1, part = r / P.wa1;
+        const int a1 = P.a1lo + ia, b1 = P.b1lo + ib;
+        const int64_t arow = I.rowbase()[a1];
+        int64_t v = kHalfINF;
+        for (int l = 2 + part; l <= lmax; l += parts) {
+            const GenLayer Lc = G.left[l], Ld = G.right[l];
+            int64_t w = kHalfINF;
+#pragma unroll 2
+            for (int i = 0; i < Lc.cnt; i++)
+                w = mn(w, mn(Gt[arow + Lc.first + i], kHalfINF) + Bt[Lc.row + (int64_t)i * Lc.len + b1]);
+#pragma unroll 2
+            for (int i = 0; i < Ld.cnt; i++)
+                w = mn(w, mn(Gt[Ld.row + (int64_t)i * Ld.len + b1], kHalfINF) + Bt[arow + Ld.first + i]);
+            v = mn(v, w + fx(S.bulge[l] - S.ml_intern, s));
         }
-        // l2 = 1, l1 = 3..29: the inner right states are the sources of row j's edges
-        const int i0 = io[P.p1 + 3], i1 = io[min(P.p1 + 29, P.q1 - 6) + 1];
-        for (int i = i0 + lane; i < i1; i += 64) {
-            const GenRow& row = I.grows()[i];
-            const int l1 = row.layer - P.p1;
-            int64_t r = kHalfINF;
-            for (int m = 0; m < R[j].cnt; m++) {
-                const int f = re[R[j].first + m];
-                r = mn(r, IN2[(int64_t)i * win + f % win] + E[f].U);
-            }
-            c2 = mn(c2, r + LG[row.lgbase + e] + fx(interior_base(S, l1, 1), s));
-        }
-    }
-    if (g1 >= 10) {
-#pragma unroll 1
-        for (int l1 = 2; l1 <= 3; l1++) {
-            const int l2 = 5 - l1, i0 = io[P.p1 + l1], ni = io[P.p1 + l1 + 1] - i0;
-            const int f0 = eo[P.q1 - l2], nf = eo[P.q1 - l2 + 1] - f0;
-            for (int k = lane; k < ni * nf; k += 64) {
-                const int i = i0 + k / nf, f = f0 + k % nf;
-                c1 = mn(c1, mn(LG[I.grows()[i].lgbase + e], kHalfINF) + IN1[(int64_t)i * win + f % win] + mn(LGj[f], kHalfINF));
-            }
-        }
-        c1 += fx(interior_base(S, 2, 3), s);
-    }
-    c2 = wave_min(c2);
-    c1 = wave_min(c1);
-    if (lane < 6) {
-        const int xi = E[e].lab, xj = R[j].lab;
-        gen_min(w6 + lane, mn(c2 + fx(S.mm1n[lane][xi][xj], s), c1 + fx(S.mm23[lane][xi][xj], s)));
+        if (v < kGenBig)
+#pragma unroll
+            for (int t = 0; t < 6; t++) gen_min(G.w + (ia * P.wb1 + ib) * 6 + t, v + fx(au_pen(S, t), s));
     }
 }
 
-// Hairpins of listless sizes, bulges of two bases and more, and the multiloop around (a1, b1), by one wave.
-__device__ __forceinline__ void gen_around(const Inst& I, const SmallE& S, const GenPair& P, int a1, int b1, int64_t* w6, int lane) {
-    const IntPtr off = (IntPtr)(uintptr_t)I.off();
-    const int s = I.shift, g1 = P.g - 2, m = g1;
+// Hairpins of listless sizes, one thread per (edge out of a1, edge into b1), and multiloops, one thread per
+// (a1, b1, type).
+__device__ __forceinline__ void gen_hairpins(const Inst& I, const SmallE& S, const GenPair& P, int64_t* w, int tid, int nt) {
+    const IntPtr eo = (IntPtr)(uintptr_t)I.geoff();
+    const int s = I.shift, m = P.g - 2;
     if (m == 5 || m >= 7) {
-        // a1 -x2-> a2 ~~> b2 -z-> b1: lanes over (x2, in-edge of b1)
-        const int j0 = I.in_start()[b1], nj = I.in_start()[b1 + 1] - j0;
-        for (int k = lane; k < 4 * nj; k += 64) {
-            const int x2 = k & 3, j = j0 + (k >> 2), a2 = I.out_dst()[a1 * 4 + x2];
-            if (a2 < 0) continue;
-            const int64_t gg = I.Gt()[I.rowoff()[a2] + (I.in_src()[j] - off[P.p1 + 2])];
+        const int f0 = eo[P.q1 - 1], nf = eo[P.q1] - f0;
+        const int64_t init = fx(I.hp_init()[m], s);
+        for (int k = tid; k < P.ne * nf; k += nt) {
+            const GenEdge& e = I.gedges()[P.e0 + k / nf];
+            const GenEdge& f = I.gedges()[f0 + k % nf];
+            const int64_t gg = I.Gt()[I.rowbase()[e.dst] + f.src];
             if (gg >= kINF) continue;
-            const int64_t h = I.out_U()[a1 * 4 + x2] + gg + I.in_U()[j] + fx(I.hp_init()[m], s);
-            const int z = I.in_lab()[j];
+            const int64_t h = e.U + gg + f.U + init;
+            int64_t* w6 = w + ((e.src - P.a1lo) * P.wb1 + (f.dst - P.b1lo)) * 6;
 #pragma unroll
-            for (int t = 0; t < 6; t++) gen_min(w6 + t, h + fx(S.mmH[t][x2][z], s));
+            for (int t = 0; t < 6; t++) gen_min(w6 + t, h + fx(S.mmH[t][e.lab][f.lab], s));
         }
     }
-    if (g1 >= 7) {
-        int64_t v = kHalfINF;
-        const int64_t arow = I.rowoff()[a1] - off[P.p1 + 1];
-        const int mi = S.ml_intern;
-        const int c0 = off[P.p1 + 2], c1 = off[min(P.p1 + 30, P.q1 - 5) + 1];
-        for (int c = c0 + lane; c < c1; c += 64) {
-            const int lc = I.layer()[c];
-            const int64_t x = mn(I.Gt()[arow + c], kHalfINF) + I.Bt()[I.rowoff()[c] + (b1 - I.off()[lc + 1])];
-            v = mn(v, x + fx(S.bulge[lc - P.p1] - mi, s));
+    if (m >= 10)
+        for (int k = tid; k < P.wa1 * P.wb1 * 6; k += nt) {
+            const int t = k % 6, r = k / 6, ia = r / P.wb1, ib = r - ia * P.wb1;
+            gen_min(w + k, I.S2()[I.rowbase()[P.a1lo + ia] + P.b1lo + ib] + fx(S.ml_closing + S.ml_intern + au_pen(S, t), s));
         }
-        const int d0 = off[max(P.q1 - 30, P.p1 + 5)], d1 = off[P.q1 - 1];
-        for (int d = d0 + lane; d < d1; d += 64) {
-            const int ld = I.layer()[d];
-            const int64_t x = mn(I.Gt()[I.rowoff()[d] + (b1 - I.off()[ld + 1])], kHalfINF) + I.Bt()[arow + d];
-            v = mn(v, x + fx(S.bulge[P.q1 - ld] - mi, s));
+}
+
+// The split part of cells (S2, P_S), sixteen lanes per cell: a wave takes four at once.
+__device__ __forceinline__ void gen_scan(const Inst& I, GenShared& G, int p, int q, int a, int b, int ci, bool valid, int lane) {
+    const int l16 = lane & 15;
+    int64_t s2 = kINF, ps = kINF;
+    int committed = 0;
+    if (valid) {
+        const int64_t arow = I.rowbase()[a], cbase = I.coff()[b];
+        const int64_t* S1r = I.S1() + arow;
+        const int64_t* S2r = I.S2() + arow;
+        committed = I.ccnt()[b];
+        if (q - p >= 2) {
+            const int j1 = I.in_start()[b + 1];
+            for (int j = I.in_start()[b] + l16; j < j1; j += 16) {
+                const int c = I.in_src()[j];
+                const int64_t u = I.in_U()[j] + I.mlbase_fx;
+                s2 = mn(s2, S2r[c] + u);
+                ps = mn(ps, S1r[c] + u);
+            }
+            if (l16 < 4) {
+                const int ap = I.out_dst()[a * 4 + l16];
+                if (ap >= 0) ps = mn(ps, I.S1()[I.rowbase()[ap] + b] + I.out_U()[a * 4 + l16] + I.mlbase_fx);
+            }
         }
-        v = wave_min(v);
-        if (lane < 6) gen_min(w6 + lane, v + fx(au_pen(S, lane), s));
+        const int* cc = I.cc() + cbase;
+        const int64_t* cB = I.cB() + cbase;
+#pragma unroll 4
+        for (int k = l16; k < committed; k += 16) s2 = mn(s2, S1r[cc[k] & 0x7fffffff] + cB[k]);
     }
-    if (g1 >= 10 && lane < 6)
-        gen_min(w6 + lane, I.S2()[I.rowoff()[a1] + (b1 - off[P.p1 + 1])] + fx(S.ml_closing + S.ml_intern + au_pen(S, lane), s));
+    s2 = norm_inf(row_min(s2));
+    ps = norm_inf(mn(s2, row_min(ps)));
+    if (valid && l16 == 0) {
+        G.s2[ci] = s2;
+        G.ps[ci] = ps;
+        G.committed[ci] = committed;
+    }
 }
 
 // Stacks, bulges of one base and the loops of the 1x1, 1x2, 2x2 tables: one (left walk, right walk,
@@ -1288,7 +1304,7 @@ __device__ __forceinline__ void gen_small(const Inst& I, const SmallE& S, const 
             U += e.U;
             if (l2 == 1) xj = xl;
         }
-        const int64_t* vv = I.V() + (I.rowoff()[c] + (d - I.off()[P.p1 + l1 + 1])) * 6;
+        const int64_t* vv = I.V() + (I.rowbase()[c] + d) * 6;
         int64_t best = kINF;
 #pragma unroll
         for (int tp = 0; tp < 6; tp++) {
@@ -1301,73 +1317,139 @@ __device__ __forceinline__ void gen_small(const Inst& I, const SmallE& S, const 
     }
 }
 
-// Interior loops with both sides of two bases or more except 2x2 and 2x3: the two products.  Rounds of
-// up to kGenTasks accumulator sets; a set's rows are dealt to the waves that share it.  `rest` is the other
-// work of the step, done by each wave between its share of the first round's left product and the barrier.
-template <class F>
-__device__ __forceinline__ void gen_products(const Inst& I, const SmallE& S, const GenPair& P, GenShared& G, int wave, int nw,
-                                             int lane, F rest) {
+// Interior loops other than the tabulated ones: both products.  A task is eight left edges x 64 right edges
+// of one part, generic loops and those with l2 = 1 (part 0), 2x3 loops (1), loops with l1 = 1 (2);
+// its rows are cut into units of kGenRows, dealt to the waves.  The second product has one thread per (left
+// edge, row of layer q1, share of the right edges).  `rest` is the other work of the step, done by each wave
+// between its units of the first round and the barrier.
+template <int NT, class F>
+__device__ __forceinline__ void gen_products(const Inst& I, const SmallE& S, const GenPair& P, GenShared& G, int wave, int lane, F rest) {
+    constexpr int NW = NT / 64;
     const GenEdgePtr E = (GenEdgePtr)(uintptr_t)I.gedges();
     const GenRowPtr R = (GenRowPtr)(uintptr_t)I.grows();
     const IntPtr eo = (IntPtr)(uintptr_t)I.geoff(), io = (IntPtr)(uintptr_t)I.groff();
     const LongPtr LG4 = (LongPtr)(uintptr_t)I.LG();
     const int s = I.shift, g1 = P.g - 2, win = I.win, smax = min(kGenLoopWin, g1 - 5);
-    // right edges with l2 = 2..28, rows with l1 = 2..28, inner span >= 5
-    const int f0 = g1 >= 9 ? eo[max(P.q1 - 28, P.p1 + 7)] : 0, f1 = g1 >= 9 ? eo[P.q1 - 1] : 0;
-    const int i0 = g1 >= 9 ? io[P.p1 + 2] : 0, i1 = g1 >= 9 ? io[min(P.p1 + 28, P.q1 - 7) + 1] : 0;
-    const int nblk = (f1 - f0 + 63) / 64, ngrp = (P.ne + kGenGroup - 1) / kGenGroup;
-    const int rb = min(nblk, kGenTasks), rg = rb ? kGenTasks / rb : 1;  // blocks and edge groups per round
-    bool first = true;
-    for (int grp0 = 0; grp0 < ngrp || first; grp0 += rg)
-        for (int blk0 = 0; blk0 < nblk || first; blk0 += rb) {
-            const int cb = min(rb, nblk - blk0), cg = min(rg, ngrp - grp0), ntask = g1 >= 11 ? cb * cg : 0;
-            if (!first) {
-                for (int k = wave * 64 + lane; k < kGenTasks * kGenGroup * 64; k += nw * 64) (&G.q[0][0][0])[k] = kHalfINF;
-                __syncthreads();
-            }
-            const int share = ntask ? max(1, nw / ntask) : 1;  // waves per set
-            for (int k = wave; k < ntask * share; k += nw) {
-                const int task = k % ntask, part = k / ntask, e = P.e0 + (grp0 + task / cb) * kGenGroup;
-                const int f = min(f0 + (blk0 + task % cb) * 64 + lane, f1 - 1);
-                const int l2 = P.q1 - I.gedges()[f].layer, col = f % win;
-                const int64_t* IN0 = I.IN() + col;
-                int64_t acc[kGenGroup];
-#pragma unroll
-                for (int x = 0; x < kGenGroup; x++) acc[x] = kHalfINF;
-#pragma unroll 4
-                for (int i = i0 + part; i < i1; i += share) {
-                    const int l1 = R[i].layer - P.p1, sum = l1 + l2;
-                    const LongPtr lg = LG4 + (R[i].lgbase + e);
-                    const int64_t in = IN0[(int64_t)i * win];
-                    const int dd = l1 > l2 ? l1 - l2 : l2 - l1;
-                    const int32_t base = S.interior[min(sum, kGenLoopWin)] + min(S.ninio * dd, S.ninio_max);
-                    const int64_t x = sum >= 6 && sum <= smax ? in + fx(base, s) : kHalfINF;
-#pragma unroll
-                    for (int y = 0; y < kGenGroup; y++) acc[y] = mn(acc[y], lg[y] + x);
-                }
-#pragma unroll
-                for (int y = 0; y < kGenGroup; y++) gen_min(&G.q[task][y][lane], acc[y]);
-            }
-            if (first) rest();
-            first = false;
-            __syncthreads();
-            const int items = ntask ? min(cg * kGenGroup, P.ne - grp0 * kGenGroup) * P.nj : 0;
-            for (int it = wave; it < items; it += nw) {
-                const int k = it / P.nj, j = P.j0 + it % P.nj, e = P.e0 + grp0 * kGenGroup + k;
-                const int64_t* LGj = I.LG() + R[j].lgbase;
-                int64_t v = kHalfINF;
-                for (int b = 0; b < cb; b++) {
-                    const int f = f0 + (blk0 + b) * 64 + lane;
-                    if (f < f1) v = mn(v, G.q[(k / kGenGroup) * cb + b][k % kGenGroup][lane] + LGj[f]);
-                }
-                v = wave_min(v);
-                const int xi = E[e].lab, xj = R[j].lab;
-                if (lane < 6)
-                    gen_min(G.w + ((E[e].src - P.a1lo) * P.wb1 + (R[j].state - P.b1lo)) * 6 + lane,
-                            v + fx(S.mmI[lane][xi][xj], s));
-            }
+    // right edges of the parts (inner span >= 5), blocks of 64 of each
+    int fa[3] = {0, 0, 0}, fb[3] = {0, 0, 0};
+    if (g1 >= 9) {
+        fa[0] = eo[max(P.q1 - 28, P.p1 + 7)];
+        fb[0] = eo[P.q1];
+        fa[2] = eo[max(P.q1 - 29, P.p1 + 6)];
+        fb[2] = eo[P.q1 - 2];
+    }
+    if (g1 >= 10) {
+        fa[1] = eo[P.q1 - 3];
+        fb[1] = eo[P.q1 - 1];
+    }
+    const int n0 = (fb[0] - fa[0] + 63) / 64, n1 = (fb[1] - fa[1] + 63) / 64, nbt = n0 + n1 + (fb[2] - fa[2] + 63) / 64;
+    const int ntask = nbt * ((P.ne + kGenGroup - 1) / kGenGroup);
+    for (int t0 = 0; t0 < ntask || t0 == 0; t0 += kGenTasks) {
+        if (t0) {
+            for (int k = wave * 64 + lane; k < kGenTasks * 64 * (kGenGroup + 1); k += NT) (&G.q[0][0][0])[k] = kHalfINF + kGenBias;
             __syncthreads();
         }
+        // lane t describes task t0 + t of the round
+        const int nt = min(kGenTasks, ntask - t0);
+        int part = 0, tf = 0, te = 0, ti0 = 0, ti1 = 0, te0 = 0;
+        if (lane < nt) {
+            const int grp = (t0 + lane) / nbt, r = (t0 + lane) - grp * nbt;
+            part = r < n0 ? 0 : r < n0 + n1 ? 1 : 2;
+            tf = (part == 0 ? fa[0] + r * 64 : part == 1 ? fa[1] + (r - n0) * 64 : fa[2] + (r - n0 - n1) * 64);
+            te = min(tf + 64, part == 0 ? fb[0] : part == 1 ? fb[1] : fb[2]);
+            te0 = P.e0 + grp * kGenGroup;
+            const int l1a = part == 2 ? 1 : 2, l1b = part == 0 ? smax - (P.q1 - I.gedges()[te - 1].layer) : part == 1 ? 3 : 1;
+            ti0 = I.groff()[P.p1 + l1a];
+            ti1 = l1b >= l1a ? I.groff()[P.p1 + l1b + 1] : ti0;
+        }
+        int units = (ti1 - ti0 + kGenRows - 1) / kGenRows, cum = units;  // inclusive prefix over the tasks
+#pragma unroll
+        for (int o = 1; o < kGenTasks; o <<= 1) {
+            const int w = __shfl_up(cum, o, 64);
+            if (lane >= o) cum += w;
+        }
+        const int total = nt > 0 ? uni(__shfl(cum, nt - 1, 64)) : 0;
+        for (int u = wave; u < total; u += NW) {
+            const int task = __popcll(__ballot(lane < nt && cum <= u));
+            const int X = __builtin_amdgcn_readlane(part, task), f0 = __builtin_amdgcn_readlane(tf, task),
+                      f1 = __builtin_amdgcn_readlane(te, task), e = __builtin_amdgcn_readlane(te0, task);
+            const int first = __builtin_amdgcn_readlane(ti0, task) +
+                              (u - __builtin_amdgcn_readlane(cum - units, task)) * kGenRows;
+            const int last = min(first + kGenRows, __builtin_amdgcn_readlane(ti1, task));
+            const int f = min(f0 + lane, f1 - 1), l2 = P.q1 - I.gedges()[f].layer;
+            // class of the lane's loops and the left sizes it takes
+            const int cls = X == 0 ? (l2 == 1 ? 2 : 0) : X;
+            const int lo = X == 0 ? (l2 == 1 ? 3 : l2 < 4 ? 6 - l2 : 2) : X == 1 ? 5 - l2 : 1;
+            const int hi = X == 0 ? smax - l2 : X == 1 ? 5 - l2 : 1;
+            const int64_t* INf = I.IN() + (int64_t)cls * I.nil * win + f % win;
+            int64_t acc[kGenGroup];
+#pragma unroll
+            for (int y = 0; y < kGenGroup; y++) acc[y] = kHalfINF + kGenBias;
+            // the unit's rows are read at once (rows past its end repeat the last one)
+            const GenRow& mine = I.grows()[min(first + (lane & (kGenRows - 1)), last - 1)];
+            const int ml1 = mine.layer - P.p1;
+            const int64_t mlg = mine.lgbase;
+            int64_t in[kGenRows];
+#pragma unroll
+            for (int k = 0; k < kGenRows; k++) in[k] = INf[(int64_t)min(first + k, last - 1) * win];
+#pragma unroll
+            for (int k = 0; k < kGenRows; k++) {
+                const int l1 = __builtin_amdgcn_readlane(ml1, k);
+                const LongPtr lg = LG4 + (readlane64(mlg, k) + e);
+                const int64_t x = l1 >= lo && l1 <= hi ? in[k] + G.size[l1][l2] : kHalfINF + kGenBias;
+#pragma unroll
+                for (int y = 0; y < kGenGroup; y++) acc[y] = min_positive(acc[y], lg[y] + x);
+            }
+#pragma unroll
+            for (int y = 0; y < kGenGroup; y++)
+                if (acc[y] < kGenBig + kGenBias)
+                    __hip_atomic_fetch_min(&G.q[task][lane][y], acc[y], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+        if (t0 == 0) rest();
+        __syncthreads();
+        if (nt > 0) {
+            const int ga = t0 / nbt, gb = (t0 + nt - 1) / nbt;  // edge groups of the round
+            const int ea = P.e0 + ga * kGenGroup, en = min(P.e0 + P.ne, P.e0 + (gb + 1) * kGenGroup) - ea, outs = en * P.nj;
+            const int parts = max(1, min(32, NT / outs));
+            for (int k = wave * 64 + lane; k < outs * parts; k += NT) {
+                const int e = ea + k % en, r = k / en, j = P.j0 + r % P.nj, share = r / P.nj;
+                const int grp = (e - P.e0) / kGenGroup, y = (e - P.e0) % kGenGroup;
+                const GenRow& row = I.grows()[j];
+                const int64_t* LGj = I.LG() + row.lgbase;
+                int64_t c[3];
+                c[0] = c[1] = c[2] = kHalfINF + kGenBias;
+                const int fl1 = eo[P.q1 - 1];  // right edges from here on have l2 = 1
+                for (int t = max(0, grp * nbt - t0); t < min(nt, (grp + 1) * nbt - t0); t++) {
+                    const int b = t0 + t - grp * nbt, X = b < n0 ? 0 : b < n0 + n1 ? 1 : 2;
+                    const int f0 = X == 0 ? fa[0] + b * 64 : X == 1 ? fa[1] + (b - n0) * 64 : fa[2] + (b - n0 - n1) * 64;
+                    const int cnt = min(64, (X == 0 ? fb[0] : X == 1 ? fb[1] : fb[2]) - f0);
+                    int64_t v = kHalfINF + kGenBias, v1 = v;  // v1: l2 = 1
+#pragma unroll 4
+                    for (int m = share; m < cnt; m += parts) {
+                        const int64_t x = G.q[t][m][y] + LGj[f0 + m];
+                        if (f0 + m >= fl1) v1 = min_positive(v1, x);
+                        else v = min_positive(v, x);
+                    }
+                    if (X == 0) {
+                        c[0] = min_positive(c[0], v);
+                        c[2] = min_positive(c[2], v1);
+                    } else if (X == 1) {
+                        c[1] = min_positive(c[1], v);
+                    } else {
+                        c[2] = min_positive(c[2], v);
+                    }
+                }
+                const GenEdge& ed = I.gedges()[e];
+                int64_t* w6 = G.w + ((ed.src - P.a1lo) * P.wb1 + (row.state - P.b1lo)) * 6;
+                if (mn(mn(c[0], c[1]), c[2]) >= kGenBig + kGenBias) continue;
+#pragma unroll
+                for (int t = 0; t < 6; t++)
+                    gen_min(w6 + t, mn(mn(c[0] + fx(S.mmI[t][ed.lab][row.lab], s), c[1] + fx(S.mm23[t][ed.lab][row.lab], s)),
+                                       c[2] + fx(S.mm1n[t][ed.lab][row.lab], s)) - kGenBias);
+            }
+        }
+        __syncthreads();
+    }
 }
 
 // One layer pair of span step g by one workgroup.  Between the first barriers every wave takes its share
@@ -1400,38 +1482,34 @@ __device__ __forceinline__ void gen_span_group(const Inst& I, const SmallE& S, c
         G.w[k] = kHalfINF;
         G.v[k] = kINF;
     }
-    for (int k = tid; k < kGenTasks * kGenGroup * 64; k += NT) (&G.q[0][0][0])[k] = kHalfINF;
+    if (tid < 2 * (kGenLoopWin + 1)) {
+        const int l = tid >> 1, y = tid & 1 ? P.q1 - l : P.p1 + l;
+        GenLayer L{0, 0, 0, 0};
+        if (y >= 0 && y <= I.n) {
+            L.first = I.off()[y];
+            L.cnt = I.off()[y + 1] - L.first;
+            L.row = I.rowbase()[L.first];
+            L.len = I.N - I.off()[y + 1];
+        }
+        (tid & 1 ? G.right : G.left)[l] = L;
+    }
+    for (int k = tid; k < kGenTasks * 64 * (kGenGroup + 1); k += NT) (&G.q[0][0][0])[k] = kHalfINF + kGenBias;
+    for (int k = tid; k < kGenLoopWin * 32; k += NT) {
+        const int l1 = k >> 5, l2 = k & 31;
+        G.size[l1][l2] = l1 > 0 && l2 > 0 && l1 + l2 <= kGenLoopWin ? fx(interior_base(S, l1, l2), s) + kGenBias : kGenBias;
+    }
     GroupCounters ctr{0, 0};
     __syncthreads();
     auto rest = [&]() {
-        const int nthin = g >= 11 ? P.ne * P.nj : 0, naround = g >= 5 ? P.wa1 * P.wb1 : 0;
-        const int nspec = g == 5 || g == 6 || g == 8 ? ncell * 6 : 0, ntask = nthin + naround + ncell + nspec;
-        for (int k0 = NW - 1 - wave; k0 < ntask; k0 += NW) {
-            int k = k0;
-            if (k < nthin) {
-                const int e = P.e0 + k / P.nj, j = P.j0 + k % P.nj;
-                gen_thin(I, S, P, e, j, G.w + ((E[e].src - P.a1lo) * P.wb1 + (R[j].state - P.b1lo)) * 6, lane);
-                continue;
-            }
-            k -= nthin;
-            if (k < ncell) {
-                const int a = a_lo + k / wb, b = b_lo + k % wb, committed = uni(I.ccnt()[b]);
-                int64_t s2, ps;
-                multiloop_scan(I, a, b, p, q, I.rowoff()[a] + (b - off[p + 1]), lane, committed, I.coff()[b], &s2, &ps);
-                if (lane == 0) {
-                    G.s2[k] = s2;
-                    G.ps[k] = ps;
-                    G.committed[k] = committed;
-                }
-                continue;
-            }
-            k -= ncell;
-            if (k < naround) {
-                gen_around(I, S, P, P.a1lo + k / P.wb1, P.b1lo + k % P.wb1, G.w + k * 6, lane);
-                continue;
-            }
+        for (int c0 = wave * 4; c0 < ncell; c0 += NW * 4) {
+            const int ci = c0 + (lane >> 4), cv = min(ci, ncell - 1);
+            gen_scan(I, G, p, q, a_lo + cv / wb, b_lo + cv % wb, ci, ci < ncell, lane);
+        }
+        if (g >= 9) gen_bulges(I, S, P, G, tid, NT);
+        if (g >= 5) gen_hairpins(I, S, P, G.w, tid, NT);
+        const int nspec = g == 5 || g == 6 || g == 8 ? ncell * 6 : 0;
+        for (int k = wave; k < nspec; k += NW) {
             // hairpins of 3, 4 and 6 bases, whose listed loops depend on the whole label path
-            k -= naround;
             const int t = k % 6, ci = k / 6, a = a_lo + ci / wb, b = b_lo + ci % wb, a1 = I.out_dst()[a * 4 + type_x(t)];
             if (a1 < 0) continue;
             const int64_t v = wave_min(hairpin_lane(I, S, spec, a, b, t, a1, I.out_U()[a * 4 + type_x(t)], p, g, lane));
@@ -1469,7 +1547,7 @@ __device__ __forceinline__ void gen_span_group(const Inst& I, const SmallE& S, c
             }
         }
     };
-    gen_products(I, S, P, G, wave, NW, lane, rest);
+    gen_products<NT>(I, S, P, G, wave, lane, rest);
     // typed values, branch value, S1 and the retention test: eight lanes per cell, one per type
     for (int k = tid; k < ncell * 8; k += NT) {
         const int ci = k >> 3, t = k & 7, a = a_lo + ci / wb, b = b_lo + ci % wb;
@@ -1859,7 +1937,7 @@ hipError_t launch_span_gen(const Inst& I, const EnergyTables* E, const int32_t* 
     const int nblk = layers > 0 ? layers : 0;
     const int total = nblk + (ext_layer >= 0 ? 1 : 0);
     if (total == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_span_gen<512>, dim3(total), dim3(512), 0, st, I, E, spec, g, ext_layer, nblk);
+    hipLaunchKernelGGL(k_span_gen<1024>, dim3(total), dim3(1024), 0, st, I, E, spec, g, ext_layer, nblk);
     return hipGetLastError();
 }
 

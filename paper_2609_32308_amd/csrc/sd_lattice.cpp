@@ -679,13 +679,13 @@ static void build_generic_tables(Lattice& L) {
         }
     }
     wo[n + 1] = (int)L.gwalks.size();
-    // a row's LG words: the edges of the kGenLoopWin layers before it, and three more that a group of
-    // four edges reaches past the last layer's end
+    // a row's LG words: the edges of the kGenLoopWin layers before it, and seven more that a group of
+    // eight edges reaches past the last layer's end
     int64_t words = 0;
     for (GenRow& r : L.grows) {
         const int lo = eo[std::max(r.layer - kGenLoopWin, 0)];
         r.lgbase = words - lo;
-        words += eo[r.layer] - lo + 3;
+        words += eo[r.layer] - lo + 7;
     }
     L.lgsize = words;
     // a span reads right layers down to kGenLoopWin + 2 behind the one it writes
@@ -828,8 +828,9 @@ int build_motif_lattice(const char* protein, const CodonTable& T, const Params& 
     hairpin_init(L, P);
     layout_rows(L, cp);
     // the trie's closed-form arrays are not used on a generic lattice: neutral fillers that keep
-    // the device layout's extents
+    // the device layout's extents, and the base of every cell row in place of the tails
     L.tail.assign(N, 0);
+    for (int u = 0; u < N; u++) L.tail[u] = L.rowoff[u] - L.off[L.layer[u] + 1];
     L.pfx.assign(N, 0);
     L.P.assign(L.A + 1, 0);
     L.generic = true;
