@@ -92,19 +92,41 @@ __device__ __forceinline__ int64_t readlane64(int64_t v, int l) {
     const int hi = __builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)v >> 32), l);
     return (int64_t)(((uint64_t)(uint32_t)hi << 32) | (uint64_t)(uint32_t)lo);
 }
-// minimum over each row of 16 lanes (every lane of the wave active)
-__device__ __forceinline__ int64_t row_min(int64_t v) {
-    v = mn(v, dpp64<kDppXor1>(v));
-    v = mn(v, dpp64<kDppXor2>(v));
-    v = mn(v, dpp64<kDppHalfMirror>(v));
-    return mn(v, dpp64<kDppMirror>(v));
+// Minimum of two int64 in [2^52, 2^63 - 2^53): positive patterns of finite doubles order as the integers do,
+// so one instruction replaces a compare and two selects.  kBias brings every value of the tables and
+// their sums (finite ones within 2^60, infinite ones up to 2^62 and a little) into that range.
+constexpr int64_t kBias = (int64_t)1 << 60;
+__device__ __forceinline__ int64_t min_positive(int64_t a, int64_t b) {
+    int64_t r;
+    asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
 }
-// minimum over the whole wave (every lane active): DPP within each row of 16 lanes, then the
-// four row minima on the scalar unit
-__device__ __forceinline__ int64_t wave_min(int64_t v) {
-    v = row_min(v);
-    return mn(mn(readlane64(v, 0), readlane64(v, 16)), mn(readlane64(v, 32), readlane64(v, 48)));
+template <int CTRL>
+__device__ __forceinline__ int64_t min_dpp(int64_t v) { return min_positive(v, dpp64<CTRL>(v)); }
+// the minimum with the value 16 or 32 lanes away (lane xor 16 / 32): one swap per half of the value
+__device__ __forceinline__ int64_t min_xor16(int64_t v) {
+    const auto l = __builtin_amdgcn_permlane16_swap((unsigned)v, (unsigned)v, false, false);
+    const auto h = __builtin_amdgcn_permlane16_swap((unsigned)((uint64_t)v >> 32), (unsigned)((uint64_t)v >> 32), false, false);
+    return min_positive((int64_t)((uint64_t)h[0] << 32 | l[0]), (int64_t)((uint64_t)h[1] << 32 | l[1]));
 }
+__device__ __forceinline__ int64_t min_xor32(int64_t v) {
+    const auto l = __builtin_amdgcn_permlane32_swap((unsigned)v, (unsigned)v, false, false);
+    const auto h = __builtin_amdgcn_permlane32_swap((unsigned)((uint64_t)v >> 32), (unsigned)((uint64_t)v >> 32), false, false);
+    return min_positive((int64_t)((uint64_t)h[0] << 32 | l[0]), (int64_t)((uint64_t)h[1] << 32 | l[1]));
+}
+// minimum over each row of 16 lanes (every lane of the wave active) of biased values
+__device__ __forceinline__ int64_t row_min_biased(int64_t v) {
+    return min_dpp<kDppMirror>(min_dpp<kDppHalfMirror>(min_dpp<kDppXor2>(min_dpp<kDppXor1>(v))));
+}
+__device__ __forceinline__ int64_t row_min(int64_t v) { return row_min_biased(v + kBias) - kBias; }
+// minimum over the whole wave (every lane active) of biased values, in every lane's scalar copy
+__device__ __forceinline__ int64_t wave_min_biased(int64_t v) {
+    v = min_xor32(min_xor16(row_min_biased(v)));
+    const int lo = __builtin_amdgcn_readfirstlane((int)v), hi = __builtin_amdgcn_readfirstlane((int)((uint64_t)v >> 32));
+    return (int64_t)((uint64_t)(uint32_t)hi << 32 | (uint32_t)lo);
+}
+// minimum over the whole wave (every lane active): about half the instructions of 64-bit compares and selects
+__device__ __forceinline__ int64_t wave_min(int64_t v) { return wave_min_biased(v + kBias) - kBias; }
 
 template <class IT>
 __device__ __forceinline__ int64_t cell_of(const IT& I, int a, int b) {

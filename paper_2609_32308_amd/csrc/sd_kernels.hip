@@ -295,20 +295,18 @@ __device__ __forceinline__ void closed_pair(const Inst& I, const SmallE& S, cons
         if (lane < nt && x23 && w < kHalfINF)
             lds_min(ab + 8 + out, cost + w + fx(interior_base(S, 2, 3), s) + (left ? rq->pb2 : -rp->pa2));
     }
-    int B0, St, Sr;
-    bool spl, half;
-    // this lane's special loop closed by type t: byte address B0 + t St + rev(t') Sr, entries of 4 or
-    // (1x2, 2x1, 2x2) 2 bytes
+    int B0, St, Sr, sl = 0, sr = 0, live = 0;
+    bool spl;
+    // this lane's special loop closed by type t, biased: the word at byte B0 + t St + rev(t') Sr, whose entry
+    // (4 bytes, or for 1x2, 2x1, 2x2 one of its halves, the same for every t and t') two shifts cut
+    // out; vin then holds the inner cell's values + path costs + bias
     auto special = [&](int t) {
-        int64_t v = kINF;
+        int64_t v = kINF + kBias;
 #pragma unroll
         for (int tp = 0; tp < 6; tp++) {
-            const bool fin = spl && vin[tp] < kINF;
-            if (!__ballot(fin)) continue;
-            const int ad = B0 + type_rev(tp) * Sr + t * St;
-            const int w = *reinterpret_cast<const int*>(reinterpret_cast<const char*>(&S) + (ad & ~3));
-            const int e2 = half ? ((ad & 2) ? w >> 16 : (int)(int16_t)w) : w;
-            v = mn(v, (fin ? bs + vin[tp] : kINF) + fx(e2, s));
+            if (!((live >> tp) & 1)) continue;
+            const int w = *reinterpret_cast<const int*>(reinterpret_cast<const char*>(&S) + (B0 + type_rev(tp) * Sr + t * St));
+            v = min_positive(v, vin[tp] + fx((int)((unsigned)w << sl) >> sr, s));
         }
         return v;
     };
@@ -324,16 +322,23 @@ __device__ __forceinline__ void closed_pair(const Inst& I, const SmallE& S, cons
             // inner minimum over the inner pair's types for the boundary classes
             {
                 const int32_t* tab = &S.mmH[0][0][0] + KK * 96 + xl * 4 + xk;
-                int64_t in = kINF;
+                int64_t in = kINF + kBias;
+                live = 0;
 #pragma unroll
-                for (int tp = 0; tp < 6; tp++) in = mn(in, vin[tp] + fx(tab[type_rev(tp) * 16], s));
-                in += bs;
+                for (int tp = 0; tp < 6; tp++) {
+                    vin[tp] += kBias;
+                    in = min_positive(in, vin[tp] + fx(tab[type_rev(tp) * 16], s));
+                    const bool fin = spl && vin[tp] < kINF + kBias;
+                    live |= __ballot(fin) ? 1 << tp : 0;
+                    vin[tp] = fin ? vin[tp] + bs : kINF + kBias;
+                }
+                in += bs - kBias;
                 if (!spl) {
                     if (KK == 4) ta = mn(ta, in);
                     else if (in < kHalfINF) lds_min(&X.T[KK * 16 + xi * 4 + xj], in);
                 }
             }
-            half = l1 + l2 > 2;
+            sl = sr = l1 + l2 > 2 ? 16 : 0;
             if (l1 + l2 <= 1) {
                 B0 = offsetof(SmallE, stack), St = 24, Sr = 4;
             } else if (l1 + l2 == 2) {
@@ -345,13 +350,15 @@ __device__ __forceinline__ void closed_pair(const Inst& I, const SmallE& S, cons
             } else {
                 B0 = (int)offsetof(SmallE, int21) + (xl * 16 + xi * 4 + xk) * 2, St = 128, Sr = 768;
             }
-            if (!spl) B0 = 0, St = 0, Sr = 0, half = true;  // any valid entry: added to an infinite value
+            if (!spl) B0 = 0, St = 0, Sr = 0, sl = sr = 16;  // any valid entry: added to an infinite value
+            if (B0 & 2) sl = 0;
+            B0 &= ~3;
             idx += 64;
             if (idx - lane >= tot) break;
 #pragma unroll 1
             for (int t = 0; t < 6; t++) {
                 if (!((tm >> t) & 1)) continue;
-                const int64_t v = wave_min(special(t));
+                const int64_t v = wave_min_biased(special(t)) - kBias;
                 if (lane == 0) wout[t] = mn(wout[t], v);
             }
             read_cells(idx);
@@ -371,12 +378,13 @@ __device__ __forceinline__ void closed_pair(const Inst& I, const SmallE& S, cons
         }
     }
     ta = wave_min(ta);
+    T += kBias;
     const int32_t* tab = &S.mmH[0][0][0] + K * 96 + (lane & 15);
 #pragma unroll 1
     for (int t = 0; t < 6; t++) {
         if (!((tm >> t) & 1)) continue;
-        const int64_t sv = paths ? special(t) : kINF;
-        const int64_t v = mn(wave_min(mn(sv, T + fx(tab[t * 16], s))), ta + fx(au_pen(S, t), s));
+        const int64_t x = T + fx(tab[t * 16], s);
+        const int64_t v = mn(wave_min_biased(paths ? min_positive(special(t), x) : x) - kBias, ta + fx(au_pen(S, t), s));
         if (lane == 0) wout[t] = norm_inf(mn(wout[t], v));
     }
     if (rings && (m == 3 || m == 4 || m == 6)) {
@@ -471,8 +479,10 @@ __device__ __forceinline__ void produce_one_sided(const Inst& I, const SmallE& S
         in0[h] = T[ring_idx(st, gr, 0, lab)];
         in2[h] = T[ring_idx(st, gr, 2, lab)];
         if (!ok) in0[h] = in2[h] = kINF;
+        in0[h] += kBias;
+        in2[h] += kBias;
     }
-    int64_t o[3] = {kINF, kINF, kINF};
+    int64_t o[3] = {kINF + kBias, kINF + kBias, kINF + kBias};
 #pragma unroll
     for (int h = 0; h < 2; h++) {
         const int ls = 3 + grp + 16 * h;
@@ -480,19 +490,16 @@ __device__ __forceinline__ void produce_one_sided(const Inst& I, const SmallE& S
         for (int le = 1; le <= 3; le++) {
             if (le + ls > kMaxLoop || (le == 2 && ls == 3)) continue;
             // the energy depends on |l1 - l2| and l1 + l2 only
-            o[le - 1] = mn(o[le - 1], (le == 1 ? in2[h] : in0[h]) + fx(interior_base(S, le, ls), s));
+            o[le - 1] = min_positive(o[le - 1], (le == 1 ? in2[h] : in0[h]) + fx(interior_base(S, le, ls), s));
         }
     }
 #pragma unroll
     for (int j = 0; j < 3; j++) {
         // over the lanes that share lane & 3: rotations by 4 and 8 within each row, then rows
-        o[j] = mn(o[j], dpp64<kDppRor4>(o[j]));
-        o[j] = mn(o[j], dpp64<kDppRor8>(o[j]));
-        o[j] = mn(o[j], shfl_xor64(o[j], 16));
-        o[j] = mn(o[j], shfl_xor64(o[j], 32));
+        o[j] = min_xor32(min_xor16(min_dpp<kDppRor8>(min_dpp<kDppRor4>(o[j]))));
     }
     if (grp < 3)
-        (left ? I.RS() : I.LS())[rs_idx(st, g, grp + 1, lab)] = norm_inf((grp == 0 ? o[0] : grp == 1 ? o[1] : o[2]) + cod);
+        (left ? I.RS() : I.LS())[rs_idx(st, g, grp + 1, lab)] = norm_inf((grp == 0 ? o[0] : grp == 1 ? o[1] : o[2]) + (cod - kBias));
 }
 
 // Inner minima of the pair's left or right states for span g, by one wave: IDL and BI (left states, and
@@ -1118,18 +1125,9 @@ __global__ void k_checksum(Inst I, int g, unsigned long long* out) {
 // Infinite operands: LG is kINF, IN and the accumulators kHalfINF, finite values lie within 2^60, so a
 // sum of all three neither overflows nor falls below kGenBig.
 constexpr int64_t kGenBig = kHalfINF >> 1;
-constexpr int64_t kGenBias = kHalfINF >> 1;  // makes finite sums positive (see min_positive)
 constexpr int kGenGroup = 8;   // left edges per task
 constexpr int kGenRows = 16;   // rows per unit
 constexpr int kGenTasks = 16;  // (eight left edges, 64 right edges) per round
-
-// Minimum of two int64 in [2^52, 2^63 - 2^53): positive patterns of finite doubles order as the integers do,
-// so one instruction replaces a compare and two selects.
-__device__ __forceinline__ int64_t min_positive(int64_t a, int64_t b) {
-    int64_t r;
-    asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
-    return r;
-}
 
 typedef const __attribute__((address_space(4))) GenEdge* GenEdgePtr;
 typedef const __attribute__((address_space(4))) GenRow* GenRowPtr;
@@ -1148,8 +1146,8 @@ struct GenShared {
     int committed[kGenMaxWidth * kGenMaxWidth];
     int8_t keep[kGenMaxWidth * kGenMaxWidth];
     GenLayer left[kGenLoopWin + 1], right[kGenLoopWin + 1];  // layers p1 + l, q1 - l
-    int64_t size[kGenLoopWin][32];               // size(l1, l2) + kGenBias in fixed point
-    int64_t q[kGenTasks][64][kGenGroup + 1];     // Q + kGenBias of one round
+    int64_t size[kGenLoopWin][32];               // size(l1, l2) + kBias in fixed point
+    int64_t q[kGenTasks][64][kGenGroup + 1];     // Q + kBias of one round
 };
 
 // minimum into a shared word; values that hold an infinite operand are left out
@@ -1349,7 +1347,7 @@ __device__ __forceinline__ void gen_products(const Inst& I, const SmallE& S, con
     const int ntask = nbt * ((P.ne + kGenGroup - 1) / kGenGroup);
     for (int t0 = 0; t0 < ntask || t0 == 0; t0 += kGenTasks) {
         if (t0) {
-            for (int k = wave * 64 + lane; k < kGenTasks * 64 * (kGenGroup + 1); k += NT) (&G.q[0][0][0])[k] = kHalfINF + kGenBias;
+            for (int k = wave * 64 + lane; k < kGenTasks * 64 * (kGenGroup + 1); k += NT) (&G.q[0][0][0])[k] = kHalfINF + kBias;
             __syncthreads();
         }
         // lane t describes task t0 + t of the round
@@ -1387,7 +1385,7 @@ __device__ __forceinline__ void gen_products(const Inst& I, const SmallE& S, con
             const int64_t* INf = I.IN() + (int64_t)cls * I.nil * win + f % win;
             int64_t acc[kGenGroup];
 #pragma unroll
-            for (int y = 0; y < kGenGroup; y++) acc[y] = kHalfINF + kGenBias;
+            for (int y = 0; y < kGenGroup; y++) acc[y] = kHalfINF + kBias;
             // the unit's rows are read at once (rows past its end repeat the last one)
             const GenRow& mine = I.grows()[min(first + (lane & (kGenRows - 1)), last - 1)];
             const int ml1 = mine.layer - P.p1;
@@ -1399,13 +1397,13 @@ __device__ __forceinline__ void gen_products(const Inst& I, const SmallE& S, con
             for (int k = 0; k < kGenRows; k++) {
                 const int l1 = __builtin_amdgcn_readlane(ml1, k);
                 const LongPtr lg = LG4 + (readlane64(mlg, k) + e);
-                const int64_t x = l1 >= lo && l1 <= hi ? in[k] + G.size[l1][l2] : kHalfINF + kGenBias;
+                const int64_t x = l1 >= lo && l1 <= hi ? in[k] + G.size[l1][l2] : kHalfINF + kBias;
 #pragma unroll
                 for (int y = 0; y < kGenGroup; y++) acc[y] = min_positive(acc[y], lg[y] + x);
             }
 #pragma unroll
             for (int y = 0; y < kGenGroup; y++)
-                if (acc[y] < kGenBig + kGenBias)
+                if (acc[y] < kGenBig + kBias)
                     __hip_atomic_fetch_min(&G.q[task][lane][y], acc[y], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         }
         if (t0 == 0) rest();
@@ -1420,13 +1418,13 @@ __device__ __forceinline__ void gen_products(const Inst& I, const SmallE& S, con
                 const GenRow& row = I.grows()[j];
                 const int64_t* LGj = I.LG() + row.lgbase;
                 int64_t c[3];
-                c[0] = c[1] = c[2] = kHalfINF + kGenBias;
+                c[0] = c[1] = c[2] = kHalfINF + kBias;
                 const int fl1 = eo[P.q1 - 1];  // right edges from here on have l2 = 1
                 for (int t = max(0, grp * nbt - t0); t < min(nt, (grp + 1) * nbt - t0); t++) {
                     const int b = t0 + t - grp * nbt, X = b < n0 ? 0 : b < n0 + n1 ? 1 : 2;
                     const int f0 = X == 0 ? fa[0] + b * 64 : X == 1 ? fa[1] + (b - n0) * 64 : fa[2] + (b - n0 - n1) * 64;
                     const int cnt = min(64, (X == 0 ? fb[0] : X == 1 ? fb[1] : fb[2]) - f0);
-                    int64_t v = kHalfINF + kGenBias, v1 = v;  // v1: l2 = 1
+                    int64_t v = kHalfINF + kBias, v1 = v;  // v1: l2 = 1
 #pragma unroll 4
                     for (int m = share; m < cnt; m += parts) {
                         const int64_t x = G.q[t][m][y] + LGj[f0 + m];
@@ -1444,11 +1442,11 @@ __device__ __forceinline__ void gen_products(const Inst& I, const SmallE& S, con
                 }
                 const GenEdge& ed = I.gedges()[e];
                 int64_t* w6 = G.w + ((ed.src - P.a1lo) * P.wb1 + (row.state - P.b1lo)) * 6;
-                if (mn(mn(c[0], c[1]), c[2]) >= kGenBig + kGenBias) continue;
+                if (mn(mn(c[0], c[1]), c[2]) >= kGenBig + kBias) continue;
 #pragma unroll
                 for (int t = 0; t < 6; t++)
                     gen_min(w6 + t, mn(mn(c[0] + fx(S.mmI[t][ed.lab][row.lab], s), c[1] + fx(S.mm23[t][ed.lab][row.lab], s)),
-                                       c[2] + fx(S.mm1n[t][ed.lab][row.lab], s)) - kGenBias);
+                                       c[2] + fx(S.mm1n[t][ed.lab][row.lab], s)) - kBias);
             }
         }
         __syncthreads();
@@ -1496,10 +1494,10 @@ __device__ __forceinline__ void gen_span_group(const Inst& I, const SmallE& S, c
         }
         (tid & 1 ? G.right : G.left)[l] = L;
     }
-    for (int k = tid; k < kGenTasks * 64 * (kGenGroup + 1); k += NT) (&G.q[0][0][0])[k] = kHalfINF + kGenBias;
+    for (int k = tid; k < kGenTasks * 64 * (kGenGroup + 1); k += NT) (&G.q[0][0][0])[k] = kHalfINF + kBias;
     for (int k = tid; k < kGenLoopWin * 32; k += NT) {
         const int l1 = k >> 5, l2 = k & 31;
-        G.size[l1][l2] = l1 > 0 && l2 > 0 && l1 + l2 <= kGenLoopWin ? fx(interior_base(S, l1, l2), s) + kGenBias : kGenBias;
+        G.size[l1][l2] = l1 > 0 && l2 > 0 && l1 + l2 <= kGenLoopWin ? fx(interior_base(S, l1, l2), s) + kBias : kBias;
     }
     GroupCounters ctr{0, 0};
     __syncthreads();
