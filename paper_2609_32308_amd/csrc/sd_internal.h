@@ -249,9 +249,9 @@ constexpr int kGenLoopWin = 30;   // layer distances covered by the labelled gap
 constexpr int kMaxWaves = 16;  // waves per workgroup of the span-step kernels (1024 threads)
 static_assert(sizeof(Inst) % 8 == 0, "instance descriptors are copied as 8-byte words");
 
-// Batched persistent launch: barrier and work-ticket state shared by all workgroups.  Every contended
-// word sits on its own 128-byte line.  Barrier words are per XCD (the one a workgroup runs on); the
-// work bands and their tickets are per group, block index mod 8.
+// Batched persistent launch: barrier state shared by all workgroups.  Every contended word sits on its
+// own 128-byte line.  Barrier words are per XCD (the one a workgroup runs on); the work bands are per
+// group, block index mod 8.
 struct alignas(128) CtlWord {
     unsigned int v;
     unsigned int pad[31];
@@ -264,7 +264,6 @@ struct BatchCtl {
     CtlWord top;               // XCDs complete at the current barrier
     CtlWord gen;               // barrier generation
     CtlWord release[kMaxXcd];  // generation each XCD's workgroups are released to
-    CtlWord next[8];    // work tickets handed out per group (its band of every step, in order)
     CtlWord err;        // set when a barrier wait exceeds its spin limit (every group then exits)
     CtlWord steps_done; // spans completed (diagnostics)
 };

@@ -1780,10 +1780,13 @@ __device__ __forceinline__ int item_instance(const int* pref, int ninst, int ite
 
 // Persistent launch.  The workgroup's waves share the staged energy tables and the step's prefix and
 // work in teams of consecutive waves, one work item per team at a time.  A step with more items than
-// the launch has waves gives every wave items of its own, drawn from the band's ticket counter (the
-// items' costs differ); with fewer items the teams grow (to the whole workgroup when there is at
-// most one item per workgroup), since a step then takes its longest item's time, and each team's
-// items follow from its index.  min_team is the schedule's waves per item (1, or all of a 256- or
+// the launch has waves gives every workgroup of a band each grp_blocks-th item, drawn by its waves from a
+// counter in LDS (the items' costs differ; neighbouring items cost alike, so the workgroups' shares do not);
+// with fewer items the teams grow (to the whole workgroup when there is at most one item per
+// workgroup), since a step then takes its longest item's time, and each team's items follow from its index.
+// Tickets of a band drawn by every wave from one word in memory cost 455 ms instead of 430 for 64 proteins
+// of 50-1,000 aa and 70.4 instead of 63.4 for 24 of 50-400; runs of 2, 4, 8 neighbouring items per workgroup
+// 434, 438, 444.  min_team is the schedule's waves per item (1, or all of a 256- or
 // 512-thread workgroup's).
 template <int NT>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_persistent(
@@ -1796,16 +1799,16 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
     __shared__ int wsum[NWV];
     __shared__ unsigned team_ctr[NWV];
     __shared__ int s_flag;
+    __shared__ unsigned s_next;
     BarrierTeam B;
     if (threadIdx.x == 0) barrier_join(ctl, B);
     stage_tables(S, E);
     const unsigned grp = blockIdx.x & 7, ngrp = gridDim.x < 8 ? gridDim.x : 8;
     const unsigned grp_blocks = (gridDim.x - grp + 7) >> 3;  // workgroups of this group
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    unsigned ticket = 0, base = 0;
-    bool have_ticket = false;
     for (int step = 0; step < nsteps; step++) {
         if (threadIdx.x < NWV) team_ctr[threadIdx.x] = 0;
+        if (threadIdx.x == 0) s_next = 0;
         step_prefix<NT>(insts, ninst, step, pref, wsum);
         const unsigned total = (unsigned)__builtin_amdgcn_readfirstlane(pref[ninst]);
         const unsigned lo_item = (unsigned)((uint64_t)total * grp / ngrp);
@@ -1818,22 +1821,16 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
         T.w = wave & (tw - 1);
         T.ctr = &team_ctr[wave - T.w];
         GroupShared* Gs = &G[wave - T.w];
-        // team 1: tickets; larger teams: every grp_blocks * NWV / tw -th item
+        // team 1: the workgroup's items, drawn by its waves; larger teams: every grp_blocks * NWV / tw -th item
         const unsigned stride = grp_blocks * (unsigned)(NWV / tw);
         unsigned next = (blockIdx.x >> 3) * (unsigned)(NWV / tw) + (unsigned)(wave / tw);
-        if (tw == 1 && !have_ticket) {
-            unsigned t0 = 0;
-            if (T.lane() == 0) t0 = atomicAdd(&ctl->next[grp].v, 1u);
-            ticket = __builtin_amdgcn_readfirstlane(t0);
-            have_ticket = true;
-        }
         for (;;) {
-            unsigned k = next, nxt = 0;
+            unsigned k = next;
             if (tw == 1) {
-                // tickets number the items of the band over the steps that draw them; one drawn beyond
-                // this step is kept for the step it belongs to
-                k = ticket - base;
-                if (k < band && T.lane() == 0) nxt = atomicAdd(&ctl->next[grp].v, 1u);  // used after the item
+                unsigned j = 0;
+                if (T.lane() == 0) j = __hip_atomic_fetch_add(&s_next, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                j = __builtin_amdgcn_readfirstlane(j);
+                k = j * grp_blocks + (blockIdx.x >> 3);
             }
             if (k >= band) break;
             const int item = (int)(lo_item + k);
@@ -1843,25 +1840,24 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
             const int n = I.n, ncell_items = g <= n ? n - g + 1 : 0;
             if (local < ncell_items) flush_counters(I, span_group(I, S, spec, local, local + g, Gs, T), local, T.lane());
             else ext_column(I, S, n - g + 1, Gs, T);
-            if (tw == 1) ticket = __builtin_amdgcn_readfirstlane(nxt);
-            else T.sync();  // the team's shared state is free for its next item
+            if (tw > 1) T.sync();  // the team's shared state is free for its next item
             next += stride;
         }
-        if (tw == 1) base += band;
         if (!grid_barrier(ctl, B, spin_cap, &s_flag)) return;
         if (blockIdx.x == 0 && threadIdx.x == 0) ctl->steps_done.v = step + 1;
     }
 }
 
-// Resets the barrier state and initialises every instance whose g0 is 1 (new instances).
+// Resets the barrier state and initialises every instance whose g0 is 1 (new instances): gridDim.y
+// workgroups per instance.  The rings are 31 KB per state, so one workgroup per instance took 1.3 ms for 64
+// proteins of 50-1,000 aa and 0.18 ms for 7 of 50-150.
 __global__ void k_batch_init(const Inst* __restrict__ insts, int ninst, BatchCtl* ctl) {
     const Inst I = load_inst(insts + blockIdx.x);
-    const int tid = threadIdx.x, nt = blockDim.x;
+    const int tid = blockIdx.y * blockDim.x + threadIdx.x, nt = gridDim.y * blockDim.x;
     if (blockIdx.x == 0 && tid < kMaxXcd) {
         ctl->arrive[tid].v = 0;
         ctl->release[tid].v = 0;
         ctl->count[tid].v = 0;
-        if (tid < 8) ctl->next[tid].v = 0;
         if (tid == 0) {
             ctl->joined.v = 0;
             ctl->top.v = 0;
@@ -1944,7 +1940,8 @@ hipError_t launch_span_gen(const Inst& I, const EnergyTables* E, const int32_t* 
 
 hipError_t launch_batch_init(const Inst* insts_dev, int ninst, BatchCtl* ctl, hipStream_t st) {
     if (ninst <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_batch_init, dim3(ninst), dim3(256), 0, st, insts_dev, ninst, ctl);
+    const int parts = std::max(1, 1024 / ninst);
+    hipLaunchKernelGGL(k_batch_init, dim3(ninst, parts), dim3(256), 0, st, insts_dev, ninst, ctl);
     return hipGetLastError();
 }
 
