@@ -381,9 +381,8 @@ sd_status sd_occupancy(sd_context *ctx, int n, const char *const *proteins, cons
  * context's sizing policy), runs one persistent launch of steps_per_round span steps over all
  * active requests (each at its own span), and retires finished ones (their tracebacks in one
  * device launch), freeing their memory for the next admissions.  A launch's schedule is the one
- * fixed in the context's sd_options, else chosen per round from the mix: every wave on its own
- * layer pairs when the round starts with at least 12 pairs per resident wave, else four waves
- * per pair.  While a server runs, its context must not be used by other calls.  Results are
+ * fixed in the context's sd_options, else every wave on its own layer pairs, in teams of waves per
+ * pair where a step has fewer pairs than waves.  While a server runs, its context must not be used by other calls.  Results are
  * identical to sd_design; t_total_s is the latency from submission to completion. */
 typedef struct sd_server sd_server;
 typedef struct sd_server_cfg {
