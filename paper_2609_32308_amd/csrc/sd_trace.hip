@@ -191,6 +191,8 @@ struct SegIter {
 constexpr int kTraceWaves = 8;
 constexpr unsigned kTraceSpinCap = 1u << 24;  // polls before a wait is declared failed
 
+constexpr int kHelix = 16;  // stacks replayed per look-up of their cells
+
 // one wave's scratch for the decision it is working on
 struct TraceScratch {
     int pre[kNumPairs + 1];  // tuples of the two-loop pairs before pair k
@@ -200,6 +202,10 @@ struct TraceScratch {
     int64_t gl[64], row[64];  // gap a1 ~> c (infinite: no such state or path), row base of c
     int64_t gr[2][64];        // gap d ~> b1 for each slot of b1
     int st[64];               // state of d
+    // helices: values of the cells (layer p + k + 1, layer q - k - 1) at index 4 k + 2 slot + slot, costs and
+    // targets (a byte per label) of the edges out of layers p + k and q - 1 - k at index 2 k + slot
+    int64_t hv[4 * kHelix][6], lu[2 * kHelix + 2][4], ru[2 * kHelix + 2][4];
+    int ldst[2 * kHelix + 2], rdst[2 * kHelix + 2];
 };
 
 struct TraceLds {
@@ -227,6 +233,8 @@ struct Tracer {
     bool known = false;
     int kp = 0, kq = 0, kia = 0, kib = 0;
     int64_t kv = 0;
+    bool no_stack = false;     // the next closed value is known not to be a stack
+    int64_t El = 0, Ul = 0;    // this lane's shares of E and U beside the wave's
 
     __device__ Tracer(const Inst& I_, TraceLds& L_, TraceScratch& W_, const int32_t* sp_, int ln)
         : I(I_), L(L_), W(W_), spec(sp_), lane(ln) {}
@@ -356,7 +364,7 @@ struct Tracer {
     __device__ void go(int kind, int a, int b, int t) {
         next = TFrame{kind, a, b, t};
         have_next = true;
-        known = false;
+        known = no_stack = false;
     }
     __device__ void emit_at(int pos, int lab, int64_t cost) {
         if (lane == 0) I.tr_seq()[pos] = lab;
@@ -399,6 +407,7 @@ struct Tracer {
     __device__ bool hairpin(int a, int b, int t, int64_t v, int ea, int a1);
     __device__ bool twoloop(int a, int b, int t, int64_t v, int ea, int a1);
     __device__ void closed_trie(int a, int b, int t, int p, int q, int ia, int ib, int64_t v);
+    __device__ bool helix(int t, int p, int q, int ia, int ib, int64_t v);
     __device__ void s1(int a, int b);
     __device__ void s2(int a, int b);
     __device__ void branch(int a, int b);
@@ -744,14 +753,135 @@ __device__ bool Tracer::twoloop(int a, int b, int t, int64_t v, int ea, int a1) 
     return false;
 }
 
+// The stacks a closed value on the codon trie continues with, up to kHelix at once: the cells of every pair
+// of slots along the diagonal are read in two levels of loads, then each stack is one comparison of the
+// twelve (closing edge, inner type) candidates in LDS.  A stack is the first two-loop of the order, so only a
+// hairpin can come before it: the hairpin minima of all pairs found are compared side by side
+// afterwards, and the first that matches ends the helix.  Spans below 9 (listed hairpin sizes) are left to
+// the caller.  False if no stack was taken.
+// A stack costs 0.3 us this way plus 3 us per helix, 8 us as a decision of its own.
+__device__ bool Tracer::helix(int t, int p, int q, int ia, int ib, int64_t v) {
+    const int g = q - p, kmax = min(kHelix, (g - 9) / 2 + 1);
+    if (g < 9) return false;
+    const SlotRec* R = I.recs();
+    // records of layers p + k and q - 1 - k, k = 0..kmax, two lanes each
+    const int rk = min(lane >> 1, kmax), rs = lane & 1;
+    const SlotRec& rl = R[2 * (p + rk) + rs];
+    const SlotRec& rr = R[2 * (q - 1 - rk) + rs];
+    const int lstate = rl.state, rstate = rr.state;
+    const int64_t lrow = rl.rowbase;
+    if (lane < 2 * kHelix + 2) {
+        W.ldst[lane] = *reinterpret_cast<const int*>(rl.dst);
+        W.rdst[lane] = *reinterpret_cast<const int*>(rr.dst);
+#pragma unroll
+        for (int x = 0; x < 4; x++) {
+            W.lu[lane][x] = rl.outU[x];
+            W.ru[lane][x] = rr.outU[x];
+        }
+    }
+    {
+        const int k = lane >> 2, sl = (lane >> 1) & 1, sr = lane & 1;
+        const int cs = __shfl(lstate, 2 * k + 2 + sl, 64), ds = __shfl(rstate, 2 * k + sr, 64);
+        const int64_t row = ((int64_t)__shfl((int)(lrow >> 32), 2 * k + 2 + sl, 64) << 32) |
+                            (uint32_t)__shfl((int)lrow, 2 * k + 2 + sl, 64);
+        const bool ok = k < kmax && cs >= 0 && ds >= 0;
+        if (ok) {
+            const longlong2* vp = reinterpret_cast<const longlong2*>(I.V() + (row + ds) * 6);
+            const longlong2 v0 = vp[0], v1 = vp[1], v2 = vp[2];
+            int64_t* h = W.hv[lane];
+            h[0] = v0.x, h[1] = v0.y, h[2] = v1.x, h[3] = v1.y, h[4] = v2.x, h[5] = v2.y;
+        } else {
+#pragma unroll
+            for (int tp = 0; tp < 6; tp++) W.hv[lane][tp] = kINF;
+        }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    // lane k keeps level k: the pair's slots, type, value, source slot and inner type of its stack
+    int mia = 0, mib = 0, mt = 0, ms = 0, mtp = 0;
+    int64_t mv = 0;
+    const int ls = lane < 6 ? 0 : 1, ltp = lane < 6 ? lane : min(lane - 6, 5);
+    int n = 0;
+    for (; n < kmax; n++) {
+        const int x = kTX[t], y = kTY[t], ia1 = bcast((int)(int8_t)(W.ldst[2 * n + ia] >> (8 * x)));
+        if (ia1 < 0) break;
+        const int64_t val = W.hv[4 * n + 2 * ia1 + ls][ltp];
+        const bool ok = lane < 12 && (int)(int8_t)(W.rdst[2 * n + ls] >> (8 * y)) == ib && val < kINF &&
+                        W.lu[2 * n + ia][x] + W.ru[2 * n + ls][y] + val + fxe(L.S.stack[t][kRev[ltp]]) == v;
+        const unsigned long long hit = __ballot(ok);
+        if (!hit) break;
+        const int w = first_lane(hit), tp = w < 6 ? w : w - 6;
+        if (lane == n) {
+            mia = ia, mib = ib, mt = t, mv = v;
+            ms = w >= 6, mtp = tp;
+        }
+        v = readlane64(val, w);
+        ia = ia1;
+        ib = w >= 6;
+        t = tp;
+    }
+    if (n == 0) return false;
+    // hairpins before a stack: lanes 4 k + x2
+    {
+        const int k = lane >> 2, x2 = lane & 3;
+        const int ht = __shfl(mt, k, 64), hia = __shfl(mia, k, 64), hib = __shfl(mib, k, 64);
+        const int64_t hvv = ((int64_t)__shfl((int)(mv >> 32), k, 64) << 32) | (uint32_t)__shfl((int)mv, k, 64);
+        bool bad = false;
+        if (k < n) {
+            const int x = kTX[ht], y = kTY[ht], m = g - 2 * k - 2, ia1 = (int8_t)(W.ldst[2 * k + hia] >> (8 * x));
+            const int64_t al = R[2 * (p + k + 1) + ia1].alpha[x2];
+            const int64_t base = W.lu[2 * k + hia][x] + al + R[2 * (q - k)].pb2 - R[2 * (p + k)].pa2;
+            const int init = I.hp_init()[m];
+#pragma unroll
+            for (int sr = 0; sr < 2; sr++) {
+                if ((int)(int8_t)(W.rdst[2 * k + sr] >> (8 * y)) != hib) continue;
+#pragma unroll
+                for (int z = 0; z < 4; z++) {
+                    const int64_t be = R[2 * (q - 1 - k) + sr].beta[z];
+                    bad = bad || (al < kINF && be < kINF &&
+                                  base + W.ru[2 * k + sr][y] + be + fxe(init + L.S.mmH[ht][x2][z]) == hvv);
+                }
+            }
+        }
+        const unsigned long long bm = __ballot(bad);
+        if (bm) {
+            n = first_lane(bm) >> 2;
+            if (n == 0) return false;
+            ia = bcast(__shfl(mia, n, 64));
+            ib = bcast(__shfl(mib, n, 64));
+            t = bcast(__shfl(mt, n, 64));
+            v = readlane64(mv, n);
+        }
+    }
+    if (lane < n) {
+        const int x = kTX[mt], y = kTY[mt], i = p + lane, j = q - 1 - lane;
+        I.tr_seq()[i] = x;
+        I.tr_seq()[j] = y;
+        I.tr_pair()[i] = j;
+        I.tr_pair()[j] = i;
+        Ul += W.lu[2 * lane + mia][x] + W.ru[2 * lane + ms][y];
+        El += L.S.stack[mt][kRev[mtp]];
+    }
+    emitted += 2 * n;
+    go(kFV, bcast(__shfl(lstate, 2 * n + ia, 64)), bcast(__shfl(rstate, 2 * n - 2 + ib, 64)), t);
+    known = true;
+    no_stack = n < kmax;
+    kp = p + n;
+    kq = q - n;
+    kia = ia;
+    kib = ib;
+    kv = v;
+    return true;
+}
+
 // A closed value on the codon trie, inner span >= 5.  A replay is one chain of decisions, so what bounds
 // it is the dependent loads of each: the general functions look states, layers, edges and gaps up one
 // after another (two-loop decision 17 us, hairpin test 3 us at 300 residues).  Here one level of loads
 // brings the slot records of every layer a two-loop can reach, the next one the inner cells, and a helix
 // carries layers, slots and the closed value from pair to pair.  The hairpin is enumerated only if its
 // separable minimum equals v: the value is the minimum over all loops, so nothing else can match.
-// 17 -> 8 us per decision; 50 residues 1.00 -> 0.73 ms between the fill and the result, 300 residues
-// 2.44 -> 2.31, 1,976 residues 19.9 -> 17.8 (there the cells themselves come from beyond the caches).
+// 17 -> 8 us per decision; with the helices above, between the fill and the result: 50 residues 1.00 -> 0.42 ms,
+// 300 residues 2.44 -> 1.16, 1,976 residues 19.9 -> 8.6 (there the cells come from beyond the caches).
 __device__ void Tracer::closed_trie(int a, int b, int t, int p, int q, int ia, int ib, int64_t v) {
     const int g = q - p, m = g - 2, x = kTX[t], y = kTY[t];
     const SlotRec* R = I.recs();
@@ -970,8 +1100,10 @@ __device__ void Tracer::closed(int a, int b, int t) {
             ib = b - bcast(I.off()[q]);
             v = tV(I, t, a, b);
         }
-        known = false;
+        const bool stack = !no_stack;
+        known = no_stack = false;
         if (q - p >= 7) {
+            if (stack && v < kINF && helix(t, p, q, ia, ib, v)) return;
             closed_trie(a, b, t, p, q, ia, ib, v);
             return;
         }
@@ -1169,10 +1301,10 @@ __device__ void trace_instance(const Inst& I, const EnergyTables* __restrict__ E
             default: tr.branch(f.a, f.b); break;
         }
     }
-    if (lane == 0) {
-        atomicAdd(&L.E, (unsigned long long)tr.E);
-        atomicAdd(&L.U, (unsigned long long)tr.U);
-        atomicAdd(&L.emitted, tr.emitted);
+    if (tr.El || tr.Ul || lane == 0) {
+        atomicAdd(&L.E, (unsigned long long)(tr.El + (lane == 0 ? tr.E : 0)));
+        atomicAdd(&L.U, (unsigned long long)(tr.Ul + (lane == 0 ? tr.U : 0)));
+        if (lane == 0) atomicAdd(&L.emitted, tr.emitted);
     }
     __syncthreads();
     if (tid == 0) {
