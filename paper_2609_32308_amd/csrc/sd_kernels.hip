@@ -162,7 +162,10 @@ __device__ __forceinline__ int64_t special_hairpin(const IT& I, const SmallE& S,
         for (int i = nfree - 1; i >= 0 && ok; i--) {
             const int lab = (k >> (2 * i)) & 3, e = st2 * 4 + lab, d = I.out_dst()[e];
             ok = d >= 0;
-            if (!ok) break;
+            if (!ok) {  // no path spells these labels: on to the next label here
+                k |= (1 << (2 * i)) - 1;
+                break;
+            }
             c2 += I.out_U()[e];
             key2 = key2 * 4 + lab;
             st2 = d;
@@ -409,10 +412,11 @@ __device__ __forceinline__ int lane_id() {
     asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
     return l;
 }
+template <int NT>
 struct BlockTeam {
     __device__ int wave() const { return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); }
     __device__ int lane() const { return lane_id(); }
-    __device__ int waves() const { return blockDim.x >> 6; }
+    __device__ static constexpr int waves() { return NT / 64; }
     __device__ void sync() { __syncthreads(); }
 };
 // `n` consecutive waves of a workgroup, ordered by an LDS arrival counter (zero when the team is
@@ -453,6 +457,7 @@ struct GroupShared {
     int64_t abeta[kTrieWidth][4], balpha[kTrieWidth][4]; // beta of the left states, alpha of the right ones
     int64_t btail[kTrieWidth], boff[kTrieWidth];         // right states: tail, candidate segment,
     int bcnt[kTrieWidth], bcap[kTrieWidth];              //   committed count and capacity
+    int task;                         // next task of phase 1 (zero between items)
     int8_t adst[kTrieWidth][4], bdst[kTrieWidth][4];     // the edges' targets by slot (-1 none)
     int8_t keep[kTrieCells];          // 0 none, 1 strict, 2 retained non-strict
 };
@@ -818,8 +823,18 @@ __device__ __forceinline__ GroupCounters span_group(const Inst& I, const SmallE&
     }
     // teams of eight waves or more give the two parts of a closed value to different waves
     const int split = nw >= 8 ? 2 : 1, nclosed = g >= 5 ? wa1 * wb1 * split : 0, nstate = g >= 5 ? wa + wb : 0;
-    const int ntask = nclosed + ncell + nstate + (g + 1 >= 12 && q + 1 <= I.n ? 1 : 0);
-    for (int k0 = wave; k0 < ntask; k0 += nw) {
+    const int nmini = g + 1 >= 12 && q + 1 <= I.n ? 1 : 0, ntask = nclosed + ncell + nmini + nstate;
+    // With more tasks than waves, every wave draws its next one (they differ threefold: closed values and
+    // splits first): 1,976 aa fill 271 -> 252 ms, 925 aa 74.8 -> 70.0, 300 aa 14.7 -> 14.3; with fewer
+    // (sixteen waves: 17 tasks at most) there is nothing to draw, and the counter's latency cost 2.5 % at 50 aa.
+    const bool draw = nw > 1 && nw < 16 && ntask > nw;
+    auto next_task = [&](int k0) {
+        if (!draw) return k0 + nw;
+        int d = 0;
+        if (lane == 0) d = __hip_atomic_fetch_add(&G.task, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        return nw + uni(d);
+    };
+    for (int k0 = wave; k0 < ntask; k0 = next_task(k0)) {
         int k = k0;
         const Inst J = rebased(I);
         if (k < nclosed) {
@@ -846,14 +861,16 @@ __device__ __forceinline__ GroupCounters span_group(const Inst& I, const SmallE&
             continue;
         }
         k -= ncell;
-        if (k < nstate) {
-            const bool left = k < wa;
-            produce_one_sided(J, S, p, q, left, left ? slot_ptr(J)[2 * p + k].state : slot_ptr(J)[2 * q + k - wa].state, lane);
+        if (k < nmini) {
+            prepare_mini(J, S, p, q + 1, lane);
             continue;
         }
-        prepare_mini(J, S, p, q + 1, lane);
+        k -= nmini;
+        const bool left = k < wa;
+        produce_one_sided(J, S, p, q, left, left ? slot_ptr(J)[2 * p + k].state : slot_ptr(J)[2 * q + k - wa].state, lane);
     }
     T.sync();
+    if (draw && wave == 0 && lane == 0) G.task = 0;
     const bool left_role = g >= 5 && (1 % nw) == wave, right_role = g >= 5 && (2 % nw) == wave;
     if (wave != 0 && !left_role && !right_role) return ctr;
     complete_cells(rebased(I), S, p, q, wa, wb, wb1, split, wave == 0, left_role, right_role, lane, G, ctr);
@@ -933,9 +950,10 @@ void k_span(Inst I, const EnergyTables* __restrict__ E, const int32_t* __restric
     __shared__ SmallE S;
     __shared__ GroupShared G[NT / 64];
     stage_begin(S, E);
+    if (threadIdx.x == 0) G[0].task = 0;
     if ((int)blockIdx.x < npairs) prefetch_records(I, xcd_band(blockIdx.x, npairs), g);
     stage_wait();
-    BlockTeam T;
+    BlockTeam<NT> T;
     const int items = npairs + (ext_layer >= 0 ? 1 : 0);
     for (int i = blockIdx.x; i < items; i += gridDim.x) {
         if (i < npairs) {
@@ -973,7 +991,7 @@ __global__ __launch_bounds__(256) void k_ext(Inst I, const EnergyTables* __restr
     __shared__ SmallE S;
     __shared__ GroupShared G[4];
     stage_tables(S, E);
-    BlockTeam T;
+    BlockTeam<256> T;
     ext_column(I, S, L, G, T);
 }
 
@@ -1619,7 +1637,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
     } G;
     stage_tables(S, E);
     if ((int)blockIdx.x >= npairs) {
-        BlockTeam T;
+        BlockTeam<NT> T;
         if (ext_layer >= 0) ext_column(I, S, ext_layer, G.x, T);
         return;
     }
@@ -1807,7 +1825,10 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
     const unsigned grp_blocks = (gridDim.x - grp + 7) >> 3;  // workgroups of this group
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     for (int step = 0; step < nsteps; step++) {
-        if (threadIdx.x < NWV) team_ctr[threadIdx.x] = 0;
+        if (threadIdx.x < NWV) {
+            team_ctr[threadIdx.x] = 0;
+            G[threadIdx.x].task = 0;
+        }
         if (threadIdx.x == 0) s_next = 0;
         step_prefix<NT>(insts, ninst, step, pref, wsum);
         const unsigned total = (unsigned)__builtin_amdgcn_readfirstlane(pref[ninst]);
