@@ -441,6 +441,14 @@ struct WaveTeam {
     }
 };
 
+// A wave by itself.
+struct SoloTeam {
+    __device__ static constexpr int wave() { return 0; }
+    __device__ int lane() const { return lane_id(); }
+    __device__ static constexpr int waves() { return 1; }
+    __device__ void sync() { wave_lds_order(); }
+};
+
 // LDS of one team; a wave's own scratch lies in the element of its own index, so that an array of
 // as many elements as waves serves teams of any size.
 constexpr int kTrieCells = kTrieWidth * kTrieWidth;
@@ -1680,7 +1688,7 @@ __device__ __forceinline__ unsigned xcd_id() { return __builtin_amdgcn_s_getreg(
 
 // Thread 0's share of the barrier state.
 struct BarrierTeam {
-    unsigned xcd = 0, members = 0, xcds = 0, gen = 0;
+    unsigned xcd, members, xcds, gen;
 };
 
 // Waits until `w` no longer holds `old`; false when the wait exceeds its cap or another workgroup has
@@ -1804,7 +1812,8 @@ __device__ __forceinline__ int item_instance(const int* pref, int ninst, int ite
 // workgroup), since a step then takes its longest item's time, and each team's items follow from its index.
 // Tickets of a band drawn by every wave from one word in memory cost 455 ms instead of 430 for 64 proteins
 // of 50-1,000 aa and 70.4 instead of 63.4 for 24 of 50-400; runs of 2, 4, 8 neighbouring items per workgroup
-// 434, 438, 444.  min_team is the schedule's waves per item (1, or all of a 256- or
+// 434, 438, 444.  Waves by themselves have a code path of their own (no team size to carry: 431 -> 414 ms), and
+// the barrier's state lies in LDS (409; 24 proteins 59.7 ms, 7 of 50-150 aa 10.6 -> 10.4).  min_team is the schedule's waves per item (1, or all of a 256- or
 // 512-thread workgroup's).
 template <int NT>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_persistent(
@@ -1818,8 +1827,11 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
     __shared__ unsigned team_ctr[NWV];
     __shared__ int s_flag;
     __shared__ unsigned s_next;
-    BarrierTeam B;
-    if (threadIdx.x == 0) barrier_join(ctl, B);
+    __shared__ BarrierTeam B;  // thread 0's (in LDS: as registers it would be held by every lane)
+    if (threadIdx.x == 0) {
+        B = BarrierTeam();
+        barrier_join(ctl, B);
+    }
     stage_tables(S, E);
     const unsigned grp = blockIdx.x & 7, ngrp = gridDim.x < 8 ? gridDim.x : 8;
     const unsigned grp_blocks = (gridDim.x - grp + 7) >> 3;  // workgroups of this group
@@ -1845,24 +1857,29 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
         // team 1: the workgroup's items, drawn by its waves; larger teams: every grp_blocks * NWV / tw -th item
         const unsigned stride = grp_blocks * (unsigned)(NWV / tw);
         unsigned next = (blockIdx.x >> 3) * (unsigned)(NWV / tw) + (unsigned)(wave / tw);
-        for (;;) {
-            unsigned k = next;
-            if (tw == 1) {
-                unsigned j = 0;
-                if (T.lane() == 0) j = __hip_atomic_fetch_add(&s_next, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                j = __builtin_amdgcn_readfirstlane(j);
-                k = j * grp_blocks + (blockIdx.x >> 3);
-            }
-            if (k >= band) break;
+        auto work = [&](unsigned k, auto& team) {
             const int item = (int)(lo_item + k);
             const int inst = __builtin_amdgcn_readfirstlane(item_instance(pref, ninst, item));
             const Inst I = load_inst(insts + inst);  // a few scalar registers: bases and sizes
             const int local = __builtin_amdgcn_readfirstlane(item - pref[inst]), g = I.g0 + step;
             const int n = I.n, ncell_items = g <= n ? n - g + 1 : 0;
-            if (local < ncell_items) flush_counters(I, span_group(I, S, spec, local, local + g, Gs, T), local, T.lane());
-            else ext_column(I, S, n - g + 1, Gs, T);
-            if (tw > 1) T.sync();  // the team's shared state is free for its next item
-            next += stride;
+            if (local < ncell_items) flush_counters(I, span_group(I, S, spec, local, local + g, Gs, team), local, team.lane());
+            else ext_column(I, S, n - g + 1, Gs, team);
+        };
+        if (tw == 1) {
+            SoloTeam solo;
+            for (;;) {
+                unsigned j = 0;
+                if (solo.lane() == 0) j = __hip_atomic_fetch_add(&s_next, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                const unsigned k = __builtin_amdgcn_readfirstlane(j) * grp_blocks + (blockIdx.x >> 3);
+                if (k >= band) break;
+                work(k, solo);
+            }
+        } else {
+            for (; next < band; next += stride) {
+                work(next, T);
+                T.sync();  // the team's shared state is free for its next item
+            }
         }
         if (!grid_barrier(ctl, B, spin_cap, &s_flag)) return;
         if (blockIdx.x == 0 && threadIdx.x == 0) ctl->steps_done.v = step + 1;
