@@ -20,6 +20,10 @@ struct sd_context {
     bool external = false;  // arena and stream belong to the caller (sd_context_create_external)
     void* staging = nullptr;  // pinned host image of the input region
     size_t staging_bytes = 0;
+    // pinned copy of a design's results; larger ones (from about 400 residues) go through pageable memory,
+    // so that no call has to allocate one
+    static constexpr size_t kResultBytes = 128 << 10;
+    char* rbuf = nullptr;
     struct Sched {
         int grid = 0, threads = 256, item_waves = 4;
     };
@@ -85,7 +89,7 @@ struct InstLayout {
 struct Lattice;
 struct Params;
 InstLayout layout_instance(const Lattice& L, char* A, char* B, Inst& I);
-hipError_t read_stats(const Inst& I, hipStream_t st, unsigned long long out[4]);
+hipError_t read_stats(sd_context* c, const Inst& I, unsigned long long out[4]);
 void stage_inputs(const Lattice& L, const Inst& I, const char* devA, char* image);
 hipError_t launch_init(const Inst& I, hipStream_t st);
 // one span step: threads per workgroup with item_waves = threads / 64 (the waves share each layer

@@ -79,9 +79,9 @@ struct TFrame {
 // Region A (inputs and small mutable state) is cut into units of U bytes, U >= 8 * (N + 2),
 // >= 8 * (n + 2) and >= 8 * (A + 1), a multiple of 256; unit k starts at ra + k * U:
 //   0 layer[N]  1 off[n+2]  2 in_start[N+1]  3 tail[N]  4 pfx[N]  5 P[A+1]  6 hp_init[n+1]
-//   7 rowoff[N]  8 coff[N]  9 ccap[N]  10 ccnt[N]  11 X[N]  12-13 out_dst[4N]  14-17 out_U[4N]
+//   7 rowoff[N]  8 coff[N]  9 ccap[N]  10 inmask[N]  11 X[N]  12-13 out_dst[4N]  14-17 out_U[4N]
 //   18 stats[4], trace results [8..11]
-//   19 visits[n+1]  20 feasible[n+1]  21 inmask[N]  22 tr_seq[n]  23 tr_pair[n]
+//   19 visits[n+1]  20 feasible[n+1]  21 ccnt[N]  22 tr_seq[n]  23 tr_pair[n]
 //   24-25 tr_stack[n+2] (16-byte frames)  26 cstrict[N]
 //   27.. in_src[nE], in_lab[nE], in_U[nE] (each start 8-byte aligned), then for the codon trie
 //        recs[nrec] (64-byte aligned, SlotRec)
@@ -186,17 +186,21 @@ struct Inst {
     __host__ __device__ const int64_t* rowoff() const { return (const int64_t*)ua(7); }
     __host__ __device__ const int64_t* coff() const { return (const int64_t*)ua(8); }
     __host__ __device__ const int* ccap() const { return (const int*)ua(9); }
-    __host__ __device__ int* ccnt() const { return (int*)ua(10); }
+    __host__ __device__ int* ccnt() const { return (int*)ua(21); }
     __host__ __device__ int64_t* X() const { return (int64_t*)ua(11); }
     __host__ __device__ const int* out_dst() const { return (const int*)ua(12); }
     __host__ __device__ const int64_t* out_U() const { return (const int64_t*)ua(14); }
     __host__ __device__ unsigned long long* stats() const { return (unsigned long long*)ua(18); }
     __host__ __device__ unsigned long long* visits() const { return (unsigned long long*)ua(19); }
     __host__ __device__ unsigned long long* feasible() const { return (unsigned long long*)ua(20); }
-    __host__ __device__ const int* inmask() const { return (const int*)ua(21); }
+    __host__ __device__ const int* inmask() const { return (const int*)ua(10); }
     __host__ __device__ int* tr_seq() const { return (int*)ua(22); }
     __host__ __device__ int* tr_pair() const { return (int*)ua(23); }
     __host__ __device__ TFrame* tr_stack() const { return (TFrame*)ua(24); }
+    // everything a finished design returns lies in one range: units 18..23
+    __host__ __device__ const char* results() const { return ua(18); }
+    __host__ __device__ size_t stats_bytes() const { return (size_t)(2 * U + 8 * ((int64_t)n + 1)); }
+    __host__ __device__ size_t results_bytes() const { return (size_t)(5 * U + 4 * (int64_t)n); }
     __host__ __device__ int* cstrict() const { return (int*)ua(26); }
     __host__ __device__ long long* tr_res() const { return (long long*)ua(18) + 8; }
     __host__ __device__ const int* in_src() const { return (const int*)ua(27); }

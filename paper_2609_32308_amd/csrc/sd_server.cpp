@@ -280,7 +280,7 @@ sd_status round_once(sd_server* S) {
             continue;
         }
         unsigned long long stats[4];
-        e = read_stats(a.I, st, stats);
+        e = read_stats(S->ctx, a.I, stats);
         if (e != hipSuccess) return hip_fail(e, "server stats");
         if (ok && stats[2] != ~0ull) {
             // candidate overflow of a predicted reservation: the request goes back to the head
