@@ -453,8 +453,8 @@ hipError_t read_stats(sd_context* c, const Inst& I, unsigned long long out[4]) {
 // Tile of the span step for a span with `pairs` layer pairs when no tuning data decide it: the widest
 // workgroup of which the chip holds one per pair (one of 16 waves per CU, two of 8, four of 4), since
 // a span then takes its slowest pair's time and more waves shorten it; four waves beyond.  Fill times
-// with one tile for every span, 16 / 8 / 4 waves: 50 aa (150 pairs at most) 2.10 / 2.19 / 2.49 ms, 120 aa
-// (360) 5.74 / 5.47 / 6.12 ms, 300 aa (900) 20.5 / 17.1 / 16.7 ms, 925 aa (2,775) 134 / 93 / 79 ms.
+// with one tile for every span, 16 / 8 / 4 waves: 50 aa (150 pairs at most) 1.88 / 1.92 / 2.02 ms, 120 aa
+// (360) 5.24 / 4.85 / 5.01 ms, 300 aa (900) 19.0 / 15.5 / 14.0 ms, 925 aa (2,775) 126 / 87 / 67 ms.
 constexpr int kSpanXwidePerCu = 1, kSpanWidePerCu = 2;
 sd_status run_plain_on(sd_context* c, const Lattice& L, Inst& I, const EnergyTables* Et, const int32_t* spec,
                        int kernel_timing, int64_t* overflow_span);

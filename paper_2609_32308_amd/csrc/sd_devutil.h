@@ -1,6 +1,6 @@
 // Device helpers shared by the span-step kernels and the traceback kernel: pair types, the loop
 // tables staged in LDS, fixed-point and INF arithmetic, wavefront reductions over DPP moves, cell
-// addressing and the codon trie's closed-form gap (Sec. 4.3), and the loop energies of the
+// addressing, and the loop energies of the
 // nearest-neighbour model (Sec. 3).
 #pragma once
 #include <hip/hip_runtime.h>
@@ -15,7 +15,6 @@ namespace sd {
 static __constant__ int kTX[6] = {0, 1, 2, 2, 3, 3};  // 5' base of AU CG GC GU UA UG
 static __constant__ int kTY[6] = {3, 2, 1, 3, 0, 2};  // 3' base
 static __constant__ int kRev[6] = {4, 2, 1, 5, 0, 3}; // type of the reversed pair
-static __constant__ int kPairType[16] = {-1, -1, -1, 0, -1, -1, 1, -1, -1, 2, -1, 3, 4, -1, 5, -1};
 
 // Copies the loop tables to LDS, straight from memory (no registers in between): one KiB per wave and
 // instruction.  stage_wait ends the copy for the whole workgroup; loads that do not need the tables
@@ -62,7 +61,6 @@ __device__ __forceinline__ Inst load_inst(const Inst* p) {
     return rebased(I);
 }
 
-__device__ __forceinline__ int ptype(int x, int y) { return kPairType[x * 4 + y]; }
 __device__ __forceinline__ int32_t au_pen(const SmallE& S, int t) {
     return (t == 1 || t == 2) ? 0 : S.terminal_au;
 }
@@ -127,24 +125,6 @@ __device__ __forceinline__ int64_t wave_min_biased(int64_t v) {
 }
 // minimum over the whole wave (every lane active): about half the instructions of 64-bit compares and selects
 __device__ __forceinline__ int64_t wave_min(int64_t v) { return wave_min_biased(v + kBias) - kBias; }
-
-template <class IT>
-__device__ __forceinline__ int64_t cell_of(const IT& I, int a, int b) {
-    return I.rowoff()[a] + (b - I.off()[I.layer()[a] + 1]);
-}
-
-// Minimum path cost between states of the codon trie (closed form; INF if unreachable).
-template <class IT>
-__device__ __forceinline__ int64_t gap(const IT& I, int a, int b) {
-    int la = I.layer()[a], lb = I.layer()[b];
-    if (la == lb) return a == b ? 0 : kINF;
-    int ka = la / 3, kb = lb / 3;
-    if (ka == kb) {
-        if (la % 3 == 0) return 0;
-        return (I.pfx()[b] >> 2) == I.pfx()[a] ? 0 : kINF;
-    }
-    return I.tail()[a] + I.P()[kb] - I.P()[ka + 1];
-}
 
 __device__ __forceinline__ int32_t bulge_e(const SmallE& S, int t, int tr, int l) {
     return l == 1 ? S.bulge[1] + S.stack[t][tr] : S.bulge[l] + au_pen(S, t) + au_pen(S, tr);

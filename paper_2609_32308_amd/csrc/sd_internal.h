@@ -250,7 +250,6 @@ constexpr int kLMRing = 64;
 constexpr int kMaxWidth = 4;  // states per layer of an abstract DAG (the multiloop test hook)
 constexpr int kGenMaxWidth = 16;  // states per layer of a generic (motif-constrained) lattice
 constexpr int kGenLoopWin = 30;   // layer distances covered by the labelled gap table
-constexpr int kMaxWaves = 16;  // waves per workgroup of the span-step kernels (1024 threads)
 static_assert(sizeof(Inst) % 8 == 0, "instance descriptors are copied as 8-byte words");
 
 // Batched persistent launch: barrier state shared by all workgroups.  Every contended word sits on its

@@ -1,15 +1,14 @@
 // gfx950 kernels of the span wavefront (Sec. 5, Algorithm 1, re-designed for the GPU).
 //
 // One step per span length g.  A team owns one layer pair (p, q = p + g) and therefore every
-// cell (a, b) with a in layer p and b in layer q: a workgroup of 4, 8 or 16 wavefronts, or one
-// wavefront of a workgroup whose waves work on pairs of their own.  It is the only writer of the
-// candidate segments C_b of its right endpoints in this step (the endpoint-ownership rule of
-// Sec. 5), so appends need no atomics and land in start-state order.  Its waves split the
-// (cell, type) jobs of the closed values into parts, and inside a part or a cell the lanes split
-// the enumeration and the candidate-prefix scan of eq. (7), then reduce with wavefront min
-// shuffles.  One extra team fills the external column one layer behind.
+// cell (a, b) with a in layer p and b in layer q: a workgroup of 4, 8 or 16 wavefronts, one wavefront of a
+// workgroup whose waves work on pairs of their own, or 2 to 16 of them.  It is the only writer of
+// the candidate segments C_b of its right endpoints in this step (the endpoint-ownership rule of
+// Sec. 5), so appends need no atomics and land in start-state order.  Its waves share out the closed
+// values of the inner boundary pairs, the candidate scans of eq. (7) and the tables later spans read; after one
+// barrier the cells are completed.  One extra team fills the external column one layer behind.
 // Generic lattices (a forbidden-motif matcher intersected with the codon automaton) have their
-// own span kernels in a section of their own below.
+// own span kernel in a section of its own below.
 //
 // Two-loop closure (stack / bulge / interior, l1 + l2 <= 30).  For a generic interior loop the
 // energy is init(l1+l2) + asymmetry + mm[t][x_{i+1}][x_{j-1}] + mm[t'][x_{l+1}][x_{k-1}]: the
@@ -20,8 +19,8 @@
 //     OUT(a1, b1, t)  [closing-pair side]  +  IN(c, d)  [inner-pair side]  +  layer constants.
 // IN depends on the inner cell only, so its minimum over the states of a layer pair, LM, is
 // stored once per layer pair (ring over the last 64 spans) when that pair is finished; a later
-// cell then needs one lookup per (l1, l2) instead of an enumeration.  Every other (l1, l2)
-// (bulges, 1xn, 1x1/1x2/2x2 tables, segments inside one codon) is enumerated explicitly.
+// cell then needs one lookup per (l1, l2) instead of an enumeration, and one per loop when only one
+// segment separates.  The short segments that do not cross a codon boundary are enumerated.
 #include <hip/hip_runtime.h>
 
 #include <stddef.h>
