@@ -92,8 +92,8 @@ def kernel_source_sha():
     return h.hexdigest()
 
 
-COUNTER_FILES = {"plain300": "k_span_plain300_counters.json", "batch256": "k_persistent_waves_batch256_counters.json",
-                 "motifs": "k_gen_closed_motifs_105aa_counters.json"}
+COUNTER_FILES = {"plain300": "k_span_plain300_counters.json", "batch256": "k_persistent_batch256_counters.json",
+                 "motifs": "k_span_gen_motifs_105aa_counters.json"}
 
 
 def profile_record(name):
@@ -466,13 +466,12 @@ def main():
     fill = sum(r.t_fill_s for s_ in results for r in s_)
     designs = len(items) * args.steps
     counters = profile_record(args.workload)
-    kernel = "k_gen_closed+k_span_gen" if motifs else None
+    kernel = "k_span_gen" if motifs else None
     if batch:
-        # the persistent kernel the settled schedule ran; the committed counters count only if
-        # they were taken on that kernel
+        # the committed counters count only if they were taken on the schedule the tuner settled on
         r0 = results[-1][0]
-        kernel = "k_persistent_waves" if (r0.sched_item_waves == 1 and r0.sched_threads != 64) else "k_persistent"
-        if counters and not counters.get("kernel", "").startswith(kernel + "<"):
+        kernel = "k_persistent"
+        if r0.sched_item_waves != 1 or r0.sched_threads == 64:
             counters = None
     line = {
         "metric": METRIC,
