@@ -1234,8 +1234,8 @@ __device__ __forceinline__ void gen_hairpins(const Inst& I, const SmallE& S, con
             for (int t = 0; t < 6; t++) gen_min(w6 + t, h + fx(S.mmH[t][e.lab][f.lab], s));
         }
     }
-    if (m >= 10)
-        for (int k = tid; k < P.wa1 * P.wb1 * 6; k += nt) {
+    if (m >= 10)  // from the next wave on
+        for (int k = (tid - 64) & (nt - 1); k < P.wa1 * P.wb1 * 6; k += nt) {
             const int t = k % 6, r = k / 6, ia = r / P.wb1, ib = r - ia * P.wb1;
             gen_min(w + k, I.S2()[I.rowbase()[P.a1lo + ia] + P.b1lo + ib] + fx(S.ml_closing + S.ml_intern + au_pen(S, t), s));
         }
@@ -1526,13 +1526,16 @@ __device__ __forceinline__ void gen_span_group(const Inst& I, const SmallE& S, c
     }
     GroupCounters ctr{0, 0};
     __syncthreads();
+    // the loops beside the products: each starts at a wave of its own, since most fill only a few waves and one
+    // wave would otherwise run all of their load chains one after another
+    auto from = [&](int w) { return (tid - 64 * w) & (NT - 1); };
     auto rest = [&]() {
         for (int c0 = wave * 4; c0 < ncell; c0 += NW * 4) {
             const int ci = c0 + (lane >> 4), cv = min(ci, ncell - 1);
             gen_scan(I, G, p, q, a_lo + cv / wb, b_lo + cv % wb, ci, ci < ncell, lane);
         }
-        if (g >= 9) gen_bulges(I, S, P, G, tid, NT);
-        if (g >= 5) gen_hairpins(I, S, P, G.w, tid, NT);
+        if (g >= 9) gen_bulges(I, S, P, G, from(4), NT);
+        if (g >= 5) gen_hairpins(I, S, P, G.w, from(10), NT);
         const int nspec = g == 5 || g == 6 || g == 8 ? ncell * 6 : 0;
         for (int k = wave; k < nspec; k += NW) {
             // hairpins of 3, 4 and 6 bases, whose listed loops depend on the whole label path
@@ -1541,9 +1544,9 @@ __device__ __forceinline__ void gen_span_group(const Inst& I, const SmallE& S, c
             const int64_t v = wave_min(hairpin_lane(I, S, spec, a, b, t, a1, I.out_U()[a * 4 + type_x(t)], p, g, lane));
             if (lane == 0) G.v[k] = v;
         }
-        if (g >= 7) gen_small(I, S, P, G.w, tid, NT);
+        if (g >= 7) gen_small(I, S, P, G.w, from(3), NT);
         // gap table of this span's cells and labelled gaps (later spans read them)
-        for (int ci = tid; ci < ncell; ci += NT) {
+        for (int ci = from(12); ci < ncell; ci += NT) {
             const int a = a_lo + ci / wb, b = b_lo + ci % wb;
             int64_t gv = kINF;
             for (int eb = I.in_start()[b]; eb < I.in_start()[b + 1]; eb++) {
@@ -1555,7 +1558,7 @@ __device__ __forceinline__ void gen_span_group(const Inst& I, const SmallE& S, c
         }
         if (g <= kGenLoopWin) {
             const int f0 = eo[p], nf = eo[p + 1] - f0, i0 = io[q], ni = io[q + 1] - i0;
-            for (int k = tid; k < nf * ni; k += NT) {
+            for (int k = from(13); k < nf * ni; k += NT) {
                 const int f = f0 + k % nf, i = i0 + k / nf;
                 const GenEdge& e = I.gedges()[f];
                 const GenRow& row = I.grows()[i];
