@@ -463,15 +463,35 @@ __device__ bool Tracer::hairpin(int a, int b, int t, int64_t v, int ea, int a1) 
         // lexicographic order: the middle g - 2 bases are the digits of the lane's combination
         const int mid = g - 2, combos = 1 << (2 * mid);
         const int off = m == 3 ? kSpecOff5 : m == 4 ? kSpecOff6 : kSpecOff8;
+        // the bases before the last three are the whole wave's: they are walked once, and a missing label
+        // skips every combination that begins alike (of the 64 beginnings of a 6-base loop a few exist; trying
+        // them all took 78 us)
+        const int np = mid - 2;  // edges walked together: the closing one and mid - 3
         for (int base = 0; base < combos; base += 64) {
+            int st0 = a, key0 = 0, first = 0, miss = -1;
+            int64_t cost0 = 0;
+            for (int i = 0; i < np && miss < 0; i++) {
+                const int lab = i == 0 ? kTX[t] : (base >> (2 * (mid - i))) & 3;
+                const int e = st0 * 4 + lab, d = bcast(I.out_dst()[e]);
+                if (i == 1) first = lab;
+                cost0 += I.out_U()[e];
+                key0 = key0 * 4 + lab;
+                if (d < 0) miss = i;
+                st0 = d;
+            }
+            if (miss == 0) return false;
+            if (miss > 0) {
+                base |= (64 << (2 * (np - 1 - miss))) - 64;
+                continue;
+            }
             const int cmb = base + lane;
             bool ok = false;
             int32_t en = 0;
             if (cmb < combos) {
-                int st = a, key = 0, l1 = 0, lm = 0;
-                int64_t cost = 0;
+                int st = st0, key = key0, l1 = first, lm = 0;
+                int64_t cost = cost0;
                 ok = true;
-                for (int i = 0; i < g && ok; i++) {
+                for (int i = np; i < g && ok; i++) {
                     const int lab = i == 0 ? kTX[t] : i == g - 1 ? kTY[t] : (cmb >> (2 * (mid - i))) & 3;
                     if (i == 1) l1 = lab;
                     if (i == g - 2) lm = lab;
