@@ -70,8 +70,8 @@ typedef struct sd_options {
                               span, autotuned per span band; see span_item_waves), 64, 256, 512
                               or 1024 for every span; anything else gives SD_E_ARG at create */
     int span_item_waves;   /* with span_threads set: 0 (the workgroup's waves share each layer
-                              pair) or 1 with span_threads 256 (every wave on its own pair, four
-                              pairs per workgroup); must be 0 when span_threads is 0          */
+                              pair) or 1 with span_threads 256 (every wave on its own pair,
+                              sixteen to a workgroup); must be 0 when span_threads is 0       */
     int batch_threads;     /* persistent (batched / served) launch: threads per workgroup, 64,
                               256 or 512, with batch_per_cu workgroups per CU; both 0: autotuned */
     int batch_per_cu;
