@@ -1143,7 +1143,7 @@ extern "C" sd_status sd_multiloop_abstract(sd_context* c, int N, const int32_t* 
             L.inmask[x.dst] |= 1 << x.lab;
         }
         for (int v = 0; v < N; v++) L.in_start[v + 1] += L.in_start[v];
-        L.tail.assign(N, 0);
+        L.tail.assign(N, 0);  // row bases (below), as on a generic lattice
         L.pfx.assign(N, 0);
         L.P.assign(2, 0);
         L.hp_init.assign(L.n + 1, 0);
@@ -1154,6 +1154,7 @@ extern "C" sd_status sd_multiloop_abstract(sd_context* c, int N, const int32_t* 
         int64_t cells = 0, slots = 0;
         for (int a = 0; a < N; a++) {
             L.rowoff[a] = cells;
+            L.tail[a] = cells - L.off[layer[a] + 1];
             cells += N - L.off[layer[a] + 1];
             L.coff[a] = slots;
             L.ccap[a] = L.off[layer[a]];

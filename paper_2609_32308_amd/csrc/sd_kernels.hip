@@ -613,41 +613,47 @@ __device__ __forceinline__ int64_t scan_candidates(const int* __restrict__ cc, c
     return s2;
 }
 
-// The split part of one cell (a, b) of layer pair (p, q), by one wave: S2 (eq. 7: in-edge
-// extensions, then the committed prefix of C_b) and P_S; neither depends on the cell's direct cost.
-template <class IT>
-__device__ __forceinline__ void multiloop_scan(const IT& I, int a, int b, int p, int q, int64_t cell, int lane, int committed,
-                               int64_t cbase, int64_t* s2_out, int64_t* ps_out) {
-    // Every edge joins consecutive layers, so the in-edge sources of b are the states of layer q - 1
-    // with an edge to b and the out-edge targets of a lie in layer p + 1: both are inner states of
-    // the pair exactly when g >= 2, and their cells are found without reading their layers.
-    const int g = q - p;
-    const int64_t arow = cell - b;  // cell(a, c) = arow + c for every c
-    const int64_t* __restrict__ S1r = I.S1() + arow;
-    const int64_t* __restrict__ S2r = I.S2() + arow;
+// The split part of one cell (a, b) of layer pair (p, q) on a lattice without slot records: S2 (eq. 7: in-edge
+// extensions, then the committed prefix of C_b) and P_S; neither depends on the cell's direct cost.  Sixteen lanes per
+// cell: a wave takes four at once.
+__device__ __forceinline__ void gen_scan(const Inst& I, int p, int q, int a, int b, bool valid, int lane, int64_t* s2_out, int64_t* ps_out,
+                                         int* committed_out) {
+    const int l16 = lane & 15;
     int64_t s2 = kINF, ps = kINF;
-    if (g >= 2) {
-        const int blo = I.off()[q - 1], n4 = 4 * (I.off()[q] - blo);
-        for (int k = lane; k < n4; k += 64) {
-            const int c = blo + (k >> 2);
-            const int64_t x2 = S2r[c], x1 = S1r[c];
-            if (I.out_dst()[blo * 4 + k] == b) {
-                const int64_t u = I.out_U()[blo * 4 + k] + I.mlbase_fx;
-                s2 = mn(s2, x2 + u);
-                ps = mn(ps, x1 + u);
+    int committed = 0;
+    if (valid) {
+        const int64_t arow = I.rowbase()[a], cbase = I.coff()[b];
+        const int64_t* S1r = I.S1() + arow;
+        const int64_t* S2r = I.S2() + arow;
+        committed = I.ccnt()[b];
+        if (q - p >= 2) {
+            const int j1 = I.in_start()[b + 1];
+            for (int j = I.in_start()[b] + l16; j < j1; j += 16) {
+                const int c = I.in_src()[j];
+                const int64_t u = I.in_U()[j] + I.mlbase_fx;
+                s2 = mn(s2, S2r[c] + u);
+                ps = mn(ps, S1r[c] + u);
+            }
+            if (l16 < 4) {
+                const int ap = I.out_dst()[a * 4 + l16];
+                if (ap >= 0) ps = mn(ps, I.S1()[I.rowbase()[ap] + b] + I.out_U()[a * 4 + l16] + I.mlbase_fx);
             }
         }
-        if (lane < 4) {
-            const int ap = I.out_dst()[a * 4 + lane];
-            if (ap >= 0) ps = mn(ps, I.S1()[I.rowoff()[ap] + (b - I.off()[p + 2])] + I.out_U()[a * 4 + lane] + I.mlbase_fx);
-        }
+        const int* cc = I.cc() + cbase;
+        const int64_t* cB = I.cB() + cbase;
+#pragma unroll 4
+        for (int k = l16; k < committed; k += 16) s2 = mn(s2, S1r[cc[k] & 0x7fffffff] + cB[k]);
     }
-    s2 = norm_inf(wave_min(mn(s2, scan_candidates(I.cc() + cbase, I.cB() + cbase, S1r, committed, lane))));
-    *s2_out = s2;
-    *ps_out = norm_inf(mn(s2, wave_min(ps)));
+    s2 = norm_inf(row_min(s2));
+    ps = norm_inf(mn(s2, row_min(ps)));
+    if (valid && l16 == 0) {
+        *s2_out = s2;
+        *ps_out = ps;
+        *committed_out = committed;
+    }
 }
 
-// The same on the codon trie, from the slot records: ia / ib the slots of a and b in their layers.
+// The same on the codon trie, by one wave, from the slot records: ia / ib the slots of a and b in their layers.
 __device__ __forceinline__ void trie_scan(const Inst& I, int p, int q, int ia, int ib, int lane, int64_t* s2_out, int64_t* ps_out) {
     const SlotPtr rp = slot_ptr(I) + 2 * p, rq = slot_ptr(I) + 2 * q;
     const int b = rq[ib].state;
@@ -673,28 +679,6 @@ __device__ __forceinline__ void trie_scan(const Inst& I, int p, int q, int ia, i
     s2 = norm_inf(wave_min(mn(s2, scan_candidates(I.cc() + cbase, I.cB() + cbase, S1r, committed, lane))));
     *s2_out = s2;
     *ps_out = norm_inf(mn(s2, wave_min(ps)));
-}
-
-// The multiloop part of one cell given its direct branch cost Bv (eq. 2), by one wave: the split
-// part, S1 = min(B, P_S) and the retention test B < P_S (eq. 6).  Lane 0 writes B, S2 and S1 and
-// returns the keep flag: 0 none, 1 strict, 2 retained non-strict (retain-all control).
-template <class IT>
-__device__ int multiloop_cell(const IT& I, int a, int b, int p, int q, int64_t cell, int64_t Bv, int lane,
-                              GroupCounters& ctr) {
-    const int committed = I.ccnt()[b];
-    int64_t s2, ps;
-    multiloop_scan(I, a, b, p, q, cell, lane, committed, I.coff()[b], &s2, &ps);
-    int keep = 0;
-    if (lane == 0) {
-        I.Bt()[cell] = Bv;
-        I.S2()[cell] = s2;
-        I.S1()[cell] = mn(Bv, ps);
-        const bool strict = Bv < ps;
-        keep = I.retain_all ? (Bv < kINF ? (strict ? 1 : 2) : 0) : (strict ? 1 : 0);
-    }
-    ctr.visits += (unsigned long long)committed;
-    ctr.feasible += Bv < kINF;
-    return keep;
 }
 
 // Appends the retained entries (a, B(a, b)) of layer pair (p, q) to the segments C_b in
@@ -1036,26 +1020,36 @@ __global__ void k_init(Inst I) {
 // ---- the multiloop recurrences alone on an abstract layered DAG (test hook) -----------------------
 // Direct branch costs B are given per cell (row layout, in the V array of the instance) instead of
 // coming from loop energies; the unpaired-edge costs are the automaton's edge costs (ML_base 0).
-// One wave per layer pair of span g runs the span step's own multiloop_cell and
+// One wave per layer pair of span g runs the generic span step's own gen_scan and
 // append_candidates: the exact-integer abstract test of Sec. 7.1 on the GPU code path.
 __global__ __launch_bounds__(64) void k_ml_abstract(Inst I, int g) {
-    __shared__ int8_t keep[kMaxWidth * kMaxWidth];
-    __shared__ int64_t cellB[kMaxWidth * kMaxWidth];
+    constexpr int kCells = kMaxWidth * kMaxWidth;
+    __shared__ int8_t keep[kCells];
+    __shared__ int64_t s2[kCells], ps[kCells], cellB[kCells];
+    __shared__ int committed[kCells];
     const int p = blockIdx.x, q = p + g, lane = threadIdx.x;
-    const int a_lo = I.off()[p], wa = I.off()[p + 1] - a_lo, b_lo = I.off()[q], wb = I.off()[q + 1] - b_lo;
+    const int a_lo = I.off()[p], wa = I.off()[p + 1] - a_lo, b_lo = I.off()[q], wb = I.off()[q + 1] - b_lo, ncell = wa * wb;
     GroupCounters ctr{0, 0};
-    for (int ci = 0; ci < wa * wb; ci++) {
-        const int a = a_lo + ci / wb, b = b_lo + ci % wb;
-        const int64_t cell = I.rowoff()[a] + (b - I.off()[p + 1]);
-        const int64_t Bv = I.V()[cell];
-        const int k = multiloop_cell(I, a, b, p, q, cell, Bv, lane, ctr);
-        if (lane == 0) {
-            keep[ci] = k;
-            cellB[ci] = Bv;
-        }
+    for (int c0 = 0; c0 < ncell; c0 += 4) {
+        const int ci = c0 + (lane >> 4), cv = min(ci, ncell - 1);
+        gen_scan(I, p, q, a_lo + cv / wb, b_lo + cv % wb, ci < ncell, lane, s2 + cv, ps + cv, committed + cv);
+    }
+    __syncthreads();
+    if (lane < ncell) {
+        const int64_t cell = I.rowbase()[a_lo + lane / wb] + b_lo + lane % wb, Bv = I.V()[cell];
+        I.Bt()[cell] = Bv;
+        I.S2()[cell] = s2[lane];
+        I.S1()[cell] = mn(Bv, ps[lane]);
+        const bool strict = Bv < ps[lane];
+        keep[lane] = I.retain_all ? (Bv < kINF ? (strict ? 1 : 2) : 0) : (strict ? 1 : 0);
+        cellB[lane] = Bv;
     }
     __syncthreads();
     append_candidates(I, a_lo, wa, b_lo, wb, keep, cellB, g, lane);
+    for (int ci = 0; ci < ncell; ci++) {
+        ctr.visits += (unsigned long long)committed[ci];
+        ctr.feasible += cellB[ci] < kINF;
+    }
     flush_counters(I, ctr, p, lane);
 }
 
@@ -1239,43 +1233,6 @@ __device__ __forceinline__ void gen_hairpins(const Inst& I, const SmallE& S, con
             const int t = k % 6, r = k / 6, ia = r / P.wb1, ib = r - ia * P.wb1;
             gen_min(w + k, I.S2()[I.rowbase()[P.a1lo + ia] + P.b1lo + ib] + fx(S.ml_closing + S.ml_intern + au_pen(S, t), s));
         }
-}
-
-// The split part of cells (S2, P_S), sixteen lanes per cell: a wave takes four at once.
-__device__ __forceinline__ void gen_scan(const Inst& I, GenShared& G, int p, int q, int a, int b, int ci, bool valid, int lane) {
-    const int l16 = lane & 15;
-    int64_t s2 = kINF, ps = kINF;
-    int committed = 0;
-    if (valid) {
-        const int64_t arow = I.rowbase()[a], cbase = I.coff()[b];
-        const int64_t* S1r = I.S1() + arow;
-        const int64_t* S2r = I.S2() + arow;
-        committed = I.ccnt()[b];
-        if (q - p >= 2) {
-            const int j1 = I.in_start()[b + 1];
-            for (int j = I.in_start()[b] + l16; j < j1; j += 16) {
-                const int c = I.in_src()[j];
-                const int64_t u = I.in_U()[j] + I.mlbase_fx;
-                s2 = mn(s2, S2r[c] + u);
-                ps = mn(ps, S1r[c] + u);
-            }
-            if (l16 < 4) {
-                const int ap = I.out_dst()[a * 4 + l16];
-                if (ap >= 0) ps = mn(ps, I.S1()[I.rowbase()[ap] + b] + I.out_U()[a * 4 + l16] + I.mlbase_fx);
-            }
-        }
-        const int* cc = I.cc() + cbase;
-        const int64_t* cB = I.cB() + cbase;
-#pragma unroll 4
-        for (int k = l16; k < committed; k += 16) s2 = mn(s2, S1r[cc[k] & 0x7fffffff] + cB[k]);
-    }
-    s2 = norm_inf(row_min(s2));
-    ps = norm_inf(mn(s2, row_min(ps)));
-    if (valid && l16 == 0) {
-        G.s2[ci] = s2;
-        G.ps[ci] = ps;
-        G.committed[ci] = committed;
-    }
 }
 
 // Stacks, bulges of one base and the loops of the 1x1, 1x2, 2x2 tables: one (left walk, right walk,
@@ -1532,7 +1489,7 @@ __device__ __forceinline__ void gen_span_group(const Inst& I, const SmallE& S, c
     auto rest = [&]() {
         for (int c0 = wave * 4; c0 < ncell; c0 += NW * 4) {
             const int ci = c0 + (lane >> 4), cv = min(ci, ncell - 1);
-            gen_scan(I, G, p, q, a_lo + cv / wb, b_lo + cv % wb, ci, ci < ncell, lane);
+            gen_scan(I, p, q, a_lo + cv / wb, b_lo + cv % wb, ci < ncell, lane, G.s2 + ci, G.ps + ci, G.committed + ci);
         }
         if (g >= 9) gen_bulges(I, S, P, G, from(4), NT);
         if (g >= 5) gen_hairpins(I, S, P, G.w, from(10), NT);
