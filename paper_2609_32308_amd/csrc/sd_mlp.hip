@@ -152,8 +152,9 @@ struct sd_sizer {
     float* M = nullptr;  // Adam first moment
     float* Vm = nullptr; // Adam second moment
     int64_t adam_t = 0;
-    // workspace kept between calls (up to kKeepBytes; larger calls allocate their own): device memory,
-    // pinned staging.  Calls on one sizer hold the mutex, each until its stream has drained.
+    // workspace kept between calls: device memory up to kKeepBytes (larger calls allocate their own), pinned
+    // staging up to kPinBytes (larger calls do without).  Calls on one sizer hold the mutex, each until
+    // its stream has drained.
     std::mutex mu;
     float *dev = nullptr, *pin = nullptr;
     size_t dev_n = 0, pin_n = 0;
@@ -165,6 +166,11 @@ thread_local std::string g_mlp_err;
 int cdiv(int a, int b) { return (a + b - 1) / b; }
 
 constexpr size_t kKeepBytes = (size_t)64 << 20;
+// Staged copies pay for small calls only (prediction, 22 -> 8 -> 8: 500 samples 62 -> 32 us, 2,000 samples 132 ->
+// 43 us).  From 10,000 samples (1.2 MB) on a call takes as long without them, and pinning grows with the
+// call: above 2 MB a sizer's first call took 1.3 ms instead of 0.5, and 600,000 samples 22 ms on every
+// call instead of 3.7.
+constexpr size_t kPinBytes = (size_t)1 << 20;
 
 // Chunks of samples per weight gradient: about 2^18 partial sums keep the chip busy where one thread per
 // weight left all but 20 workgroups idle for n steps (1,800 samples, gradient and prediction: 1.71 ms
@@ -174,21 +180,25 @@ int weight_chunks(int n, int tot) { return std::max(1, std::min(cdiv(n, 32), (1 
 struct Work {
     float *X = nullptr, *Y = nullptr, *H1 = nullptr, *H2 = nullptr, *O = nullptr, *D3 = nullptr,
           *D2 = nullptr, *D1 = nullptr, *part = nullptr, *loss = nullptr;
-    float* pin = nullptr;  // pinned: n * (kFeat + K) floats in, at least 1 + total out
-    float *own_dev = nullptr, *own_pin = nullptr;
+    float* pin = nullptr;  // pinned: n * (kFeat + K) floats in, at least 1 + total out; null: copies from and to the caller's memory
+    float* own_dev = nullptr;
     hipError_t alloc(sd_sizer* z, int n) {
         const int H = z->sh.H, K = z->sh.K;
         size_t parts = 0;
         for (int tot : {K * H + K, H * H + H, H * kFeat + H}) parts = std::max(parts, (size_t)weight_chunks(n, tot) * tot);
         const size_t dn = (size_t)n * (kFeat + K + 4 * H + 2 * K) + parts + 1;
         const size_t pn = std::max((size_t)n * (kFeat + K), (size_t)z->sh.total + 1);
-        hipError_t e = grow(z->dev, z->dev_n, own_dev, dn, [](float** p, size_t b) { return hipMalloc(p, b); },
-                            [](float* p) { return hipFree(p); });
-        if (e == hipSuccess)
-            e = grow(z->pin, z->pin_n, own_pin, pn, [](float** p, size_t b) { return hipHostMalloc((void**)p, b, hipHostMallocDefault); },
+        hipError_t e;
+        if (dn * sizeof(float) > kKeepBytes)
+            e = hipMalloc(&own_dev, dn * sizeof(float));
+        else
+            e = grow(z->dev, z->dev_n, dn, [](float** p, size_t b) { return hipMalloc(p, b); }, [](float* p) { return hipFree(p); });
+        if (e == hipSuccess && pn * sizeof(float) <= kPinBytes) {
+            e = grow(z->pin, z->pin_n, pn, [](float** p, size_t b) { return hipHostMalloc((void**)p, b, hipHostMallocDefault); },
                      [](float* p) { return hipHostFree(p); });
+            pin = z->pin;
+        }
         if (e != hipSuccess) return e;
-        pin = own_pin ? own_pin : z->pin;
         X = own_dev ? own_dev : z->dev;
         Y = X + (size_t)n * kFeat;
         H1 = Y + (size_t)n * K;
@@ -201,11 +211,10 @@ struct Work {
         loss = part + parts;
         return hipSuccess;
     }
-    // the kept buffer if it holds `need` floats, grown up to the limit; beyond it one of this call's own
+    // the kept buffer, grown to hold `need` floats
     template <class A, class F>
-    static hipError_t grow(float*& keep, size_t& keep_n, float*& own, size_t need, A a, F f) {
+    static hipError_t grow(float*& keep, size_t& keep_n, size_t need, A a, F f) {
         if (need <= keep_n) return hipSuccess;
-        if (need * sizeof(float) > kKeepBytes) return a(&own, need * sizeof(float));
         if (keep) f(keep);
         keep = nullptr;
         keep_n = 0;
@@ -214,16 +223,27 @@ struct Work {
         else keep = nullptr;
         return e;
     }
-    // inputs through the pinned buffer in one copy (Y may be null)
+    // inputs, in one copy if they are staged (Yh may be null)
     hipError_t upload(const sd_sizer* z, int n, const float* Xh, const float* Yh, hipStream_t st) {
         const size_t nx = (size_t)n * kFeat, ny = Yh ? (size_t)n * z->sh.K : 0;
+        if (!pin) {
+            hipError_t e = hipMemcpyAsync(X, Xh, nx * sizeof(float), hipMemcpyHostToDevice, st);
+            if (e == hipSuccess && Yh) e = hipMemcpyAsync(X + nx, Yh, ny * sizeof(float), hipMemcpyHostToDevice, st);
+            return e;
+        }
         memcpy(pin, Xh, nx * sizeof(float));
         if (Yh) memcpy(pin + nx, Yh, ny * sizeof(float));
         return hipMemcpyAsync(X, pin, (nx + ny) * sizeof(float), hipMemcpyHostToDevice, st);
     }
+    // `cnt` floats of device memory to `out`, by way of word `at` of the staging; `take` them once the stream has drained
+    hipError_t fetch(float* out, const float* src, size_t at, size_t cnt, hipStream_t st) {
+        return hipMemcpyAsync(pin ? pin + at : out, src, cnt * sizeof(float), hipMemcpyDeviceToHost, st);
+    }
+    void take(float* out, size_t at, size_t cnt) {
+        if (pin) memcpy(out, pin + at, cnt * sizeof(float));
+    }
     ~Work() {
         if (own_dev) hipFree(own_dev);
-        if (own_pin) hipHostFree(own_pin);
     }
 };
 
@@ -335,12 +355,12 @@ extern "C" sd_status sd_sizer_gradient(sd_sizer* z, int n, const float* X, const
     if (e == hipSuccess) e = W.upload(z, n, X, Y, st);
     if (e == hipSuccess) e = fwd_bwd(z, W, n, true, st);
     // (the inputs' copy has left the pinned buffer before the results' copies start: one stream)
-    if (e == hipSuccess) e = hipMemcpyAsync(W.pin, z->G, sizeof(float) * z->sh.total, hipMemcpyDeviceToHost, st);
-    if (e == hipSuccess) e = hipMemcpyAsync(W.pin + z->sh.total, W.loss, sizeof(float), hipMemcpyDeviceToHost, st);
+    if (e == hipSuccess) e = W.fetch(grad, z->G, 0, z->sh.total, st);
+    if (e == hipSuccess) e = W.fetch(loss, W.loss, z->sh.total, 1, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     if (e == hipSuccess) {
-        memcpy(grad, W.pin, sizeof(float) * z->sh.total);
-        *loss = W.pin[z->sh.total];
+        W.take(grad, 0, z->sh.total);
+        W.take(loss, z->sh.total, 1);
     }
     return e == hipSuccess ? SD_OK : mlp_fail(SD_E_DEVICE, hipGetErrorString(e));
 }
@@ -388,9 +408,10 @@ extern "C" sd_status sd_sizer_predict(sd_sizer* z, int n, const float* X, float*
         e = W.upload(z, n, X, nullptr, st);
     }
     if (e == hipSuccess) e = fwd_bwd(z, W, n, false, st);
-    if (e == hipSuccess) e = hipMemcpyAsync(W.pin, W.O, sizeof(float) * n * z->sh.K, hipMemcpyDeviceToHost, st);
+    const size_t outs = (size_t)n * z->sh.K;
+    if (e == hipSuccess) e = W.fetch(Yhat, W.O, 0, outs, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
-    if (e == hipSuccess) memcpy(Yhat, W.pin, sizeof(float) * n * z->sh.K);
+    if (e == hipSuccess) W.take(Yhat, 0, outs);
     return e == hipSuccess ? SD_OK : mlp_fail(SD_E_DEVICE, hipGetErrorString(e));
 }
 

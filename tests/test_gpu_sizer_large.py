@@ -1,0 +1,56 @@
+"""Sizer calls beyond the kept workspaces: small calls are staged through pinned memory, larger ones copy
+from and to the caller's arrays, the largest also allocate device memory of their own.  Every size against
+the FP64 reference, small calls between large ones on one sizer, and no size class that is slow for its
+number of samples."""
+import time
+
+import numpy as np
+import pytest
+
+from oracle import mlp_ref as R
+from tests.test_sizer import _magnitudes
+
+pytestmark = pytest.mark.gpu
+
+
+# staging ends at 2^18 floats in and out, kept device memory at 2^24 floats: per sample 22 + K and
+# 22 + 3 K + 4 H of them
+@pytest.mark.parametrize("H,K,sizes", [(4, 2, (100, 10922, 10923, 381000, 390000, 99)), (64, 8, (8738, 8739, 51000, 58000, 50))])
+def test_predictions_around_the_limits(H, K, sizes):
+    import paper_2609_32308_amd as sd
+    ctx = sd.Context(0)
+    z = sd.Sizer(ctx, H, K, seed=5)
+    flat = z.get_params()
+    for n in sizes:
+        print("sizer", H, K, "samples", n, flush=True)
+        X = np.random.default_rng(n).random((n, 22)).astype(np.float32)
+        Y = np.full((n, K), 0.25, np.float32)
+        _, _, ry = R.loss_and_grad(flat, X, Y, H, K)
+        _, mag_y, _ = _magnitudes(flat, X, Y, H, K)
+        # FP32 rounding of each term and sum, per entry
+        assert np.all(np.abs(z.predict(X) - ry) <= 4 * (H + 26) * 2.0 ** -24 * mag_y + 2e-7)
+        loss, g = z.gradient(X, Y)
+        l2, g2 = z.gradient(X, Y)
+        assert loss == l2 and np.array_equal(g, g2)
+        assert abs(loss - np.mean((ry - Y) ** 2)) <= 1e-5 * max(1e-3, loss)
+    ctx.close()
+
+
+def test_time_grows_with_the_samples():
+    # a prediction copies 120 bytes per sample; pinning those on every call took six times as long
+    import paper_2609_32308_amd as sd
+    ctx = sd.Context(0)
+    z = sd.Sizer(ctx, 8, 8, seed=5)
+    best = {}
+    for n in (100000, 600000):
+        X = np.random.default_rng(n).random((n, 22)).astype(np.float32)
+        z.predict(X)
+        ts = []
+        for _ in range(7):
+            t0 = time.perf_counter()
+            z.predict(X)
+            ts.append(time.perf_counter() - t0)
+        best[n] = min(ts)
+        print("sizer", n, best[n], flush=True)
+    ctx.close()
+    assert best[600000] <= 3 * 6 * best[100000]
