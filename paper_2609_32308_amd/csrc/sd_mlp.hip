@@ -174,8 +174,10 @@ constexpr size_t kPinBytes = (size_t)1 << 20;
 
 // Chunks of samples per weight gradient: about 2^18 partial sums keep the chip busy where one thread per
 // weight left all but 20 workgroups idle for n steps (1,800 samples, gradient and prediction: 1.71 ms
-// with that and buffers allocated per call, 0.21 ms now); at least 32 samples each, so that the chunk sum stays the smaller part.
-int weight_chunks(int n, int tot) { return std::max(1, std::min(cdiv(n, 32), (1 << 18) / tot)); }
+// with that and buffers allocated per call, 0.17 ms now); at least 32 samples each, so that the chunk sum stays the smaller part.
+// A launch takes at most 65,535 workgroups in y, which networks of four parameters or fewer per layer would pass.
+constexpr int kMaxChunks = 65535;
+int weight_chunks(int n, int tot) { return std::max(1, std::min(std::min(cdiv(n, 32), (1 << 18) / tot), kMaxChunks)); }
 
 struct Work {
     float *X = nullptr, *Y = nullptr, *H1 = nullptr, *H2 = nullptr, *O = nullptr, *D3 = nullptr,

@@ -36,6 +36,26 @@ def test_predictions_around_the_limits(H, K, sizes):
     ctx.close()
 
 
+def test_smallest_network_with_the_most_samples():
+    # two parameters in the last layer: more chunks of 32 samples than a launch has workgroups in y
+    import paper_2609_32308_amd as sd
+    n, H, K = 65535 * 32 + 40000, 1, 1
+    ctx = sd.Context(0)
+    z = sd.Sizer(ctx, H, K, seed=5)
+    flat = z.get_params()
+    rng = np.random.default_rng(3)
+    X, Y = rng.random((n, 22), np.float32), rng.random((n, K), np.float32)
+    print("sizer", H, K, "samples", n, flush=True)
+    loss, g = z.gradient(X, Y)
+    rl, rg, _ = R.loss_and_grad(flat, X, Y, H, K)
+    mag, _, _ = _magnitudes(flat, X, Y, H, K)
+    # a chunk's sum, then the chunks' sums, and the terms of each sample
+    tol = 4 * (64 + 65535 + 22) * 2.0 ** -24 * mag + 1e-12
+    assert abs(loss - rl) <= 1e-3 * rl
+    assert np.all(np.abs(g - rg) <= tol), (g - rg, tol)
+    ctx.close()
+
+
 def test_time_grows_with_the_samples():
     # a prediction copies 120 bytes per sample; pinning those on every call took six times as long
     import paper_2609_32308_amd as sd
