@@ -90,9 +90,11 @@ __device__ __forceinline__ int64_t readlane64(int64_t v, int l) {
     const int hi = __builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)v >> 32), l);
     return (int64_t)(((uint64_t)(uint32_t)hi << 32) | (uint64_t)(uint32_t)lo);
 }
-// Minimum of two int64 in [2^52, 2^63 - 2^53): positive patterns of finite doubles order as the integers do,
+// Minimum of two int64 in [0, 2^63 - 2^52): positive patterns of finite doubles order as the integers do,
 // so one instruction replaces a compare and two selects.  kBias brings every value of the tables and
-// their sums (finite ones within 2^60, infinite ones up to 2^62 and a little) into that range.
+// their sums into that range: finite ones, sums of unfinished loops included, lie strictly between -2^60 and
+// 2^60 (see energy_bound; patterns below 2^52 are denormal doubles, which the FP64 mode of every kernel
+// keeps), infinite ones reach 2^62 and a little.
 constexpr int64_t kBias = (int64_t)1 << 60;
 __device__ __forceinline__ int64_t min_positive(int64_t a, int64_t b) {
     int64_t r;

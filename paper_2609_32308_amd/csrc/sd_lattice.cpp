@@ -361,6 +361,15 @@ void layout_rows(Lattice& L, const CapPolicy& cp) {
 // The loop range covers hairpins of every size up to n (initiation plus a terminal AU or a
 // mismatch, or a listed special loop), stacks, bulges, the interior-loop tables and generic
 // interior loops (initiation, Ninio asymmetry, two mismatches), and the multiloop closing pair.
+//
+// The bound also holds for the sums the kernels compare before a loop is whole: an inner value plus one
+// mismatch or AU term, plus initiation, asymmetry and one mismatch, plus a bulge with one AU term, or
+// plus a multiloop's closing and branch terms.  What is added lies in [min(0, lo), max(0, hi)], or is a
+// single mismatch or AU term, no larger than max(-lo, hi) because hi - lo spans two of them; and the pair
+// that it would close is one the inner value has not used: with three unpaired bases in every hairpin n
+// nucleotides hold at most (n - 3) / 2 pairs, at least one fewer than the n / 2 counted.  So under the range
+// rule every compared value, partial or whole, lies strictly between -2^60 and 2^60: the kernels' biased
+// minima (min_positive) and the limit that tells finite from infinite sums (kGenBig) rely on both sides.
 static int64_t energy_bound(const Params& P, int n) {
     const EnergyTables& E = P.E;
     int64_t lo = INT64_MAX, hi = INT64_MIN;
