@@ -73,13 +73,16 @@ typedef struct sd_options {
                               pair) or 1 with span_threads 256 (every wave on its own pair,
                               sixteen to a workgroup); must be 0 when span_threads is 0       */
     int batch_threads;     /* persistent (batched / served) launch: threads per workgroup, 64,
-                              256 or 512, with batch_per_cu workgroups per CU; both 0: autotuned */
+                              256 or 512, with batch_per_cu workgroups per CU; both 0: autotuned
+                              (a server: 256 and full residency).  2 or 4 workgroups of 256
+                              threads per CU run as one of 512 or 1024 (the same waves)        */
     int batch_per_cu;
-    int batch_item_waves;  /* with batch_threads set: waves per work item (layer pair) of the
-                              persistent launch -- 0 or threads / 64 (the workgroup's waves
-                              share each item), or 1 with 64 or 256 threads (every wave works on
-                              its own items); must be 0 when batch_threads is 0; anything else
-                              gives SD_E_ARG at create                                        */
+    int batch_item_waves;  /* with batch_threads set: least waves per work item (layer pair) of
+                              the persistent launch -- 0 or threads / 64 (a team of as many
+                              waves shares each item), or 1 with 64 or 256 threads (a wave by
+                              itself); in a step with fewer items than teams the teams grow, up
+                              to the workgroup.  Must be 0 when batch_threads is 0; anything
+                              else gives SD_E_ARG at create                                   */
     int span_check;        /* debug mode (race detection): 1 = plain designs run every span step
                               twice, the second time with another workgroup size after restoring
                               the committed candidate counts and the counters, and compare digests
@@ -118,11 +121,11 @@ typedef struct sd_result {
     int32_t path;            /* which forward fill produced the result (sd_path below)         */
     int32_t graph_captured;  /* 1 if that fill was a persistent launch replayed from a captured
                                 hipGraph, else 0                                               */
-    int32_t sched_threads;   /* persistent launch behind the result: threads per workgroup
-                                (0 for the plain paths)                                        */
-    int32_t sched_grid;      /* ... and its workgroup count (resident workgroups per CU times
+    int32_t sched_threads;   /* schedule of the persistent launch behind the result, in the terms
+                                of sd_options: threads per workgroup (0 for the plain paths)   */
+    int32_t sched_grid;      /* ... its workgroup count (resident workgroups per CU times
                                 the CU count; 0 for the plain paths)                           */
-    int32_t sched_item_waves;/* ... and its waves per work item (0 for the plain paths)        */
+    int32_t sched_item_waves;/* ... and its least waves per work item (0 for the plain paths)  */
     int32_t sched_tuned;     /* 1 if that schedule was fixed by the caller or is the autotuner's
                                 settled choice for the batch's size class; 0 while the tuner
                                 still explores (it runs one candidate per call).  Plain results:

@@ -1844,6 +1844,13 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
     }
 }
 
+// The schedules of full residency need four 256-thread workgroups of 160 KB of LDS per CU: launch_persistent
+// runs 4 (or 2) per CU as one workgroup, and three would stay 768 workgroups that all arrive at the
+// grid barrier (31 us per step against 4.8).  64 bytes for what the alignment of the arrays takes.
+static_assert(4 * (sizeof(SmallE) + 4 * (sizeof(GroupShared) + sizeof(unsigned)) + (kMaxBatch + 1) * sizeof(int) + sizeof(int) +
+                   sizeof(unsigned) + sizeof(BarrierTeam) + 64) <= 160 << 10,
+              "four 256-thread workgroups of k_persistent fit a CU's LDS");
+
 // Resets the barrier state and initialises every instance whose g0 is 1 (new instances): gridDim.y
 // workgroups per instance.  The rings are 31 KB per state, so one workgroup per instance took 1.3 ms for 64
 // proteins of 50-1,000 aa and 0.18 ms for 7 of 50-150.
