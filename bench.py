@@ -85,9 +85,12 @@ def workload(name):
     raise SystemExit(f"unknown workload {name}")
 
 
+KERNEL_SOURCES = ("sd_kernels.hip", "sd_internal.h", "sd_devutil.h")  # the span kernels and the headers they include
+
+
 def kernel_source_sha():
     h = hashlib.sha256()
-    for f in ("sd_kernels.hip", "sd_internal.h"):
+    for f in KERNEL_SOURCES:
         h.update(open(os.path.join(ROOT, "paper_2609_32308_amd", "csrc", f), "rb").read())
     return h.hexdigest()
 
