@@ -36,6 +36,40 @@ def test_predictions_around_the_limits(H, K, sizes):
     ctx.close()
 
 
+def rows_clear_of_kinks(n, K, flat, H, seed):
+    """Random rows whose FP64 pre-activations all sit clear of the ReLU kink."""
+    W1, b1, W2, b2, _, _ = R.unpack(flat, H, K)
+    rng = np.random.default_rng(seed)
+    X = np.zeros((0, 22), np.float32)
+    while len(X) < n:
+        x = rng.random((4 * n, 22)).astype(np.float32)
+        z1 = x.astype(np.float64) @ W1.T + b1
+        z2 = np.maximum(z1, 0.0) @ W2.T + b2
+        X = np.concatenate([X, x[np.minimum(np.abs(z1).min(1), np.abs(z2).min(1)) > 1e-4]])
+    return X[:n], rng.random((n, K)).astype(np.float32)
+
+
+# a layer of H * H + H sums is split into at most 2^18 / (H * H + H) chunks: 6 of up to 33, 34 and 67
+# samples, the last one ragged; 63 of up to 72
+@pytest.mark.parametrize("H,K,n", [(200, 1, 193), (200, 1, 200), (200, 1, 400), (64, 8, 4500)])
+def test_gradient_with_as_many_chunks_as_allowed(H, K, n):
+    import paper_2609_32308_amd as sd
+    ctx = sd.Context(0)
+    z = sd.Sizer(ctx, H, K, seed=3)
+    flat = z.get_params()
+    X, Y = rows_clear_of_kinks(n, K, flat, H, n)
+    print("sizer", H, K, "samples", n, flush=True)
+    loss, g = z.gradient(X, Y)
+    rl, rg, _ = R.loss_and_grad(flat, X, Y, H, K)
+    mag, _, _ = _magnitudes(flat, X, Y, H, K)
+    assert abs(loss - rl) <= 1e-5 * max(1e-3, abs(rl))
+    # FP32 rounding of each term and sum, per entry, as for the chunks of 32 samples
+    tol = 4 * (max(n, H, 22) + 4) * 2.0 ** -24 * mag + 1e-4 * np.abs(rg) + 1e-12
+    bad = np.flatnonzero(np.abs(g - rg) > tol)
+    assert bad.size == 0, (bad[:10], g[bad[:10]], rg[bad[:10]])
+    ctx.close()
+
+
 def test_smallest_network_with_the_most_samples():
     # two parameters in the last layer: more chunks of 32 samples than a launch has workgroups in y
     import paper_2609_32308_amd as sd
