@@ -12,7 +12,7 @@ SOURCES = ["sd_kernels.hip", "sd_trace.hip", "sd_mlp.hip", "sd_api.cpp", "sd_ser
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-         "-Wall", "-Wno-unused-function", "-Wno-unused-variable", "-Wno-unused-value",
+         "-Wall", "-Wno-unused-value",
          "-Wno-unused-result"]
 
 

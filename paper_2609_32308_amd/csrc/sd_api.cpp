@@ -571,7 +571,7 @@ sd_status run_plain_on(sd_context* c, const Lattice& L, Inst& I, const EnergyTab
         if (timed && e == hipSuccess) e = hipEventRecord(c->tev[2 * (g - 1)], st);
         const SpanTile tile = tile_for(L.n - g + 1);
         if (e == hipSuccess && L.generic)
-            e = launch_span_gen(I, Et, spec, g, ext, c->num_cu, st);
+            e = launch_span_gen(I, Et, spec, g, ext, st);
         else if (e == hipSuccess)
             e = launch_span(I, Et, spec, g, ext, tile.threads, tile.item_waves, c->num_cu, st);
         if (timed && e == hipSuccess) e = hipEventRecord(c->tev[2 * (g - 1) + 1], st);

@@ -109,7 +109,7 @@ hipError_t launch_checksum(const Inst& I, int g, unsigned long long* out, hipStr
 // strict candidates per right endpoint into cstrict (retain-all control)
 hipError_t launch_strict_count(const Inst& I, hipStream_t st);
 hipError_t launch_span_gen(const Inst& I, const EnergyTables* E, const int32_t* spec, int g,
-                           int ext_layer, int num_cu, hipStream_t st);
+                           int ext_layer, hipStream_t st);
 hipError_t launch_batch_init(const Inst* insts_dev, int ninst, BatchCtl* ctl, hipStream_t st);
 // persistent schedules: (64, 1), (256, 4), (256, 1), (512, 8) as (threads, waves per work item)
 bool persistent_schedule_valid(int threads, int item_waves);

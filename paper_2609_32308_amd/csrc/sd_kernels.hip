@@ -41,7 +41,7 @@ __device__ __forceinline__ constexpr int type_rev(int t) { return t == 0 ? 4 : t
 // ---- hairpin closure ------------------------------------------------------------------------
 template <class IT>
 __device__ int64_t hairpin_lane(const IT& I, const SmallE& S, const int32_t* __restrict__ spec,
-                                int a, int b, int t, int a1, int64_t Ua, int la, int g, int lane) {
+                                int b, int t, int a1, int64_t Ua, int g, int lane) {
     const int m = g - 2, s = I.shift;
     const int x = kTX[t], y = kTY[t];
     int64_t best = kINF;
@@ -784,7 +784,7 @@ template <class Team>
 __device__ __forceinline__ GroupCounters span_group(const Inst& I, const SmallE& S, const int32_t* __restrict__ spec, int p, int q,
                                     GroupShared* Gs, Team& T) {
     // Gs: the team's elements, one per wave; the first holds the pair's shared state
-    const int g = q - p, s = I.shift;
+    const int g = q - p;
     const int wave = T.wave(), lane = T.lane(), nw = T.waves();
     GroupShared& G = Gs[0];
     GroupCounters ctr{0, 0};
@@ -1148,8 +1148,6 @@ constexpr int kGenGroup = 8;   // left edges per task
 constexpr int kGenRows = 16;   // rows per unit
 constexpr int kGenTasks = 16;  // (eight left edges, 64 right edges) per round
 
-typedef const __attribute__((address_space(4))) GenEdge* GenEdgePtr;
-typedef const __attribute__((address_space(4))) GenRow* GenRowPtr;
 typedef const __attribute__((address_space(4))) int* IntPtr;
 typedef const __attribute__((address_space(4))) int64_t* LongPtr;
 
@@ -1308,9 +1306,7 @@ __device__ __forceinline__ void gen_small(const Inst& I, const SmallE& S, const 
 template <int NT, class F>
 __device__ __forceinline__ void gen_products(const Inst& I, const SmallE& S, const GenPair& P, GenShared& G, int wave, int lane, F rest) {
     constexpr int NW = NT / 64;
-    const GenEdgePtr E = (GenEdgePtr)(uintptr_t)I.gedges();
-    const GenRowPtr R = (GenRowPtr)(uintptr_t)I.grows();
-    const IntPtr eo = (IntPtr)(uintptr_t)I.geoff(), io = (IntPtr)(uintptr_t)I.groff();
+    const IntPtr eo = (IntPtr)(uintptr_t)I.geoff();
     const LongPtr LG4 = (LongPtr)(uintptr_t)I.LG();
     const int s = I.shift, g1 = P.g - 2, win = I.win, smax = min(kGenLoopWin, g1 - 5);
     // right edges of the parts (inner span >= 5), blocks of 64 of each
@@ -1444,8 +1440,6 @@ __device__ __forceinline__ void gen_span_group(const Inst& I, const SmallE& S, c
     constexpr int NW = NT / 64;
     const IntPtr off = (IntPtr)(uintptr_t)I.off(), eo = (IntPtr)(uintptr_t)I.geoff(), io = (IntPtr)(uintptr_t)I.groff(),
                  re = (IntPtr)(uintptr_t)I.growedge();
-    const GenEdgePtr E = (GenEdgePtr)(uintptr_t)I.gedges();
-    const GenRowPtr R = (GenRowPtr)(uintptr_t)I.grows();
     const int a_lo = off[p], wa = off[p + 1] - a_lo, b_lo = off[q], wb = off[q + 1] - b_lo, ncell = wa * wb;
     GenPair P;
     P.p = p;
@@ -1498,7 +1492,7 @@ __device__ __forceinline__ void gen_span_group(const Inst& I, const SmallE& S, c
             // hairpins of 3, 4 and 6 bases, whose listed loops depend on the whole label path
             const int t = k % 6, ci = k / 6, a = a_lo + ci / wb, b = b_lo + ci % wb, a1 = I.out_dst()[a * 4 + type_x(t)];
             if (a1 < 0) continue;
-            const int64_t v = wave_min(hairpin_lane(I, S, spec, a, b, t, a1, I.out_U()[a * 4 + type_x(t)], p, g, lane));
+            const int64_t v = wave_min(hairpin_lane(I, S, spec, b, t, a1, I.out_U()[a * 4 + type_x(t)], g, lane));
             if (lane == 0) G.v[k] = v;
         }
         if (g >= 7) gen_small(I, S, P, G.w, from(3), NT);
@@ -1854,7 +1848,7 @@ static_assert(4 * (sizeof(SmallE) + 4 * (sizeof(GroupShared) + sizeof(unsigned))
 // Resets the barrier state and initialises every instance whose g0 is 1 (new instances): gridDim.y
 // workgroups per instance.  The rings are 31 KB per state, so one workgroup per instance took 1.3 ms for 64
 // proteins of 50-1,000 aa and 0.18 ms for 7 of 50-150.
-__global__ void k_batch_init(const Inst* __restrict__ insts, int ninst, BatchCtl* ctl) {
+__global__ void k_batch_init(const Inst* __restrict__ insts, BatchCtl* ctl) {
     const Inst I = load_inst(insts + blockIdx.x);
     const int tid = blockIdx.y * blockDim.x + threadIdx.x, nt = gridDim.y * blockDim.x;
     if (blockIdx.x == 0 && tid < kMaxXcd) {
@@ -1930,9 +1924,9 @@ hipError_t launch_span(const Inst& I, const EnergyTables* E, const int32_t* spec
     return hipGetLastError();
 }
 
-// one span step on a generic lattice (same grid as launch_span)
+// one span step on a generic lattice: a workgroup per layer pair, and one for the external column
 hipError_t launch_span_gen(const Inst& I, const EnergyTables* E, const int32_t* spec, int g,
-                           int ext_layer, int num_cu, hipStream_t st) {
+                           int ext_layer, hipStream_t st) {
     const int layers = I.n - g + 1;
     const int nblk = layers > 0 ? layers : 0;
     const int total = nblk + (ext_layer >= 0 ? 1 : 0);
@@ -1944,7 +1938,7 @@ hipError_t launch_span_gen(const Inst& I, const EnergyTables* E, const int32_t* 
 hipError_t launch_batch_init(const Inst* insts_dev, int ninst, BatchCtl* ctl, hipStream_t st) {
     if (ninst <= 0) return hipSuccess;
     const int parts = std::max(1, 1024 / ninst);
-    hipLaunchKernelGGL(k_batch_init, dim3(ninst, parts), dim3(256), 0, st, insts_dev, ninst, ctl);
+    hipLaunchKernelGGL(k_batch_init, dim3(ninst, parts), dim3(256), 0, st, insts_dev, ctl);
     return hipGetLastError();
 }
 

@@ -636,7 +636,7 @@ int build_lattice(const char* protein, const CodonTable& T, const Params& P, dou
 // Edge, walk and row lists of a generic lattice, and the extents of its LG and IN tables.
 static void build_generic_tables(Lattice& L) {
     const int n = L.n, N = L.N;
-    std::vector<int> row4((size_t)4 * N, -1), first_edge((size_t)4 * N, -1);
+    std::vector<int> row4((size_t)4 * N, -1);
     L.goff.assign(3 * (size_t)(n + 2), 0);
     int* eo = L.goff.data();
     int* io = eo + n + 2;
@@ -657,7 +657,6 @@ static void build_generic_tables(Lattice& L) {
             for (int x = 0; x < 4; x++) {
                 const int d = L.out_dst[(size_t)4 * u + x];
                 if (d < 0) continue;
-                first_edge[(size_t)4 * u + x] = (int)L.gedges.size();
                 const int r = row4[(size_t)4 * d + x];
                 L.gedges.push_back(GenEdge{u, d, x, l, L.out_U[(size_t)4 * u + x], r, 0});
                 L.grows[r].cnt++;
