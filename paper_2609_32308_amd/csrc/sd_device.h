@@ -20,8 +20,9 @@ struct sd_context {
     bool external = false;  // arena and stream belong to the caller (sd_context_create_external)
     void* staging = nullptr;  // pinned host image of the input region
     size_t staging_bytes = 0;
-    // pinned copy of a design's results; larger ones (from about 400 residues) go through pageable memory,
-    // so that no call has to allocate one
+    // pinned copy of a design's results (five units of region A and the partners, 212 bytes per residue at
+    // most); larger ones, of designs from 600 to 900 residues on, go through pageable memory, so that no
+    // call has to allocate one
     static constexpr size_t kResultBytes = 128 << 10;
     char* rbuf = nullptr;
     struct Sched {

@@ -930,8 +930,9 @@ __device__ __forceinline__ void prefetch_records(const Inst& I, int p, int g) {
 // ---- the span step (plain mode) ----------------------------------------------------------------
 // Items are the span's layer pairs (item x is pair xcd_band(x)), then the external column.  A span
 // with more items than the chip holds workgroups runs as many workgroups as it holds, each taking
-// every gridDim.x-th item with one staging of the energy tables.  Held to 128 VGPRs, without spills: four
-// workgroups of 256 threads fit a CU, two of 512.  With 148 VGPRs (three) the 1,976-aa fill took 384 ms
+// every gridDim.x-th item with one staging of the energy tables.  Held to 128 VGPRs: four workgroups of 256
+// threads fit a CU, two of 512.  (k_span<512> spills two VGPRs, the others none; about 230 scalar registers
+// go to vector lanes.)  With 148 VGPRs (three) the 1,976-aa fill took 384 ms
 // instead of 324; one staging per resident workgroup, direct copies to LDS and the records brought
 // to L2 beside them made it 279 ms (300 aa 17.7 -> 16.7 ms).
 template <int NT>
@@ -1137,10 +1138,10 @@ __global__ void k_checksum(Inst I, int g, unsigned long long* out) {
 // a handful of rows; stacks, bulges of one base and the tabulated 1x1, 1x2, 2x2 loops enumerate the
 // label walks of up to two edges on both sides.
 // One workgroup of sixteen waves per layer pair (one per CU: 143 KB of LDS).  What bounds a span is the chain
-// of loads and barriers of its widest pair: about 22 us for pairs of ten states (left product 7, right product 4.5,
-// the loops beside them 13 in parallel shares), 10 us where layers hold two.  105 residues under 16 motifs
-// (3.1 states per layer, up to 10): 600 us per span with a (cell, type) per wave and job tickets, 110 us with
-// these products on eight waves, 45 us as it is; 31 residues under 5 motifs: 205 -> 30 us.
+// of loads and barriers of its widest pair, and more than 256 pairs take a second round.  105 residues under
+// 16 motifs (3.1 states per layer, up to 10): a launch takes 58 us on average with 166 to 285 pairs, 37 with 66
+// to 115, 23 with five or fewer; over all spans 45 us, against 110 with these products on eight waves and 600
+// with a (cell, type) per wave and job tickets.  31 residues under 5 motifs: 205 -> 30 us.
 // Infinite operands: LG is kINF, IN and the accumulators kHalfINF, finite values lie within 2^60, so a
 // sum of all three neither overflows nor falls below kGenBig.
 constexpr int64_t kGenBig = kHalfINF >> 1;
@@ -1757,8 +1758,9 @@ __device__ __forceinline__ int item_instance(const int* pref, int ninst, int ite
 // Tickets of a band drawn by every wave from one word in memory cost 455 ms instead of 430 for 64 proteins
 // of 50-1,000 aa and 70.4 instead of 63.4 for 24 of 50-400; runs of 2, 4, 8 neighbouring items per workgroup
 // 434, 438, 444.  Waves by themselves have a code path of their own (no team size to carry: 431 -> 414 ms), and
-// the barrier's state lies in LDS (409; 24 proteins 59.7 ms, 7 of 50-150 aa 10.6 -> 10.4).  min_team is the schedule's waves per item (1, or all of a 256- or
-// 512-thread workgroup's).
+// the barrier's state lies in LDS (409; 24 proteins 59.7 ms, 7 of 50-150 aa 10.6 -> 10.4).  At 128 VGPRs, eight of
+// them spilled (36 B of scratch per lane) and 450 scalar registers in vector lanes.  min_team is the schedule's waves
+// per item (1, or all of a 256- or 512-thread workgroup's).
 template <int NT>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_persistent(
     const Inst* __restrict__ insts, int ninst, int nsteps, const EnergyTables* __restrict__ E,

@@ -415,8 +415,8 @@ extern "C" sd_status sd_server_start(sd_context* ctx, const sd_codon_table* tabl
         return fail(SD_E_NOMEM, "server pool allocation");
     }
     S->pool.init(cfg->pool_bytes);
-    // the schedule: fixed by the caller (validated at context creation), else chosen per round
-    // from the mix (round_once) between the full-residency grids of the two 256-thread schedules
+    // the schedule: fixed by the caller (validated at context creation), else full residency of independent
+    // waves
     if (ctx->opt.batch_threads > 0) {
         S->threads = ctx->opt.batch_threads;
         S->grid = ctx->opt.batch_per_cu * ctx->num_cu;

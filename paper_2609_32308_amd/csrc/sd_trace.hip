@@ -900,8 +900,9 @@ __device__ bool Tracer::helix(int t, int p, int q, int ia, int ib, int64_t v) {
 // brings the slot records of every layer a two-loop can reach, the next one the inner cells, and a helix
 // carries layers, slots and the closed value from pair to pair.  The hairpin is enumerated only if its
 // separable minimum equals v: the value is the minimum over all loops, so nothing else can match.
-// 17 -> 8 us per decision; with the helices above, between the fill and the result: 50 residues 1.00 -> 0.42 ms,
-// 300 residues 2.44 -> 1.16, 1,976 residues 19.9 -> 8.6 (there the cells come from beyond the caches).
+// 17 -> 8 us per decision; with the helices above, between the fill and the result: 50 residues 0.95 -> 0.35 ms,
+// 300 residues 4.7 -> 1.6, 1,976 residues 20 -> 8.6 (there the cells come from beyond the caches).  The
+// compiler spills 310 VGPRs of the traceback kernels (1,216 B of scratch per lane).
 __device__ void Tracer::closed_trie(int a, int b, int t, int p, int q, int ia, int ib, int64_t v) {
     const int g = q - p, m = g - 2, x = kTX[t], y = kTY[t];
     const SlotRec* R = I.recs();
